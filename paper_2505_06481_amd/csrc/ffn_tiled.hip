@@ -3,21 +3,21 @@
 // where the layer's time goes (section 5.1).
 //
 // Both products are  out[r, n] = sum_k A[r, k] * W[s][n][k]  over the packed pool, bf16
-// inputs, fp32 accumulation on v_mfma_f32_32x32x16_bf16.
+// inputs, fp32 accumulation on v_mfma_f32_16x16x32_bf16.
 //
 // Tile: 256 token rows x 256 weight rows x 64 k per step, one workgroup of four
 // wavefronts per compute unit.  Each wavefront owns all 256 token rows and 64 weight rows
 // (for the gated product: 32 rows of W1 and the same 32 rows of W3, so that SiLU(gate)*up
-// is lane-local): 8 x 2 accumulator tiles of 32x32, 256 accumulator registers.  Weights are
-// the 32-row matrix-core operand and tokens the 32-column one, hence a lane owns, for one
-// token, groups of 4 consecutive output features and stores 8 or 16 bytes at a time.
+// is lane-local): 16 x 4 accumulator tiles of 16x16, 256 accumulator registers.  Weights are
+// the row operand of the matrix instruction and tokens the column one, hence a lane owns, for one
+// token, groups of 4 consecutive output features and stores 16 bytes at a time.
 //
-// Memory pipeline: the pool is stored as matrix-core fragments, so a wavefront loads its
-// weight operands straight from global memory into registers (16 bytes per lane, 1 KB per
-// instruction, contiguous), four steps ahead of their use.  Token rows are copied global ->
-// LDS without passing registers (global_load_lds, 16 bytes per lane) into a four-stage ring
-// of LDS tiles, [row][64 k] bf16 (128 bytes a row) with the 16-byte pieces xor-swizzled by
-// (row >> 1) & 7, two steps ahead, and are read back as fragments; one barrier per step.
+// Memory pipeline: the pool is stored as fragments of 32 rows x 16 k, two of which hold, for each
+// half of their rows, a 16 x 32 operand: a wavefront loads its weight operands straight from global
+// memory into registers (16 bytes per lane, 256-byte runs), three 32-k slices ahead of their use (seven where the tile leaves the registers).
+// Token rows are copied global -> LDS without passing registers (global_load_lds, 16 bytes per lane)
+// into a four-stage ring of LDS tiles, [row][64 k] bf16 (128 bytes a row) with the 16-byte pieces
+// xor-swizzled by (row >> 1) & 7, and are read back as fragments; one barrier per step.
 //
 // Ragged groups: row ranges come from the device array `offsets`.  A one-workgroup
 // preparation kernel turns them into lists of tiles; the product kernels map their
@@ -96,117 +96,117 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
 
     constexpr int kWaves = 4;         // one per SIMD
     constexpr int kThreads = kWaves * 64;
-    constexpr int kNJ = BM / 32;      // 32-row token sub-tiles per wavefront (all rows of the tile)
-    // 16-k slices between a weight fragment's load and its use: what the registers allow
-    constexpr int kBAhead = (BM == kBMBig || NB == 1) ? 16 : 8;
+    constexpr int kNF = BM / 16;      // 16-row token fragments of a full tile (a wavefront takes all of them)
+    constexpr int kNW = 2 * NB;       // 16-row weight blocks per wavefront
     constexpr int kNP = BM * 8 / kThreads;  // 16-byte pieces of a token tile per thread
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: keeps bases in scalar registers
-    const int lr = lane & 31;
-    const int wn = wave;              // which 64 weight rows of the tile
+    const int lr = lane & 15, lg = lane >> 4;  // row of a 16-row fragment, one of its four groups of 8 k
+    const int wn = wave;              // which 32 NB weight rows of the tile
 
     // ---- token operand: global -> LDS ------------------------------------------------------------
-    // Piece id = i*kThreads + tid (i < kNP) of a [256 rows][8 pieces of 16 bytes] tile: 8
+    // Piece id = i*kThreads + tid (i < kNP) of a [BM rows][8 pieces of 16 bytes] tile: 8
     // consecutive threads read one row's 128 contiguous bytes.  Rows past the end of the group
     // re-read its last row (they are multiplied but never stored).
     // Grouped row r is row r of A, or, when a permutation is given, row perm[r] / kdiv of A (the
     // gather of the token rows folded into this product's loads).
+    // Copy instruction i of a wavefront writes its 64 pieces to 1 KB of consecutive LDS addresses
+    // (M0 + 16*lane), 8 rows of 128 bytes, so the swizzle is applied on the global side: the lane
+    // that fills physical piece q of a row fetches logical piece q ^ ((row >> 1) & 7).
     const char* a_base = reinterpret_cast<const char*>(A);
-    uint32_t a_row[kNP];  // byte offset of the row each piece comes from
+    uint32_t a_goff[kNP];  // byte offset of the piece
 #pragma unroll
     for (int i = 0; i < kNP; ++i) {
         const int row = i * (kThreads / 8) + (tid >> 3);
         const int r = r0 + min(row, cnt - 1);
-        a_row[i] = (uint32_t)(perm ? perm[r] / kdiv : r) * (uint32_t)K * 2u;
+        a_goff[i] = (uint32_t)(perm ? perm[r] / kdiv : r) * (uint32_t)K * 2u + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
     }
-    // Copy instruction i of a wavefront writes its 64 pieces to 1 KB of consecutive LDS addresses
-    // (M0 + 16*lane), 8 rows of 128 bytes, so the swizzle is applied on the global side: the lane
-    // that fills physical piece q of a row fetches logical piece q ^ ((row >> 1) & 7).
-    uint32_t a_goff[kNP];
-#pragma unroll
-    for (int i = 0; i < kNP; ++i) a_goff[i] = a_row[i] + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
     // The copies are written in assembly so that the compiler's wait-count bookkeeping does not
     // see them (it would drain every load in flight before each LDS read); the waits that order
     // them are written out next to the barriers.  M0 is only used here.
-    auto copy_a = [&](int stage, int kt) {
+    auto copy_a = [&](int stage, int kt, int i) {
         const char* ab = a_base + (size_t)kt * (kBK * 2);
-#pragma unroll
-        for (int i = 0; i < kNP; ++i) {
-            const uint32_t dst =
-                (uint32_t)(uintptr_t)(lptr_t)(lds_a + stage * kTileBytes + (i * kThreads + wave * 64) * 16);
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :
-                         : "v"(a_goff[i]), "s"(ab), "s"(dst)
-                         : "m0", "memory");
-        }
+        const uint32_t dst =
+            (uint32_t)(uintptr_t)(lptr_t)(lds_a + stage * kTileBytes + (i * kThreads + wave * 64) * 16);
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                     :
+                     : "v"(a_goff[i]), "s"(ab), "s"(dst)
+                     : "m0", "memory");
     };
     // ---- weight operand: fragment-packed pool -> registers ------------------------------------------
-    // A wavefront owns weight rows [64 wn, 64 wn + 64) of the tile, two 32-row blocks; for the
-    // gated product they are block (n0 + 32 wn)/32 of W1 (gate) and the same block of W3 (up), so
-    // that a lane holds matching gate and up values.  Fragment ks of a block is 1 KB at ks*1024.
+    // A wavefront owns 32 NB weight rows of the tile: NB packed 32-row blocks, each two 16-row blocks of
+    // the matrix instruction.  For the gated product they are block (n0 + 32 wn)/32 of W1 (gate) and the
+    // same block of W3 (up), so that a lane holds matching gate and up values.  Packed fragment ks (16 k)
+    // of a 32-row block is 1 KB at ks*1024; slice g of the matrix instruction (32 k) is fragments 2g and
+    // 2g + 1: lane group lg takes half lg%2 of fragment 2g + lg/2, 256 contiguous bytes per group.
     const size_t frag_bytes_per_block = (size_t)(K / 16) * 1024;
     const char* wb[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const uint16_t* w = (MODE == kTModeSwigluH && i == 1) ? W1 : W0;
         const int nb = MODE == kTModeSwigluH ? (n0 + wn * 32) / 32 : (n0 + wn * (32 * NB) + i * 32) / 32;
-        wb[i] = reinterpret_cast<const char*>(w) + ((size_t)s * (N / 32) + nb) * frag_bytes_per_block + lane * 16;
+        wb[i] = reinterpret_cast<const char*>(w) + ((size_t)s * (N / 32) + nb) * frag_bytes_per_block;
     }
+    const uint32_t w_off = (lg >> 1) * 1024 + (lg & 1) * 512 + lr * 16;
 
     // ---- token fragments from LDS ------------------------------------------------------------------
-    // Slice kk (16 k) of a step: lane (row lane%32, half h = lane/32) reads logical piece 4h + kk,
-    // the 8 k values that the packed weight fragment pairs with it.
-    int frag_off[4];
+    // Slice q (32 k) of a step: lane (row lr, group lg) reads logical piece 4 (lg%2) + 2q + lg/2, the
+    // 8 k values that its weight fragment holds.
+    int frag_off[2];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-        frag_off[kk] = lr * 128 + ((((lane >> 5) * 4 + kk) ^ ((lr >> 1) & 7)) << 4);
+    for (int q = 0; q < 2; ++q)
+        frag_off[q] = lr * 128 + (((4 * (lg & 1) + 2 * q + (lg >> 1)) ^ ((lr >> 1) & 7)) << 4);
 
-    // Gated output rows (GateSink): the coefficient of this lane's token column of every sub-tile, and
-    // the output row (token) of every row this lane stores in the epilogue.  Two dependent loads each;
-    // short-lived 128-row tiles start them here, behind the main loop's own loads, tall tiles (no
-    // registers to spare in the main loop, and an epilogue that is a hundredth of the tile) when
-    // the main loop is over.
-    constexpr int kSinkLpr = 4;   // lanes per stored row of 32 bf16 features (the epilogue's kLpr)
-    constexpr int kSinkRpi = 16;  // rows per store instruction (its kRpi)
-    constexpr bool kEarlySink = BM == kBMSmall;
-    float gate_w[kNJ];
-    int sink_row[kNJ][32 / kSinkRpi];
+    // Gated output rows (GateSink): output row (token) and coefficient of this lane's token of every
+    // fragment.  Two dependent loads each; tiles of 128 x 128 (short-lived, with registers to spare)
+    // start them here, in front of the main loop's own loads, the others when the main loop is over.
+    constexpr bool kEarlySink = BM == kBMSmall && NB == 1;
+    float gate_w[kNF];
+    int sink_row[kNF];
     auto fetch_sink = [&]() {
 #pragma unroll
-        for (int j = 0; j < kNJ; ++j) {
-            gate_w[j] = sink_w[sink_perm[r0 + min(j * 32 + lr, cnt - 1)]];
-#pragma unroll
-            for (int it = 0; it < 32 / kSinkRpi; ++it)
-                sink_row[j][it] = sink_perm[r0 + min(j * 32 + it * kSinkRpi + lane / kSinkLpr, cnt - 1)];
+        for (int j = 0; j < kNF; ++j) {
+            sink_row[j] = sink_perm[r0 + min(j * 16 + lr, cnt - 1)];
+            gate_w[j] = sink_w[sink_row[j]];
         }
     };
     if (MODE == kTModeGatedY && kEarlySink) fetch_sink();
 
-    f32x16 acc[kNJ][NB];  // [token sub-tile][weight block]
+    f32x4 acc[kNF][kNW];  // [token fragment][16-row weight block]
 #pragma unroll
-    for (int j = 0; j < kNJ; ++j)
+    for (int j = 0; j < kNF; ++j)
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.0f;
+        for (int i = 0; i < kNW; ++i) acc[j][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // Main loop, instantiated for NJ = number of this wavefront's 32-row token sub-tiles that
-    // hold rows (all 8 for every tile but the last one of a slot).
+    // Main loop, instantiated for NJ = number of the tile's 32-row token sub-tiles that hold rows.
     //
-    // Pipeline (k step t = 64 k = four 16-k slices; step t's tokens live in LDS stage t mod 4):
-    //   weights   slice g is loaded straight into registers kBAhead slices (four steps) before
-    //             use; these are ordinary loads and the compiler inserts their waits;
-    //   tokens    the copies of step t+4 are issued right after the barrier of step t, into the
-    //             stage that step t has just finished with, and must have landed by the barrier
-    //             of step t+2; token fragments roll through one set of registers: as soon as the
-    //             two matrix instructions that use fragment j have been issued, fragment j of
-    //             the next slice is fetched into it;
-    //   barrier   one per step, in the middle of its last slice: by then every wavefront's
-    //             reads of the step's stage have returned (only the first NJ/2 fetches of the
-    //             next stage may be in flight), so nobody waits for LDS.
-    // The loop is unrolled by kBAhead/4 steps so that the ring of weight registers is indexed
-    // statically.
+    // What bounds it: power.  Under matrix load on real data the chip lowers its clock (1.6 to 1.9 GHz
+    // of 2.4), so what counts is energy per flop first and idle matrix cycles second.
+    //   - 16x16x32 instructions instead of 32x32x16: a register-only loop on random operands runs at
+    //     2.04 against 1.84 PFLOP/s (half the accumulator traffic per flop).
+    //   - One vector-memory instruction at a time between groups of matrix instructions, never a burst:
+    //     the memory pipeline takes 16 cycles for each 1 KB instruction of each of the four wavefronts, and a
+    //     wavefront that issues eight in a row stands still for several hundred cycles.
+    // (16384 x 28672 x 4096, uniform tiles, random data: 1.26 -> 1.34 -> 1.41 PFLOP/s.)
+    //
+    // The matrix instructions are written in assembly with the accumulators tied to AGPRs: from 64
+    // small accumulators the compiler's own choice of destination registers moves them around in
+    // the loop.  Hazards it can then not see: nothing in the loop writes a matrix operand with a
+    // vector instruction (fragments come from LDS and memory reads, whose waits the compiler
+    // inserts), and the accumulators are read behind the s_nops that follow the loop.
+    //
+    // Pipeline (k step t = 64 k = two 32-k slices; step t's tokens live in LDS stage t mod 4):
+    //   weights   slice g is loaded straight into registers kSlices - 1 slices ahead of its use; these
+    //             are ordinary loads and the compiler inserts their waits;
+    //   tokens    the copies of step t+3 are issued during step t, into the stage that step t-1 has
+    //             left, and must have landed by the barrier of step t+1; token fragments roll through a
+    //             ring of RF register sets: as soon as the kNW matrix instructions that use a fragment
+    //             have been issued, the fragment RF further on is fetched into its registers;
+    //   barrier   one per step, RF/2 groups before its end: by then every wavefront's reads of the
+    //             step's stage have returned (only the first RF/2 fetches of the next stage may be in
+    //             flight), so nobody waits for LDS.
+    // The loop is unrolled by kUnroll steps so that the rings of registers are indexed statically.
     //
     // What orders the copies.  The compiler does not see them, so the wait that makes them
     // land is written out next to every barrier: s_waitcnt vmcnt(N) returns when at most N of
@@ -221,193 +221,194 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     // What orders the LDS reads.  Before a stage is handed back to the copies, the fragments
     // of that stage that are still to be used are made operands of an (empty) asm statement in
     // front of the barrier, so the compiler itself waits for exactly those reads and for nothing
-    // younger (the NH fetches of the next stage stay in flight across the barrier).
-    const int nkt = K / kBK;         // even: K is a multiple of 256
+    // younger (the RF/2 fetches of the next stage stay in flight across the barrier).
+    const int nkt = K / kBK;         // a multiple of 4: K is a multiple of 256
     const int last = nkt - 1;
-    const int last_slice = K / 16 - 1;
+    const int last_slice = K / 32 - 1;
+    constexpr int kUnroll = (BM == kBMBig || NB == 1) ? 4 : 2;
+    constexpr int kSlices = NB == 1 ? 8 : 4;  // ring of weight slices in registers (four steps, two steps)
     auto run = [&](auto njc) {
         constexpr int NJ = decltype(njc)::value;
-        constexpr int NH = NJ / 2;  // fetches of the next stage issued before the barrier
+        constexpr int NF = 2 * NJ;              // token fragments per slice
+        constexpr int G = 2 * NF;               // groups (one fragment against kNW weight blocks) per step
+        // fragments in flight: the lead stays within the next step, and 128 x 256 tiles have 256 registers
+        constexpr int RF = (NJ == 1 || (BM == kBMSmall && NB == 2)) ? 4 : 8;
+        static_assert(G >= RF && (kUnroll * G) % RF == 0, "the fragment ring is indexed statically");
         struct BFrags {
-            u32x4 b[NB];
+            u32x4 b[kNW];
         };
-        bf16x8 fa[NJ];
-        auto frag_ptr = [&](int stage, int kk) { return lds_a + stage * kTileBytes + frag_off[kk]; };
-        auto load_bf = [&](BFrags& fr, int g) {
-            const size_t o = (size_t)min(g, last_slice) * 1024;  // past the end: a harmless reload
-#pragma unroll
-            for (int i = 0; i < NB; ++i) fr.b[i] = *reinterpret_cast<const u32x4*>(wb[i] + o);
+        bf16x8 fa[RF];
+        BFrags bq[kSlices];
+        auto load_bf = [&](BFrags& fr, int g, int i) {
+            const size_t o = (size_t)min(g, last_slice) * 2048;  // past the end: a harmless reload
+            fr.b[i] = *reinterpret_cast<const u32x4*>(wb[i >> 1] + o + (w_off + (i & 1) * 256));
         };
-        // one token sub-tile against both weight blocks, then its fragment of the next slice
-        auto mma_roll = [&](int j, const BFrags& fb, const char* next) {
+        // prologue: copies of steps 0..2, then the first weight slices; the wait leaves at most the
+        // copies of step 2 in flight
 #pragma unroll
-            for (int i = 0; i < NB; ++i)
-                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb.b[i]), fa[j],
-                                                                    acc[j][i], 0, 0, 0);
-            fa[j] = *reinterpret_cast<const bf16x8*>(next + j * 32 * 128);
-        };
-        // a slice whose successor lies in the same LDS stage
-        auto slice = [&](BFrags& fb, const char* next, int g_reload) {
+        for (int t = 0; t < 3; ++t)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) mma_roll(j, fb, next);
-            load_bf(fb, g_reload);
+            for (int i = 0; i < kNP; ++i) copy_a(t, t, i);
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x020, NB, 0);
-        };
-
-        BFrags bq[kBAhead];
-        // prologue: copies of steps 0..3 into the four stages, then the first weight fragments;
-        // the wait leaves at most the copies of step 3 in flight
-        copy_a(0, 0);
-        copy_a(1, min(1, last));
-        copy_a(2, min(2, last));
-        copy_a(3, min(3, last));
+        for (int g = 0; g < kSlices - 1; ++g)
 #pragma unroll
-        for (int g = 0; g < kBAhead; ++g) load_bf(bq[g], g);
-        static_assert(kNP + NB * kBAhead <= 63, "vmcnt is a 6-bit counter");
+            for (int i = 0; i < kNW; ++i) load_bf(bq[g], g, i);
+        static_assert(kNP + kNW * (kSlices - 1) <= 63, "vmcnt is a 6-bit counter");
         __builtin_amdgcn_sched_barrier(0);  // the weight loads are issued before the wait, not after it
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kNP + NB * kBAhead) : "memory");
-        {
-            const char* p0 = frag_ptr(0, 0);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kNP + kNW * (kSlices - 1)) : "memory");
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) fa[j] = *reinterpret_cast<const bf16x8*>(p0 + j * 32 * 128);
-        }
+        for (int j = 0; j < RF; ++j)
+            fa[j] = *reinterpret_cast<const bf16x8*>(lds_a + (j < NF ? frag_off[0] + j * 2048 : frag_off[1] + (j - NF) * 2048));
 
         int st = 0;  // LDS stage of step kt
-        constexpr int kUnroll = kBAhead / 4;  // steps per trip: the weight ring is indexed statically
         int kt = 0;
         do {  // at least one trip (K >= 256): the prologue's loads have nowhere to sink to
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const int t = kt + u;
-                const int stn = st == kStagesA - 1 ? 0 : st + 1;
-                const int g = 4 * t;
-                slice(bq[(4 * u + 0) % kBAhead], frag_ptr(st, 1), g + kBAhead);
-                slice(bq[(4 * u + 1) % kBAhead], frag_ptr(st, 2), g + kBAhead + 1);
-                slice(bq[(4 * u + 2) % kBAhead], frag_ptr(st, 3), g + kBAhead + 2);
-                // last slice of the step: its fragments are in flight or in registers
-                {
-                    BFrags& fb = bq[(4 * u + 3) % kBAhead];
-                    const char* next = frag_ptr(stn, 0);
+                const int stn = (st + 1) & (kStagesA - 1), stp = (st + kStagesA - 1) & (kStagesA - 1);
+                const char* cur = lds_a + st * kTileBytes;
+                const char* nxt = lds_a + stn * kTileBytes;
+                BFrags& f0 = bq[(2 * u) % kSlices];
+                BFrags& f1 = bq[(2 * u + 1) % kSlices];
+                BFrags& fp = bq[(2 * u + kSlices - 1) % kSlices];  // the slice in front of this step's
+                // Vector-memory instructions of one half of the step, op = 0 .. kHalf-1: half of the copies
+                // and kNW weight loads in turn.  First half: the slice used last in the step before; second
+                // half: this step's first slice, used up by then.
+                constexpr int kHalf = kNP / 2 + kNW;
+                auto vmem = [&](int half, int op) {
+                    constexpr int kTwo = 2 * (kNP / 2 < kNW ? kNP / 2 : kNW);  // ops that alternate
+                    const bool copy = op < kTwo ? op % 2 == 0 : kNP / 2 > kNW;
+                    const int n = op < kTwo ? op / 2 : op - kTwo / 2;
+                    if (copy) copy_a(stp, min(t + 3, last), half * (kNP / 2) + n);
+                    else if (half == 0) load_bf(fp, 2 * t + kSlices - 1, n);
+                    else load_bf(f0, 2 * t + kSlices, n);
+                };
 #pragma unroll
-                    for (int j = 0; j < NH; ++j) mma_roll(j, fb, next);
+                for (int gi = 0; gi < G; ++gi) {
+                    constexpr int kBar = G - RF / 2;  // the barrier stands in front of this group
+                    if (gi == kBar) {
+                        // Stage st goes back to the copies after this barrier.  Its fragments that are still
+                        // to be used become operands here, so the compiler waits for those reads; every other
+                        // read of the stage has been consumed by a matrix instruction above.
 #pragma unroll
-                    for (int j = 0; j < NH; ++j) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        for (int j = kBar; j < G; ++j) asm volatile("" ::"v"(fa[(u * G + j) % RF]));
+                        // All vector-memory instructions of step t stand in front of its barrier: kNP copies
+                        // (step t+3's) and 2 kNW weight loads, all of them behind the copies of step t+2, which
+                        // were issued during step t-1.  A wait that leaves that many outstanding leaves
+                        // the copies of step t+2 landed, and after the barrier every wavefront may read that
+                        // step, whose first fragments are fetched before the next barrier.
+                        constexpr int kWaitN = kNP + 2 * kNW;
+                        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kWaitN) : "memory");
                     }
-                    // Stage st goes back to the copies after this barrier.  Its fragments that are still
-                    // to be used (sub-tiles NH.. of this slice) become operands here, so the compiler
-                    // waits for those reads; every other read of the stage has been consumed by a matrix
-                    // instruction above.  The NH fetches just issued read the next stage and stay in flight.
+                    const int q = gi / NF, j = gi % NF, slot = (u * G + gi) % RF;
+                    const BFrags& fb = q ? f1 : f0;
 #pragma unroll
-                    for (int j = NH; j < NJ; ++j) asm volatile("" ::"v"(fa[j]));
-                    // This wavefront's copies of step t+2 were issued two steps ago, after the barrier of
-                    // step t-2 (for t < 2: in the prologue); since then it has issued the kNP copies of
-                    // step t+3 and, in the order written here, 8*NB weight-fragment loads (NB in the rest
-                    // of that slice, 4*NB in step t-1, 3*NB in this step): a wait that leaves at most
-                    // kWaitN = min(16, kNP + 8*NB - 4) instructions outstanding leaves the copies of step
-                    // t+2 landed, and after the barrier every wavefront may read that step, whose first
-                    // fragments are fetched before the next barrier.
-                    constexpr int kWaitN = kNP + 8 * NB - 4 < 16 ? kNP + 8 * NB - 4 : 16;
-                    static_assert(kWaitN >= kNP, "the copies of step t+3 stay in flight");
-                    static_assert(kNP + NB * kBAhead + 3 * NB >= kWaitN, "first step: after the copies of step 2");
-                    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kWaitN) : "memory");
-                    copy_a(st, min(t + 4, last));  // tokens of step t+4; past the end: a harmless reload
+                    for (int i = 0; i < kNW; ++i)
+                        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                                     : "+a"(acc[j][i])
+                                     : "v"(fb.b[i]), "v"(fa[slot]));
+                    const int n = gi + RF;  // the fragment that takes this one's registers
+                    const char* src = n < NF  ? cur + frag_off[0] + n * 2048
+                                      : n < G ? cur + frag_off[1] + (n - NF) * 2048
+                                      : n < G + NF ? nxt + frag_off[0] + (n - G) * 2048
+                                                   : nxt + frag_off[1] + (n - G - NF) * 2048;
+                    fa[slot] = *reinterpret_cast<const bf16x8*>(src);
+                    __builtin_amdgcn_sched_barrier(0);
+                    // groups of this half that memory instructions may follow: all before the barrier
+                    const int half = gi / NF, ng = half ? kBar - NF : NF, at = gi - half * NF;
+                    // NJ = 1: the barrier stands in front of the second half, whose instructions join the first
+                    if (kBar > NF) {
 #pragma unroll
-                    for (int j = NH; j < NJ; ++j) mma_roll(j, fb, next);
-                    load_bf(fb, g + kBAhead + 3);
+                        for (int op = 0; op < kHalf; ++op)
+                            if (gi < kBar && op * ng / kHalf == at) vmem(half, op);
+                    } else if (gi == NF - 1) {
 #pragma unroll
-                    for (int q = 0; q < NJ - NH; ++q) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                        for (int op = 0; op < 2 * kHalf; ++op) vmem(op / kHalf, op % kHalf);
                     }
-                    __builtin_amdgcn_sched_group_barrier(0x020, NB, 0);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
                 st = stn;
             }
             kt += kUnroll;
         } while (kt < nkt);
-        // no copy may still be on its way into LDS when the epilogue reuses it or the workgroup ends
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // no copy may still be on its way into LDS when the workgroup ends; and the matrix pipeline's last
+        // results are there before the accumulators are read
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     };
-    switch (min(kNJ, (cnt + 31) / 32)) {  // uniform over the workgroup
-        case 8: if constexpr (kNJ >= 8) run(std::integral_constant<int, 8>{}); break;
-        case 7: if constexpr (kNJ >= 8) run(std::integral_constant<int, 7>{}); break;
-        case 6: if constexpr (kNJ >= 8) run(std::integral_constant<int, 6>{}); break;
-        case 5: if constexpr (kNJ >= 8) run(std::integral_constant<int, 5>{}); break;
+    switch (min(BM / 32, (cnt + 31) / 32)) {  // uniform over the workgroup
+        case 8: if constexpr (BM == kBMBig) run(std::integral_constant<int, 8>{}); break;
+        case 7: if constexpr (BM == kBMBig) run(std::integral_constant<int, 7>{}); break;
+        case 6: if constexpr (BM == kBMBig) run(std::integral_constant<int, 6>{}); break;
+        case 5: if constexpr (BM == kBMBig) run(std::integral_constant<int, 5>{}); break;
         case 4: run(std::integral_constant<int, 4>{}); break;
         case 3: run(std::integral_constant<int, 3>{}); break;
         case 2: run(std::integral_constant<int, 2>{}); break;
         default: run(std::integral_constant<int, 1>{}); break;
     }
+    // the accumulators stay where the matrix instructions left them until the epilogue reads them
+#pragma unroll
+    for (int j = 0; j < kNF; ++j)
+#pragma unroll
+        for (int i = 0; i < kNW; ++i) asm volatile("" : "+a"(acc[j][i]));
 
     // ---- epilogue -------------------------------------------------------------------------------
-    // Accumulator element e of lane l is weight row 8*(e/4) + 4*(l/32) + e%4 of token column
-    // l%32: a lane holds scattered 4-feature groups of one token.  Each wavefront therefore
-    // passes its results through a private LDS patch, 32 tokens x 32 features at a time, and
-    // reads them back row by row, so that every global store instruction writes whole
-    // contiguous row segments (128 bytes for fp32 output, 64 for bf16).
+    // Accumulator element e of lane (lr, lg) is weight row 4 lg + e of the block, token lr of the
+    // fragment.  fp32 output: a lane's four values of a block are 16 consecutive bytes of the token's
+    // row, stored as they are.  bf16 output: two blocks are packed to 8 bytes per lane each, and one
+    // exchange between neighbouring lane groups (v_permlane16_swap) gives every lane 8 consecutive
+    // features of one block: lane group lg holds features 8 (lg/2) .. +7 of block lg%2, 16 bytes,
+    // and the four groups of a token cover 64 contiguous bytes.  No LDS, no barrier.
     constexpr int kEsz = MODE == kTModePlainF32 ? 4 : 2;
-    constexpr int kRowB = 32 * kEsz;                  // bytes of one staged row
-    constexpr int kPitch = kRowB + 16;                // padded: conflict-free 16-byte column writes
-    constexpr int kLpr = kRowB / 16;                  // lanes that read one row back
-    constexpr int kRpi = 64 / kLpr;                   // rows per read-back instruction
-    static_assert(MODE != kTModeGatedY || (kLpr == kSinkLpr && kRpi == kSinkRpi), "the sink rows follow the stores");
-    constexpr int kChunks = MODE == kTModeSwigluH ? 1 : NB;       // 32-feature chunks this wavefront stores
-    const int wfeat = MODE == kTModeSwigluH ? wn * 32 : wn * (32 * NB);
-    // the patches reuse the token ring: every wavefront has left the main loop
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    char* ebuf = lds_a + wave * (32 * (32 * 4 + 16));
-    char* const obase = reinterpret_cast<char*>(out) + ((size_t)r0 * N + n0 + wfeat) * kEsz +
-                        (size_t)(lane / kLpr) * N * kEsz + (lane % kLpr) * 16;
+    constexpr int kOutBlocks = MODE == kTModeSwigluH ? kNW / 2 : kNW;  // 16-feature blocks this wavefront stores
+    const int wfeat = wn * 16 * kOutBlocks;
     if (MODE == kTModeGatedY && !kEarlySink) fetch_sink();
-    char* const ybase = reinterpret_cast<char*>(out) + (size_t)(n0 + wfeat) * kEsz + (lane % kLpr) * 16;
-    // o[4q + e]: the 16 finished values of this lane for token sub-tile j, feature chunk c
-    auto emit = [&](int j, int c, const float (&o)[16]) {
+    char* const obase = reinterpret_cast<char*>(out) + (size_t)(n0 + wfeat) * kEsz +
+                        (kEsz == 4 ? lg * 16 : ((lg & 1) * 16 + (lg >> 1) * 8) * 2);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            char* at = ebuf + lr * kPitch + (8 * q + 4 * (lane >> 5)) * kEsz;
-            if (kEsz == 4) {
-                *reinterpret_cast<f32x4*>(at) = f32x4{o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]};
-            } else {
-                u32x2 pk;
-                pk[0] = (uint32_t)f32_to_bf16_bits(o[4 * q]) | ((uint32_t)f32_to_bf16_bits(o[4 * q + 1]) << 16);
-                pk[1] = (uint32_t)f32_to_bf16_bits(o[4 * q + 2]) | ((uint32_t)f32_to_bf16_bits(o[4 * q + 3]) << 16);
-                *reinterpret_cast<u32x2*>(at) = pk;
+    for (int j = 0; j < kNF; ++j) {
+        if (j * 16 >= cnt) break;  // uniform over the workgroup
+        const int row = MODE == kTModeGatedY ? sink_row[j] : r0 + j * 16 + lr;
+        char* const dst = obase + (size_t)row * N * kEsz;
+        f32x4 o[kOutBlocks];
+#pragma unroll
+        for (int i = 0; i < kOutBlocks; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = acc[j][i][e];
+                if (MODE == kTModeSwigluH) o[i][e] = silu_mul_t(v, acc[j][i + kNW / 2][e]);
+                else if (MODE == kTModeReluH) o[i][e] = fmaxf(v, 0.0f);
+                else if (MODE == kTModeGeluH) o[i][e] = 0.5f * v * (1.0f + erff(v * 0.70710678118654752440f));
+                else if (MODE == kTModeGatedY) o[i][e] = __builtin_fmaf(gate_w[j], v, 0.0f);
+                else o[i][e] = v;
+            }
+        if constexpr (kEsz == 4) {
+            if (j * 16 + lr < cnt) {
+#pragma unroll
+                for (int i = 0; i < kOutBlocks; ++i) *reinterpret_cast<f32x4*>(dst + i * 64) = o[i];
+            }
+        } else {
+            u32x4 pk[kOutBlocks / 2];
+#pragma unroll
+            for (int p = 0; p < kOutBlocks / 2; ++p) {
+                u32x2 lo, hi;  // features 4 lg .. +3 of block 2p, of block 2p + 1
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    lo[h] = (uint32_t)f32_to_bf16_bits(o[2 * p][2 * h]) |
+                            ((uint32_t)f32_to_bf16_bits(o[2 * p][2 * h + 1]) << 16);
+                    hi[h] = (uint32_t)f32_to_bf16_bits(o[2 * p + 1][2 * h]) |
+                            ((uint32_t)f32_to_bf16_bits(o[2 * p + 1][2 * h + 1]) << 16);
+                }
+                const u32x2 s0 = __builtin_amdgcn_permlane16_swap(lo[0], hi[0], false, false);
+                const u32x2 s1 = __builtin_amdgcn_permlane16_swap(lo[1], hi[1], false, false);
+                pk[p] = u32x4{s0[0], s1[0], s0[1], s1[1]};
+            }
+            if (j * 16 + lr < cnt) {
+#pragma unroll
+                for (int p = 0; p < kOutBlocks / 2; ++p) *reinterpret_cast<u32x4*>(dst + p * 64) = pk[p];
             }
         }
-#pragma unroll
-        for (int it = 0; it < 32 / kRpi; ++it) {
-            const int row = it * kRpi + lane / kLpr;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(ebuf + row * kPitch + (lane % kLpr) * 16);
-            if (j * 32 + row < cnt) {
-                char* dst = MODE == kTModeGatedY ? ybase + ((size_t)sink_row[j][it % (32 / kSinkRpi)] * N + c * 32) * kEsz
-                                                 : obase + ((size_t)(j * 32 + it * kRpi) * N + c * 32) * kEsz;
-                *reinterpret_cast<u32x4*>(dst) = v;
-            }
-        }
-    };
-#pragma unroll
-    for (int j = 0; j < kNJ; ++j) {
-        if (j * 32 >= cnt) break;  // uniform over the workgroup
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) {
-            float o[16];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                if (MODE == kTModeSwigluH) o[e] = silu_mul_t(acc[j][0][e], acc[j][NB - 1][e]);
-                else if (MODE == kTModeReluH) o[e] = fmaxf(acc[j][c][e], 0.0f);
-                else if (MODE == kTModeGeluH) o[e] = 0.5f * acc[j][c][e] * (1.0f + erff(acc[j][c][e] * 0.70710678118654752440f));
-                else if (MODE == kTModeGatedY) o[e] = __builtin_fmaf(gate_w[j], acc[j][c][e], 0.0f);
-                else o[e] = acc[j][c][e];
-            }
-            emit(j, c, o);
-        }
+        __builtin_amdgcn_sched_barrier(0);  // one fragment at a time: few registers
     }
 }
 

@@ -107,6 +107,17 @@ def test_both_tile_heights(mm, gc, oracle, cfg, rows):
     staged_vs_oracle(mm, gc, oracle, cfg, tile_rows=rows)
 
 
+@pytest.mark.parametrize("rows", [256, 128])
+@pytest.mark.parametrize("act,k", [("swiglu", 1), ("relu", 1), ("gelu", 2)])
+def test_tiled_row_remainders(mm, gc, oracle, act, k, rows):
+    """Every number of 16-row fragments a tile can end in, full and one-row remainders, one and two
+    tiles in the slot: a single slot (two when k = 2) that holds T rows.  A cut at a wrong row or lane
+    shows as a whole wrong row, so the tolerance is the storage type's."""
+    for T in (33, 47, 48, 49, 65, 97, 112, 128, 129, 161, 193, 225, 241, 255, 256, 257, 300):
+        staged_vs_oracle(mm, gc, oracle, synth.Config(f"rem_{act}_{T}", T, 256, 256, 1, k, k, "bf16", act, seed=400 + T),
+                         tile_rows=rows)
+
+
 GATES_AND_ACTS = [
     # Switch-style gate (probability over all experts, not renormalised), top-1, ReLU and GELU experts,
     # three variants; streaming kernels and matrix-core kernels, fp32 and bf16
