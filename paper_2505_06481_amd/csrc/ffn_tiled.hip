@@ -19,13 +19,12 @@
 // into a four-stage ring of LDS tiles, [row][64 k] bf16 (128 bytes a row) with the 16-byte pieces
 // xor-swizzled by (row >> 1) & 7, and are read back as fragments; one barrier per step.
 //
-// Ragged groups: row ranges come from the device array `offsets`.  A one-workgroup
-// preparation kernel turns them into lists of tiles; the product kernels map their
+// Ragged groups: row ranges come from the device array `offsets`.  A small
+// preparation step turns them into lists of tiles; the product kernels map their
 // workgroup id to (slot, row tile, feature tile) through those lists, so the host never
 // waits for the histogram.  Workgroup ids are dealt round-robin to the 8 XCDs by the
-// hardware; the id -> tile map gives XCD x the feature tiles nt with nt mod 8 == x, so the
-// workgroups resident on one XCD share weight and activation panels in that XCD's L2 and
-// every XCD sees the same mix of row tiles.
+// hardware; every XCD has a list of its own share of the tiles, ordered so that the workgroups
+// resident on it share weight and activation panels in that XCD's L2.
 #include <type_traits>
 
 #include "mmoe_internal.h"
@@ -51,20 +50,26 @@ __device__ __forceinline__ float silu_mul_t(float g, float u)
     return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
 
-__global__ __launch_bounds__(256) void tile_table_kernel(const int32_t* __restrict__ offsets,
-                                                         int32_t* __restrict__ tab, int S, int nt_up, int nt_down,
-                                                         int bm, TileLists L, SlotFilter filt)
+// The lists of product blockIdx.x, for callers that bring the offsets.
+__global__ __launch_bounds__(kListThreads) void tile_table_kernel(const int32_t* __restrict__ offsets,
+                                                                  int32_t* __restrict__ tab, int S, int nt_up,
+                                                                  int nt_down, int bm, TileLists L, SlotFilter filt)
 {
-    build_tile_lists(offsets, tab, S, nt_up, nt_down, bm, L, filt);
+    __shared__ int off[kMaxS + 1];
+    __shared__ int first[kXcds * kMaxS];
+    for (int s = threadIdx.x; s <= S; s += kListThreads) off[s] = offsets[s];
+    __syncthreads();
+    const int p = blockIdx.x;
+    build_tile_lists(off, tab, S, p, p == 0 ? nt_up : nt_down, bm, L, first, filt);
 }
 
 template <int MODE, int BM, int NB>
 __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const uint16_t* __restrict__ A,
                                                        const int32_t* __restrict__ perm, int kdiv,
-                                                            const int32_t* __restrict__ tab, int hdr, int list_hi,
-                                                            int list_lo, const uint16_t* __restrict__ W0,
+                                                            const int32_t* __restrict__ tab, int hdr, int list_at,
+                                                            int list_stride, const uint16_t* __restrict__ W0,
                                                             const uint16_t* __restrict__ W1,
-                                                            void* __restrict__ out, int K, int N, int NT,
+                                                            void* __restrict__ out, int K, int N,
                                                             const int32_t* __restrict__ sink_perm,
                                                             const float* __restrict__ sink_w)
 {
@@ -72,18 +77,16 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     __shared__ __attribute__((aligned(1024))) char lds_a[kStagesA * kTileBytes];
 
     // ---- workgroup id -> tile ------------------------------------------------------------
-    // XCD x (= workgroup id mod 8) owns the feature tiles nt with nt mod 8 == x, for every slot
-    // and row tile: every XCD gets the same mix of full and partial row tiles, and all row
-    // tiles that share a weight panel run on the XCD whose L2 holds it.  One 16-byte entry of
-    // the prepared list says which tile this workgroup computes.
+    // XCD x (= workgroup id mod 8) works through its list of tiles (tile_table.h): all row tiles that
+    // share a weight panel run on the XCD whose L2 holds it, and every XCD has the same share of the
+    // work.  One 16-byte entry of the list says which tile this workgroup computes.
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-    const int nt_x = (NT - xcd + kXcds - 1) / kXcds;  // feature tiles owned by this XCD
-    const int4* list = reinterpret_cast<const int4*>(tab) + (nt_x == (NT + kXcds - 1) / kXcds ? list_hi : list_lo);
-    const int total_m = tab[hdr];
+    const int4* list = reinterpret_cast<const int4*>(tab) + list_at + xcd * list_stride;
+    const int n_mine = tab[hdr + xcd];
     const int4 ent = list[local];                     // in bounds for every workgroup of the grid
-    if (local >= total_m * nt_x) return;              // uniform over the workgroup
+    if (local >= n_mine) return;                      // uniform over the workgroup
     const int s = ent.x;
-    const int nt = ent.y * kXcds + xcd;
+    const int nt = list_stride ? ent.y : ent.y * kXcds + xcd;
     const int r0 = ent.z;                             // first row of the tile
     const int cnt = ent.w;                            // rows of the tile that exist (1..256)
 
@@ -469,9 +472,15 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
 
 size_t tiled_table_bytes(const mmoe_shape& s)
 {
-    // the most entries any plan of this shape can have: the shortest tiles, the narrowest feature tiles
-    const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / (kBN / 2) : s.d_ff / 128;
-    return align256(tile_lists(s.T * s.top_k, s.S, nt_up, s.d_model / 128, 1, 1).bytes);
+    if (use_skinny(s)) return 0;
+    size_t most = 0;
+    for (int rows : {kBMSmall, kBMBig}) {  // tile_rows is a field of the call, not of the workspace
+        mmoe_shape forced = s;
+        forced.tile_rows = rows;
+        const size_t b = align256(tiled_plan(forced).L.bytes);
+        most = b > most ? b : most;
+    }
+    return most;
 }
 
 template <int MODE, int BM, int NB>
@@ -479,9 +488,9 @@ static void launch_product(const TiledPlan& p, int prod, const void* A, const in
                            const void* W0, const void* W1, void* out, int K, int N, hipStream_t st,
                            GateSink sink = GateSink())
 {
-    hipLaunchKernelGGL((tiled_kernel<MODE, BM, NB>), dim3(p.L.cap[prod] * kXcds), dim3(256), 0, st, (const uint16_t*)A,
-                       perm, kdiv, tab, p.L.hdr + prod, p.L.list[prod][0], p.L.list[prod][1], (const uint16_t*)W0,
-                       (const uint16_t*)W1, out, K, N, prod == 0 ? p.nt_up : p.nt_down, sink.perm, sink.w);
+    hipLaunchKernelGGL((tiled_kernel<MODE, BM, NB>), dim3(p.L.len[prod] * kXcds), dim3(256), 0, st, (const uint16_t*)A,
+                       perm, kdiv, tab, kXcds * prod, p.L.list[prod], p.L.lists[prod] == 1 ? 0 : p.L.len[prod],
+                       (const uint16_t*)W0, (const uint16_t*)W1, out, K, N, sink.perm, sink.w);
 }
 
 // one weight block per wavefront exists for 128-row tiles only (planned_nb)
@@ -494,6 +503,13 @@ static void launch_plain_product(const TiledPlan& p, int prod, const void* A, co
     if (p.bm == kBMBig) launch_product<MODE, kBMBig, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else if (nb == 2) launch_product<MODE, kBMSmall, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else launch_product<MODE, kBMSmall, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
+}
+
+void launch_tile_lists(const mmoe_shape& s, const int32_t* offsets, int32_t* tab, hipStream_t st, SlotFilter filt)
+{
+    const TiledPlan p = tiled_plan(s);
+    hipLaunchKernelGGL(tile_table_kernel, dim3(2), dim3(kListThreads), 0, st, offsets, tab, s.S, p.nt_up, p.nt_down, p.bm,
+                       p.L, filt);
 }
 
 TileJob tile_job(const mmoe_shape& s, int32_t* tab)
@@ -516,9 +532,7 @@ int launch_ffn_tiled(const mmoe_shape& s, const void* rows, const int32_t* perm,
     const int P = s.T * s.top_k, d = s.d_model, f = s.d_ff;
     if ((int64_t)P * (d > f ? d : f) >= ((int64_t)1 << 31)) return MMOE_ERR_LIMIT;  // 32-bit byte offsets inside a panel
     const TiledPlan p = tiled_plan(s);
-    if (!tab_ready)
-        hipLaunchKernelGGL(tile_table_kernel, dim3(1), dim3(256), 0, st, offsets, tab, s.S, p.nt_up, p.nt_down, p.bm, p.L,
-                           filt);
+    if (!tab_ready) launch_tile_lists(s, offsets, tab, st, filt);
     if (s.act == MMOE_SWIGLU) {
         if (p.bm == kBMBig)
             launch_product<kTModeSwigluH, kBMBig, 2>(p, 0, rows, perm, s.top_k, tab, W1p, W3p, H, d, f, st);

@@ -363,12 +363,26 @@ int mmoe_layer_forward(const mmoe_shape* shape, const void* X, const int32_t* vi
 // Same kernels as mmoe_layer_forward; the intermediates live in a fixed array in device memory
 // that is part of the loaded code object instead of in a caller's workspace.  Each GPU holds its
 // own copy of the array at its own address; the address is looked up once per device.
-static __device__ __align__(256) unsigned char scratch[MMOE_STATIC_WORKSPACE_BYTES];
+// The size limit a caller sees counts the tile lists with a plain bound of its own (static_need), so
+// that it does not move when the lists' layout does; the slack covers a layout that needs more than
+// that: at most 20 bytes per (row tile, feature tile), under a hundredth of the H and Yg beside them.
+constexpr size_t kStaticSlack = (size_t)1 << 20;
+static __device__ __align__(256) unsigned char scratch[MMOE_STATIC_WORKSPACE_BYTES + kStaticSlack];
 
 namespace {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device, null until looked up
+
+// What a shape counts against MMOE_STATIC_WORKSPACE_BYTES: its workspace, the tile lists taken as two
+// lists per product of one 16-byte entry per 32-row tile and per eight blocks of 128 features.
+size_t static_need(const mmoe_shape& s)
+{
+    const size_t P = (size_t)s.T * s.top_k, tiles = (P + 31) / 32 + s.S;
+    const size_t groups = (s.d_ff / 128 + 7) / 8 + (s.d_model / 128 + 7) / 8;
+    const size_t lists = align256(256 + 32 * (tiles + (tiles + 7) / 8) * groups);
+    return ws_layout(s).total - align256(tiled_table_bytes(s)) + lists;
+}
 
 // Device address of `scratch` on the current device (looked up on the first call on that device).
 int static_scratch(void** out)
@@ -392,11 +406,12 @@ int mmoe_layer_forward_static(const mmoe_shape* shape, const void* X, const int3
 {
     int rc = check_shape(shape);
     if (rc) return rc;
-    if (ws_layout(*shape).total > (size_t)MMOE_STATIC_WORKSPACE_BYTES) return MMOE_ERR_STATIC_LIMIT;
+    if (static_need(*shape) > (size_t)MMOE_STATIC_WORKSPACE_BYTES || ws_layout(*shape).total > sizeof(scratch))
+        return MMOE_ERR_STATIC_LIMIT;
     void* ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
     return mmoe_layer_forward_events(shape, X, vid, Wr, br, M, W1p, W3p, W2p, Y, ws,
-                                     (size_t)MMOE_STATIC_WORKSPACE_BYTES, stream, nullptr);
+                                     sizeof(scratch), stream, nullptr);
 }
 
 int mmoe_expert_plan(const mmoe_shape* shape, int* streaming, int* tile_rows)

@@ -6,24 +6,20 @@
 // Deterministic by construction: the rank of pair p inside its slot is the number of
 // lower pair ids with the same slot, computed from wavefront ballots and integer
 // prefix sums.  There are no cursors bumped by atomics and no waiting between
-// workgroups: three short kernels (histogram, scan, scatter; two when the scatter workgroups can
-// afford to sum the histograms themselves) and one gather.
+// workgroups.  Up to kGroupMaxP pairs one kernel does it all (group_kernel); larger batches take
+// two or three short ones (histogram, scan, scatter; two when the scatter workgroups can afford to sum
+// the histograms themselves).
 //
-// Work split: workgroup b owns pairs [b*2048, (b+1)*2048); inside it wavefront w owns a
-// contiguous quarter, walked 64 pairs at a time in ascending order.
+// Work split of the large form: workgroup b owns pairs [b*2048, (b+1)*2048); inside it wavefront w
+// owns a contiguous quarter, walked 64 pairs at a time in ascending order.
 #include "mmoe_internal.h"
 #include "tile_table.h"
 
 namespace mmoe {
 
 constexpr int kPermThreads = 256;
-static_assert(kPermThreads == 256, "build_tile_lists is written for one workgroup of 256 threads");
 constexpr int kPermWaves = kPermThreads / kWave;
 constexpr int kPairsPerWave = kPermChunk / kPermWaves;  // 512
-// Most grouping workgroups (of 2048 pairs) that each count the whole batch's slots themselves: the LDS
-// atomics of one workgroup serialise on a few slot counters, so beyond two workgroups' worth of pairs
-// the separate histogram kernel (2048 pairs per workgroup) is faster (measured at 8: 31 us against 18).
-constexpr int kOwnHistMaxBlk = 2;
 constexpr int kOwnScanMax = 1 << 14;  // most per-workgroup counts (workgroups x slots) a scatter workgroup sums by itself
 static_assert(kMaxS % kPermThreads == 0, "slots per thread");
 
@@ -55,8 +51,7 @@ __global__ __launch_bounds__(kPermThreads) void slot_hist_kernel(
 __global__ __launch_bounds__(kPermThreads) void slot_scan_kernel(const int32_t* __restrict__ blk_counts,
                                                                  int32_t* __restrict__ blk_base,
                                                                  int32_t* __restrict__ counts,
-                                                                 int32_t* __restrict__ offsets, int nblk, int S,
-                                                                 TileJob tiles)
+                                                                 int32_t* __restrict__ offsets, int nblk, int S)
 {
     __shared__ int tot[kMaxS];
     __shared__ int off[kMaxS + 1];
@@ -93,20 +88,10 @@ __global__ __launch_bounds__(kPermThreads) void slot_scan_kernel(const int32_t* 
         int o = off[s];
         for (int b = 0; b < nblk; ++b) blk_base[(size_t)b * S + s] += o;
     }
-    // the tile lists of the matrix-core expert kernels, from the offsets this workgroup has just written
-    if (tiles.tab) {
-        __syncthreads();
-        build_tile_lists(offsets, tiles.tab, S, tiles.nt_up, tiles.nt_down, tiles.bm, tiles.L);
-    }
 }
 
-// Stable placement of up to 64 pairs, one per lane, behind the pairs placed before them:
-// lane l's peers are the lanes that hold the same slot, found with one ballot per bit of the
-// slot id; its row is the slot's cursor plus the number of peers in lower lanes; the lowest
-// peer then advances the cursor.  `cur` is this wavefront's private cursor row in LDS, and
-// LDS operations of one wavefront execute in program order.
-__device__ __forceinline__ void place_pairs(volatile int* cur, int s, bool valid, int lane, int sbits, int p,
-                                            int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm)
+// Lanes of the wavefront whose pair has this lane's slot: one ballot per bit of the slot id.
+__device__ __forceinline__ unsigned long long same_slot(int s, bool valid, int sbits)
 {
     unsigned long long m = __ballot(valid);
     for (int b = 0; b < sbits; ++b) {
@@ -114,6 +99,17 @@ __device__ __forceinline__ void place_pairs(volatile int* cur, int s, bool valid
         const unsigned long long bal = __ballot(bit);
         m &= bit ? bal : ~bal;
     }
+    return m;
+}
+
+// Stable placement of up to 64 pairs, one per lane, behind the pairs placed before them:
+// a lane's row is the slot's cursor plus the number of peers in lower lanes; the lowest
+// peer then advances the cursor.  `cur` is this wavefront's private cursor row in LDS, and
+// LDS operations of one wavefront execute in program order.
+__device__ __forceinline__ void place_pairs(volatile int* cur, int s, bool valid, int lane, int sbits, int p,
+                                            int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm)
+{
+    const unsigned long long m = same_slot(s, valid, sbits);
     const int rank = __popcll(m & ((1ull << lane) - 1ull));
     int base = 0;
     if (valid) {
@@ -132,12 +128,9 @@ __device__ __forceinline__ void place_pairs(volatile int* cur, int s, bool valid
 //   kFromScan    `blk_base`, written by slot_scan_kernel;
 //   kOwnScan     few workgroups, few slots, so the table of per-workgroup counts is small: every
 //                workgroup sums that table itself, and the scan kernel and its launch are not needed;
-//   kOwnHist     few workgroups, and slot[] already written by the router: every workgroup counts the
-//                pairs in front of its own and the pairs of the whole batch itself (a read of P integers
-//                and integer LDS atomics), and the histogram kernel is not needed either.
-// In the last two the grid has one more workgroup, which places no pairs and writes counts, offsets and
-// the tile lists instead.
-enum { kFromScan = 0, kOwnScan = 1, kOwnHist = 2 };
+// With kOwnScan the grid has one more workgroup, which places no pairs and writes counts and offsets
+// instead.
+enum { kFromScan = 0, kOwnScan = 1 };
 template <int SRC>
 __global__ __launch_bounds__(kPermThreads) void slot_scatter_kernel(const int32_t* __restrict__ slot,
                                                                     const int32_t* __restrict__ blk_base,
@@ -145,51 +138,29 @@ __global__ __launch_bounds__(kPermThreads) void slot_scatter_kernel(const int32_
                                                                     int32_t* __restrict__ counts,
                                                                     int32_t* __restrict__ offsets,
                                                                     int32_t* __restrict__ perm,
-                                                                    int32_t* __restrict__ inv_perm, int P, int S,
-                                                                    TileJob tiles)
+                                                                    int32_t* __restrict__ inv_perm, int P, int S)
 {
     __shared__ int wtot[kPermWaves][kMaxS];  // pairs of each slot owned by each wavefront
     __shared__ int cursor[kPermWaves][kMaxS];
-    constexpr bool SCAN = SRC != kFromScan;
-    __shared__ int tot[SCAN ? kMaxS : 1];      // pairs of each slot in the whole batch, then its first row
-    __shared__ int lower[SRC == kOwnHist ? kMaxS : 1];  // pairs of each slot in front of this workgroup's
+    constexpr bool SCAN = SRC == kOwnScan;
+    __shared__ int tot[SCAN ? kMaxS : 1];    // pairs of each slot in the whole batch, then its first row
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int sbits = 32 - __clz(max(S - 1, 1));  // bits of a slot id
     int before[kMaxS / kPermThreads];             // this workgroup's first row of slot threadIdx.x + 256 i
     if (SCAN) {
         const int b = blockIdx.x;  // nblk: the workgroup that writes the tables
-        if (SRC == kOwnHist) {
-            for (int sl = threadIdx.x; sl < S; sl += kPermThreads) {
-                tot[sl] = 0;
-                lower[sl] = 0;
-            }
-            __syncthreads();
-            const int first = b * kPermChunk;  // this workgroup's first pair (the table writer's: unused)
-            for (int p = threadIdx.x; p < P; p += kPermThreads) {
-                const int sl = slot[p];
-                atomicAdd(&tot[sl], 1);  // integer LDS atomics: the sums do not depend on order
-                if (p < first) atomicAdd(&lower[sl], 1);
-            }
-            __syncthreads();
 #pragma unroll
-            for (int i = 0; i < kMaxS / kPermThreads; ++i) {
-                const int sl = threadIdx.x + i * kPermThreads;
-                before[i] = sl < S ? lower[sl] : 0;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < kMaxS / kPermThreads; ++i) {
-                const int sl = threadIdx.x + i * kPermThreads;
-                int run = 0, mine = 0;
-                if (sl < S)
-                    for (int bb = 0; bb < nblk; ++bb) {
-                        if (bb == b) mine = run;
-                        run += blk_counts[(size_t)bb * S + sl];
-                    }
-                before[i] = mine;
-                if (sl < S) tot[sl] = run;
-            }
+        for (int i = 0; i < kMaxS / kPermThreads; ++i) {
+            const int sl = threadIdx.x + i * kPermThreads;
+            int run = 0, mine = 0;
+            if (sl < S)
+                for (int bb = 0; bb < nblk; ++bb) {
+                    if (bb == b) mine = run;
+                    run += blk_counts[(size_t)bb * S + sl];
+                }
+            before[i] = mine;
+            if (sl < S) tot[sl] = run;
         }
         __syncthreads();
         if (b == nblk)
@@ -200,12 +171,7 @@ __global__ __launch_bounds__(kPermThreads) void slot_scatter_kernel(const int32_
             for (int s0 = 0; s0 < S; s0 += kWave) {
                 const int sl = s0 + threadIdx.x;
                 const int c = sl < S ? tot[sl] : 0;
-                int incl = c;
-#pragma unroll
-                for (int dlt = 1; dlt < kWave; dlt <<= 1) {
-                    const int o = __shfl_up(incl, dlt, kWave);
-                    if ((int)threadIdx.x >= dlt) incl += o;
-                }
+                const int incl = wave_scan(c, lane);
                 if (sl < S) {
                     tot[sl] = carry + incl - c;
                     if (b == nblk) offsets[sl] = carry + incl - c;
@@ -215,10 +181,7 @@ __global__ __launch_bounds__(kPermThreads) void slot_scatter_kernel(const int32_
             if (b == nblk && threadIdx.x == 0) offsets[S] = carry;
         }
         __syncthreads();
-        if (b == nblk) {  // uniform over the workgroup
-            if (tiles.tab) build_tile_lists(offsets, tiles.tab, S, tiles.nt_up, tiles.nt_down, tiles.bm, tiles.L);
-            return;
-        }
+        if (b == nblk) return;  // uniform over the workgroup
     }
     for (int i = threadIdx.x; i < kPermWaves * S; i += kPermThreads) wtot[i / S][i % S] = 0;
     __syncthreads();
@@ -252,83 +215,129 @@ __global__ __launch_bounds__(kPermThreads) void slot_scatter_kernel(const int32_
     }
 }
 
-// The three kernels above in one, for batches whose pairs fit one workgroup's chunk (decode):
-// same ranks, same results, two launches fewer.
-__global__ __launch_bounds__(kPermThreads) void slot_group_small_kernel(
+// Grouping in one launch.  It stands between the router and the expert kernels with nothing to
+// overlap it, so its cost is the length of its dependency chain: every workgroup counts the whole
+// batch by itself (sixteen wavefronts, each a contiguous sixteenth of the pairs, ranks from ballots, the
+// wavefront's running counts in LDS), so that nothing is handed from one workgroup or launch to the
+// next, and workgroup b < nblk then places the pairs of its own four steps.  The last two workgroups
+// write the tile lists of the up and of the down product instead.  Ranks and rows are the large
+// form's.
+// Measured against one workgroup of 256 threads that walked 512 pairs per wavefront, or three to nine
+// workgroups that counted with atomics, list building included: 543 pairs 16.4 -> 7.3 us, 4096 pairs
+// 16.3 -> 9.6 us, 4148 pairs in 90 slots 25.3 -> 12.5 us, 16384 pairs 24 -> 17 us.  Beyond that every
+// workgroup's count of the whole batch outgrows the launches it saves (about 0.5 us per 1024 pairs).
+constexpr int kGroupThreads = kListThreads;
+constexpr int kGroupWaves = kGroupThreads / kWave;
+constexpr int kGroupSteps = 4;                                 // steps of 1024 pairs whose pairs one workgroup places
+constexpr int kGroupChunk = kGroupThreads * kGroupSteps;
+constexpr int kGroupMaxP = 4 * kGroupChunk;
+static_assert(kGroupMaxP <= 65535, "running counts are 16 bits wide");
+
+// LOOKUP: slot[p] is looked up here and written; otherwise the router has written it.
+template <bool LOOKUP>
+__global__ __launch_bounds__(kGroupThreads) void group_kernel(
     const int32_t* __restrict__ vid, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ M,
     int32_t* __restrict__ slot, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm, int P, int k, int V, int E, int S, TileJob tiles)
+    int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm, int P, int k, int V, int E, int S, int nblk,
+    TileJob tiles)
 {
-    __shared__ int wtot[kPermWaves][kMaxS];
-    __shared__ int cursor[kPermWaves][kMaxS];
-    __shared__ int tot[kMaxS];
-    __shared__ int myslot[kPermChunk];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
+    // running counts of every wavefront, then the rows of the slot in front of the wavefront's; the list
+    // builder's scratch at the end
+    __shared__ __align__(16) int scratch[kXcds * kMaxS];
+    static_assert(sizeof(scratch) >= sizeof(uint16_t) * kGroupWaves * kMaxS, "one array for both");
+    __shared__ int off[kMaxS + 1];
+    __shared__ int part[kGroupWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int b = blockIdx.x;
     const int sbits = 32 - __clz(max(S - 1, 1));  // bits of a slot id
-    for (int i = threadIdx.x; i < kPermWaves * S; i += kPermThreads) wtot[i / S][i % S] = 0;
-    __syncthreads();
-    const int wbase = wave * kPairsPerWave;
-    for (int i = lane; i < kPairsPerWave; i += kWave) {
-        int p = wbase + i;
-        if (p < P) {
-            int v = min(max(vid[p / k], 0), V - 1);
-            int e = min(max(topk_idx[p], 0), E - 1);
-            int s = min(max(M[v * E + e], 0), S - 1);
-            slot[p] = s;
-            myslot[p] = s;
-            atomicAdd(&wtot[wave][s], 1);
+    const int steps = (P + kGroupThreads - 1) / kGroupThreads;  // of 64 pairs, per wavefront
+    const int wbase = wave * steps * kWave;
+    volatile uint16_t* row = reinterpret_cast<uint16_t*>(scratch) + wave * kMaxS;
+    for (int s = lane; s < S; s += kWave) row[s] = 0;
+
+    auto slot_of = [&](int step) {
+        const int p = wbase + step * kWave + lane;
+        if (step >= steps || p >= P) return -1;
+        if (!LOOKUP) return slot[p];
+        // clamps keep every later index in range even for invalid ids (results then undefined)
+        const int v = min(max(vid[p / k], 0), V - 1);
+        const int e = min(max(topk_idx[p], 0), E - 1);
+        return min(max(M[v * E + e], 0), S - 1);
+    };
+    int cur[kGroupSteps], nxt[kGroupSteps];
+    int my_slot[kGroupSteps], my_rank[kGroupSteps];  // of the pairs this workgroup places
+#pragma unroll
+    for (int u = 0; u < kGroupSteps; ++u) {
+        nxt[u] = slot_of(u);
+        my_slot[u] = -1;
+    }
+    for (int blk = 0; blk < nblk; ++blk) {
+#pragma unroll
+        for (int u = 0; u < kGroupSteps; ++u) {
+            cur[u] = nxt[u];
+            nxt[u] = slot_of((blk + 1) * kGroupSteps + u);
         }
-    }
-    __syncthreads();
-    for (int s = threadIdx.x; s < S; s += kPermThreads) {
-        int run = 0;
 #pragma unroll
-        for (int w = 0; w < kPermWaves; ++w) run += wtot[w][s];
-        tot[s] = run;
-        counts[s] = run;
-    }
-    __syncthreads();
-    if (threadIdx.x < kWave) {  // exclusive scan of the S totals, 64 at a time; tot[s] becomes offsets[s]
-        int carry = 0;
-        for (int s0 = 0; s0 < S; s0 += kWave) {
-            int s = s0 + threadIdx.x;
-            int c = s < S ? tot[s] : 0;
-            int incl = c;
-#pragma unroll
-            for (int dlt = 1; dlt < kWave; dlt <<= 1) {
-                int o = __shfl_up(incl, dlt, kWave);
-                if ((int)threadIdx.x >= dlt) incl += o;
+        for (int u = 0; u < kGroupSteps; ++u) {
+            if (blk * kGroupSteps + u >= steps) break;  // uniform over the workgroup
+            const int s = cur[u];
+            const bool valid = s >= 0;
+            const unsigned long long m = same_slot(valid ? s : 0, valid, sbits);
+            const int rank = __popcll(m & ((1ull << lane) - 1ull));
+            int prev = 0;
+            if (valid) prev = row[s];
+            __builtin_amdgcn_wave_barrier();
+            if (valid && rank == 0) row[s] = (uint16_t)(prev + __popcll(m));
+            __builtin_amdgcn_wave_barrier();
+            if (blk == b) {
+                my_slot[u] = s;
+                my_rank[u] = prev + rank;
             }
-            if (s < S) {
-                tot[s] = carry + incl - c;
-                offsets[s] = carry + incl - c;
-            }
-            carry += __shfl(incl, kWave - 1, kWave);
         }
-        if (threadIdx.x == 0) offsets[S] = carry;
     }
     __syncthreads();
-    for (int s = threadIdx.x; s < S; s += kPermThreads) {
-        int run = tot[s];
+    uint16_t* const all = reinterpret_cast<uint16_t*>(scratch);
+    int tot = 0;
+    if (tid < S) {  // a slot to a thread (S <= 1024)
 #pragma unroll
-        for (int w = 0; w < kPermWaves; ++w) {
-            cursor[w][s] = run;
-            run += wtot[w][s];
+        for (int w = 0; w < kGroupWaves; ++w) {
+            const int c = all[w * kMaxS + tid];
+            all[w * kMaxS + tid] = (uint16_t)tot;
+            tot += c;
         }
     }
+    const int incl = wave_scan(tot, lane);
+    if (lane == kWave - 1) part[wave] = incl;
     __syncthreads();
-    volatile int* cur = cursor[wave];
-    for (int i0 = 0; i0 < kPairsPerWave; i0 += kWave) {
-        int p = wbase + i0 + lane;
-        bool valid = p < P;
-        if (!__ballot(valid)) break;  // uniform over the wavefront
-        int s = valid ? myslot[p] : 0;
-        place_pairs(cur, s, valid, lane, sbits, p, perm, inv_perm);
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < kGroupWaves; ++w)
+        if (w < wave) before += part[w];
+    if (tid < S) {
+        off[tid] = before + incl - tot;
+        if (b == 0) {
+            counts[tid] = tot;
+            offsets[tid] = before + incl - tot;
+        }
     }
-    if (tiles.tab) {  // uniform over the workgroup; the offsets were written before the barriers above
-        __syncthreads();
-        build_tile_lists(offsets, tiles.tab, S, tiles.nt_up, tiles.nt_down, tiles.bm, tiles.L);
+    if (tid == 0) {
+        off[S] = P;
+        if (b == 0) offsets[S] = P;
+    }
+    __syncthreads();
+    if (b >= nblk) {  // uniform over the workgroup; these two exist only when lists are wanted
+        const int prod = b - nblk;
+        build_tile_lists(off, tiles.tab, S, prod, prod == 0 ? tiles.nt_up : tiles.nt_down, tiles.bm, tiles.L, scratch);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < kGroupSteps; ++u) {
+        if (my_slot[u] < 0) continue;
+        const int p = wbase + (b * kGroupSteps + u) * kWave + lane;
+        const int r = off[my_slot[u]] + all[wave * kMaxS + my_slot[u]] + my_rank[u];
+        if (LOOKUP) slot[p] = my_slot[u];
+        perm[r] = p;
+        inv_perm[p] = r;
     }
 }
 
@@ -375,24 +384,28 @@ int launch_permute(const mmoe_shape& s, const void* X, const int32_t* vid, const
 {
     const int P = s.T * s.top_k;
     const TileJob tiles = tile_job(s, tile_tab);
-    if (nblk == 1)
-        hipLaunchKernelGGL(slot_group_small_kernel, dim3(1), dim3(kPermThreads), 0, st, vid, topk_idx, M, slot, counts,
-                           offsets, perm, inv_perm, P, s.top_k, s.V, s.E, s.S, tiles);
-    else if (slot_ready && nblk <= kOwnHistMaxBlk) {
-        hipLaunchKernelGGL(slot_scatter_kernel<kOwnHist>, dim3(nblk + 1), dim3(kPermThreads), 0, st, slot, blk_base,
-                           blk_counts, nblk, counts, offsets, perm, inv_perm, P, s.S, tiles);
+    if (P <= kGroupMaxP) {
+        const int n = (P + kGroupChunk - 1) / kGroupChunk;
+        const dim3 grid(n + (tiles.tab ? 2 : 0)), block(kGroupThreads);
+        if (slot_ready)
+            hipLaunchKernelGGL(group_kernel<false>, grid, block, 0, st, vid, topk_idx, M, slot, counts, offsets, perm,
+                               inv_perm, P, s.top_k, s.V, s.E, s.S, n, tiles);
+        else
+            hipLaunchKernelGGL(group_kernel<true>, grid, block, 0, st, vid, topk_idx, M, slot, counts, offsets, perm,
+                               inv_perm, P, s.top_k, s.V, s.E, s.S, n, tiles);
     } else {
         hipLaunchKernelGGL(slot_hist_kernel, dim3(nblk), dim3(kPermThreads), 0, st, vid, topk_idx, M, slot,
                            blk_counts, P, s.top_k, s.V, s.E, s.S);
         if ((int64_t)nblk * s.S <= kOwnScanMax) {
             hipLaunchKernelGGL(slot_scatter_kernel<kOwnScan>, dim3(nblk + 1), dim3(kPermThreads), 0, st, slot, blk_base,
-                               blk_counts, nblk, counts, offsets, perm, inv_perm, P, s.S, tiles);
+                               blk_counts, nblk, counts, offsets, perm, inv_perm, P, s.S);
         } else {
             hipLaunchKernelGGL(slot_scan_kernel, dim3(1), dim3(kPermThreads), 0, st, blk_counts, blk_base, counts,
-                               offsets, nblk, s.S, tiles);
+                               offsets, nblk, s.S);
             hipLaunchKernelGGL(slot_scatter_kernel<kFromScan>, dim3(nblk), dim3(kPermThreads), 0, st, slot, blk_base,
-                               blk_counts, nblk, counts, offsets, perm, inv_perm, P, s.S, TileJob());
+                               blk_counts, nblk, counts, offsets, perm, inv_perm, P, s.S);
         }
+        if (tiles.tab) launch_tile_lists(s, offsets, tiles.tab, st);
     }
     if (!Xg) return launch_status();
     const int row_vec = (int)((size_t)s.d_model * elem_size(s.dtype) / 16);

@@ -1,6 +1,6 @@
 // Tile lists of the matrix-core expert kernels: layout, sizes, and the device code that writes
-// them from the device-side `offsets` (run by one workgroup of 256 threads: either the kernel
-// that finishes the grouping, or a kernel of its own when the caller brings the offsets).
+// them from the slots' first rows (one workgroup per product: of the kernel that groups the pairs, or
+// of a kernel of its own when the caller brings the offsets).
 #pragma once
 
 #include "mmoe_internal.h"
@@ -22,24 +22,33 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // for an eighth of the arithmetic), and no matrix instruction is spent on padding beyond the last
 // partial sub-tile.
 //
-// Order.  tab[0], tab[1] = number of row tiles of the up and of the down product; four lists of int4 entries {slot, feature tile within
-// the XCD, first row, rows}, one per (product, feature tiles per XCD): a product with NT feature
-// tiles gives XCD x the tiles nt with nt mod 8 == x, that is ceil or floor of NT/8 of them; list
-// entry `local` is the tile that the workgroup with id 8*local + x computes.  Entries are listed
-// by (slot, group of feature tiles, row tile, feature tile within the group): workgroups start
-// in id order, so the ones that share a token panel and the ones that share a weight panel run
-// close enough in time to find the panel in L2.  The group is sized so that the workgroups
-// resident on an XCD at one time form a block of row tiles x feature tiles that is as square as
-// the slot allows (8 x 4 for a slot of 8 row tiles, 4 x 8 for one of 4).
+// Order.  The tiles of a product are listed by (slot, group of feature tiles, row tile, feature tile
+// within the group): workgroups start in id order, so the ones that share a token panel and the ones
+// that share a weight panel run close enough in time to find the panel in L2.  The group is sized so
+// that the workgroups resident on an XCD at one time form a block of row tiles x feature tiles that is
+// as square as the slot allows (8 x 4 for a slot of 8 row tiles, 4 x 8 for one of 4).
+//
+// XCDs.  Workgroup id 8*local + x runs on XCD x and computes entry `local` of the XCD's list, an int4
+// {slot, feature tile, first row, rows}; tab[8 p + x] = number of entries of product p's list for XCD x.
+// The weight panels of the batch -- the feature tiles of the slots that hold rows, slot after slot -- are
+// dealt to the XCDs in turn: panel c to XCD c mod 8, with all its row tiles, so a weight panel is read
+// by one XCD and every XCD has the same number of panels to within one.  Where NT is a multiple of 8 this
+// gives XCD x the feature tiles nt with nt mod 8 == x of every slot, and the XCDs share one list whose
+// feature tiles count within the XCD (nt = 8*entry + x).  Dealing by nt mod 8 alone whatever NT gave 10
+// feature tiles to the XCDs as 2,2,1,1,1,1,1,1 (1.6 times an even share) and 6 as 1,1,1,1,1,1,0,0.
+// (64 experts of 2048 x 1280, 1037 tokens, 10 up panels a slot: up product 226 -> 179 us; 768 x 3072,
+// 4096 tokens, 6 down panels: 53 -> 47 us.)  Cutting the list into 8 contiguous runs instead was slower
+// where the tiles' costs differ, as they are not known here (4096 x 14336, 777 tokens: 1629 against 1310 us).
+//
 // Target heights of a row tile that the table builder may choose from, in quarters of a 32-row
 // sub-tile: from a full tile (4 upt) down to five eighths of one.
 __host__ __device__ inline int min_height_q(int upt) { return (5 * upt + 1) / 2; }
 constexpr int kMaxHeightCands = 16;
 
 struct TileLists {
-    int hdr;        // int32 index of tab[0]
-    int list[2][2]; // [product: up, down][0: ceil(NT/8) per XCD, 1: floor] -> int4 index into tab
-    int cap[2];     // entries reserved per list of each product
+    int list[2];    // [product: up, down] -> int4 index into tab of XCD 0's list
+    int lists[2];   // 1: the XCDs share one list; kXcds: one list each, `len` entries apart
+    int len[2];     // entries reserved per list of each product: workgroups per XCD
     int upt[2];     // most 32-row sub-tiles of a row tile, per product
     int rows_cap[2]; // most row tiles of each product
     size_t bytes;
@@ -48,7 +57,6 @@ struct TileLists {
 inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down)
 {
     TileLists L;
-    L.hdr = 0;
     L.upt[0] = upt_up;
     L.upt[1] = upt_down;
     // Row tiles the lists have room for: an eighth more than full tiles can need, which is
@@ -58,146 +66,184 @@ inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, in
     auto most_tiles = [&](int upt) { const int full = (P + 32 * upt - 1) / (32 * upt) + S; return full + (full + 7) / 8; };
     L.rows_cap[0] = most_tiles(upt_up);
     L.rows_cap[1] = most_tiles(upt_down);
-    L.cap[0] = L.rows_cap[0] * ((nt_up + kXcds - 1) / kXcds);
-    L.cap[1] = L.rows_cap[1] * ((nt_down + kXcds - 1) / kXcds);
     int at = 16;  // int4 units; the header takes the first 256 bytes
-    for (int p = 0; p < 2; ++p)
-        for (int c = 0; c < 2; ++c) {
-            L.list[p][c] = at;
-            at += L.cap[p];
-        }
+    for (int p = 0; p < 2; ++p) {
+        const int NT = p == 0 ? nt_up : nt_down;
+        L.lists[p] = NT % kXcds == 0 ? 1 : kXcds;
+        L.len[p] = L.rows_cap[p] * ((NT + kXcds - 1) / kXcds);  // a slot's panels on one XCD: ceil(NT / 8) at most
+        L.list[p] = at;
+        at += L.lists[p] * L.len[p];
+    }
     L.bytes = (size_t)at * 16;
     return L;
 }
 
-// One workgroup of 256 threads; every thread of it must call.  `offsets` must be visible to the
-// whole workgroup (written before a workgroup barrier, or by an earlier kernel).
-// Slots that `filt` skips get no tiles.
-__device__ __forceinline__ void build_tile_lists(const int32_t* offsets, int32_t* __restrict__ tab, int S, int nt_up,
-                                                 int nt_down, int bm, TileLists L, SlotFilter filt = SlotFilter())
+// x / d for 0 <= x < 2^24, d > 0: the hardware reciprocal is within one unit in the last place, so the
+// truncated product is off by at most one (an integer division in full is some forty instructions, and
+// the list builder is one serial chain in front of the expert kernels).
+__device__ __forceinline__ int div24(int x, int d)
 {
-    __shared__ int cnt_s[kMaxS];       // rows of each slot
-    __shared__ int off_s[kMaxS];       // first row of each slot
+    const int q = (int)((float)x * __builtin_amdgcn_rcpf((float)d));
+    const int r = x - q * d;
+    return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+}
+
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_scan(int v, int lane)
+{
+#pragma unroll
+    for (int dlt = 1; dlt < kWave; dlt <<= 1) {
+        const int o = __shfl_up(v, dlt, kWave);
+        if (lane >= dlt) v += o;
+    }
+    return v;
+}
+
+// Writes the lists of product p.  One workgroup of kListThreads threads, a slot to a thread; every thread
+// must call.  LDS, both visible to the whole workgroup: `off` holds the first row of every slot and, at S,
+// the number of rows; `first` is kXcds * kMaxS ints of scratch.  Slots that `filt` skips get no tiles.
+constexpr int kListThreads = 1024;
+constexpr int kListWaves = kListThreads / kWave;
+static_assert(kMaxS <= kListThreads && kXcds <= kListWaves, "a slot to a thread, an XCD to a wavefront");
+
+__device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __restrict__ tab, int S, int p, int NT, int bm,
+                                                 const TileLists& L, int* first, SlotFilter filt = SlotFilter())
+{
     __shared__ int base[kMaxS + 1];    // row tiles of the slots before each slot
-    __shared__ int part[256];
+    __shared__ int pbase[kMaxS];       // slots that hold rows before each slot
     __shared__ int cand[kMaxHeightCands];  // row tiles of the whole batch at every candidate height
-    __shared__ int chosen_hq;
-    const int tid = threadIdx.x;
+    __shared__ int part[kListWaves], ppart[kListWaves];
+    __shared__ int total[kXcds];       // entries of every XCD's list
+    __shared__ int units_all, chosen_hq;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int conc = bm == kBMBig ? 32 : 64;   // workgroups resident on one XCD
-    for (int s = tid; s < S; s += 256) {
-        const int o = offsets[s];
-        off_s[s] = o;
-        cnt_s[s] = filt.skips(s) ? 0 : offsets[s + 1] - o;
+    const int upt = L.upt[p];                  // 4 or 8
+    int4* lists = reinterpret_cast<int4*>(tab);
+    auto units_of = [&](int s) { return s >= S || filt.skips(s) ? 0 : (off[s + 1] - off[s] + 31) >> 5; };
+    auto tiles_at = [&](int u, int hq) { return max((u + upt - 1) / upt, div24(4 * u + hq - 1, hq)); };
+    // Target height.  A slot of u sub-tiles is cut into max(ceil(u / upt), ceil(u / h)) tiles, h the
+    // target height, the same for all slots.  h is chosen here, from the counts, so that the product's
+    // tiles fill whole rounds of the chip: with `conc` workgroups resident per XCD a product of M row
+    // tiles takes about ceil(M NT / (8 conc)) rounds of one tile each, a tile costing a fixed part
+    // (half a sub-tile's worth of time: prologue and epilogue) plus its height.  Lower targets also
+    // bring the slots' tile heights closer together.  The cut decides where tiles begin, not what a
+    // row's result is.
+    const int hq_hi = 4 * upt, hq_lo = min_height_q(upt), ncand = hq_hi - hq_lo + 1;  // <= kMaxHeightCands
+    if (tid < kMaxHeightCands) cand[tid] = 0;
+    if (tid == 0) units_all = 0;
+    __syncthreads();
+    {   // thread = (candidate c, one of 64 groups of slots): integer sums, so their order does not matter
+        const int c = tid % kMaxHeightCands;
+        int tiles = 0, units = 0;
+        for (int s = tid / kMaxHeightCands; s < S; s += kListThreads / kMaxHeightCands) {
+            const int u = units_of(s);
+            units += u;
+            if (c < ncand) tiles += tiles_at(u, hq_hi - c);
+        }
+        if (tiles) atomicAdd(&cand[c], tiles);
+        if (c == 0 && units) atomicAdd(&units_all, units);
     }
     __syncthreads();
-    int4* lists = reinterpret_cast<int4*>(tab);
-    for (int p = 0; p < 2; ++p) {
-        const int NT = p == 0 ? nt_up : nt_down;
-        const int upt = L.upt[p];
-        // Target height.  A slot of u sub-tiles is cut into max(ceil(u / upt), ceil(u / h)) tiles, h the
-        // target height, the same for all slots.  h is chosen here, from the counts, so that the product's
-        // tiles fill whole rounds of the chip: with `conc` workgroups resident per XCD a product of M row
-        // tiles takes about ceil(M NT / (8 conc)) rounds of one tile each, a tile costing a fixed part
-        // (half a sub-tile's worth of time: prologue and epilogue) plus its height.  Lower targets also
-        // bring the slots' tile heights closer together.  The cut decides where tiles begin, not what a
-        // row's result is.
-        const int hq_hi = 4 * upt, hq_lo = min_height_q(upt), ncand = hq_hi - hq_lo + 1;  // <= kMaxHeightCands
-        auto tiles_at = [&](int u, int hq) { return max((u + upt - 1) / upt, (4 * u + hq - 1) / hq); };
-        __syncthreads();  // the lists of the product before have been written: cand is free
-        if (tid < kMaxHeightCands) cand[tid] = 0;
-        if (tid == 0) chosen_hq = 0;
-        __syncthreads();
-        {   // thread = (candidate c, one of 16 groups of slots): integer sums, so their order does not matter
-            const int c = tid % kMaxHeightCands;
-            int tiles = 0, units = 0;
-            for (int s = tid / kMaxHeightCands; s < S; s += 256 / kMaxHeightCands) {
-                const int u = (cnt_s[s] + 31) >> 5;
-                units += u;
-                if (c < ncand) tiles += tiles_at(u, hq_hi - c);
-            }
-            if (tiles) atomicAdd(&cand[c], tiles);
-            if (c == 0 && units) atomicAdd(&chosen_hq, units);  // sub-tiles of the whole batch, for now
+    if (tid < kMaxHeightCands) {  // a candidate to a lane; of equal costs the tallest
+        const int U = units_all, M = cand[lane];
+        float cost = INFINITY;
+        // no rows at all, or more tiles than the lists hold (the tallest candidate always fits)
+        if (lane < ncand && M > 0 && M <= L.rows_cap[p]) {
+            const int rounds = (int)(((int64_t)M * NT + kXcds * conc - 1) / (kXcds * conc));
+            cost = (float)rounds * (0.5f + (float)U / (float)M);
         }
-        __syncthreads();
-        if (tid == 0) {
-            const int U = chosen_hq;
-            int best = 0;
-            float best_cost = 0.0f;
-            for (int c = 0; c < ncand; ++c) {
-                const int M = cand[c];
-                if (M == 0 || M > L.rows_cap[p]) break;  // no rows at all, or more tiles than the lists hold
-                const int rounds = (M * NT + kXcds * conc - 1) / (kXcds * conc);
-                const float cost = (float)rounds * (0.5f + (float)U / (float)M);
-                if (c == 0 || cost < best_cost) {
-                    best = c;
-                    best_cost = cost;
+        int best = lane;
+#pragma unroll
+        for (int o = kMaxHeightCands / 2; o >= 1; o >>= 1) {
+            const float oc = __shfl_xor(cost, o, kMaxHeightCands);
+            const int ob = __shfl_xor(best, o, kMaxHeightCands);
+            if (oc < cost || (oc == cost && ob < best)) {
+                cost = oc;
+                best = ob;
+            }
+        }
+        if (lane == 0) chosen_hq = hq_hi - best;
+    }
+    __syncthreads();
+    // exclusive prefix sums of the row tiles and of the slots that hold rows, a slot to a thread
+    const int u_mine = units_of(tid);
+    const int mine = tiles_at(u_mine, chosen_hq), pmine = u_mine > 0 ? 1 : 0;
+    const int incl = wave_scan(mine, lane), pincl = wave_scan(pmine, lane);
+    if (lane == kWave - 1) {
+        part[wave] = incl;
+        ppart[wave] = pincl;
+    }
+    __syncthreads();
+    int before = 0, pbefore = 0, total_m = 0;
+#pragma unroll
+    for (int w = 0; w < kListWaves; ++w) {
+        if (w < wave) {
+            before += part[w];
+            pbefore += ppart[w];
+        }
+        total_m += part[w];
+    }
+    if (tid < S) {
+        base[tid] = before + incl - mine;
+        pbase[tid] = pbefore + pincl - pmine;
+    }
+    if (tid == 0) base[S] = total_m;
+    __syncthreads();
+    const bool shared_list = L.lists[p] == 1;
+    // Panels of slot s (the r-th that holds rows) on XCD x: the c = r NT + nt with c mod 8 == x.
+    // panels_before(x, c) of them lie before panel c.
+    auto panels_before = [](int x, int c) { return (c + kXcds - 1 - x) / kXcds; };
+    if (!shared_list) {
+        // first entry of every slot in every XCD's list: an XCD to a wavefront, 64 slots at a time
+        if (wave < kXcds) {
+            const int x = wave;
+            int carry = 0;
+            for (int s0 = 0; s0 < S; s0 += kWave) {
+                const int s = s0 + lane;
+                int c = 0;
+                if (s < S) {
+                    const int c0 = pbase[s] * NT;
+                    c = (base[s + 1] - base[s]) * (panels_before(x, c0 + NT) - panels_before(x, c0));
                 }
+                const int inc = wave_scan(c, lane);
+                if (s < S) first[x * kMaxS + s] = carry + inc - c;
+                carry += __shfl(inc, kWave - 1, kWave);
             }
-            chosen_hq = hq_hi - best;
-        }
-        __syncthreads();
-        const int hq = chosen_hq;
-        // exclusive prefix sum of the row tiles per slot: a run of slots per thread, then a scan of the runs
-        auto tiles_of = [&](int s) { return tiles_at((cnt_s[s] + 31) >> 5, hq); };
-        const int chunk = (S + 255) / 256;
-        const int s_lo = min(tid * chunk, S), s_hi = min(s_lo + chunk, S);
-        int mine = 0;
-        for (int s = s_lo; s < s_hi; ++s) mine += tiles_of(s);
-        __syncthreads();  // the lists of the product before have been written: base and part are free
-        part[tid] = mine;
-        __syncthreads();
-        if (tid < kWave) {  // inclusive scan of the 256 runs by the first wavefront: four per lane, then across the lanes
-            int v[4], sum = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                sum += part[4 * tid + i];
-                v[i] = sum;
-            }
-            int incl = sum;
-#pragma unroll
-            for (int dlt = 1; dlt < kWave; dlt <<= 1) {
-                const int o = __shfl_up(incl, dlt, kWave);
-                if (tid >= dlt) incl += o;
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) part[4 * tid + i] = incl - sum + v[i];
-        }
-        __syncthreads();
-        int run = part[tid] - mine;
-        for (int s = s_lo; s < s_hi; ++s) {
-            base[s] = run;
-            run += tiles_of(s);
-        }
-        const int total_m = part[255];
-        if (tid == 0) {
-            base[S] = total_m;
-            tab[L.hdr + p] = total_m;
-        }
-        __syncthreads();
-        for (int c = 0; c < 2; ++c) {
-            if (c == 1 && NT % kXcds == 0) break;  // every XCD has the same number of feature tiles: one list
-            const int nt_x = c == 0 ? (NT + kXcds - 1) / kXcds : NT / kXcds;
-            const int n = total_m * nt_x;
-            for (int e = tid; e < n; e += 256) {
-                int lo = 0, hi = S;  // largest s with base[s]*nt_x <= e (empty slots have equal bounds)
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (base[mid] * nt_x <= e) lo = mid; else hi = mid;
-                }
-                const int s = lo, mt = base[s + 1] - base[s];
-                const int rem = e - base[s] * nt_x;
-                // groups of g feature tiles; inside a group the feature tile runs fastest
-                const int g = min(nt_x, max(kNtGroup, conc / mt));
-                const int grp = rem / (g * mt), within = rem - grp * (g * mt);
-                const int g_sz = min(g, nt_x - grp * g);
-                const int i = within / g_sz, ntl = grp * g + within - i * g_sz;
-                // row tile i of the slot: the first `extra` tiles are one sub-tile taller
-                const int u = (cnt_s[s] + 31) >> 5, h = u / mt, extra = u - h * mt;
-                const int row0 = 32 * (i * h + min(i, extra));
-                const int rows = 32 * (h + (i < extra ? 1 : 0));
-                lists[L.list[p][c] + e] = make_int4(s, ntl, off_s[s] + row0, min(rows, cnt_s[s] - row0));
+            if (lane == 0) {
+                tab[kXcds * p + x] = carry;
+                total[x] = carry;
             }
         }
+        __syncthreads();
+    } else if (tid < kXcds) {
+        tab[kXcds * p + tid] = total_m * (NT / kXcds);
+    }
+    // the lists: all threads on the shared one, an eighth of them on each XCD's own
+    constexpr int kPerXcd = kListThreads / kXcds;
+    const int x = shared_list ? 0 : tid / kPerXcd;
+    const int n = shared_list ? total_m * (NT / kXcds) : total[x];
+    for (int e = shared_list ? tid : tid % kPerXcd; e < n; e += shared_list ? kListThreads : kPerXcd) {
+        auto first_of = [&](int s) { return shared_list ? base[s] * (NT / kXcds) : first[x * kMaxS + s]; };
+        int lo = 0, hi = S;  // largest s with first_of(s) <= e (slots without entries have equal bounds)
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (first_of(mid) <= e) lo = mid; else hi = mid;
+        }
+        const int s = lo, mt = base[s + 1] - base[s];
+        const int rem = e - first_of(s);
+        const int c0 = pbase[s] * NT, j0 = panels_before(x, c0);
+        const int nt_x = shared_list ? NT / kXcds : panels_before(x, c0 + NT) - j0;  // the slot's panels on this XCD
+        // groups of g feature tiles; inside a group the feature tile runs fastest
+        const int g = min(nt_x, max(kNtGroup, div24(conc, mt)));
+        const int grp = div24(rem, g * mt), within = rem - grp * (g * mt);
+        const int g_sz = min(g, nt_x - grp * g);
+        const int i = div24(within, g_sz), j = grp * g + within - i * g_sz;  // j-th panel of the slot here
+        const int ntl = shared_list ? j : (j0 + j) * kXcds + x - c0;
+        // row tile i of the slot: the first `extra` tiles are one sub-tile taller
+        const int u = units_of(s), h = div24(u, mt), extra = u - h * mt;
+        const int row0 = 32 * (i * h + min(i, extra));
+        const int rows = 32 * (h + (i < extra ? 1 : 0));
+        lists[L.list[p] + x * L.len[p] + e] = make_int4(s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
     }
 }
 
@@ -211,5 +257,9 @@ struct TileJob {
 
 // The job for this shape (host side; defined beside the matrix-core kernels).  Null `tab`: no job.
 TileJob tile_job(const mmoe_shape& s, int32_t* tab);
+
+// The lists of both products from the device-side `offsets`, in a launch of their own.
+void launch_tile_lists(const mmoe_shape& s, const int32_t* offsets, int32_t* tab, hipStream_t st,
+                       SlotFilter filt = SlotFilter());
 
 }  // namespace mmoe

@@ -118,6 +118,51 @@ def test_tiled_row_remainders(mm, gc, oracle, act, k, rows):
                          tile_rows=rows)
 
 
+@pytest.mark.parametrize("S", [1, 2, 63, 64, 65, 1024])
+def test_grouping_sizes(mm, S):
+    """Integer outputs of the grouping at the edges of its steps and of its two forms, against a stable sort:
+    slots in use at random, all in one slot, some empty."""
+    import torch
+    for P, k in ((1, 1), (63, 1), (64, 2), (1023, 1), (1024, 4), (1025, 1), (4096, 2), (4097, 1), (8200, 4), (16384, 2),
+                 (16385, 1), (40000, 1)):
+        for spread in (S, max(1, S // 3)):
+            g = torch.Generator().manual_seed(P * 7 + S)
+            T, E = (P + k - 1) // k, 8
+            V = (S + E - 1) // E
+            shape = mm.make_shape(T, 256, 256, V, E, S, k, "bf16", "relu")
+            vid = torch.randint(0, V, (T,), generator=g, dtype=torch.int32)
+            idx = torch.randint(0, E, (T, k), generator=g, dtype=torch.int32)
+            M = torch.randint(0, spread, (V, E), generator=g, dtype=torch.int32)
+            out = mm.remap_permute(shape, torch.zeros((T, 256), dtype=torch.bfloat16, device="cuda"), vid.cuda(),
+                                   idx.cuda(), M.cuda(), mm.alloc_workspace(shape))
+            slot = M[vid.long().repeat_interleave(k), idx.flatten().long()]
+            perm = torch.argsort(slot, stable=True)
+            counts = torch.bincount(slot, minlength=S)
+            inv = torch.empty_like(perm)
+            inv[perm] = torch.arange(T * k)
+            offsets = torch.cat([torch.zeros(1, dtype=torch.long), counts.cumsum(0)])
+            for name, got, want in zip(("slot", "counts", "offsets", "perm", "inv_perm"), out,
+                                       (slot, counts, offsets, perm, inv)):
+                assert torch.equal(got.cpu().long(), want.long()), (P, S, spread, name)
+
+
+UNEVEN_TILES = [
+    # feature tiles that do not divide among the XCDs, one list of tiles per XCD: fewer tiles than XCDs, one
+    # slot, many slots (some empty), one slot with most of the rows, an even up product beside an uneven down
+    synth.Config("uneven_one_tile", 200, 256, 256, 1, 1, 1, "bf16", "relu", seed=700),
+    synth.Config("uneven_d768_f1280", 900, 768, 1280, 2, 8, 2, "bf16", "swiglu", seed=701),
+    synth.Config("uneven_skew", 2100, 768, 1536, 3, 16, 2, "bf16", "gelu", seed=702, bias_alpha=2.5, vid_mode="zipf"),
+    synth.Config("uneven_empty_slots", 1500, 1280, 256, 4, 16, 1, "bf16", "relu", seed=703, bias_alpha=6.0),
+    synth.Config("uneven_down_only", 700, 768, 1024, 2, 4, 4, "bf16", "swiglu", seed=704),
+]
+
+
+@pytest.mark.parametrize("rows", [256, 128])
+@pytest.mark.parametrize("cfg", UNEVEN_TILES, ids=lambda c: c.name)
+def test_uneven_feature_tiles(mm, gc, oracle, cfg, rows):
+    staged_vs_oracle(mm, gc, oracle, cfg, tile_rows=rows)
+
+
 GATES_AND_ACTS = [
     # Switch-style gate (probability over all experts, not renormalised), top-1, ReLU and GELU experts,
     # three variants; streaming kernels and matrix-core kernels, fp32 and bf16
