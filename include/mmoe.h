@@ -266,9 +266,9 @@ int mmoe_layer_forward_events(const mmoe_shape *shape, const void *X, const int3
 /*
  * Host only, pure: which expert-stage kernels
  * mmoe_expert_ffn and mmoe_layer_forward will use for this shape.  *streaming = 1: the
- * weight-streaming kernels (every fp32 shape; bf16 with few rows per slot), *tile_rows = 32
+ * weight-streaming kernels (few rows per slot), *tile_rows = 32
  * (rows of a slot per pass over its weights); *streaming = 0: the matrix-core kernels with
- * tiles of *tile_rows (128 or 256) token rows.  The choice depends on the shape only.
+ * tiles of *tile_rows (128 or 256; fp32: 96) token rows.  The choice depends on the shape only.
  */
 int mmoe_expert_plan(const mmoe_shape *shape, int *streaming, int *tile_rows);
 

@@ -53,14 +53,14 @@ __device__ __forceinline__ float silu_mul_t(float g, float u)
 // The lists of product blockIdx.x, for callers that bring the offsets.
 __global__ __launch_bounds__(kListThreads) void tile_table_kernel(const int32_t* __restrict__ offsets,
                                                                   int32_t* __restrict__ tab, int S, int nt_up,
-                                                                  int nt_down, int bm, TileLists L, SlotFilter filt)
+                                                                  int nt_down, TileLists L, SlotFilter filt)
 {
     __shared__ int off[kMaxS + 1];
     __shared__ int first[kXcds * kMaxS];
     for (int s = threadIdx.x; s <= S; s += kListThreads) off[s] = offsets[s];
     __syncthreads();
     const int p = blockIdx.x;
-    build_tile_lists(off, tab, S, p, p == 0 ? nt_up : nt_down, bm, L, first, filt);
+    build_tile_lists(off, tab, S, p, p == 0 ? nt_up : nt_down, L, first, filt);
 }
 
 template <int MODE, int BM, int NB>
@@ -428,6 +428,12 @@ static int planned_nb(const mmoe_shape& s, int bm, int N, bool gated)
 
 static void tiled_nts(const mmoe_shape& s, int bm, int& nt_up, int& nt_down, int& nb_up, int& nb_down)
 {
+    if (s.dtype == MMOE_F32) {
+        nb_up = nb_down = 1;
+        nt_up = s.d_ff / kFeatF32;
+        nt_down = s.d_model / kFeatF32;
+        return;
+    }
     nb_up = planned_nb(s, bm, s.d_ff, s.act == MMOE_SWIGLU);
     nb_down = planned_nb(s, bm, s.d_model, false);
     nt_up = s.act == MMOE_SWIGLU ? s.d_ff / (kBN / 2) : s.d_ff / (128 * nb_up);
@@ -443,6 +449,7 @@ static void tiled_nts(const mmoe_shape& s, int bm, int& nt_up, int& nt_down, int
 // lose from 79 rows per slot (512 tokens) on.
 int planned_tile_rows(const mmoe_shape& s)
 {
+    if (s.dtype == MMOE_F32) return kFRows;  // the fp32 kernel has one height
     if (s.tile_rows) return s.tile_rows;  // forced for this call (checked by check_shape: 128 or 256)
     const int64_t P = (int64_t)s.T * s.top_k;
     return (s.d_model <= 1024 || P < (int64_t)64 * s.S) ? kBMSmall : kBMBig;
@@ -451,22 +458,15 @@ int planned_tile_rows(const mmoe_shape& s)
 // Most sub-tiles of a row tile: a full tile.  (Shorter tiles for products with few tiles were
 // measured on the Switch shape and lose: every tile streams its whole weight panel, and a step of
 // a short tile is over before the copies issued two steps earlier have landed.)
-static int planned_upt(const mmoe_shape&, int bm, int) { return bm / 32; }
-
-// Everything the launches of one shape share: tile height, weight blocks per wavefront and feature
-// tiles of both products, and the tile lists' layout.
-struct TiledPlan {
-    int bm, nt_up, nt_down, nb_up, nb_down;
-    TileLists L;
-};
+static int planned_upt(const mmoe_shape&, int bm) { return bm / 32; }
 
 static TiledPlan tiled_plan(const mmoe_shape& s)
 {
     TiledPlan p;
     p.bm = planned_tile_rows(s);
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
-    p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm, p.nt_up),
-                     planned_upt(s, p.bm, p.nt_down));
+    p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm), planned_upt(s, p.bm), p.bm,
+                     s.dtype == MMOE_F32);
     return p;
 }
 
@@ -508,7 +508,7 @@ static void launch_plain_product(const TiledPlan& p, int prod, const void* A, co
 void launch_tile_lists(const mmoe_shape& s, const int32_t* offsets, int32_t* tab, hipStream_t st, SlotFilter filt)
 {
     const TiledPlan p = tiled_plan(s);
-    hipLaunchKernelGGL(tile_table_kernel, dim3(2), dim3(kListThreads), 0, st, offsets, tab, s.S, p.nt_up, p.nt_down, p.bm,
+    hipLaunchKernelGGL(tile_table_kernel, dim3(2), dim3(kListThreads), 0, st, offsets, tab, s.S, p.nt_up, p.nt_down,
                        p.L, filt);
 }
 
@@ -519,7 +519,6 @@ TileJob tile_job(const mmoe_shape& s, int32_t* tab)
     j.tab = tab;
     j.nt_up = p.nt_up;
     j.nt_down = p.nt_down;
-    j.bm = p.bm;
     j.L = p.L;
     return j;
 }
@@ -528,11 +527,12 @@ int launch_ffn_tiled(const mmoe_shape& s, const void* rows, const int32_t* perm,
                      const void* W1p, const void* W3p, const void* W2p, void* H, float* Yg, int32_t* tab,
                      hipStream_t st, hipEvent_t mid, bool tab_ready, SlotFilter filt, GateSink sink)
 {
-    if (s.dtype != MMOE_BF16) return MMOE_ERR_DTYPE;
     const int P = s.T * s.top_k, d = s.d_model, f = s.d_ff;
     if ((int64_t)P * (d > f ? d : f) >= ((int64_t)1 << 31)) return MMOE_ERR_LIMIT;  // 32-bit byte offsets inside a panel
+    if (sink.w && (s.top_k != 1 || !sink.perm || !sink.Y)) return MMOE_ERR_DIM;
     const TiledPlan p = tiled_plan(s);
     if (!tab_ready) launch_tile_lists(s, offsets, tab, st, filt);
+    if (s.dtype == MMOE_F32) return launch_products_f32(s, p, rows, perm, tab, W1p, W3p, W2p, H, Yg, st, mid, sink);
     if (s.act == MMOE_SWIGLU) {
         if (p.bm == kBMBig)
             launch_product<kTModeSwigluH, kBMBig, 2>(p, 0, rows, perm, s.top_k, tab, W1p, W3p, H, d, f, st);
@@ -545,7 +545,6 @@ int launch_ffn_tiled(const mmoe_shape& s, const void* rows, const int32_t* perm,
     }
     if (mid && hipEventRecord(mid, st) != hipSuccess) return MMOE_ERR_LAUNCH;
     if (sink.w) {
-        if (s.top_k != 1 || !sink.perm || !sink.Y) return MMOE_ERR_DIM;
         launch_plain_product<kTModeGatedY>(p, 1, H, nullptr, 1, tab, W2p, sink.Y, f, d, st, sink);
     } else {
         launch_plain_product<kTModePlainF32>(p, 1, H, nullptr, 1, tab, W2p, Yg, f, d, st);

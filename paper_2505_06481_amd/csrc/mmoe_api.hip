@@ -50,17 +50,25 @@ WsLayout ws_layout(const mmoe_shape& s)
     return L;
 }
 
+// fp32: most rows per slot, on average, for the streaming kernels.  Measured with each kernel forced:
+// 768 x 3072 top-1, 13 slots: 77 (streaming) against 83 us at 9.8 rows per slot, 90 against 84 at 15.4;
+// 1024 x 2048 SwiGLU top-2: 95 against 92 us at 8 rows, 115 against 91 at 17; 2048 x 4096 SwiGLU: equal at 10.
+constexpr int kF32StreamRows = 12;
+
 bool use_skinny(const mmoe_shape& s)
 {
-    // fp32 always streams (fp32 MFMA, full precision).  bf16 streams when a slot sees few
-    // rows: the weights are then read once from HBM and that read is the bound.  The
+    // A batch streams when a slot sees few rows: the weights are then read once from HBM and that
+    // read is the bound.  The
     // streaming kernel takes 32 rows of a slot per pass over its weights, so it only pays
     // while the fullest slot stays near that.  Measured with each kernel forced: on the
     // Mixtral shape (352 MB a slot) it wins up to an average of 16 rows per slot and loses
     // quickly beyond (1.21 ms against 0.83 ms at 40); on the Switch shape (9 MB a slot, a
     // second pass finds the weights in cache) up to 32.
-    if (s.dtype == MMOE_F32) return true;
     const int64_t P = (int64_t)s.T * s.top_k;
+    if (s.dtype == MMOE_F32) {
+        const int64_t widest = s.d_model > s.d_ff ? s.d_model : s.d_ff;
+        return P <= (int64_t)kF32StreamRows * s.S || P * widest >= ((int64_t)1 << 31);  // the tile lists' limit
+    }
     const bool small_experts = (int64_t)s.d_model * s.d_ff <= ((int64_t)4 << 20);
     return P <= (int64_t)(small_experts ? 32 : 16) * s.S;
 }

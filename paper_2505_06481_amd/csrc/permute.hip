@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(
     __syncthreads();
     if (b >= nblk) {  // uniform over the workgroup; these two exist only when lists are wanted
         const int prod = b - nblk;
-        build_tile_lists(off, tiles.tab, S, prod, prod == 0 ? tiles.nt_up : tiles.nt_down, tiles.bm, tiles.L, scratch);
+        build_tile_lists(off, tiles.tab, S, prod, prod == 0 ? tiles.nt_up : tiles.nt_down, tiles.L, scratch);
         return;
     }
 #pragma unroll

@@ -41,8 +41,9 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // where the tiles' costs differ, as they are not known here (4096 x 14336, 777 tokens: 1629 against 1310 us).
 //
 // Target heights of a row tile that the table builder may choose from, in quarters of a 32-row
-// sub-tile: from a full tile (4 upt) down to five eighths of one.
-__host__ __device__ inline int min_height_q(int upt) { return (5 * upt + 1) / 2; }
+// sub-tile: from a full tile (4 upt) down to hq_lo.  bf16: five eighths of a full tile (shorter tiles are
+// bound by what they move).  fp32: one sub-tile (the matrix rate bounds tiles of any height, and short
+// ones share out a product of few tiles evenly).
 constexpr int kMaxHeightCands = 16;
 
 struct TileLists {
@@ -50,22 +51,29 @@ struct TileLists {
     int lists[2];   // 1: the XCDs share one list; kXcds: one list each, `len` entries apart
     int len[2];     // entries reserved per list of each product: workgroups per XCD
     int upt[2];     // most 32-row sub-tiles of a row tile, per product
+    int hq_lo[2];   // least target height, in quarters of a sub-tile
+    int conc;       // workgroups that an XCD works on at a time, for the choice of the height
     int rows_cap[2]; // most row tiles of each product
     size_t bytes;
 };
 
-inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down)
+inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down, int bm, bool f32)
 {
     TileLists L;
     L.upt[0] = upt_up;
     L.upt[1] = upt_down;
-    // Row tiles the lists have room for: an eighth more than full tiles can need, which is
-    // sum_s ceil(ceil(c_s / 32) / upt) <= P / (32 upt) + S.  The grid of a product is sized by this bound
-    // (the host does not know the counts), and a workgroup without a tile still waits for a compute unit
-    // before it can leave, so the room for lower target heights is kept small.
-    auto most_tiles = [&](int upt) { const int full = (P + 32 * upt - 1) / (32 * upt) + S; return full + (full + 7) / 8; };
-    L.rows_cap[0] = most_tiles(upt_up);
-    L.rows_cap[1] = most_tiles(upt_down);
+    // fp32: two workgroups of a compute unit share its matrix pipes, so they count as one round of two
+    L.conc = bm == kBMBig || f32 ? 32 : 64;
+    for (int p = 0; p < 2; ++p) {
+        // Row tiles the lists have room for: an eighth more than full tiles can need (fp32: than tiles of two
+        // sub-tiles), which is sum_s ceil(ceil(c_s / 32) / upt) <= P / (32 upt) + S.  The grid of a product is
+        // sized by this bound (the host does not know the counts), and a workgroup without a tile still waits
+        // for a compute unit before it can leave, so the room for lower target heights is kept small.
+        const int upt = L.upt[p], u = f32 ? 2 : upt;
+        const int full = (P + 32 * u - 1) / (32 * u) + S;
+        L.rows_cap[p] = full + (full + 7) / 8;
+        L.hq_lo[p] = f32 ? 4 : (5 * upt + 1) / 2;
+    }
     int at = 16;  // int4 units; the header takes the first 256 bytes
     for (int p = 0; p < 2; ++p) {
         const int NT = p == 0 ? nt_up : nt_down;
@@ -106,7 +114,7 @@ constexpr int kListThreads = 1024;
 constexpr int kListWaves = kListThreads / kWave;
 static_assert(kMaxS <= kListThreads && kXcds <= kListWaves, "a slot to a thread, an XCD to a wavefront");
 
-__device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __restrict__ tab, int S, int p, int NT, int bm,
+__device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __restrict__ tab, int S, int p, int NT,
                                                  const TileLists& L, int* first, SlotFilter filt = SlotFilter())
 {
     __shared__ int base[kMaxS + 1];    // row tiles of the slots before each slot
@@ -116,11 +124,10 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     __shared__ int total[kXcds];       // entries of every XCD's list
     __shared__ int units_all, chosen_hq;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int conc = bm == kBMBig ? 32 : 64;   // workgroups resident on one XCD
-    const int upt = L.upt[p];                  // 4 or 8
+    const int conc = L.conc, upt = L.upt[p];
     int4* lists = reinterpret_cast<int4*>(tab);
     auto units_of = [&](int s) { return s >= S || filt.skips(s) ? 0 : (off[s + 1] - off[s] + 31) >> 5; };
-    auto tiles_at = [&](int u, int hq) { return max((u + upt - 1) / upt, div24(4 * u + hq - 1, hq)); };
+    auto tiles_at = [&](int u, int hq) { return max(div24(u + upt - 1, upt), div24(4 * u + hq - 1, hq)); };
     // Target height.  A slot of u sub-tiles is cut into max(ceil(u / upt), ceil(u / h)) tiles, h the
     // target height, the same for all slots.  h is chosen here, from the counts, so that the product's
     // tiles fill whole rounds of the chip: with `conc` workgroups resident per XCD a product of M row
@@ -128,7 +135,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     // (half a sub-tile's worth of time: prologue and epilogue) plus its height.  Lower targets also
     // bring the slots' tile heights closer together.  The cut decides where tiles begin, not what a
     // row's result is.
-    const int hq_hi = 4 * upt, hq_lo = min_height_q(upt), ncand = hq_hi - hq_lo + 1;  // <= kMaxHeightCands
+    const int hq_hi = 4 * upt, ncand = hq_hi - L.hq_lo[p] + 1;  // <= kMaxHeightCands
     if (tid < kMaxHeightCands) cand[tid] = 0;
     if (tid == 0) units_all = 0;
     __syncthreads();
@@ -248,10 +255,23 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
 }
 
 
+// Everything the launches of one shape share: tile height, weight blocks per wavefront and feature
+// tiles of both products, and the tile lists' layout.
+struct TiledPlan {
+    int bm, nt_up, nt_down, nb_up, nb_down;
+    TileLists L;
+};
+
+// fp32 (ffn_tiled_f32.hip): tiles of up to 96 rows x 64 features.
+constexpr int kFRows = 96, kFeatF32 = 64;
+int launch_products_f32(const mmoe_shape& s, const TiledPlan& p, const void* rows, const int32_t* perm, const int32_t* tab,
+                        const void* W1p, const void* W3p, const void* W2p, void* H, float* Yg, hipStream_t st,
+                        hipEvent_t mid, GateSink sink);
+
 // What the grouping kernels need to write the lists themselves (null `tab`: they do not).
 struct TileJob {
     int32_t* tab;
-    int nt_up, nt_down, bm;
+    int nt_up, nt_down;
     TileLists L;
 };
 

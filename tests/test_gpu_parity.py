@@ -118,6 +118,16 @@ def test_tiled_row_remainders(mm, gc, oracle, act, k, rows):
                          tile_rows=rows)
 
 
+@pytest.mark.parametrize("act,k,d,f", [("swiglu", 1, 256, 512), ("relu", 1, 768, 256), ("gelu", 2, 512, 1280)])
+def test_tiled_f32_row_remainders(mm, gc, oracle, act, k, d, f):
+    """Every number of 16-row fragments of the fp32 tiles, full and one-row remainders, one to three tiles in
+    a slot, one and several chains of the reduction: a single slot (two when k = 2) that holds T rows."""
+    for T in (25, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 128, 129, 192, 193, 200, 300):
+        cfg = synth.Config(f"rem32_{act}_{T}", T, d, f, 1, k, k, "f32", act, seed=800 + T)
+        case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
+        assert mm.expert_plan(case.shape) == (False, 96)
+
+
 @pytest.mark.parametrize("S", [1, 2, 63, 64, 65, 1024])
 def test_grouping_sizes(mm, S):
     """Integer outputs of the grouping at the edges of its steps and of its two forms, against a stable sort:
