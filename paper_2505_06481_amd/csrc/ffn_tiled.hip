@@ -128,10 +128,10 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     // The copies are written in assembly so that the compiler's wait-count bookkeeping does not
     // see them (it would drain every load in flight before each LDS read); the waits that order
     // them are written out next to the barriers.  M0 is only used here.
-    auto copy_a = [&](int stage, int kt, int i) {
+    auto copy_a = [&](int stage, int kt, int i) {  // stage: byte offset in lds_a
         const char* ab = a_base + (size_t)kt * (kBK * 2);
         const uint32_t dst =
-            (uint32_t)(uintptr_t)(lptr_t)(lds_a + stage * kTileBytes + (i * kThreads + wave * 64) * 16);
+            (uint32_t)(uintptr_t)(lptr_t)(lds_a + stage + (i * kThreads + wave * 64) * 16);
         asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                      :
                      : "v"(a_goff[i]), "s"(ab), "s"(dst)
@@ -199,11 +199,16 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     // vector instruction (fragments come from LDS and memory reads, whose waits the compiler
     // inserts), and the accumulators are read behind the s_nops that follow the loop.
     //
-    // Pipeline (k step t = 64 k = two 32-k slices; step t's tokens live in LDS stage t mod 4):
+    // Short tiles (small NJ) are bound by the latency of memory instead: a step is over long before a load
+    // issued in it has come back.  They copy only the 32 NJ rows they have (NJ instructions per wavefront and
+    // step, not BM / 32), use the LDS and the registers that this leaves for more steps in flight, and so have as
+    // many bytes on the way as a full tile.  (4096 x 14336, 777 tokens, tiles of 1 to 4 sub-tiles: 1259 -> 1235 us; 768 x 3072 top-1, 543 tokens: 59.4 -> 55.9 us.)
+    //
+    // Pipeline (k step t = 64 k = two 32-k slices; step t's tokens live in LDS stage t mod kStages):
     //   weights   slice g is loaded straight into registers kSlices - 1 slices ahead of its use; these
     //             are ordinary loads and the compiler inserts their waits;
-    //   tokens    the copies of step t+3 are issued during step t, into the stage that step t-1 has
-    //             left, and must have landed by the barrier of step t+1; token fragments roll through a
+    //   tokens    the copies of step t + kStages - 1 are issued during step t, into the stage that step
+    //             t-1 has left, and must have landed kDeep steps later; token fragments roll through a
     //             ring of RF register sets: as soon as the kNW matrix instructions that use a fragment
     //             have been issued, the fragment RF further on is fetched into its registers;
     //   barrier   one per step, RF/2 groups before its end: by then every wavefront's reads of the
@@ -214,10 +219,10 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     // What orders the copies.  The compiler does not see them, so the wait that makes them
     // land is written out next to every barrier: s_waitcnt vmcnt(N) returns when at most N of
     // this wavefront's vector-memory instructions are outstanding, and they complete in issue
-    // order.  Rule at every such wait: only the most recent group of kNP copies may still be in
-    // flight, every older one has landed.  That holds if at least N vector-memory instructions
-    // were issued after the last copy of the second most recent group: the kNP copies of the most
-    // recent group plus weight-fragment loads, whose place in the instruction stream the compiler
+    // order.  Rule at every such wait: only the most recent kDeep steps' copies (NJ each, kNP at most
+    // together) may still be in flight, every older one has landed.  That holds if at least N
+    // vector-memory instructions were issued after the last of the older ones: the kDeep NJ copies
+    // plus weight-fragment loads, whose place in the instruction stream the compiler
     // chooses.  Their count is therefore not taken on trust: tests/test_tiled_wait_counts.py
     // reads the compiler's assembly output for this file and checks the rule at every written-out
     // wait of every instantiation, along every path that reaches it.
@@ -229,9 +234,14 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     const int last = nkt - 1;
     const int last_slice = K / 32 - 1;
     constexpr int kUnroll = (BM == kBMBig || NB == 1) ? 4 : 2;
-    constexpr int kSlices = NB == 1 ? 8 : 4;  // ring of weight slices in registers (four steps, two steps)
     auto run = [&](auto njc) {
         constexpr int NJ = decltype(njc)::value;
+        // ring of weight slices in registers (four steps, two steps): what the accumulators leave room for
+        constexpr int kSlices = NB == 1 || (BM == kBMBig && NJ <= 4) ? 8 : 4;
+        constexpr int kDeep = kNP / NJ;
+        constexpr int kStages = kDeep + 3;
+        constexpr int kStageBytes = NJ * 32 * kBK * 2;
+        static_assert(kStages * kStageBytes <= kStagesA * kTileBytes && kDeep * NJ <= kNP, "LDS; copies in flight");
         constexpr int NF = 2 * NJ;              // token fragments per slice
         constexpr int G = 2 * NF;               // groups (one fragment against kNW weight blocks) per step
         // fragments in flight: the lead stays within the next step, and 128 x 256 tiles have 256 registers
@@ -246,44 +256,46 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
             const size_t o = (size_t)min(g, last_slice) * 2048;  // past the end: a harmless reload
             fr.b[i] = *reinterpret_cast<const u32x4*>(wb[i >> 1] + o + (w_off + (i & 1) * 256));
         };
-        // prologue: copies of steps 0..2, then the first weight slices; the wait leaves at most the
-        // copies of step 2 in flight
+        // prologue: copies of steps 0 .. kStages-2, then the first weight slices; the wait leaves at most
+        // the copies of the last kDeep of those steps in flight
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+        for (int t = 0; t < kStages - 1; ++t)
 #pragma unroll
-            for (int i = 0; i < kNP; ++i) copy_a(t, t, i);
+            for (int i = 0; i < NJ; ++i) copy_a(t * kStageBytes, min(t, last), i);
 #pragma unroll
         for (int g = 0; g < kSlices - 1; ++g)
 #pragma unroll
             for (int i = 0; i < kNW; ++i) load_bf(bq[g], g, i);
-        static_assert(kNP + kNW * (kSlices - 1) <= 63, "vmcnt is a 6-bit counter");
+        static_assert(kDeep * NJ + kNW * (kSlices - 1) <= 63, "vmcnt is a 6-bit counter");
         __builtin_amdgcn_sched_barrier(0);  // the weight loads are issued before the wait, not after it
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kNP + kNW * (kSlices - 1)) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kDeep * NJ + kNW * (kSlices - 1)) : "memory");
 #pragma unroll
         for (int j = 0; j < RF; ++j)
             fa[j] = *reinterpret_cast<const bf16x8*>(lds_a + (j < NF ? frag_off[0] + j * 2048 : frag_off[1] + (j - NF) * 2048));
 
-        int st = 0;  // LDS stage of step kt
+        int st = 0;  // LDS stage of step kt (byte offset)
+        constexpr int kLastStage = (kStages - 1) * kStageBytes;
         int kt = 0;
         do {  // at least one trip (K >= 256): the prologue's loads have nowhere to sink to
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const int t = kt + u;
-                const int stn = (st + 1) & (kStagesA - 1), stp = (st + kStagesA - 1) & (kStagesA - 1);
-                const char* cur = lds_a + st * kTileBytes;
-                const char* nxt = lds_a + stn * kTileBytes;
+                const int stn = st == kLastStage ? 0 : st + kStageBytes, stp = st == 0 ? kLastStage : st - kStageBytes;
+                const char* cur = lds_a + st;
+                const char* nxt = lds_a + stn;
                 BFrags& f0 = bq[(2 * u) % kSlices];
                 BFrags& f1 = bq[(2 * u + 1) % kSlices];
                 BFrags& fp = bq[(2 * u + kSlices - 1) % kSlices];  // the slice in front of this step's
-                // Vector-memory instructions of one half of the step, op = 0 .. kHalf-1: half of the copies
-                // and kNW weight loads in turn.  First half: the slice used last in the step before; second
-                // half: this step's first slice, used up by then.
-                constexpr int kHalf = kNP / 2 + kNW;
+                // Vector-memory instructions of one half of the step, op = 0 .. ops(half)-1: half of the copies
+                // (the first half the larger one) and kNW weight loads in turn.  First half: the slice used last
+                // in the step before; second half: this step's first slice, used up by then.
+                auto copies = [](int half) { return half ? NJ / 2 : (NJ + 1) / 2; };
+                auto ops = [&](int half) { return copies(half) + kNW; };
                 auto vmem = [&](int half, int op) {
-                    constexpr int kTwo = 2 * (kNP / 2 < kNW ? kNP / 2 : kNW);  // ops that alternate
-                    const bool copy = op < kTwo ? op % 2 == 0 : kNP / 2 > kNW;
-                    const int n = op < kTwo ? op / 2 : op - kTwo / 2;
-                    if (copy) copy_a(stp, min(t + 3, last), half * (kNP / 2) + n);
+                    const int nc = copies(half), two = 2 * (nc < kNW ? nc : kNW);  // ops that alternate
+                    const bool copy = op < two ? op % 2 == 0 : nc > kNW;
+                    const int n = op < two ? op / 2 : op - two / 2;
+                    if (copy) copy_a(stp, min(t + kStages - 1, last), half * ((NJ + 1) / 2) + n);
                     else if (half == 0) load_bf(fp, 2 * t + kSlices - 1, n);
                     else load_bf(f0, 2 * t + kSlices, n);
                 };
@@ -296,12 +308,15 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
                         // read of the stage has been consumed by a matrix instruction above.
 #pragma unroll
                         for (int j = kBar; j < G; ++j) asm volatile("" ::"v"(fa[(u * G + j) % RF]));
-                        // All vector-memory instructions of step t stand in front of its barrier: kNP copies
-                        // (step t+3's) and 2 kNW weight loads, all of them behind the copies of step t+2, which
-                        // were issued during step t-1.  A wait that leaves that many outstanding leaves
-                        // the copies of step t+2 landed, and after the barrier every wavefront may read that
-                        // step, whose first fragments are fetched before the next barrier.
-                        constexpr int kWaitN = kNP + 2 * kNW;
+                        // All vector-memory instructions of step t stand in front of its barrier: NJ copies
+                        // (step t + kStages - 1's) and 2 kNW weight loads.  The copies of step t+2 were issued
+                        // during step t - kDeep, and the instructions of the kDeep steps since stand behind
+                        // them; or in the prologue, and then kDeep NJ copies, the prologue's weight loads and step
+                        // t's do.  A wait that leaves the lesser of the two outstanding leaves the copies of
+                        // step t+2 landed, and after the barrier every wavefront may read that step, whose
+                        // first fragments are fetched before the next barrier.
+                        constexpr int kWaitN = kDeep * NJ + kNW * (2 * kDeep < kSlices + 1 ? 2 * kDeep : kSlices + 1);
+                        static_assert(kWaitN <= 63, "vmcnt is a 6-bit counter");
                         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kWaitN) : "memory");
                     }
                     const int q = gi / NF, j = gi % NF, slot = (u * G + gi) % RF;
@@ -323,11 +338,11 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
                     // NJ = 1: the barrier stands in front of the second half, whose instructions join the first
                     if (kBar > NF) {
 #pragma unroll
-                        for (int op = 0; op < kHalf; ++op)
-                            if (gi < kBar && op * ng / kHalf == at) vmem(half, op);
+                        for (int op = 0; op < kNP + kNW; ++op)
+                            if (op < ops(half) && gi < kBar && op * ng / ops(half) == at) vmem(half, op);
                     } else if (gi == NF - 1) {
 #pragma unroll
-                        for (int op = 0; op < 2 * kHalf; ++op) vmem(op / kHalf, op % kHalf);
+                        for (int op = 0; op < ops(0) + ops(1); ++op) vmem(op >= ops(0), op < ops(0) ? op : op - ops(0));
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
