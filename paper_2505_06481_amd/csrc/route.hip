@@ -21,35 +21,31 @@ namespace mmoe {
 
 constexpr int kRouteWaves = 8;   // wavefronts per token: they share out the experts
 
-template <typename T> struct Vec4;
-template <> struct Vec4<float> {
-    static __device__ __forceinline__ void load(const float* p, float (&v)[4])
-    {
-        f32x4 t = *reinterpret_cast<const f32x4*>(p);
-        v[0] = t[0]; v[1] = t[1]; v[2] = t[2]; v[3] = t[3];
-    }
+// Four consecutive elements as loaded (bf16 stays packed until it is used, which halves the
+// registers a pending load occupies).
+template <typename T> struct Raw4;
+template <> struct Raw4<float> {
+    typedef f32x4 type;
+    static __device__ __forceinline__ float get(const type& r, int q) { return r[q]; }
 };
-template <> struct Vec4<uint16_t> {
-    static __device__ __forceinline__ void load(const uint16_t* p, float (&v)[4])
+template <> struct Raw4<uint16_t> {
+    typedef u32x2 type;
+    static __device__ __forceinline__ float get(const type& r, int q)
     {
-        u32x2 t = *reinterpret_cast<const u32x2*>(p);
-        v[0] = __uint_as_float(t[0] << 16);
-        v[1] = __uint_as_float(t[0] & 0xFFFF0000u);
-        v[2] = __uint_as_float(t[1] << 16);
-        v[3] = __uint_as_float(t[1] & 0xFFFF0000u);
+        return (q & 1) ? __uint_as_float(r[q >> 1] & 0xFFFF0000u) : __uint_as_float(r[q >> 1] << 16);
     }
 };
 
 // The k winners among E logits in LDS, found by one wavefront: lane l looks after experts
 // l, l+64, l+128, l+192; k arg-max reductions, ties to the lower index; coefficients =
 // softmax over the selected logits.
-// With a table row `map_row` (= M[vid[t]], or null) the picks are also looked up in the expert
+// Lanes from the next power of two above E on hold no expert, so the reductions stop there.
+// With a table row `map_row` (= M[vid[t]] in LDS, or null) the picks are also looked up in the expert
 // map and slot[t*k + j] is written: step M folded into the router for batches whose expert stage
 // groups the pairs itself.
 __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit, int lane, int E, int k, int t,
                                             int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
-                                            const int32_t* __restrict__ map_row, int32_t* __restrict__ slot, int S,
-                                            int gate)
+                                            const int32_t* map_row, int32_t* __restrict__ slot, int S, int gate)
 {
     constexpr int kPerLane = kMaxE / kWave;
     float mine[kPerLane];
@@ -76,6 +72,7 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
             }
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) {
+                if (off >= E) continue;
                 float ov = __shfl_xor(bv, off, kWave);
                 int oe = __shfl_xor(be, off, kWave);
                 bool other_valid = oe != 0x7FFFFFFF, self_valid = be != 0x7FFFFFFF;
@@ -95,7 +92,8 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
         for (int q = 0; q < kPerLane; ++q)
             if (lane + q * kWave < E) all += expf(mine[q] - sel[0]);
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) all += __shfl_xor(all, off, kWave);
+        for (int off = 32; off >= 1; off >>= 1)
+            if (off < E) all += __shfl_xor(all, off, kWave);
     }
     if (lane == 0) {
         float z[kMaxTopK];
@@ -120,72 +118,63 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
 
 // One workgroup per token; wavefront w scores experts w, w+8, ...  A token's dot product
 // with one expert is never split between wavefronts, so the summation order is the
-// contract's whatever the launch shape.  Four vectors per lane are fetched at a time to
-// keep eight loads in flight.
-template <typename T>
+// contract's whatever the launch shape.  What bounds it is the chain of dependent memory reads, so there
+// are two: the variant id, and then everything else at once -- KU chunks of 256 elements of both rows,
+// bias, table row (chunks past the end re-read the last one and are not summed).  With four chunks at a
+// time, the remainder one by one and the table read behind the selection one token of 4096 elements took 7.5 us
+// (now 6.6), three of 768 5.0 us (4.6), and a layer of 1037 tokens and 64 experts 361 us (346).
+template <typename T, int KU>
 __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
     const T* __restrict__ X, const int32_t* __restrict__ vid, const T* __restrict__ Wr,
     const float* __restrict__ br, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int Tn, int d,
     int V, int E, int k, const int32_t* __restrict__ M, int32_t* __restrict__ slot, int S, int gate)
 {
     __shared__ float lds_logit[kMaxE];
+    __shared__ int32_t lds_map[kMaxE];
+    static_assert(kMaxE <= kRouteWaves * kWave, "a table entry to a thread");
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int t = blockIdx.x;
+    typedef typename Raw4<T>::type raw_t;
 
+    const T* x = X + (size_t)t * d + 4 * lane;
+    const int nc = d / 256, last = nc - 1;  // chunks: d is a multiple of 256
+    raw_t xv[KU], wv[KU];
+#pragma unroll
+    for (int u = 0; u < KU; ++u) xv[u] = *reinterpret_cast<const raw_t*>(x + 256 * min(u, last));
     const int v = min(max(vid[t], 0), V - 1);  // out-of-range ids are the caller's error; stay in bounds
-    const T* x = X + (size_t)t * d;
-    const int nvec = d / 4;  // a multiple of 64: d is a multiple of 256
+    if (M && threadIdx.x < E) lds_map[threadIdx.x] = M[(size_t)v * E + threadIdx.x];
 
     for (int e = wave; e < E; e += kRouteWaves) {
-        const T* w = Wr + ((size_t)v * E + e) * d;
+        const T* w = Wr + ((size_t)v * E + e) * d + 4 * lane;
+        const float bias = br ? br[(size_t)v * E + e] : 0.0f;
         float acc = 0.0f;
-        int q = lane;
-        for (; q + 3 * kWave < nvec; q += 4 * kWave) {  // ascending i within the lane
-            float xv[4][4], wv[4][4];
+        for (int c0 = 0; c0 < nc; c0 += KU) {  // ascending i within the lane
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                Vec4<T>::load(x + 4 * (q + u * kWave), xv[u]);
-                Vec4<T>::load(w + 4 * (q + u * kWave), wv[u]);
+            for (int u = 0; u < KU; ++u) wv[u] = *reinterpret_cast<const raw_t*>(w + 256 * min(c0 + u, last));
+            if (nc > KU) {  // the token row does not fit the registers: its chunks are read again for every expert
+#pragma unroll
+                for (int u = 0; u < KU; ++u) xv[u] = *reinterpret_cast<const raw_t*>(x + 256 * min(c0 + u, last));
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < KU; ++u)
+                if (c0 + u < nc) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc = __builtin_fmaf(xv[u][c], wv[u][c], acc);
-        }
-        for (; q < nvec; q += kWave) {
-            float xv[4], wv[4];
-            Vec4<T>::load(x + 4 * q, xv);
-            Vec4<T>::load(w + 4 * q, wv);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc = __builtin_fmaf(xv[c], wv[c], acc);
+                    for (int c = 0; c < 4; ++c)
+                        acc = __builtin_fmaf(Raw4<T>::get(xv[u], c), Raw4<T>::get(wv[u], c), acc);
+                }
         }
         float p = acc;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) p = p + __shfl_xor(p, off, kWave);
-        if (br) p = p + br[(size_t)v * E + e];
+        if (br) p = p + bias;
         if (lane == 0) lds_logit[e] = p;
     }
     __syncthreads();
     if (wave != 0) return;
 
-    select_topk(lds_logit, lane, E, k, t, topk_idx, topk_w, M ? M + (size_t)v * E : nullptr, slot, S, gate);
+    select_topk(lds_logit, lane, E, k, t, topk_idx, topk_w, M ? lds_map : nullptr, slot, S, gate);
 }
-
-// Four consecutive elements as loaded (bf16 stays packed until it is used, which halves the
-// registers a pending load occupies).
-template <typename T> struct Raw4;
-template <> struct Raw4<float> {
-    typedef f32x4 type;
-    static __device__ __forceinline__ float get(const type& r, int q) { return r[q]; }
-};
-template <> struct Raw4<uint16_t> {
-    typedef u32x2 type;
-    static __device__ __forceinline__ float get(const type& r, int q)
-    {
-        return (q & 1) ? __uint_as_float(r[q >> 1] & 0xFFFF0000u) : __uint_as_float(r[q >> 1] << 16);
-    }
-};
 
 // Throughput variant for large batches: one wavefront per token.  The token's elements
 // stay in registers (NC chunks of 256, d = 256*NC exactly, so that every load of a pass is
@@ -205,6 +194,7 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
     int V, int E, int k, const int32_t* __restrict__ M, int32_t* __restrict__ slot, int S, int gate)
 {
     __shared__ float lds_logit[kRouteTokWaves][kMaxE];
+    __shared__ int32_t lds_map[kRouteTokWaves][kMaxE];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
     const int t = blockIdx.x * kRouteTokWaves + wave;
@@ -219,6 +209,8 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
 
     const T* wv0 = Wr + (size_t)v * E * d + 4 * lane;
     float* mylogit = lds_logit[wave];
+    if (M)
+        for (int e = lane; e < E; e += kWave) lds_map[wave][e] = M[(size_t)v * E + e];
     for (int e = 0; e < E; e += 2) {
         const bool two = e + 1 < E;
         const T* w0 = wv0 + (size_t)e * d;
@@ -252,11 +244,11 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
             if (two) mylogit[e + 1] = a1;
         }
     }
-    // lane 0's LDS writes before every lane's reads: one wavefront's LDS operations execute in
+    // the LDS writes of this wavefront's lanes before its reads: one wavefront's LDS operations execute in
     // program order, the fence keeps the compiler from moving them
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    select_topk(mylogit, lane, E, k, t, topk_idx, topk_w, M ? M + (size_t)v * E : nullptr, slot, S, gate);
+    select_topk(mylogit, lane, E, k, t, topk_idx, topk_w, M ? lds_map[wave] : nullptr, slot, S, gate);
 }
 
 int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const void* Wr, const float* br,
@@ -291,12 +283,19 @@ int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const v
         return launch_status();
     }
     dim3 grid(s.T), block(kRouteWaves * kWave);
-    if (s.dtype == MMOE_BF16)
-        hipLaunchKernelGGL(route_kernel<uint16_t>, grid, block, 0, st, (const uint16_t*)X, vid,
-                           (const uint16_t*)Wr, br, topk_idx, topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S, s.gate);
-    else
-        hipLaunchKernelGGL(route_kernel<float>, grid, block, 0, st, (const float*)X, vid, (const float*)Wr, br,
-                           topk_idx, topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S, s.gate);
+#define MMOE_ROUTE(TT, KU)                                                                                          \
+    hipLaunchKernelGGL((route_kernel<TT, KU>), grid, block, 0, st, (const TT*)X, vid, (const TT*)Wr, br, topk_idx,     \
+                       topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S, s.gate)
+    // chunks in flight: the whole row where the registers hold it (64 for both rows)
+    if (s.dtype == MMOE_BF16) {
+        if (nc <= 4) MMOE_ROUTE(uint16_t, 4);
+        else if (nc <= 8) MMOE_ROUTE(uint16_t, 8);
+        else MMOE_ROUTE(uint16_t, 16);
+    } else {
+        if (nc <= 4) MMOE_ROUTE(float, 4);
+        else MMOE_ROUTE(float, 8);
+    }
+#undef MMOE_ROUTE
     return launch_status();
 }
 

@@ -128,6 +128,29 @@ def test_tiled_f32_row_remainders(mm, gc, oracle, act, k, d, f):
         assert mm.expert_plan(case.shape) == (False, 96)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [256, 768, 1024, 1280, 2048, 2304, 4096, 4352])
+def test_router_row_lengths(mm, gc, oracle, dtype, d):
+    """Rows that fill, end inside and exceed the chunks the router holds in registers, expert counts on both
+    sides of the reductions' powers of two, both gates: picks equal, coefficients to fp32."""
+    import torch
+    rng = np.random.default_rng(d)
+    for E, k, gate in ((1, 1, "selected"), (2, 2, "all"), (3, 1, "all"), (5, 4, "selected"), (8, 2, "selected"),
+                       (9, 8, "all"), (64, 4, "selected"), (65, 2, "all")):
+        T, V = 7, 3
+        def stored(a):
+            t = torch.from_numpy(a.astype(np.float32))
+            return t if dtype == "f32" else t.bfloat16()
+        X, Wr = stored(rng.standard_normal((T, d))), stored(0.05 * rng.standard_normal((V, E, d)))
+        vid = torch.from_numpy(rng.integers(0, V, T).astype(np.int32))
+        br = torch.from_numpy(rng.standard_normal((V, E)).astype(np.float32))
+        shape = mm.make_shape(T, d, 256, V, E, E, k, dtype, "relu", gate=gate)
+        idx, w = mm.route(shape, X.cuda(), vid.cuda(), Wr.cuda(), br.cuda())
+        ref_idx, ref_w, _ = oracle.route(gc.bits(X), vid.numpy(), gc.bits(Wr), br.numpy(), k, dtype, gate=gate)
+        assert np.array_equal(idx.cpu().numpy(), ref_idx), (E, k, gate)
+        np.testing.assert_allclose(w.cpu().numpy(), ref_w, rtol=2e-6, atol=1e-7)
+
+
 @pytest.mark.parametrize("S", [1, 2, 63, 64, 65, 1024])
 def test_grouping_sizes(mm, S):
     """Integer outputs of the grouping at the edges of its steps and of its two forms, against a stable sort:
