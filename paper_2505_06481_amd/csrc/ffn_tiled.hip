@@ -459,15 +459,17 @@ static void tiled_nts(const mmoe_shape& s, int bm, int& nt_up, int& nt_down, int
 // behind the other's main loop) when a tile is short-lived -- a short reduction in the up
 // product, or slots with few rows -- and 256 rows (deeper weight prefetch, half the weight
 // traffic per row) otherwise.  The host knows P and S, not the counts.  Measured with each
-// height forced: on the Switch shape (d = 768) 128 rows win at every batch size up to 16384
-// tokens; on the Mixtral shape (d = 4096) they win up to 59 rows per slot (384 tokens) and
-// lose from 79 rows per slot (512 tokens) on.
+// height forced, 128 against 256 rows, us: d = 768 62 : 78 at 154 rows per slot, 223 : 243 at 1231; d = 1280 75 : 94 at
+// 125, 373 : 453 at 1000; d = 1536 99 : 128 at 67, 367 : 383 at 1000; d = 1792 109 : 139 at 67, 442 : 428 at 1000;
+// d = 2048 134 : 146 (f = 3072) and 200 : 206 (5120) at 67, 231 : 218 at 133, 473 : 449 at 1000; d = 4096 833 : 831 at
+// 46, 965 : 851 at 65, 1418 : 969 at 139.
 int planned_tile_rows(const mmoe_shape& s)
 {
     if (s.dtype == MMOE_F32) return kFRows;  // the fp32 kernel has one height
     if (s.tile_rows) return s.tile_rows;  // forced for this call (checked by check_shape: 128 or 256)
     const int64_t P = (int64_t)s.T * s.top_k;
-    return (s.d_model <= 1024 || P < (int64_t)64 * s.S) ? kBMSmall : kBMBig;
+    if (s.d_model <= 1536) return kBMSmall;
+    return P < (int64_t)(s.d_model <= 2048 ? 100 : 64) * s.S ? kBMSmall : kBMBig;
 }
 
 // Most sub-tiles of a row tile: a full tile.  (Shorter tiles for products with few tiles were

@@ -58,19 +58,20 @@ constexpr int kF32StreamRows = 12;
 bool use_skinny(const mmoe_shape& s)
 {
     // A batch streams when a slot sees few rows: the weights are then read once from HBM and that
-    // read is the bound.  The
-    // streaming kernel takes 32 rows of a slot per pass over its weights, so it only pays
-    // while the fullest slot stays near that.  Measured with each kernel forced: on the
-    // Mixtral shape (352 MB a slot) it wins up to an average of 16 rows per slot and loses
-    // quickly beyond (1.21 ms against 0.83 ms at 40); on the Switch shape (9 MB a slot, a
-    // second pass finds the weights in cache) up to 32.
+    // read is the bound.  The streaming kernel takes 32 rows of a slot per pass over its weights, so it
+    // only pays while the fullest slot stays near that, and each of its workgroups looks through all pairs
+    // for its slot's, so it only pays while they are few.  Measured with each kernel forced, streaming
+    // against matrix-core tiles, us: 4096 x 14336 SwiGLU 777 : 793 at 12 rows per slot, 826 : 792 at 15;
+    // 2048 x 2048 SwiGLU 68 : 72 at 17, 82 : 73 at 25; 1280 x 2560 GELU 43 : 48 at 17, 52 : 51 at 25; 768 x 3072
+    // 37 : 39 at 15, 45 : 42 at 23; with many slots, 512 x 1024 SwiGLU 48 : 46 at 500 pairs, 57 : 49 at 800;
+    // 2048 x 1280 SwiGLU 284 : 279 at 800 pairs, 333 : 303 at 1800.
     const int64_t P = (int64_t)s.T * s.top_k;
     if (s.dtype == MMOE_F32) {
         const int64_t widest = s.d_model > s.d_ff ? s.d_model : s.d_ff;
         return P <= (int64_t)kF32StreamRows * s.S || P * widest >= ((int64_t)1 << 31);  // the tile lists' limit
     }
     const bool small_experts = (int64_t)s.d_model * s.d_ff <= ((int64_t)4 << 20);
-    return P <= (int64_t)(small_experts ? 32 : 16) * s.S;
+    return small_experts ? P <= (int64_t)20 * s.S && P <= 512 : P <= (int64_t)16 * s.S;
 }
 
 static inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0; }

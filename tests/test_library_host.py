@@ -188,3 +188,18 @@ def test_expert_plan_follows_the_documented_dispatch(mm):
     assert plan("mixtral_prefill_bf16_v2_t8192", 13, tile_rows=128) == (False, 128)
     assert plan("mixtral_decode_bf16_v2_t64", 13, tile_rows=128) == (True, 32)
     assert plan("mixtral_prefill_bf16_v2_t8192", 13) == (False, 256)
+
+
+@pytest.mark.parametrize("d,f,S,P,want", [
+    (2048, 2048, 12, 240, (True, 32)), (2048, 2048, 12, 241, (False, 128)),     # small experts: 20 rows per slot
+    (512, 1024, 64, 512, (True, 32)), (512, 1024, 64, 513, (False, 128)),       # and at most 512 pairs
+    (1536, 3072, 8, 16000, (False, 128)), (1792, 3072, 8, 799, (False, 128)), (1792, 3072, 8, 800, (False, 256)),
+    (2304, 3072, 8, 511, (False, 128)), (2304, 3072, 8, 512, (False, 256)),     # tall tiles by rows per slot
+])
+def test_expert_plan_at_its_lines(mm, d, f, S, P, want):
+    assert mm.expert_plan(mm.make_shape(P, d, f, 1, S, S, 1, "bf16", "relu")) == want
+
+
+@pytest.mark.parametrize("P,want", [(96, (True, 32)), (97, (False, 96))])
+def test_expert_plan_f32(mm, P, want):
+    assert mm.expert_plan(mm.make_shape(P, 768, 3072, 1, 8, 8, 1, "f32", "relu")) == want
