@@ -1,5 +1,5 @@
 // Step R: per-variant gate, top-k selection and coefficients (Algorithm 2, "gate(act)";
-// section 3.2).  Two launch shapes with the same arithmetic: small batches give a token to a
+// section 3.2).  Three launch shapes with the same arithmetic: small batches give a token to a
 // workgroup whose wavefronts share out the experts (latency); large batches give a token to
 // one wavefront that keeps the token row in registers and walks the experts (throughput).
 //
@@ -176,6 +176,101 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
     select_topk(lds_logit, lane, E, k, t, topk_idx, topk_w, M ? lds_map : nullptr, slot, S, gate);
 }
 
+// Batches with much to score: a workgroup takes kRouteGroup tokens, so a router row is read once for
+// those of them that share a variant instead of once per token, and unpacked once.  Token rows in LDS as
+// stored; wavefront w of sixteen scores experts w, w+16, ... for all of the group's tokens.  The sums of the
+// group's tokens go through the butterfly together: at the first two levels half of the lanes keep one token
+// and half the other, and what a lane adds is its partner's partial sum either way, so every sum is the
+// contract's.  Bound by the chain of reads per expert at the small end, by vector issue at the large.
+// 1024 tokens of 3072 elements, 64 experts, bf16: 39.1 (workgroup per token) -> 27.5 us, fp32 62.7 -> 25.5;
+// 8192 tokens of 4096, 64 experts: 237 (wavefront per token) -> 158 us; of 2304, 8 experts: 76.6 -> 35.7 us.
+constexpr int kRouteGroup = 4;
+constexpr int kRouteGroupWaves = 16;
+
+template <typename T>
+__global__ __launch_bounds__(kRouteGroupWaves* kWave) void route_group_kernel(
+    const T* __restrict__ X, const int32_t* __restrict__ vid, const T* __restrict__ Wr,
+    const float* __restrict__ br, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int Tn, int d,
+    int V, int E, int k, const int32_t* __restrict__ M, int32_t* __restrict__ slot, int S, int gate)
+{
+    constexpr int TB = kRouteGroup, KU = 8;
+    static_assert(TB == 4, "two levels of the butterfly");
+    extern __shared__ __align__(16) char rows[];  // [TB][d] as stored
+    __shared__ float lds_logit[TB][kMaxE];
+    __shared__ int32_t lds_map[TB][kMaxE];
+    typedef typename Raw4<T>::type raw_t;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int t0 = blockIdx.x * TB;
+    const int nc = d / 256, last = nc - 1;
+
+    int v[TB];
+#pragma unroll
+    for (int i = 0; i < TB; ++i) v[i] = min(max(vid[min(t0 + i, Tn - 1)], 0), V - 1);
+    const int pieces = d * (int)sizeof(T) / 16;  // per row
+#pragma unroll
+    for (int i = 0; i < TB; ++i) {
+        const u32x4* src = reinterpret_cast<const u32x4*>(X + (size_t)min(t0 + i, Tn - 1) * d);
+        for (int q = threadIdx.x; q < pieces; q += kRouteGroupWaves * kWave) reinterpret_cast<u32x4*>(rows)[i * pieces + q] = src[q];
+        if (M)
+            for (int e = threadIdx.x; e < E; e += kRouteGroupWaves * kWave) lds_map[i][e] = M[(size_t)v[i] * E + e];
+    }
+    __syncthreads();
+
+    const T* xrow = reinterpret_cast<const T*>(rows) + 4 * lane;
+    for (int e = wave; e < E; e += kRouteGroupWaves) {
+        float acc[TB];
+#pragma unroll
+        for (int i = 0; i < TB; ++i) acc[i] = 0.0f;
+        unsigned todo = (1u << TB) - 1;
+        while (todo) {  // uniform: the tokens of one variant at a time
+            const int first = __builtin_ctz(todo);
+            int ve = v[0];
+#pragma unroll
+            for (int i = 1; i < TB; ++i) ve = first == i ? v[i] : ve;
+            unsigned set = 0;
+#pragma unroll
+            for (int i = 0; i < TB; ++i) set |= v[i] == ve ? 1u << i : 0u;
+            todo &= ~set;
+            const T* w = Wr + ((size_t)ve * E + e) * d + 4 * lane;
+            for (int c0 = 0; c0 < nc; c0 += KU) {  // ascending i within the lane
+                raw_t wv[KU];
+#pragma unroll
+                for (int u = 0; u < KU; ++u) wv[u] = *reinterpret_cast<const raw_t*>(w + 256 * min(c0 + u, last));
+#pragma unroll
+                for (int i = 0; i < TB; ++i)
+                    if (set & (1u << i)) {
+#pragma unroll
+                        for (int u = 0; u < KU; ++u)
+                            if (c0 + u < nc) {
+                                const raw_t xv = *reinterpret_cast<const raw_t*>(xrow + (size_t)i * d + 256 * (c0 + u));
+#pragma unroll
+                                for (int c = 0; c < 4; ++c)
+                                    acc[i] = __builtin_fmaf(Raw4<T>::get(xv, c), Raw4<T>::get(wv[u], c), acc[i]);
+                            }
+                    }
+            }
+        }
+        const bool hi = lane & 32, odd = lane & 16;
+        float a = hi ? acc[1] : acc[0], b = hi ? acc[3] : acc[2];
+        a = a + __shfl_xor(hi ? acc[0] : acc[1], 32, kWave);
+        b = b + __shfl_xor(hi ? acc[2] : acc[3], 32, kWave);
+        float p = odd ? b : a;
+        p = p + __shfl_xor(odd ? a : b, 16, kWave);
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) p = p + __shfl_xor(p, off, kWave);
+        const int tok = (hi ? 1 : 0) + (odd ? 2 : 0);
+        if ((lane & 15) == 0) {
+            const int vt = tok == 0 ? v[0] : tok == 1 ? v[1] : tok == 2 ? v[2] : v[3];
+            if (br) p = p + br[(size_t)vt * E + e];
+            lds_logit[tok][e] = p;
+        }
+    }
+    __syncthreads();
+    if (wave >= TB || t0 + wave >= Tn) return;
+    select_topk(lds_logit[wave], lane, E, k, t0 + wave, topk_idx, topk_w, M ? lds_map[wave] : nullptr, slot, S, gate);
+}
+
 // Throughput variant for large batches: one wavefront per token.  The token's elements
 // stay in registers (NC chunks of 256, d = 256*NC exactly, so that every load of a pass is
 // issued before the first one is waited for) and the wavefront walks the experts
@@ -251,14 +346,32 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
     select_topk(mylogit, lane, E, k, t, topk_idx, topk_w, M ? lds_map[wave] : nullptr, slot, S, gate);
 }
 
+constexpr size_t kRouteGroupBytes = 48 << 10;  // most LDS for the token rows of a group
+
+// Four tokens to a workgroup?  Measured against the other two, bf16, us, two variants:
+//   workgroup per token (under 2048 tokens, or an uncommon hidden size): 8 experts, 768 elements 8.2 : 8.6 at 1900 tokens;
+//   1536 9.4 : 9.3 at 1500; 2048 7.8 : 8.0 at 1024; 3072 7.8 : 9.1 at 512, 12.1 : 9.2 at 768; 64 experts 2048 22.6 : 19.4 at
+//   1024, 14.2 : 18.3 at 512;
+//   wavefront per token: 4096 tokens, 64 experts 768 27.5 : 42.4, 1536 51.0 : 43.9, 4096 123 : 84; 16 experts 2048 19.9 : 20.1,
+//   3072 28.1 : 26.6, 4096 35.7 : 29.5; 8 experts 4096 20.9 : 22.5.
+static bool route_in_groups(const mmoe_shape& s, bool token_per_wave)
+{
+    if ((size_t)kRouteGroup * s.d_model * elem_size(s.dtype) > kRouteGroupBytes) return false;
+    if (token_per_wave) return s.d_model >= 1536 && (int64_t)s.E * s.d_model >= 49152;
+    return s.T >= 768 && (int64_t)s.T * s.d_model >= ((int64_t)1 << 21);
+}
+
 int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const void* Wr, const float* br,
                  int32_t* topk_idx, float* topk_w, hipStream_t st, const int32_t* M, int32_t* slot)
 {
     // Large batches of a common hidden size: a wavefront per token (the token row is read
-    // once); otherwise a workgroup per token (lower latency, any d).
+    // once); with more to score, a workgroup per four tokens; otherwise a workgroup per token (lower
+    // latency, any d).
     const int nc = s.d_model / 256;
     const bool tok_nc = nc == 1 || nc == 2 || nc == 3 || nc == 4 || nc == 6 || nc == 8 || nc == 12 || nc == 16;
-    if (s.T >= kRouteTokMinT && tok_nc && s.d_model % 256 == 0) {
+    const bool token_per_wave = s.T >= kRouteTokMinT && tok_nc;
+    const bool groups = route_in_groups(s, token_per_wave);
+    if (token_per_wave && !groups) {
         dim3 grid((s.T + kRouteTokWaves - 1) / kRouteTokWaves), block(kRouteTokWaves * kWave);
 #define MMOE_ROUTE_TOK(NC)                                                                                          \
     case NC:                                                                                                        \
@@ -283,6 +396,20 @@ int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const v
         return launch_status();
     }
     dim3 grid(s.T), block(kRouteWaves * kWave);
+    if (groups) {
+        const size_t group_bytes = (size_t)kRouteGroup * s.d_model * elem_size(s.dtype);
+        const dim3 g4((s.T + kRouteGroup - 1) / kRouteGroup);
+        const dim3 b16(kRouteGroupWaves * kWave);
+        if (s.dtype == MMOE_BF16)
+            hipLaunchKernelGGL(route_group_kernel<uint16_t>, g4, b16, group_bytes, st, (const uint16_t*)X, vid,
+                               (const uint16_t*)Wr, br, topk_idx, topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S,
+                               s.gate);
+        else
+            hipLaunchKernelGGL(route_group_kernel<float>, g4, b16, group_bytes, st, (const float*)X, vid,
+                               (const float*)Wr, br, topk_idx, topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S,
+                               s.gate);
+        return launch_status();
+    }
 #define MMOE_ROUTE(TT, KU)                                                                                          \
     hipLaunchKernelGGL((route_kernel<TT, KU>), grid, block, 0, st, (const TT*)X, vid, (const TT*)Wr, br, topk_idx,     \
                        topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S, s.gate)

@@ -151,6 +151,33 @@ def test_router_row_lengths(mm, gc, oracle, dtype, d):
         np.testing.assert_allclose(w.cpu().numpy(), ref_w, rtol=2e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("T,d,E,k,dtype", [(911, 2304, 3, 1, "bf16"), (1369, 1536, 17, 4, "f32"), (770, 2816, 130, 8, "bf16"),
+                                           (1031, 2048, 16, 2, "f32"), (2049, 3072, 16, 2, "bf16"), (2050, 1536, 64, 4, "f32"),
+                                           (2051, 3328, 8, 2, "bf16"), (2052, 6144, 1, 1, "bf16")])
+def test_router_token_groups(mm, gc, oracle, T, d, E, k, dtype):
+    """Four tokens to a workgroup: variants mixed inside the groups, a last group of one to four tokens, experts
+    that do and do not divide among the wavefronts.  Picks equal, coefficients to fp32."""
+    rng = np.random.default_rng(T)
+    def stored(a):
+        t = torch.from_numpy(a.astype(np.float32))
+        return t if dtype == "f32" else t.bfloat16()
+    V = 3
+    X, Wr = stored(rng.standard_normal((T, d))), stored(0.02 * rng.standard_normal((V, E, d)))
+    vid = torch.from_numpy(rng.integers(0, V, T).astype(np.int32))
+    br = torch.from_numpy(rng.standard_normal((V, E)).astype(np.float32))
+    for gate in ("selected", "all"):
+        shape = mm.make_shape(T, d, 256, V, E, E, k, dtype, "relu", gate=gate)
+        idx, w = mm.route(shape, X.cuda(), vid.cuda(), Wr.cuda(), br.cuda())
+        ref_idx, ref_w, _ = oracle.route(gc.bits(X), vid.numpy(), gc.bits(Wr), br.numpy(), k, dtype, gate=gate)
+        assert np.array_equal(idx.cpu().numpy(), ref_idx), gate
+        np.testing.assert_allclose(w.cpu().numpy(), ref_w, rtol=2e-6, atol=1e-7)
+
+
+def test_router_token_groups_look_up_slots(mm, gc, oracle):
+    """The layer on a batch whose router takes four tokens to a workgroup: every stage and the fused call."""
+    staged_vs_oracle(mm, gc, oracle, synth.Config("route_groups", 915, 2304, 256, 3, 8, 2, "bf16", "swiglu", seed=901))
+
+
 @pytest.mark.parametrize("S", [1, 2, 63, 64, 65, 1024])
 def test_grouping_sizes(mm, S):
     """Integer outputs of the grouping at the edges of its steps and of its two forms, against a stable sort:
