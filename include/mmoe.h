@@ -97,7 +97,7 @@ typedef struct {
                           short-lived (d_model <= 1024, or fewer than 64 rows per slot on average), 256
                           rows otherwise.  128 or 256 forces that height for the call.  Either height sums
                           every output element in the same order: the results are bit-identical.  Any
-                          other value: MMOE_ERR_DIM.  Ignored by shapes that use the streaming kernels. */
+                          other value: MMOE_ERR_DIM.  Ignored by fp32 and by shapes that use the streaming kernels. */
 } mmoe_shape;
 
 /* Host only, pure.  Workspace (bytes) sufficient for every call below, 0 if the shape is invalid. */
