@@ -26,6 +26,24 @@ int check_shape(const mmoe_shape* s)
     return MMOE_OK;
 }
 
+// The tile lists as the size limit of mmoe_layer_forward_static counts them, for every shape: a plain bound of
+// its own (two lists per product of one 16-byte entry per 32-row tile and per eight blocks of 128 features),
+// so that the limit does not move when the lists' layout does.
+static size_t counted_list_bytes(const mmoe_shape& s)
+{
+    const size_t P = (size_t)s.T * s.top_k, tiles = (P + 31) / 32 + s.S;
+    const size_t groups = (s.d_ff / 128 + 7) / 8 + (s.d_model / 128 + 7) / 8;
+    return align256(256 + 32 * (tiles + (tiles + 7) / 8) * groups);
+}
+
+// Room for the tile lists in a workspace: never less than they are counted at, so that a workspace size within
+// the limit means that the shape is accepted.
+static size_t tile_list_room(const mmoe_shape& s)
+{
+    const size_t counted = counted_list_bytes(s), need = tiled_table_bytes(s);
+    return need > counted ? need : counted;
+}
+
 WsLayout ws_layout(const mmoe_shape& s)
 {
     WsLayout L;
@@ -42,7 +60,7 @@ WsLayout ws_layout(const mmoe_shape& s)
     L.inv_perm = take(P * 4);
     L.blk_counts = take((size_t)L.nblk * s.S * 4);
     L.blk_base = take((size_t)L.nblk * s.S * 4);
-    L.tile_tab = take(tiled_table_bytes(s));
+    L.tile_tab = take(tile_list_room(s));
     L.resident = take((size_t)s.S);
     L.H = take(P * s.d_ff * es);
     L.Yg = take(P * s.d_model * 4);
@@ -383,14 +401,10 @@ constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices];  // device address of `scratch` on each device, null until looked up
 
-// What a shape counts against MMOE_STATIC_WORKSPACE_BYTES: its workspace, the tile lists taken as two
-// lists per product of one 16-byte entry per 32-row tile and per eight blocks of 128 features.
+// What a shape counts against MMOE_STATIC_WORKSPACE_BYTES: its workspace, the tile lists taken as counted_list_bytes.
 size_t static_need(const mmoe_shape& s)
 {
-    const size_t P = (size_t)s.T * s.top_k, tiles = (P + 31) / 32 + s.S;
-    const size_t groups = (s.d_ff / 128 + 7) / 8 + (s.d_model / 128 + 7) / 8;
-    const size_t lists = align256(256 + 32 * (tiles + (tiles + 7) / 8) * groups);
-    return ws_layout(s).total - align256(tiled_table_bytes(s)) + lists;
+    return ws_layout(s).total - tile_list_room(s) + counted_list_bytes(s);
 }
 
 // Device address of `scratch` on the current device (looked up on the first call on that device).

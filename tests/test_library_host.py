@@ -203,3 +203,26 @@ def test_expert_plan_at_its_lines(mm, d, f, S, P, want):
 @pytest.mark.parametrize("P,want", [(96, (True, 32)), (97, (False, 96))])
 def test_expert_plan_f32(mm, P, want):
     assert mm.expert_plan(mm.make_shape(P, 768, 3072, 1, 8, 8, 1, "f32", "relu")) == want
+
+
+def static_refuses(mm, shape):
+    """Does mmoe_layer_forward_static refuse the shape's size?  Null pointers: nothing can be launched."""
+    return mm.lib().mmoe_layer_forward_static(ctypes.byref(shape), *([None] * 10)) == -11
+
+
+@pytest.mark.parametrize("d,f,S,E,k,dtype,act,T0", [
+    (768, 3072, 18, 8, 1, "bf16", "relu", 7262), (4096, 14336, 128, 8, 2, "bf16", "swiglu", 744),
+    (768, 3072, 1024, 8, 1, "f32", "relu", 4356), (768, 3072, 13, 8, 1, "f32", "gelu", 4400),
+    (2048, 1280, 90, 64, 4, "bf16", "swiglu", 1500), (256, 256, 4, 4, 2, "bf16", "relu", 21500)])
+def test_static_entry_point_takes_what_the_workspace_size_says(mm, d, f, S, E, k, dtype, act, T0):
+    """A program that asks for the workspace size first is never refused: every batch whose workspace is within
+    MMOE_STATIC_WORKSPACE_BYTES is accepted, token by token across the limit."""
+    below = above = 0
+    for T in range(T0 - 600, T0 + 600):
+        sh = mm.make_shape(T, d, f, 2, E, S, k, dtype, act)
+        if mm.workspace_bytes(sh) <= mm.STATIC_WORKSPACE_BYTES:
+            below += 1
+            assert not static_refuses(mm, sh), (T, mm.workspace_bytes(sh))
+        else:
+            above += 1
+    assert below and above
