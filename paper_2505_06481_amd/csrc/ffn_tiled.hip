@@ -500,6 +500,23 @@ size_t tiled_table_bytes(const mmoe_shape& s)
     return most;
 }
 
+size_t tiled_table_most(const mmoe_shape& s)
+{
+    const int P = s.T * s.top_k;
+    if (s.dtype == MMOE_F32) return align256(tiled_plan(s).L.bytes);  // one height, one feature tile
+    // Fewer pairs may get the other height and narrower feature tiles (planned_tile_rows, planned_nb); with each of
+    // them fixed the lists only grow with P.
+    size_t most = 0;
+    for (int bm : {kBMSmall, kBMBig})
+        for (int nb_up : {1, 2})
+            for (int nb_down : {1, 2}) {
+                const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / (kBN / 2) : s.d_ff / (128 * nb_up);
+                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (128 * nb_down), bm / 32, bm / 32, bm, false);
+                most = L.bytes > most ? L.bytes : most;
+            }
+    return align256(most);
+}
+
 template <int MODE, int BM, int NB>
 static void launch_product(const TiledPlan& p, int prod, const void* A, const int32_t* perm, int kdiv, const int32_t* tab,
                            const void* W0, const void* W1, void* out, int K, int N, hipStream_t st,

@@ -36,12 +36,44 @@ static size_t counted_list_bytes(const mmoe_shape& s)
     return align256(256 + 32 * (tiles + (tiles + 7) / 8) * groups);
 }
 
+// fp32: most rows per slot, on average, for the streaming kernels.  Measured with each kernel forced:
+// 768 x 3072 top-1, 13 slots: 77 (streaming) against 83 us at 9.8 rows per slot, 90 against 84 at 15.4;
+// 1024 x 2048 SwiGLU top-2: 95 against 92 us at 8 rows, 115 against 91 at 17; 2048 x 4096 SwiGLU: equal at 10.
+constexpr int kF32StreamRows = 12;
+
+// Few rows per slot: the batch streams, and so does every smaller one.
+static bool few_rows(const mmoe_shape& s)
+{
+    // A batch streams when a slot sees few rows: the weights are then read once from HBM and that
+    // read is the bound.  The streaming kernel takes 32 rows of a slot per pass over its weights, so it
+    // only pays while the fullest slot stays near that, and each of its workgroups looks through all pairs
+    // for its slot's, so it only pays while they are few.  Measured with each kernel forced, streaming
+    // against matrix-core tiles, us: 4096 x 14336 SwiGLU 777 : 793 at 12 rows per slot, 826 : 792 at 15;
+    // 2048 x 2048 SwiGLU 68 : 72 at 17, 82 : 73 at 25; 1280 x 2560 GELU 43 : 48 at 17, 52 : 51 at 25; 768 x 3072
+    // 37 : 39 at 15, 45 : 42 at 23; with many slots, 512 x 1024 SwiGLU 48 : 46 at 500 pairs, 57 : 49 at 800;
+    // 2048 x 1280 SwiGLU 284 : 279 at 800 pairs, 333 : 303 at 1800.
+    const int64_t P = (int64_t)s.T * s.top_k;
+    if (s.dtype == MMOE_F32) return P <= (int64_t)kF32StreamRows * s.S;
+    const bool small_experts = (int64_t)s.d_model * s.d_ff <= ((int64_t)4 << 20);
+    return small_experts ? P <= (int64_t)20 * s.S && P <= 512 : P <= (int64_t)16 * s.S;
+}
+
+bool use_skinny(const mmoe_shape& s)
+{
+    if (few_rows(s)) return true;
+    const int64_t widest = s.d_model > s.d_ff ? s.d_model : s.d_ff;
+    return s.dtype == MMOE_F32 && (int64_t)s.T * s.top_k * widest >= ((int64_t)1 << 31);  // the tile lists' limit
+}
+
 // Room for the tile lists in a workspace: never less than they are counted at, so that a workspace size within
-// the limit means that the shape is accepted.
+// the limit means that the shape is accepted; and enough for any batch of up to this many tokens, so that a
+// workspace made for a program's largest batch holds the smaller ones, whose tiles may be other ones.
 static size_t tile_list_room(const mmoe_shape& s)
 {
-    const size_t counted = counted_list_bytes(s), need = tiled_table_bytes(s);
-    return need > counted ? need : counted;
+    const size_t counted = counted_list_bytes(s);
+    if (few_rows(s)) return counted;  // batches of up to this many tokens have no lists
+    const size_t most = tiled_table_most(s);
+    return most > counted ? most : counted;
 }
 
 WsLayout ws_layout(const mmoe_shape& s)
@@ -66,30 +98,6 @@ WsLayout ws_layout(const mmoe_shape& s)
     L.Yg = take(P * s.d_model * 4);
     L.total = off;
     return L;
-}
-
-// fp32: most rows per slot, on average, for the streaming kernels.  Measured with each kernel forced:
-// 768 x 3072 top-1, 13 slots: 77 (streaming) against 83 us at 9.8 rows per slot, 90 against 84 at 15.4;
-// 1024 x 2048 SwiGLU top-2: 95 against 92 us at 8 rows, 115 against 91 at 17; 2048 x 4096 SwiGLU: equal at 10.
-constexpr int kF32StreamRows = 12;
-
-bool use_skinny(const mmoe_shape& s)
-{
-    // A batch streams when a slot sees few rows: the weights are then read once from HBM and that
-    // read is the bound.  The streaming kernel takes 32 rows of a slot per pass over its weights, so it
-    // only pays while the fullest slot stays near that, and each of its workgroups looks through all pairs
-    // for its slot's, so it only pays while they are few.  Measured with each kernel forced, streaming
-    // against matrix-core tiles, us: 4096 x 14336 SwiGLU 777 : 793 at 12 rows per slot, 826 : 792 at 15;
-    // 2048 x 2048 SwiGLU 68 : 72 at 17, 82 : 73 at 25; 1280 x 2560 GELU 43 : 48 at 17, 52 : 51 at 25; 768 x 3072
-    // 37 : 39 at 15, 45 : 42 at 23; with many slots, 512 x 1024 SwiGLU 48 : 46 at 500 pairs, 57 : 49 at 800;
-    // 2048 x 1280 SwiGLU 284 : 279 at 800 pairs, 333 : 303 at 1800.
-    const int64_t P = (int64_t)s.T * s.top_k;
-    if (s.dtype == MMOE_F32) {
-        const int64_t widest = s.d_model > s.d_ff ? s.d_model : s.d_ff;
-        return P <= (int64_t)kF32StreamRows * s.S || P * widest >= ((int64_t)1 << 31);  // the tile lists' limit
-    }
-    const bool small_experts = (int64_t)s.d_model * s.d_ff <= ((int64_t)4 << 20);
-    return small_experts ? P <= (int64_t)20 * s.S && P <= 512 : P <= (int64_t)16 * s.S;
 }
 
 static inline bool misaligned(const void* p, size_t a) { return ((uintptr_t)p & (a - 1)) != 0; }

@@ -102,6 +102,8 @@ int launch_ffn_tiled(const mmoe_shape& s, const void* rows, const int32_t* perm,
                      hipStream_t st, hipEvent_t mid = nullptr, bool tab_ready = false,
                      SlotFilter filt = SlotFilter(), GateSink sink = GateSink());
 size_t tiled_table_bytes(const mmoe_shape& s);
+// Most that tiled_table_bytes() returns for a batch of up to this shape's tokens.
+size_t tiled_table_most(const mmoe_shape& s);
 int planned_tile_rows(const mmoe_shape& s);  // tile height launch_ffn_tiled would use for this shape
 // `inv_perm` null: Yg is indexed by pair id.
 int launch_combine(const mmoe_shape& s, const float* Yg, const int32_t* inv_perm, const float* topk_w,

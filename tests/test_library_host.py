@@ -226,3 +226,21 @@ def test_static_entry_point_takes_what_the_workspace_size_says(mm, d, f, S, E, k
         else:
             above += 1
     assert below and above
+
+
+@pytest.mark.parametrize("d,f,S,E,k,dtype,act,tile_rows", [
+    (256, 8448, 503, 4, 1, "bf16", "relu", 256), (1792, 256, 459, 64, 4, "bf16", "swiglu", 0),
+    (768, 5376, 13, 13, 1, "bf16", "gelu", 256), (1280, 2816, 556, 8, 4, "bf16", "gelu", 128),
+    (768, 3072, 18, 8, 1, "bf16", "relu", 0), (4096, 14336, 18, 8, 2, "bf16", "swiglu", 0),
+    (1024, 2048, 90, 4, 1, "f32", "swiglu", 0), (256, 16128, 1024, 8, 1, "bf16", "swiglu", 0)])
+def test_workspace_of_the_largest_batch_holds_every_smaller_one(mm, d, f, S, E, k, dtype, act, tile_rows):
+    """The workspace size never shrinks as T grows (kernels and list layouts change with T, and a program makes one
+    workspace for its largest batch), and the tile height that a call asks for does not change it."""
+    last = 0
+    for T in range(1, 5000):
+        size = mm.workspace_bytes(mm.make_shape(T, d, f, 2, E, S, k, dtype, act, tile_rows=tile_rows))
+        assert size >= last, (T, size, last)
+        last = size
+    for T in (700, 1920, 4000):
+        assert len({mm.workspace_bytes(mm.make_shape(T, d, f, 2, E, S, k, dtype, act, tile_rows=r))
+                    for r in (0, 128, 256)}) == 1
