@@ -225,9 +225,11 @@ int mmoe_layer_forward_paged(const mmoe_shape *shape, const void *X, const int32
  * results bit for bit.  The intermediates live in a fixed array of
  * MMOE_STATIC_WORKSPACE_BYTES in device memory that belongs to the library's code object (each
  * GPU the library runs on holds its own copy until the process ends).  The call allocates and
- * frees nothing.  A shape with mmoe_workspace_bytes() above that size is refused with
- * MMOE_ERR_STATIC_LIMIT before anything is launched (64 MiB covers decode-shaped batches: up to
- * about 700 tokens of the Mixtral shape, 6000 of the Switch shape).
+ * frees nothing.  A shape with mmoe_workspace_bytes() up to that size is accepted; one above it is
+ * refused with MMOE_ERR_STATIC_LIMIT before anything is launched, unless only its tile lists take it
+ * there: the limit counts them as two lists per product of 16 bytes for every 32 rows, slot and 1024
+ * features, and the array has the rest beside it.  (64 MiB covers decode-shaped batches: up to about
+ * 700 tokens of the Mixtral shape, 6000 of the Switch shape.)
  * Every call on one GPU uses that GPU's one array, whatever the stream: two calls that overlap
  * in time on one GPU race; order them (same stream, or events).  Nothing in the array has to
  * start at zero: every intermediate is written before it is read, so the contents left by an

@@ -398,10 +398,12 @@ int mmoe_layer_forward(const mmoe_shape* shape, const void* X, const int32_t* vi
 // Same kernels as mmoe_layer_forward; the intermediates live in a fixed array in device memory
 // that is part of the loaded code object instead of in a caller's workspace.  Each GPU holds its
 // own copy of the array at its own address; the address is looked up once per device.
-// The size limit a caller sees counts the tile lists with a plain bound of its own (static_need), so
-// that it does not move when the lists' layout does; the slack covers a layout that needs more than
-// that: at most 20 bytes per (row tile, feature tile), under a hundredth of the H and Yg beside them.
-constexpr size_t kStaticSlack = (size_t)1 << 20;
+// The size limit a caller sees (static_need) counts the tile lists at a plain rate of their own; the slack is for
+// what they take beyond that.  Per product, with NT feature tiles, that is 18 S (3/4 NT + 7) + P bytes at most in bf16
+// (eight lists of 9/8 (P/128 + S) ceil(NT/8) entries of 16 bytes against the rate's two).  A shape that has lists and
+// is within the limit has d_model * d_ff <= 2^22, so NT <= 128, or over 16 S pairs, so S NT <= 2^14: 2.1 MB with
+// S = 1024 and both products.  fp32 (tiles of 64 features, over 12 S pairs): under 1 MB.
+constexpr size_t kStaticSlack = (size_t)4 << 20;
 static __device__ __align__(256) unsigned char scratch[MMOE_STATIC_WORKSPACE_BYTES + kStaticSlack];
 
 namespace {

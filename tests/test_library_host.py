@@ -244,3 +244,32 @@ def test_workspace_of_the_largest_batch_holds_every_smaller_one(mm, d, f, S, E, 
     for T in (700, 1920, 4000):
         assert len({mm.workspace_bytes(mm.make_shape(T, d, f, 2, E, S, k, dtype, act, tile_rows=r))
                     for r in (0, 128, 256)}) == 1
+
+
+STATIC_LARGEST = [
+    # d, f, S, E, k, dtype, activation, largest accepted batch.  Many slots, feature tiles that do not divide among
+    # the XCDs: the lists take more than they are counted at
+    (256, 14080, 1024, 8, 1, "bf16", "swiglu", 2276),
+    (256, 8448, 1024, 8, 2, "bf16", "swiglu", 1858),
+    (256, 14592, 1024, 64, 2, "bf16", "swiglu", 1099),
+    (256, 14080, 821, 4, 4, "bf16", "relu", 570),
+    (256, 16128, 1024, 8, 1, "bf16", "gelu", 1994),
+    # and ordinary shapes
+    (2048, 1280, 90, 64, 4, "bf16", "swiglu", 1556),
+    (768, 3072, 18, 8, 1, "bf16", "relu", 7261),
+    (4096, 14336, 128, 8, 2, "bf16", "swiglu", 743),
+    (768, 3072, 1024, 8, 1, "f32", "relu", 4350),
+    (256, 5376, 300, 8, 1, "f32", "swiglu", 2971),
+]
+
+
+@pytest.mark.parametrize("d,f,S,E,k,dtype,act,largest", STATIC_LARGEST)
+def test_static_entry_point_size_limit(mm, d, f, S, E, k, dtype, act, largest):
+    """Which batches fit is a plain sum over the intermediates with the tile lists counted at a fixed rate: the
+    largest accepted batch of shapes whose lists need more room than that, and of shapes whose lists need less."""
+    def shape(T):
+        return mm.make_shape(T, d, f, 2, E, S, k, dtype, act)
+    for T in range(max(1, largest - 300), largest + 1):
+        assert not static_refuses(mm, shape(T)), T
+    for T in range(largest + 1, largest + 300):
+        assert static_refuses(mm, shape(T)), T
