@@ -36,6 +36,19 @@ template <> struct Raw4<uint16_t> {
     }
 };
 
+constexpr int kNoExpert = 0x7FFFFFFF;  // a lane with no expert left to offer
+
+// Expert e's bit among those of `lane`, which looks after experts lane, lane + 64, ...; 0 if it is another lane's.
+// kNoExpert is lane 63's by its low bits and has no bit: its shift count would be out of range.
+constexpr uint32_t expert_bit(int e, int lane)
+{
+    return e < kMaxE && (e & (kWave - 1)) == lane ? 1u << (e / kWave) : 0u;
+}
+// an out-of-range shift does not compile here
+static_assert(expert_bit(kNoExpert, kWave - 1) == 0 && expert_bit(kMaxE - 1, kWave - 1) == 1u << (kMaxE / kWave - 1) &&
+                  expert_bit(kWave, 0) == 2 && expert_bit(kWave, 1) == 0,
+              "bits of the experts a lane looks after");
+
 // The k winners among E logits in LDS, found by one wavefront: lane l looks after experts
 // l, l+64, l+128, l+192; k arg-max reductions, ties to the lower index; coefficients =
 // softmax over the selected logits.
@@ -61,11 +74,11 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
     for (int j = 0; j < kMaxTopK; ++j) {
         if (j < k) {
             float bv = -INFINITY;
-            int be = 0x7FFFFFFF;
+            int be = kNoExpert;
 #pragma unroll
             for (int q = 0; q < kPerLane; ++q) {  // ascending index: strict > keeps the lower one
                 int e = lane + q * kWave;
-                if (e < E && !(taken & (1u << q)) && (be == 0x7FFFFFFF || mine[q] > bv)) {
+                if (e < E && !(taken & (1u << q)) && (be == kNoExpert || mine[q] > bv)) {
                     bv = mine[q];
                     be = e;
                 }
@@ -75,13 +88,13 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
                 if (off >= E) continue;
                 float ov = __shfl_xor(bv, off, kWave);
                 int oe = __shfl_xor(be, off, kWave);
-                bool other_valid = oe != 0x7FFFFFFF, self_valid = be != 0x7FFFFFFF;
+                bool other_valid = oe != kNoExpert, self_valid = be != kNoExpert;
                 bool take = other_valid && (!self_valid || ov > bv || (ov == bv && oe < be));
                 if (take) { bv = ov; be = oe; }
             }
             sel[j] = bv;
             seli[j] = be;
-            if ((be & (kWave - 1)) == lane) taken |= 1u << (be / kWave);
+            taken |= expert_bit(be, lane);
         }
     }
     // gate over all experts: the normaliser is the sum of exp(logit - largest logit) over every expert
