@@ -224,8 +224,9 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     // vector-memory instructions were issued after the last of the older ones: the kDeep NJ copies
     // plus weight-fragment loads, whose place in the instruction stream the compiler
     // chooses.  Their count is therefore not taken on trust: tests/test_tiled_wait_counts.py
-    // reads the compiler's assembly output for this file and checks the rule at every written-out
-    // wait of every instantiation, along every path that reaches it.
+    // reads the compiler's assembly output for this file, where each such wait says how many copies may
+    // still be in flight at it, and checks the rule at every one of them, in every instantiation and along
+    // every path that reaches it.
     // What orders the LDS reads.  Before a stage is handed back to the copies, the fragments
     // of that stage that are still to be used are made operands of an (empty) asm statement in
     // front of the barrier, so the compiler itself waits for exactly those reads and for nothing
@@ -268,7 +269,9 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
             for (int i = 0; i < kNW; ++i) load_bf(bq[g], g, i);
         static_assert(kDeep * NJ + kNW * (kSlices - 1) <= 63, "vmcnt is a 6-bit counter");
         __builtin_amdgcn_sched_barrier(0);  // the weight loads are issued before the wait, not after it
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kDeep * NJ + kNW * (kSlices - 1)) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) ; copies in flight: %1\n\ts_barrier" ::"n"(kDeep * NJ + kNW * (kSlices - 1)),
+                     "n"(kDeep * NJ)
+                     : "memory");
 #pragma unroll
         for (int j = 0; j < RF; ++j)
             fa[j] = *reinterpret_cast<const bf16x8*>(lds_a + (j < NF ? frag_off[0] + j * 2048 : frag_off[1] + (j - NF) * 2048));
@@ -317,7 +320,9 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
                         // first fragments are fetched before the next barrier.
                         constexpr int kWaitN = kDeep * NJ + kNW * (2 * kDeep < kSlices + 1 ? 2 * kDeep : kSlices + 1);
                         static_assert(kWaitN <= 63, "vmcnt is a 6-bit counter");
-                        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kWaitN) : "memory");
+                        asm volatile("s_waitcnt vmcnt(%0) ; copies in flight: %1\n\ts_barrier" ::"n"(kWaitN),
+                                     "n"(kDeep * NJ)
+                                     : "memory");
                     }
                     const int q = gi / NF, j = gi % NF, slot = (u * G + gi) % RF;
                     const BFrags& fb = q ? f1 : f0;

@@ -4,8 +4,10 @@ compiler produced.
 The kernel copies token tiles global -> LDS with instructions the compiler does not track and
 orders them with ``s_waitcnt vmcnt(N)`` written next to every barrier.  Vector-memory
 instructions of a wavefront complete in issue order, so the wait guarantees "every copy but the
-most recent group of kNP has landed" exactly when at least N vector-memory instructions were
-issued after the last copy of the second most recent group.  Part of those N are weight loads
+most recent K has landed" exactly when at least N vector-memory instructions were issued after the
+last copy before those K.  K is the copies of the steps that may still be on their way: a step of a
+tile of NJ 32-row sub-tiles issues NJ, and floor(kNP / NJ) steps are (kNP: copies of a full tile's
+step).  The kernel writes K into a comment beside each wait.  Part of the N are weight loads
 whose position the compiler chooses, so the property is verified here, on the assembly text the
 device object is assembled from, at every such wait of every instantiation and along every path
 that reaches it.  No GPU needed.
@@ -48,7 +50,9 @@ class Func:
         cur = []
         self.blocks.append(cur)
         for ln in lines:
-            ln = ln.split(";")[0].rstrip()
+            # a wait keeps the number in its comment, as a second operand
+            m = re.search(r"; copies in flight: (\d+)", ln)
+            ln = ln.split(";")[0].rstrip() + (f", {m.group(1)}" if m else "")
             if not ln.strip():
                 continue
             m = re.match(r"^(\.LBB\w+):", ln)
@@ -90,20 +94,21 @@ def functions(text, prefix):
 
 
 def wait_sites(fn):
-    """(block, index, N) of every written-out "s_waitcnt vmcnt(N) ... ; s_barrier" pair."""
+    """(block, index, N, K) of every written-out "s_waitcnt vmcnt(N) ; copies in flight: K ; s_barrier"."""
     sites = []
     for b, ins_list in enumerate(fn.blocks):
         for i, ins in enumerate(ins_list[:-1]):
-            m = re.match(r"s_waitcnt\b.*\bvmcnt\((\d+)\)", ins)
-            if m and ins_list[i + 1].startswith("s_barrier"):
-                sites.append((b, i, int(m.group(1))))
+            if re.match(r"s_waitcnt\b.*\bvmcnt\(", ins) and ins_list[i + 1].startswith("s_barrier"):
+                m = re.match(r"s_waitcnt\s+vmcnt\((\d+)\)\s*, (\d+)$", ins)
+                assert m, f"{fn.name}: a wait in front of a barrier without its number of copies: {ins}"
+                sites.append((b, i, int(m.group(1)), int(m.group(2))))
     return sites
 
 
-def min_issued_since_older_copies(fn, block, index, knp):
+def min_issued_since_older_copies(fn, block, index, k):
     """Over every path that reaches the wait: the number of vector-memory instructions issued
-    after the last copy of the second most recent copy group (= before the (knp+1)-th copy, walking
-    backwards).  Returns the minimum, or None if some path reaches the function entry first."""
+    after the last copy that must have landed (the (k+1)-th copy, walking backwards).  Returns the
+    minimum, or None if some path reaches the function entry first."""
     best = [None]
     seen = set()
     stack = [(block, index, 0, 0)]   # block, instructions of it still to scan, copies seen, vm ops seen
@@ -114,7 +119,7 @@ def min_issued_since_older_copies(fn, block, index, knp):
             if ins.startswith(VM_PREFIXES):
                 if ins.startswith(COPY):
                     copies += 1
-                    if copies == knp + 1:
+                    if copies == k + 1:
                         best[0] = vm if best[0] is None else min(best[0], vm)
                         done = True
                         break
@@ -131,38 +136,50 @@ def min_issued_since_older_copies(fn, block, index, knp):
     return best[0]
 
 
-def check_function(fn, knp):
-    """List of (N, issued) for every written-out wait; raises on a violated one."""
+def check_function(fn):
+    """List of (N, K, issued) for every written-out wait; raises on a violated one."""
     res = []
-    for b, i, n in wait_sites(fn):
-        issued = min_issued_since_older_copies(fn, b, i, knp)
-        assert issued is not None, f"{fn.name}: a path reaches the wait before {knp + 1} copies were issued"
+    for b, i, n, k in wait_sites(fn):
+        issued = min_issued_since_older_copies(fn, b, i, k)
+        assert issued is not None, f"{fn.name}: a path reaches the wait before {k + 1} copies were issued"
         assert issued >= n, (f"{fn.name}: s_waitcnt vmcnt({n}) is preceded by only {issued} vector-memory "
-                             f"instructions since the older copy groups: an older copy could still be in flight")
-        res.append((n, issued))
+                             f"instructions since the copies that must have landed: one could still be in flight")
+        res.append((n, k, issued))
     return res
+
+
+def variants(name):
+    """(NJ, K, number of waits) of every height a tile of this instantiation can have."""
+    bm, nb = (int(x) for x in re.search(r"ILi\d+ELi(\d+)ELi(\d+)EE", name).groups())
+    knp = bm * 8 // 256                                   # copies per wavefront and step of a full tile
+    steps_per_trip = 4 if bm == 256 or nb == 1 else 2
+    # one wait in the prologue and one per unrolled step of the main loop
+    return [(nj, knp // nj * nj, 1 + steps_per_trip) for nj in range(1, bm // 32 + 1)]
 
 
 def test_checker_flags_a_short_window():
     """The checker itself: a hand-written stream in which a weight load has been moved from behind
     the copies to in front of them must be refused, the original accepted."""
     def stream(loads_after):
-        body = ["\tglobal_load_lds_dwordx4 v1, s[0:1]"] * 2                     # older group (knp = 2)
+        body = ["\tglobal_load_lds_dwordx4 v1, s[0:1]"] * 2                     # older group
         body += ["\tglobal_load_dwordx4 v[2:5], v[6:7], off"] * (3 - loads_after)
         body += ["\tglobal_load_lds_dwordx4 v1, s[0:1]"] * 2                    # older group
         body += ["\tglobal_load_dwordx4 v[2:5], v[6:7], off"] * loads_after
         body += ["\tglobal_load_lds_dwordx4 v1, s[0:1]"] * 2                    # most recent group
-        body += ["\ts_waitcnt vmcnt(5)", "\ts_barrier", "\ts_endpgm"]
+        body += ["\ts_waitcnt vmcnt(5) ; copies in flight: 2", "\ts_barrier", "\ts_endpgm"]
         return Func("f", body)
-    assert check_function(stream(3), knp=2) == [(5, 5)]
+    assert check_function(stream(3)) == [(5, 2, 5)]
     with pytest.raises(AssertionError):
-        check_function(stream(2), knp=2)
+        check_function(stream(2))
     # a loop: the window wraps around the back edge
     loop = Func("g", ["\tglobal_load_lds_dwordx4 v1, s[0:1]", ".LBB9_1:",
-                      "\tglobal_load_dwordx4 v[2:5], v[6:7], off", "\ts_waitcnt vmcnt(2)", "\ts_barrier",
+                      "\tglobal_load_dwordx4 v[2:5], v[6:7], off", "\ts_waitcnt vmcnt(2) ; copies in flight: 1", "\ts_barrier",
                       "\tglobal_load_lds_dwordx4 v1, s[0:1]", "\ts_cbranch_scc1 .LBB9_1", "\ts_endpgm"])
     with pytest.raises(AssertionError):     # first trip: only one copy precedes the wait
-        check_function(loop, knp=1)
+        check_function(loop)
+    # a wait that does not say what it leaves in flight
+    with pytest.raises(AssertionError):
+        check_function(Func("h", ["\tglobal_load_lds_dwordx4 v1, s[0:1]", "\ts_waitcnt vmcnt(0)", "\ts_barrier"]))
 
 
 def test_every_written_out_wait_of_the_tiled_kernel_is_covered():
@@ -172,10 +189,23 @@ def test_every_written_out_wait_of_the_tiled_kernel_is_covered():
     # once more with one weight block per wavefront (128-row tiles only)
     assert len(fns) == 14, [f.name for f in fns]
     for fn in fns:
-        bm, nb = (int(x) for x in re.search(r"ILi\d+ELi(\d+)ELi(\d+)EE", fn.name).groups())
-        knp = bm * 8 // 256                               # copies per wavefront and step
-        nj_variants, steps_per_trip = bm // 32 if bm == 256 else 4, (16 if bm == 256 or nb == 1 else 8) // 4
-        res = check_function(fn, knp)
-        # one wait in the prologue and one per unrolled step of the main loop, per instantiation
-        assert len(res) == nj_variants * (1 + steps_per_trip), (fn.name, len(res))
-        print(f"{fn.name}: {len(res)} waits, smallest margin {min(i - n for n, i in res)}")
+        res = check_function(fn)
+        want = sorted(k for _, k, waits in variants(fn.name) for _ in range(waits))
+        assert sorted(k for _, k, _ in res) == want, fn.name
+        print(f"{fn.name}: {len(res)} waits, smallest margin {min(i - n for n, _, i in res)}")
+
+
+def test_loads_moved_across_a_wait_are_flagged():
+    """A mistake planted in the assembly text: the waits with one number of copies in flight (tiles of 3, 5, 6 and 7
+    sub-tiles have their own) leave three more instructions outstanding than the kernel asks for, as if three loads had
+    been moved behind them.  Every kernel must be refused for each of its numbers."""
+    text = device_assembly()
+    for name in sorted({fn.name for fn in functions(text, "_ZN4mmoe12tiled_kernel")}):
+        body = re.search(r"^%s:.*?^\.Lfunc_end\d+:" % re.escape(name), text, re.S | re.M).group(0).splitlines()[1:]
+        for k in sorted({k for _, k, _ in variants(name)}):
+            pat = r"s_waitcnt vmcnt\((\d+)\) ; copies in flight: %d$" % k
+            moved = [re.sub(pat, lambda m: f"s_waitcnt vmcnt({int(m.group(1)) + 3}) ; copies in flight: {k}", ln.rstrip())
+                     for ln in body]
+            assert moved != [ln.rstrip() for ln in body]
+            with pytest.raises(AssertionError, match="could still be in flight"):
+                check_function(Func(name, moved))
