@@ -89,6 +89,9 @@ CASES = [
     (synth.Config("p_stream_f32", 50, 256, 512, 3, 4, 1, "f32", "relu", seed=62), none_resident),
     (synth.Config("p_tiled_bf16", 900, 512, 768, 2, 4, 2, "bf16", "swiglu", seed=63), every_other),
     (synth.Config("p_tiled_gelu_all", 1100, 256, 512, 3, 8, 1, "bf16", "gelu", seed=64, gate="all"), none_resident),
+    # fp32 matrix-core tiles: one table of tiles, rewritten for the second pass
+    (synth.Config("p_tiled_f32_k1", 300, 256, 512, 2, 4, 1, "f32", "gelu", seed=67), every_other),
+    (synth.Config("p_tiled_f32_k2", 260, 512, 768, 2, 4, 2, "f32", "swiglu", seed=68), none_resident),
     (synth.Config("p_all_resident", 64, 256, 256, 2, 4, 2, "bf16", "swiglu", seed=65), all_resident),
     # a pool with slots that no token touches: those are never fetched
     (synth.Config("p_untouched", 6, 256, 256, 4, 8, 1, "bf16", "relu", seed=66), none_resident),
@@ -98,6 +101,10 @@ CASES = [
 @pytest.mark.parametrize("cfg,resident_of", CASES, ids=lambda c: getattr(c, "name", None))
 def test_paged_layer(mm, oracle, cfg, resident_of):
     import gpu_common as gc
+    if "_tiled_" in cfg.name or "_stream_" in cfg.name:
+        S = int(synth.make_inputs(cfg, weights=False)["S"])
+        shape = mm.make_shape(cfg.T, cfg.d_model, cfg.d_ff, cfg.V, cfg.E, S, cfg.top_k, cfg.dtype, cfg.act)
+        assert mm.expert_plan(shape)[0] == ("_stream_" in cfg.name)
     n = paged_case(mm, gc, oracle, cfg, resident_of)
     if resident_of is all_resident:
         assert n == 0

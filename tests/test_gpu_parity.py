@@ -68,12 +68,13 @@ def staged_vs_oracle(mm, gc, oracle, cfg, inp=None, tile_rows=0):
 
 
 SMALL = [
-    # weight-streaming kernels (few rows per slot), ragged row counts, several 16-row blocks
+    # weight-streaming kernels (few rows per slot; the two fp32 cases with more have matrix-core tiles), ragged
+    # row counts, several 16-row blocks
     synth.Config("s_bf16_swiglu", 45, 512, 768, 3, 4, 2, "bf16", "swiglu", seed=1),
     synth.Config("s_bf16_relu", 70, 256, 512, 2, 8, 1, "bf16", "relu", seed=2),
     synth.Config("s_f32_relu", 33, 256, 512, 2, 4, 1, "f32", "relu", seed=3),
     synth.Config("s_f32_swiglu", 50, 512, 256, 2, 4, 2, "f32", "swiglu", seed=4, bias_alpha=0.5),
-    synth.Config("s_f32_many_rows", 300, 256, 256, 1, 2, 1, "f32", "relu", seed=5),     # > 32 rows: passes
+    synth.Config("s_f32_many_rows", 300, 256, 256, 1, 2, 1, "f32", "relu", seed=5),     # fp32 matrix-core tiles
     # few rows per slot on average, but a biased router fills one slot beyond a 32-row pass
     synth.Config("s_bf16_skewed_passes", 100, 512, 256, 1, 8, 1, "bf16", "swiglu", seed=26, bias_alpha=3.0),
     # matrix-core tiled kernels (many rows per slot), ragged tails, several tiles per slot
@@ -85,13 +86,38 @@ SMALL = [
     # batches large enough for the wavefront-per-token router, odd expert counts, fp32 and bf16
     synth.Config("r_f32_odd_e", 2100, 512, 256, 2, 5, 2, "f32", "swiglu", seed=17, bias_alpha=0.7),
     synth.Config("r_bf16_odd_e", 2060, 1536, 256, 3, 7, 2, "bf16", "relu", seed=18, bias_alpha=0.3),
-    # one pick per token (the down product writes the layer's output rows itself) where the grouping
-    # kernels have run: streaming kernels in fp32 and, with many slots, in bf16; matrix-core kernels at
-    # both tile heights are t_bf16_relu
+    # one pick per token (the down product writes the layer's output rows itself) on the matrix-core kernels, fp32
+    # and, with many slots, bf16; both tile heights are t_bf16_relu.  (Streaming after the grouping: STREAMED.)
     synth.Config("k1_f32_grouped", 1500, 256, 512, 2, 6, 1, "f32", "gelu", seed=27),
     synth.Config("k1_bf16_grouped_stream", 1300, 512, 256, 8, 16, 1, "bf16", "relu", seed=28, share_prob=0.1),
     synth.Config("k1_bf16_long_k", 1100, 2048, 256, 2, 4, 1, "bf16", "relu", seed=29),     # tall-tile shape rule
 ]
+
+
+STREAMED = [
+    # more pairs than the expert kernels group themselves: the grouping kernel, then the streaming kernels through perm
+    # (experts of over 4 Mi elements, many slots; fp32 with many slots), one and two picks per token
+    synth.Config("stream_grouped_bf16_k1", 1060, 256, 16640, 2, 64, 1, "bf16", "relu", seed=70, share_prob=0.9),
+    synth.Config("stream_grouped_bf16_k2", 530, 2048, 2304, 2, 64, 2, "bf16", "swiglu", seed=71, share_prob=0.9),
+    synth.Config("stream_grouped_f32_k1", 1300, 256, 512, 8, 16, 1, "f32", "gelu", seed=72, share_prob=0.1),
+    synth.Config("stream_grouped_f32_k2_two_chunks", 1200, 256, 256, 64, 16, 2, "f32", "relu", seed=73, share_prob=0.1),
+    # fp32: a biased router fills one slot beyond a 32-row pass
+    synth.Config("stream_f32_skewed_passes", 90, 512, 256, 1, 8, 1, "f32", "swiglu", seed=74, bias_alpha=3.0),
+    # several hundred slots, most of them empty, on the kernels that group the pairs themselves
+    synth.Config("stream_many_slots", 250, 256, 256, 64, 16, 2, "bf16", "swiglu", seed=75, share_prob=0.1),
+]
+
+
+@pytest.mark.parametrize("cfg", STREAMED, ids=lambda c: c.name)
+def test_streaming_kernels(mm, gc, oracle, cfg):
+    """Every stage and the fused call where the dispatch streams: the plan is asserted, so that a dispatch line that
+    moves does not take the case to the other kernels unseen."""
+    case, ref = staged_vs_oracle(mm, gc, oracle, cfg)
+    assert mm.expert_plan(case.shape) == (True, 32)
+    if "grouped" in cfg.name:
+        assert cfg.P > 1024
+    if "passes" in cfg.name:
+        assert ref["counts"].max() > 32
 
 
 @pytest.mark.parametrize("cfg", SMALL, ids=lambda c: c.name)
@@ -407,8 +433,7 @@ def test_limits_many_slots_and_widest_router(mm, gc, oracle):
     cfg = synth.Config("many_slots_tiled", 6000, 256, 256, 8, 16, 2, "bf16", "swiglu", seed=23, share_prob=0.3)
     case, ref = staged_vs_oracle(mm, gc, oracle, cfg)
     assert case.S > 80
-    # several hundred slots and more pairs than one grouping workgroup takes: the scatter workgroups sum
-    # four slots per thread of the per-workgroup histograms themselves
+    # several hundred slots and enough pairs for the matrix-core kernels at two or three rows per slot
     cfg = synth.Config("many_slots_two_chunks", 1200, 256, 256, 64, 16, 2, "bf16", "swiglu", seed=30, share_prob=0.1)
     case, ref = staged_vs_oracle(mm, gc, oracle, cfg)
     assert 800 < case.S <= 1024
@@ -481,7 +506,7 @@ def _random_configs(n, seed):
         k = int(rng.integers(1, min(E, 4) + 1))
         T = int(rng.choice([1, 7, 64, 200, 511, 512, 700, 1100, 2047, 2048, 2300]))
         if dtype == "f32":
-            T = min(T, 300) if i % 2 else T  # fp32 never uses the tiled kernels; half the cases stay small
+            T = min(T, 300) if i % 2 else T  # half the cases stay small (the oracle's time)
         out.append(synth.Config(f"rnd{i}_{dtype}_{act}_T{T}_d{d}_f{f}_V{V}_E{E}_k{k}", T, d, f, V, E, k, dtype, act,
                                 seed=1000 + i, bias_alpha=float(rng.choice([0.0, 0.5])),
                                 vid_mode=str(rng.choice(["uniform", "zipf", "interleave"])),

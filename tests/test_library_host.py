@@ -174,7 +174,7 @@ def test_expert_plan_follows_the_documented_dispatch(mm):
         return mm.expert_plan(mm.make_shape(c.T, c.d_model, c.d_ff, c.V, c.E, S, c.top_k, c.dtype, c.act,
                                             tile_rows=tile_rows))
 
-    assert plan("switch8_fp32_v2_t128", 12) == (True, 32)            # fp32 always streams
+    assert plan("switch8_fp32_v2_t128", 12) == (True, 32)            # fp32, 11 rows per slot
     assert plan("mixtral_decode_bf16_v2_t64", 13) == (True, 32)      # 10 rows per slot
     assert plan("switch8_bf16_v4_t4096", 20) == (False, 128)         # short reduction: 128-row tiles
     assert plan("mixtral_prefill_bf16_v2_t8192", 13) == (False, 256)

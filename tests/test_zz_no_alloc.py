@@ -44,3 +44,28 @@ def test_static_workspace_entry_point_matches_the_workspace_one(oracle):
     p = torch.zeros(64, device="cuda").data_ptr()
     rc = mmoe.lib().mmoe_layer_forward_static(ctypes.byref(big), p, p, p, None, p, p, p, p, p, None)
     assert rc == -11 and "MMOE_STATIC_WORKSPACE_BYTES" in mmoe.strerror(rc)
+
+
+def test_static_entry_point_holds_the_largest_tile_lists():
+    """The largest batch that the size limit admits of a shape whose tile lists take more than the limit counts for
+    them (a thousand slots, 110 feature tiles): the outputs equal the workspace entry point's."""
+    from paper_2505_06481_amd import mmoe
+
+    T, d, f, V, E = 2276, 256, 14080, 128, 8
+    S = V * E
+    shape = mmoe.make_shape(T, d, f, V, E, S, 1, "bf16", "swiglu")
+    assert mmoe.workspace_bytes(shape) > mmoe.STATIC_WORKSPACE_BYTES and mmoe.expert_plan(shape) == (False, 128)
+    print(f"T={T} d={d} f={f} S={S}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(76)
+    X = torch.randn((T, d), generator=gen, device="cuda").bfloat16()
+    Wr = torch.randn((V, E, d), generator=gen, device="cuda").mul_(0.1).bfloat16()
+    vid = torch.randint(0, V, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    M = torch.arange(S, dtype=torch.int32, device="cuda").view(V, E)
+    # any numbers are a packed matrix; one buffer serves as all three
+    W = torch.randn(S * d * f, generator=gen, device="cuda", dtype=torch.bfloat16).mul_(0.05)
+    Y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    mmoe.layer_forward_static(shape, X, vid, Wr, None, M, W, W, W, Y=Y)
+    torch.cuda.synchronize()
+    want = mmoe.layer_forward(shape, X, vid, Wr, None, M, W, W, W, mmoe.alloc_workspace(shape))
+    torch.cuda.synchronize()
+    assert torch.isfinite(Y.float()).all() and torch.equal(Y, want)
