@@ -94,8 +94,8 @@ typedef struct {
     int32_t gate;    /* mmoe_gate                                */
     int32_t tile_rows; /* tuning, normally 0: token rows per tile of the matrix-core expert kernels.
                           0 chooses by shape: 128 rows (two workgroups per compute unit) when tiles are
-                          short-lived (d_model <= 1024, or fewer than 64 rows per slot on average), 256
-                          rows otherwise.  128 or 256 forces that height for the call.  Either height sums
+                          short-lived (d_model <= 1536, or few rows per slot on average: under 100 up to
+                          d_model 2048, under 64 beyond), 256 rows otherwise.  128 or 256 forces that height for the call.  Either height sums
                           every output element in the same order: the results are bit-identical.  Any
                           other value: MMOE_ERR_DIM.  Ignored by fp32 and by shapes that use the streaming kernels. */
 } mmoe_shape;
@@ -279,8 +279,8 @@ int mmoe_expert_plan(const mmoe_shape *shape, int *streaming, int *tile_rows);
  * delivers for the two resources that bound the expert stage: out[0] = GB/s of a pure
  * streaming read of `buf` (DEVICE memory, `bytes` >= 64 MiB, 256-byte aligned, zero-filled by
  * the caller; its last MiB is written), out[1] = TFLOP/s of a loop of
- * v_mfma_f32_32x32x16_bf16 on register operands with no memory traffic.  `out` is a HOST
- * array of two floats.  Benchmarks print these beside the data-sheet peaks.
+ * v_mfma_f32_16x16x32_bf16, the expert kernels' instruction, on random register operands with no
+ * memory traffic.  `out` is a HOST array of two floats.  Benchmarks print these beside the data-sheet peaks.
  */
 int mmoe_probe_ceilings(void* buf, size_t bytes, float* out, void* stream);
 

@@ -16,8 +16,8 @@
 // half of their rows, a 16 x 32 operand: a wavefront loads its weight operands straight from global
 // memory into registers (16 bytes per lane, 256-byte runs), three 32-k slices ahead of their use (seven where the tile leaves the registers).
 // Token rows are copied global -> LDS without passing registers (global_load_lds, 16 bytes per lane)
-// into a four-stage ring of LDS tiles, [row][64 k] bf16 (128 bytes a row) with the 16-byte pieces
-// xor-swizzled by (row >> 1) & 7, and are read back as fragments; one barrier per step.
+// into a ring of LDS tiles (four stages of full tiles, up to eleven of short ones), [row][64 k] bf16 (128 bytes a row)
+// with the 16-byte pieces xor-swizzled by (row >> 1) & 7, and are read back as fragments; one barrier per step.
 //
 // Ragged groups: row ranges come from the device array `offsets`.  A small
 // preparation step turns them into lists of tiles; the product kernels map their
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
                     __builtin_amdgcn_sched_barrier(0);
                     // groups of this half that memory instructions may follow: all before the barrier
                     const int half = gi / NF, ng = half ? kBar - NF : NF, at = gi - half * NF;
-                    // NJ = 1: the barrier stands in front of the second half, whose instructions join the first
+                    // where few groups put the barrier in front of the second half, its instructions join the first
                     if (kBar > NF) {
 #pragma unroll
                         for (int op = 0; op < kNP + kNW; ++op)
@@ -478,8 +478,8 @@ int planned_tile_rows(const mmoe_shape& s)
 }
 
 // Most sub-tiles of a row tile: a full tile.  (Shorter tiles for products with few tiles were
-// measured on the Switch shape and lose: every tile streams its whole weight panel, and a step of
-// a short tile is over before the copies issued two steps earlier have landed.)
+// measured on the Switch shape and lost: every tile streams its whole weight panel.  That was with one step's
+// copies in flight, before short tiles had several.)
 static int planned_upt(const mmoe_shape&, int bm) { return bm / 32; }
 
 static TiledPlan tiled_plan(const mmoe_shape& s)

@@ -6,8 +6,8 @@
 // What bounds it: the fp32 matrix rate (256 flop per cycle and compute unit), a sixteenth of bf16's, so a
 // tile moves little per flop and the design is plain.  Tile: up to 96 token rows x 64 output features x
 // 32 k per step, four wavefronts, 16 features each (of both weight matrices for the gated product, so that
-// SiLU(gate)*up is lane-local) and all rows; two workgroups per compute unit, one's barriers and epilogue
-// behind the other's matrix instructions.  64 features rather than 128: the down product of a 768-wide
+// SiLU(gate)*up is lane-local) and all rows; three workgroups per compute unit (two of the gated product), one's barriers
+// and epilogue behind the others' matrix instructions.  64 features rather than 128: the down product of a 768-wide
 // layer has 12 feature tiles a slot, 6 would leave a third of the chip idle in the last round.
 //   weights   global -> registers, a row's 128 bytes per step by four lanes, two steps ahead;
 //   tokens    global -> registers two steps ahead -> LDS (three stages, 16-byte pieces xor-swizzled by
@@ -40,8 +40,8 @@ constexpr int kFRing = 4;          // weight steps in registers (static indexes 
 constexpr int kChain = 256;        // k per chain of matrix instructions
 static_assert(kChain % (kFK * kFRing) == 0, "tile and unrolling");
 
-// Workgroups per compute unit: three, as many as the token stages and the registers allow; two for the gated
-// product, whose accumulators are twice as many (three with tiles of 64 rows instead: 4 to 30 % slower).
+// Workgroups per compute unit: three, as many as the token stages and the registers allow (168 of them; the tallest
+// tile spills 8 to 12 more); two for the gated product, whose accumulators are twice as many (three with tiles of 64 rows instead: 4 to 30 % slower).
 constexpr int resident(int mode) { return mode == kModeSwigluH ? 2 : 3; }
 
 template <int MODE>

@@ -3,9 +3,10 @@
 // ceiling as well as against the data-sheet peak.
 //   stream read   every workgroup reads its share of a buffer once with 16-byte loads, many
 //                 loads in flight per lane: the HBM bandwidth a weight-streaming kernel can reach;
-//   matrix loop   every wavefront issues v_mfma_f32_32x32x16_bf16 on register operands into 16
-//                 independent accumulator tiles, no memory traffic: the matrix-core rate the
-//                 chip sustains at the clock its power limit allows.
+//   matrix loop   every wavefront issues v_mfma_f32_16x16x32_bf16, the instruction of the expert kernels, on
+//                 random register operands into 64 independent accumulator tiles, no memory traffic: the
+//                 matrix-core rate the chip sustains at the clock its power limit allows (which depends on
+//                 the operands: constant ones toggle less and run faster).
 #include "mmoe_internal.h"
 
 namespace mmoe {
@@ -30,25 +31,46 @@ __global__ __launch_bounds__(256) void probe_read_kernel(const u32x4* __restrict
 
 __global__ __launch_bounds__(256, 1) void probe_mfma_kernel(int iters, float* __restrict__ sink)
 {
-    f32x16 acc[16];
+    constexpr int kA = 4, kB = 16;  // an expert kernel's weight blocks and token fragments per wavefront
+    f32x4 acc[kB][kA];
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+    for (int j = 0; j < kB; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] = 0.0f;
-    // operands with a spread of exponents and mantissas, different in every lane
-    bf16x8 a, b;
+        for (int i = 0; i < kA; ++i) acc[j][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // operands in [-2, 2), every bit of sign and mantissa random, different in every lane and register
+    uint32_t state = (blockIdx.x * 256 + threadIdx.x) * 2654435761u + 12345u;
+    auto draw = [&]() {
+        bf16x8 v;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        a[e] = (bf16_t)(0.01f * (float)((threadIdx.x * 7 + e * 13) % 61 - 30));
-        b[e] = (bf16_t)(0.02f * (float)((threadIdx.x * 11 + e * 5) % 53 - 26));
-    }
+        for (int e = 0; e < 8; ++e) {
+            state = state * 1664525u + 1013904223u;
+            v[e] = (bf16_t)((float)(int32_t)state * 0x1p-30f);
+        }
+        return v;
+    };
+    bf16x8 a[kA], b[kB];
+#pragma unroll
+    for (int i = 0; i < kA; ++i) a[i] = draw();
+#pragma unroll
+    for (int j = 0; j < kB; ++j) b[j] = draw();
+    asm volatile("s_nop 15" :::);  // the operands and accumulators are written: nothing in the loop waits for them
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int t = 0; t < 16; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[t], 0, 0, 0);
+        for (int j = 0; j < kB; ++j)
+#pragma unroll
+            for (int i = 0; i < kA; ++i)  // in assembly: the accumulators stay where they are
+                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[j][i]) : "v"(a[i]), "v"(b[j]));
     }
+    asm volatile("s_nop 15\n\ts_nop 15" :::);  // the last results are there before they are read
+#pragma unroll
+    for (int j = 0; j < kB; ++j)
+#pragma unroll
+        for (int i = 0; i < kA; ++i) asm volatile("" : "+a"(acc[j][i]));
     float s = 0.0f;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) s += acc[t][0];
+    for (int j = 0; j < kB; ++j)
+#pragma unroll
+        for (int i = 0; i < kA; ++i) s += acc[j][i][0];
     if (s == 12345.678f) sink[blockIdx.x] = s;  // keeps the accumulators alive
 }
 
@@ -85,9 +107,9 @@ int run_probe(void* buf, size_t bytes, float* out, hipStream_t st)
     out[0] = ok ? (float)((double)(n / per_stride * per_stride) * 16.0 * reps / (ms * 1e-3) / 1e9) : 0.0f;  // GB/s
 
     // matrix loop: 1024 workgroups of four wavefronts (four rounds of one per compute unit)
-    const int iters = 4096, grid_m = 1024;
+    const int iters = 2048, grid_m = 1024;
     ms = timed([&] { hipLaunchKernelGGL(probe_mfma_kernel, dim3(grid_m), dim3(256), 0, st, iters, (float*)sink); });
-    const double flop = (double)grid_m * 4 * iters * 16 * (2.0 * 32 * 32 * 16) * reps;
+    const double flop = (double)grid_m * 4 * iters * 64 * (2.0 * 16 * 16 * 32) * reps;
     out[1] = ok ? (float)(flop / (ms * 1e-3) / 1e12) : 0.0f;  // TFLOP/s
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -62,7 +62,8 @@ inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, in
     TileLists L;
     L.upt[0] = upt_up;
     L.upt[1] = upt_down;
-    // fp32: two workgroups of a compute unit share its matrix pipes, so they count as one round of two
+    // fp32: the workgroups of a compute unit (three, two of the gated product) share its matrix pipes, which bound
+    // them, so a compute unit counts as working on one tile at a time
     L.conc = bm == kBMBig || f32 ? 32 : 64;
     for (int p = 0; p < 2; ++p) {
         // Row tiles the lists have room for: an eighth more than full tiles can need (fp32: than tiles of two
