@@ -52,10 +52,16 @@ static bool few_rows(const mmoe_shape& s)
     // 2048 x 2048 SwiGLU 68 : 72 at 17, 82 : 73 at 25; 1280 x 2560 GELU 43 : 48 at 17, 52 : 51 at 25; 768 x 3072
     // 37 : 39 at 15, 45 : 42 at 23; with many slots, 512 x 1024 SwiGLU 48 : 46 at 500 pairs, 57 : 49 at 800;
     // 2048 x 1280 SwiGLU 284 : 279 at 800 pairs, 333 : 303 at 1800.
+    // In a pool of 4 to 11 slots the tiles' grouping launch (8 us) weighs more: 32 to 21 rows per slot.  Rows spread evenly / unequally (router bias
+    // 0.5): 768 x 3072, 4 slots, 24 rows per slot 25 : 34 / 30 : 36, 32 rows 29 : 35 / 38 : 37; 8 slots, 24 rows
+    // 30 : 43 / 46 : 45, 28 rows 36 : 44 / 51 : 46; 16 slots, 24 rows 56 : 57 / 71 : 58; 2048 x 2048 SwiGLU, 4 slots, 32 rows
+    // 44 : 60 / 45 : 60, 8 slots, 24 rows 56 : 66 / 62 : 68, 28 rows 63 : 67 / 68 : 68.  (With bias 2.5 one slot has half of
+    // the rows, 8 slots, 24 rows: 72 : 36 and 61 : 57.  The host does not know the counts.)
     const int64_t P = (int64_t)s.T * s.top_k;
     if (s.dtype == MMOE_F32) return P <= (int64_t)kF32StreamRows * s.S;
     const bool small_experts = (int64_t)s.d_model * s.d_ff <= ((int64_t)4 << 20);
-    return small_experts ? P <= (int64_t)20 * s.S && P <= 512 : P <= (int64_t)16 * s.S;
+    if (!small_experts) return P <= (int64_t)16 * s.S;
+    return P <= 512 && (P <= (int64_t)20 * s.S || (s.S >= 4 && P <= (int64_t)14 * s.S + 72));
 }
 
 bool use_skinny(const mmoe_shape& s)

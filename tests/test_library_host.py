@@ -193,6 +193,9 @@ def test_expert_plan_follows_the_documented_dispatch(mm):
 @pytest.mark.parametrize("d,f,S,P,want", [
     (2048, 2048, 12, 240, (True, 32)), (2048, 2048, 12, 241, (False, 128)),     # small experts: 20 rows per slot
     (512, 1024, 64, 512, (True, 32)), (512, 1024, 64, 513, (False, 128)),       # and at most 512 pairs
+    (768, 3072, 4, 128, (True, 32)), (768, 3072, 4, 129, (False, 128)),         # 4 to 11 slots: 14 rows and 72 pairs more
+    (2048, 2048, 8, 184, (True, 32)), (2048, 2048, 8, 185, (False, 128)),
+    (768, 3072, 3, 60, (True, 32)), (768, 3072, 3, 61, (False, 128)),
     (1536, 3072, 8, 16000, (False, 128)), (1792, 3072, 8, 799, (False, 128)), (1792, 3072, 8, 800, (False, 256)),
     (2304, 3072, 8, 511, (False, 128)), (2304, 3072, 8, 512, (False, 256)),     # tall tiles by rows per slot
 ])
