@@ -33,9 +33,9 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # to one version of the kernel's sources (the kernel file and the tile-list builder that decides
 # which tiles it runs); with any other version `traffic` is null.
 TRAFFIC = {
-    "ffn_tiled.hip": {"sources": ("ffn_tiled.hip", "tile_table.h"), "sha256": "010729f1edd0a95d7f56e6be3a7c729c20803eaf7298375dcf71424eaabbcee0",
+    "ffn_tiled.hip": {"sources": ("ffn_tiled.hip", "tile_table.h"), "sha256": "43b709161827d2e82d2e9eec64b11a7e185f5a0bacb98c748417206da8ef4ae3",
                       "workload": "mixtral_prefill_bf16_v2_t8192",
-                      "fetch_bytes": 10971821914, "write_bytes": 469762380},
+                      "fetch_bytes": 11760644462, "write_bytes": 469763470},
     "ffn_skinny.hip": {"sources": ("ffn_skinny.hip",), "sha256": "6251fdfca2475672fcf8c0de351e5d1c7ea8df1bf17f56ce71ef8f3fdd6a3716",
                        "workload": "mixtral_decode_bf16_v2_t64",
                        "fetch_bytes": 3068027183, "write_bytes": 3670794},

@@ -18,8 +18,8 @@
 // rows, for each 32 rows of a slot; here once for 96.
 // Measured with it against the streaming kernel (768 x 3072, top-1, 13 slots): 640 tokens 215 -> 115 us,
 // 2000 tokens 569 -> 236 us, 4096 tokens 1108 -> 430 us; 1024 x 2048 SwiGLU, top-2, 12 slots, 600 tokens:
-// 405 -> 195 us.  At 2000 tokens the matrix pipes are busy for 65 % of the up product (its tiles: 4.9 rounds of
-// the chip, 13 % idle at the end).
+// 405 -> 195 us.  At 2000 tokens each product runs at 80 of 157 TFLOP/s; the matrix pipes are busy for 74 % of the
+// cycles in which their compute unit has work (SQ_VALU_MFMA_BUSY_CYCLES / 4 / SQ_BUSY_CU_CYCLES).
 //
 // Summation: a chain of matrix instructions runs over kChain k values from zero and is then added to
 // the running total, so rounding errors do not build up over the whole reduction dimension (the
@@ -41,7 +41,8 @@ constexpr int kChain = 256;        // k per chain of matrix instructions
 static_assert(kChain % (kFK * kFRing) == 0, "tile and unrolling");
 
 // Workgroups per compute unit: three, as many as the token stages and the registers allow (168 of them; the tallest
-// tile spills 8 to 12 more); two for the gated product, whose accumulators are twice as many (three with tiles of 64 rows instead: 4 to 30 % slower).
+// tile spills 8 to 12 more); two for the gated product, whose accumulators are twice as many (three with tiles of 64 rows
+// instead: 4 to 30 % slower).
 constexpr int resident(int mode) { return mode == kModeSwigluH ? 2 : 3; }
 
 template <int MODE>
