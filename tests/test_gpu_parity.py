@@ -101,6 +101,9 @@ STREAMED = [
     synth.Config("stream_grouped_bf16_k2", 530, 2048, 2304, 2, 64, 2, "bf16", "swiglu", seed=71, share_prob=0.9),
     synth.Config("stream_grouped_f32_k1", 1300, 256, 512, 8, 16, 1, "f32", "gelu", seed=72, share_prob=0.1),
     synth.Config("stream_grouped_f32_k2_two_chunks", 1200, 256, 256, 64, 16, 2, "f32", "relu", seed=73, share_prob=0.1),
+    # few slots: more rows per slot than elsewhere, up to the line
+    synth.Config("stream_few_slots_k1", 128, 256, 512, 1, 4, 1, "bf16", "gelu", seed=77, gate="all"),
+    synth.Config("stream_few_slots_k2", 92, 512, 768, 1, 8, 2, "bf16", "swiglu", seed=78),
     # fp32: a biased router fills one slot beyond a 32-row pass
     synth.Config("stream_f32_skewed_passes", 90, 512, 256, 1, 8, 1, "f32", "swiglu", seed=74, bias_alpha=3.0),
     # several hundred slots, most of them empty, on the kernels that group the pairs themselves
