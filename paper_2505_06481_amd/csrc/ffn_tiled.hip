@@ -17,7 +17,7 @@
 // memory into registers (16 bytes per lane, 256-byte runs), three 32-k slices ahead of their use (seven where the tile leaves the registers).
 // Token rows are copied global -> LDS without passing registers (global_load_lds, 16 bytes per lane)
 // into a ring of LDS tiles (four stages of full tiles, up to eleven of short ones), [row][64 k] bf16 (128 bytes a row)
-// with the 16-byte pieces xor-swizzled by (row >> 1) & 7, and are read back as fragments; one barrier per step.
+// with the 16-byte pieces xor-swizzled (piece_swizzle), and are read back as fragments; one barrier per step.
 //
 // Ragged groups: row ranges come from the device array `offsets`.  A small
 // preparation step turns them into lists of tiles; the product kernels map their
@@ -49,6 +49,15 @@ __device__ __forceinline__ float silu_mul_t(float g, float u)
 {
     return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
 }
+
+// Where the 16-byte pieces of a token row stand in LDS: logical piece c of a row is physical piece
+// c ^ piece_swizzle(row).  A ds_read_b128 works through its lanes in four cycles of 16: {0-3, 12-15, 20-27},
+// {4-11, 16-19, 28-31} and the same from 32 on (measured by timing lane pairs), each free of conflicts if its
+// lanes read 16 different 16-byte columns of 256 bytes.  Lane (row lr, group lg) of a fragment read wants
+// piece 4 (lg % 2) + const, so a cycle holds rows {0-3, 12-15} of one group and {4-11} of its neighbour: the
+// rows of the first set need columns that are closed under xor 4, which plain (row >> 1) & 7 does not give
+// (two lanes to a column, half of the LDS's active cycles lost) and this does.
+__device__ __forceinline__ constexpr int piece_swizzle(int row) { return ((row >> 1) & 7) ^ ((row >> 2) & 2); }
 
 // The lists of product blockIdx.x, for callers that bring the offsets.
 __global__ __launch_bounds__(kListThreads) void tile_table_kernel(const int32_t* __restrict__ offsets,
@@ -116,14 +125,14 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     // gather of the token rows folded into this product's loads).
     // Copy instruction i of a wavefront writes its 64 pieces to 1 KB of consecutive LDS addresses
     // (M0 + 16*lane), 8 rows of 128 bytes, so the swizzle is applied on the global side: the lane
-    // that fills physical piece q of a row fetches logical piece q ^ ((row >> 1) & 7).
+    // that fills physical piece q of a row fetches logical piece q ^ piece_swizzle(row).
     const char* a_base = reinterpret_cast<const char*>(A);
     uint32_t a_goff[kNP];  // byte offset of the piece
 #pragma unroll
     for (int i = 0; i < kNP; ++i) {
         const int row = i * (kThreads / 8) + (tid >> 3);
         const int r = r0 + min(row, cnt - 1);
-        a_goff[i] = (uint32_t)(perm ? perm[r] / kdiv : r) * (uint32_t)K * 2u + (((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+        a_goff[i] = (uint32_t)(perm ? perm[r] / kdiv : r) * (uint32_t)K * 2u + (((tid & 7) ^ piece_swizzle(tid >> 3)) << 4);
     }
     // The copies are written in assembly so that the compiler's wait-count bookkeeping does not
     // see them (it would drain every load in flight before each LDS read); the waits that order
@@ -159,7 +168,7 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     int frag_off[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-        frag_off[q] = lr * 128 + (((4 * (lg & 1) + 2 * q + (lg >> 1)) ^ ((lr >> 1) & 7)) << 4);
+        frag_off[q] = lr * 128 + (((4 * (lg & 1) + 2 * q + (lg >> 1)) ^ piece_swizzle(lr)) << 4);
 
     // Gated output rows (GateSink): output row (token) and coefficient of this lane's token of every
     // fragment.  Two dependent loads each; tiles of 128 x 128 (short-lived, with registers to spare)
