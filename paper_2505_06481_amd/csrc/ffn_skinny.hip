@@ -17,16 +17,13 @@
 // intermediates H and Yg are indexed by pair id instead of by grouped row.  Every row is still
 // summed in the same order, so the layer's output is bit-identical to the staged path's.
 //
-// fp32 kernel (skinny_kernel): transposed pool [S, N, K], 16 features per workgroup,
-// 16x16x4 matrix instructions, two 16-row token blocks per pass.  Reduction-index
-// permutation: per 256-byte step of a row, lane group g = lane/16 loads the contiguous 64
-// bytes [64g, 64g+64) as four 16-byte pieces q; piece q of every group feeds matrix
-// instruction q.  Weights and activations use the same permutation, and a sum does not care
-// in which order its terms are visited, so no shuffle is needed and every lane's global
-// loads are contiguous.
+// fp32 kernel (skinny_kernel): transposed pool [S, N, K], 16 features per wavefront,
+// 16x16x4 matrix instructions, one or two 16-row token blocks per pass; see its own comment.
 //
 // bf16 kernel (skinny_frag_kernel): fragment-packed pool, 32 features per workgroup,
 // 32x32x16 matrix instructions, up to 32 rows per pass; see its own comment.
+#include <type_traits>
+
 #include "mmoe_internal.h"
 
 namespace mmoe {
@@ -39,17 +36,6 @@ enum { kModeReluH = 0, kModeSwigluH = 1, kModePlainF32 = 2, kModeGeluH = 3, kMod
 constexpr int kSkThreads = 256;
 constexpr int kSkWaves = 4;
 constexpr int kSkMB = 2;  // 16-row token blocks per pass
-
-template <typename T> struct Mma;
-template <> struct Mma<float> {  // fp32, 16x16x4: one 16-byte piece = 4 elements = 4 instructions
-    static __device__ __forceinline__ f32x4 run(u32x4 w, u32x4 x, f32x4 acc)
-    {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(w[c]), __uint_as_float(x[c]), acc, 0, 0, 0);
-        return acc;
-    }
-};
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 __device__ __forceinline__ float gelu(float a) { return 0.5f * a * (1.0f + erff(a * 0.70710678118654752440f)); }
@@ -112,21 +98,36 @@ __device__ __forceinline__ RowSet slot_rows(const int32_t* __restrict__ offsets,
 // SPLITK: the four wavefronts split the reduction dimension of one 16-feature block and meet in
 // LDS (long reductions).  !SPLITK: every wavefront owns a 16-feature block of its own and walks the
 // whole reduction dimension (short reductions, where a quarter of K is one or two iterations: all
-// latency, no pipelining): 64 features per workgroup, no LDS reduction, the token rows fetched a
-// quarter as often per weight byte.
-template <typename T, int NW, int KU, int MODE, bool SPLITK>
-__global__ __launch_bounds__(kSkThreads) void skinny_kernel(const T* __restrict__ A,
+// latency, no pipelining): 64 features per workgroup, no LDS reduction.
+//
+// What bounds it is the memory pipeline of a compute unit.  A 1 KB load instruction takes 18 to 20 of its cycles
+// where four neighbouring lanes read 64 contiguous bytes and 65 where neighbouring lanes are in different rows, as
+// in the order of a matrix operand (measured on data in L2).  So weight and token rows are read along the row, 16
+// lanes to the 256 bytes of a run of 64 k, and pass through LDS of the wavefront's own to get into operand order.
+// One run is in flight per wavefront, twelve wavefronts on a compute unit (eight of the gated product): with two
+// runs in flight the registers (over 168) leave eight, or spill.
+// Measured against reading both operands in operand order (768 x 3072 top-1, 13 slots, layer): 4 tokens 36.3 -> 31.5 us,
+// 24 tokens 66.6 -> 52.6, 128 tokens 79.3 -> 64.5 (246 MB of weights); 1024 x 2048 SwiGLU top-2, 64 tokens 97.3 -> 88.9;
+// 4096 x 1024 GELU 120.1 -> 118.3.
+constexpr int kRun = 64;              // k per run
+constexpr int kRunRow = kRun * 4;     // bytes of a row per run
+constexpr int kRunBlock = 16 * kRunRow;  // bytes of 16 rows
+constexpr int kRunLoads = 4;          // load instructions per 16 rows; pieces of an operand per run
+constexpr int kChainRuns = 4;         // runs per chain of matrix instructions: rounding errors do not build up over all of K
+
+template <int NW, int MODE, bool SPLITK>
+__global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(const float* __restrict__ A,
                                                             const int32_t* __restrict__ perm, int kdiv,
                                                             const int32_t* __restrict__ offsets,
                                                             const int32_t* __restrict__ slot_of_pair, int P,
-                                                            const T* __restrict__ W0, const T* __restrict__ W1,
-                                                            void* __restrict__ out, int K, int N, SlotFilter filt,
+                                                            const float* __restrict__ W0, const float* __restrict__ W1,
+                                                            float* __restrict__ out, int K, int N, SlotFilter filt,
                                                             const int32_t* __restrict__ sink_perm,
                                                             const float* __restrict__ sink_w)
 {
-    constexpr int EPB = 16 / (int)sizeof(T);  // elements per 16-byte piece
-    constexpr int KSS = 16 * EPB;             // elements per 256-byte step
-    __shared__ float red[kSkWaves][kSkMB][NW][kWave][4];
+    __shared__ __attribute__((aligned(256))) char rows[kSkWaves][(NW + kSkMB) * kRunBlock];  // of a run: weights, tokens
+    static_assert(sizeof(rows) >= sizeof(float) * kSkWaves * kSkMB * NW * kWave * 4, "one array for the partial sums too");
+    float(*red)[kSkMB][NW][kWave][4] = reinterpret_cast<float(*)[kSkMB][NW][kWave][4]>(&rows[0][0]);
     __shared__ int mine[kSelfMaxP];
     __shared__ int mine_cnt;
 
@@ -139,81 +140,102 @@ __global__ __launch_bounds__(kSkThreads) void skinny_kernel(const T* __restrict_
     const int wave = threadIdx.x / kWave;
     const int n0 = SPLITK ? blockIdx.x * 16 : (blockIdx.x * kSkWaves + wave) * 16;
     const int li = lane & 15, g = lane >> 4;
-    const int nit = K / (KSS * KU);
-    constexpr int kFirst = SPLITK ? -1 : 0;        // first iteration of a wavefront: its index, or 0
-    constexpr int kStride = SPLITK ? kSkWaves : 1;  // iterations between two of one wavefront
+    constexpr int kStride = SPLITK ? kSkWaves : 1;  // runs between two of one wavefront
+    const int first = SPLITK ? wave : 0;
+    const int nrun = K / kRun;
 
-    const T* wrow[NW];
-    wrow[0] = W0 + ((size_t)s * N + n0 + li) * K + g * (4 * EPB);
-    if (NW == 2) wrow[NW - 1] = W1 + ((size_t)s * N + n0 + li) * K + g * (4 * EPB);
+    // Load i of a 16-row block: row 4 i + g, 16 bytes (li) of its 256.  In LDS piece q of row r stands at q ^ r: the
+    // 16 lanes that share a cycle of a read or write have 16 different columns of 256 bytes.
+    const float* wrow[NW][kRunLoads];
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+        for (int i = 0; i < kRunLoads; ++i)
+            wrow[w][i] = (w == 0 ? W0 : W1) + ((size_t)s * N + n0 + 4 * i + g) * K + 4 * li;
+    char* const myrows = rows[wave];
+    int dst[kRunLoads], src[kRunLoads];  // of load i; of piece q of an operand: lane (li, g) holds the four k from 16 q + 4 g on of row li
+#pragma unroll
+    for (int i = 0; i < kRunLoads; ++i) {
+        dst[i] = (4 * i + g) * kRunRow + ((li ^ (4 * i + g)) << 4);
+        src[i] = li * kRunRow + (((4 * i + g) ^ li) << 4);
+    }
 
-    for (int pass0 = 0; pass0 < cnt; pass0 += 16 * kSkMB) {
-        const int nmb = min(kSkMB, (cnt - pass0 + 15) / 16);
-        const T* arow[kSkMB];
+    auto pass = [&](int pass0, auto mbc) {
+        constexpr int MB = decltype(mbc)::value;  // 16-row blocks of this pass that hold rows
+        const float* arow[MB][kRunLoads];
 #pragma unroll
-        for (int mb = 0; mb < kSkMB; ++mb) {
-            int rr = min(pass0 + mb * 16 + li, cnt - 1);  // rows past the end re-read the last one; never stored
-            arow[mb] = A + (size_t)rs.in_row(rr) * K + g * (4 * EPB);
-        }
-        f32x4 acc[kSkMB][NW];
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-        for (int mb = 0; mb < kSkMB; ++mb)
-#pragma unroll
-            for (int w = 0; w < NW; ++w) acc[mb][w] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-        u32x4 wcur[NW][KU][4], wnxt[NW][KU][4];
-        int it = kFirst < 0 ? wave : kFirst;
-        if (it < nit) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int u = 0; u < KU; ++u)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        wcur[w][u][q] =
-                            *reinterpret_cast<const u32x4*>(wrow[w] + (size_t)(it * KU + u) * KSS + q * EPB);
-        }
-        for (; it < nit; it += kStride) {
-            u32x4 xa[kSkMB][KU][4];
-#pragma unroll
-            for (int mb = 0; mb < kSkMB; ++mb)
-                if (mb < nmb) {
-#pragma unroll
-                    for (int u = 0; u < KU; ++u)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            xa[mb][u][q] =
-                                *reinterpret_cast<const u32x4*>(arow[mb] + (size_t)(it * KU + u) * KSS + q * EPB);
-                }
-            const int itn = it + kStride;
-            if (itn < nit) {  // the next weights: the youngest loads, still in flight during the math below
-#pragma unroll
-                for (int w = 0; w < NW; ++w)
-#pragma unroll
-                    for (int u = 0; u < KU; ++u)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            wnxt[w][u][q] =
-                                *reinterpret_cast<const u32x4*>(wrow[w] + (size_t)(itn * KU + u) * KSS + q * EPB);
+            for (int i = 0; i < kRunLoads; ++i) {  // rows past the end re-read the last one; never stored
+                const int rr = min(pass0 + mb * 16 + 4 * i + g, cnt - 1);
+                arow[mb][i] = A + (size_t)rs.in_row(rr) * K + 4 * li;
             }
+        f32x4 tot[MB][NW], acc[MB][NW];
 #pragma unroll
-            for (int mb = 0; mb < kSkMB; ++mb)
-                if (mb < nmb) {
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int u = 0; u < KU; ++u)
+            for (int w = 0; w < NW; ++w) tot[mb][w] = acc[mb][w] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+        f32x4 wraw[NW][kRunLoads], traw[MB][kRunLoads];  // a run's rows as loaded
+        auto load = [&](int run) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
+            for (int i = 0; i < kRunLoads; ++i) {
 #pragma unroll
-                            for (int w = 0; w < NW; ++w)
-                                acc[mb][w] = Mma<T>::run(wcur[w][u][q], xa[mb][u][q], acc[mb][w]);
+                for (int mb = 0; mb < MB; ++mb) traw[mb][i] = *reinterpret_cast<const f32x4*>(arow[mb][i] + (size_t)run * kRun);
+#pragma unroll
+                for (int w = 0; w < NW; ++w) wraw[w][i] = *reinterpret_cast<const f32x4*>(wrow[w][i] + (size_t)run * kRun);
+            }
+        };
+        // A wavefront's LDS operations execute in program order; the fences keep the compiler from moving them.
+        auto fence = [] {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        auto step = [&](int next) {  // the run in the registers; `next` is fetched during its arithmetic if there is one
+            fence();
+#pragma unroll
+            for (int i = 0; i < kRunLoads; ++i) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) *reinterpret_cast<f32x4*>(myrows + (NW + mb) * kRunBlock + dst[i]) = traw[mb][i];
+#pragma unroll
+                for (int w = 0; w < NW; ++w) *reinterpret_cast<f32x4*>(myrows + w * kRunBlock + dst[i]) = wraw[w][i];
+            }
+            fence();
+            if (next >= 0) load(next);
+#pragma unroll
+            for (int q = 0; q < kRunLoads; ++q) {
+                f32x4 x[MB], wf[NW];
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) x[mb] = *reinterpret_cast<const f32x4*>(myrows + (NW + mb) * kRunBlock + src[q]);
+#pragma unroll
+                for (int w = 0; w < NW; ++w) wf[w] = *reinterpret_cast<const f32x4*>(myrows + w * kRunBlock + src[q]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                        for (int w = 0; w < NW; ++w)
+                            acc[mb][w] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[w][c], x[mb][c], acc[mb][w], 0, 0, 0);
+            }
+        };
+        // a chain of matrix instructions runs over kChainRuns runs from zero and is then added to the total
+        auto end_chain = [&] {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    tot[mb][w] += acc[mb][w];
+                    acc[mb][w] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int u = 0; u < KU; ++u)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) wcur[w][u][q] = wnxt[w][u][q];
+        };
+        int run = first, chain = 0;  // a wavefront has at least one run: K >= 256
+        load(run);
+        for (; run + kStride < nrun; run += kStride) {
+            step(run + kStride);
+            if (++chain % kChainRuns == 0) end_chain();  // uniform
         }
+        step(-1);
+        end_chain();
 
         // accumulator element i of lane l is output feature n0 + 4*(l/16) + i of token column l%16
         auto finish = [&](int row, int l, const float (&v)[NW][4]) {
@@ -232,39 +254,32 @@ __global__ __launch_bounds__(kSkThreads) void skinny_kernel(const T* __restrict_
                 else if (MODE == kModeGatedY) o[i] = __builtin_fmaf(gw, v[0][i], 0.0f);
                 else o[i] = v[0][i];
             }
-            const size_t at = (size_t)orow * N + n0 + 4 * (l >> 4);
-            if (MODE == kModePlainF32 || sizeof(T) == 4) {
-                *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(out) + at) = f32x4{o[0], o[1], o[2], o[3]};
-            } else {
-                u32x2 pk;
-                pk[0] = (uint32_t)f32_to_bf16_bits(o[0]) | ((uint32_t)f32_to_bf16_bits(o[1]) << 16);
-                pk[1] = (uint32_t)f32_to_bf16_bits(o[2]) | ((uint32_t)f32_to_bf16_bits(o[3]) << 16);
-                *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(out) + at) = pk;
-            }
+            *reinterpret_cast<f32x4*>(out + (size_t)orow * N + n0 + 4 * (l >> 4)) = f32x4{o[0], o[1], o[2], o[3]};
         };
         if (!SPLITK) {  // every wavefront finishes its own 16 features straight from its accumulators
 #pragma unroll
-            for (int mb = 0; mb < kSkMB; ++mb) {
+            for (int mb = 0; mb < MB; ++mb) {
                 const int row = pass0 + mb * 16 + (lane & 15);
-                if (mb < nmb && row < cnt) {
+                if (row < cnt) {
                     float v[NW][4];
 #pragma unroll
                     for (int w = 0; w < NW; ++w)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) v[w][i] = acc[mb][w][i];
+                        for (int i = 0; i < 4; ++i) v[w][i] = tot[mb][w][i];
                     finish(row, lane, v);
                 }
             }
-            continue;
+            return;
         }
+        __syncthreads();  // the partial sums take the place of the tokens
 #pragma unroll
-        for (int mb = 0; mb < kSkMB; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int w = 0; w < NW; ++w)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) red[wave][mb][w][lane][i] = acc[mb][w][i];
+                for (int i = 0; i < 4; ++i) red[wave][mb][w][lane][i] = tot[mb][w][i];
         __syncthreads();
-        for (int idx = threadIdx.x; idx < nmb * kWave; idx += kSkThreads) {
+        for (int idx = threadIdx.x; idx < MB * kWave; idx += kSkThreads) {
             const int mb = idx / kWave, l = idx % kWave;
             const int row = pass0 + mb * 16 + (l & 15);
             if (row < cnt) {
@@ -278,6 +293,10 @@ __global__ __launch_bounds__(kSkThreads) void skinny_kernel(const T* __restrict_
             }
         }
         __syncthreads();
+    };
+    for (int pass0 = 0; pass0 < cnt; pass0 += 16 * kSkMB) {  // uniform over the workgroup
+        if (cnt - pass0 > 16) pass(pass0, std::integral_constant<int, 2>{});
+        else pass(pass0, std::integral_constant<int, 1>{});
     }
 }
 
@@ -455,7 +474,7 @@ static int run_skinny_bf16(const mmoe_shape& s, const void* rows, const int32_t*
     return launch_status();
 }
 
-template <typename T, bool SPLITK>
+template <bool SPLITK>
 static void launch_skinny_products(const mmoe_shape& s, const void* rows, const int32_t* perm, const int32_t* offsets,
                                    const int32_t* slot_of_pair, const void* W1p, const void* W3p, const void* W2p,
                                    void* H, float* Yg, hipStream_t st, hipEvent_t mid, SlotFilter filt, bool up,
@@ -468,25 +487,25 @@ static void launch_skinny_products(const mmoe_shape& s, const void* rows, const 
     constexpr int kFeat = SPLITK ? 16 : 16 * kSkWaves;  // output features per workgroup
     dim3 block(kSkThreads);
     dim3 g1(f / kFeat, s.S), g2(d / kFeat, s.S);
-    const T* nul = nullptr;
+    const float* nul = nullptr;
     if (up) {
         if (s.act == MMOE_SWIGLU)
-            hipLaunchKernelGGL((skinny_kernel<T, 2, 1, kModeSwigluH, SPLITK>), g1, block, 0, st, (const T*)rows, perm,
-                               s.top_k, offsets, slot_of_pair, P, (const T*)W1p, (const T*)W3p, H, d, f, filt,
+            hipLaunchKernelGGL((skinny_kernel<2, kModeSwigluH, SPLITK>), g1, block, 0, st, (const float*)rows, perm,
+                               s.top_k, offsets, slot_of_pair, P, (const float*)W1p, (const float*)W3p, (float*)H, d, f, filt,
                                nosink, now);
         else if (s.act == MMOE_GELU)
-            hipLaunchKernelGGL((skinny_kernel<T, 1, 2, kModeGeluH, SPLITK>), g1, block, 0, st, (const T*)rows, perm,
-                               s.top_k, offsets, slot_of_pair, P, (const T*)W1p, nul, H, d, f, filt, nosink, now);
+            hipLaunchKernelGGL((skinny_kernel<1, kModeGeluH, SPLITK>), g1, block, 0, st, (const float*)rows, perm,
+                               s.top_k, offsets, slot_of_pair, P, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
         else
-            hipLaunchKernelGGL((skinny_kernel<T, 1, 2, kModeReluH, SPLITK>), g1, block, 0, st, (const T*)rows, perm,
-                               s.top_k, offsets, slot_of_pair, P, (const T*)W1p, nul, H, d, f, filt, nosink, now);
+            hipLaunchKernelGGL((skinny_kernel<1, kModeReluH, SPLITK>), g1, block, 0, st, (const float*)rows, perm,
+                               s.top_k, offsets, slot_of_pair, P, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
     }
     if (down && sink.w)
-        hipLaunchKernelGGL((skinny_kernel<T, 1, 2, kModeGatedY, SPLITK>), g2, block, 0, st, (const T*)H, noperm, 1,
-                           offsets, slot_of_pair, P, (const T*)W2p, nul, sink.Y, f, d, filt, sink.perm, sink.w);
+        hipLaunchKernelGGL((skinny_kernel<1, kModeGatedY, SPLITK>), g2, block, 0, st, (const float*)H, noperm, 1,
+                           offsets, slot_of_pair, P, (const float*)W2p, nul, (float*)sink.Y, f, d, filt, sink.perm, sink.w);
     else if (down)
-        hipLaunchKernelGGL((skinny_kernel<T, 1, 2, kModePlainF32, SPLITK>), g2, block, 0, st, (const T*)H, noperm, 1,
-                           offsets, slot_of_pair, P, (const T*)W2p, nul, (void*)Yg, f, d, filt, nosink, now);
+        hipLaunchKernelGGL((skinny_kernel<1, kModePlainF32, SPLITK>), g2, block, 0, st, (const float*)H, noperm, 1,
+                           offsets, slot_of_pair, P, (const float*)W2p, nul, Yg, f, d, filt, nosink, now);
     (void)mid;
 }
 
@@ -494,23 +513,22 @@ static void launch_skinny_products(const mmoe_shape& s, const void* rows, const 
 // ways keeps it whole (K <= 1024 for fp32).
 static bool whole_k(int K) { return K <= 1024; }
 
-template <typename T>
-static int run_skinny(const mmoe_shape& s, const void* rows, const int32_t* perm, const int32_t* offsets,
+static int run_skinny_f32(const mmoe_shape& s, const void* rows, const int32_t* perm, const int32_t* offsets,
                       const int32_t* slot_of_pair, const void* W1p, const void* W3p, const void* W2p, void* H, float* Yg,
                       hipStream_t st, hipEvent_t mid, SlotFilter filt, GateSink sink)
 {
     if (whole_k(s.d_model))
-        launch_skinny_products<T, false>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, true,
+        launch_skinny_products<false>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, true,
                                          false, sink);
     else
-        launch_skinny_products<T, true>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, true,
+        launch_skinny_products<true>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, true,
                                         false, sink);
     if (mid && hipEventRecord(mid, st) != hipSuccess) return MMOE_ERR_LAUNCH;
     if (whole_k(s.d_ff))
-        launch_skinny_products<T, false>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, false,
+        launch_skinny_products<false>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, false,
                                          true, sink);
     else
-        launch_skinny_products<T, true>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, false,
+        launch_skinny_products<true>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, false,
                                         true, sink);
     return launch_status();
 }
@@ -529,7 +547,7 @@ int launch_ffn_skinny(const mmoe_shape& s, const void* rows, const int32_t* perm
     if (sink.w && (s.top_k != 1 || !sink.Y || (slot_of_pair != nullptr) != (sink.perm == nullptr))) return MMOE_ERR_DIM;
     if (s.dtype == MMOE_BF16)
         return run_skinny_bf16(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, sink);
-    return run_skinny<float>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, sink);
+    return run_skinny_f32(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, sink);
 }
 
 }  // namespace mmoe
