@@ -44,7 +44,7 @@ constexpr int kSelfMaxP = 1024;  // most pairs for which the expert kernels grou
 
 // Rows of one slot.  Grouped form: rows [r0, r0 + cnt) of the grouped order; input row of grouped
 // row r is r itself, or perm[r] / kdiv (gather folded into the loads).  Self-grouping form: the
-// pairs p with slot_of_pair[p] == s, ascending, collected here into `mine` by the first
+// pairs p with slot_of_pair[p] == s, ascending, collected into `mine` by the first
 // wavefront (ballot + popcount ranks); input row p / kdiv, output row p.
 struct RowSet {
     int r0, cnt;
@@ -59,9 +59,17 @@ struct RowSet {
     __device__ __forceinline__ int out_row(int rr) const { return mine ? mine[rr] : r0 + rr; }
 };
 
+// The slot of this workgroup: blockIdx.y, or, where the batch has fewer pairs than the pool has slots (`by_pair`), the
+// slot of pair blockIdx.y (the workgroups of a pair that is not the first of its slot then find no rows).
+__device__ __forceinline__ int slot_of_block(const int32_t* __restrict__ slot_of_pair, bool by_pair)
+{
+    return by_pair ? slot_of_pair[blockIdx.y] : (int)blockIdx.y;
+}
+
+// Called by the whole workgroup.
 __device__ __forceinline__ RowSet slot_rows(const int32_t* __restrict__ offsets, const int32_t* __restrict__ perm,
                                             int kdiv, const int32_t* __restrict__ slot_of_pair, int P, int s,
-                                            int* mine, int* mine_cnt, SlotFilter filt)
+                                            bool by_pair, int* mine, SlotFilter filt)
 {
     RowSet rs;
     rs.perm = perm;
@@ -77,20 +85,26 @@ __device__ __forceinline__ RowSet slot_rows(const int32_t* __restrict__ offsets,
         rs.cnt = offsets[s + 1] - rs.r0;
         return rs;
     }
+    __shared__ int hits;
     if (threadIdx.x < kWave) {
+        constexpr int kAtOnce = 4;  // loads of 64 pairs
         int n = 0;
-        for (int p0 = 0; p0 < P; p0 += kWave) {
-            const int p = p0 + threadIdx.x;
-            const bool hit = p < P && slot_of_pair[p] == s;
-            const unsigned long long m = __ballot(hit);
-            if (hit) mine[n + __popcll(m & ((1ull << threadIdx.x) - 1ull))] = p;
-            n += __popcll(m);
+        for (int p0 = threadIdx.x; p0 < P + (int)threadIdx.x; p0 += kAtOnce * kWave) {  // uniform over the wavefront
+            int got[kAtOnce];
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) got[j] = p0 + j * kWave < P ? slot_of_pair[p0 + j * kWave] : -1;
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j) {
+                const unsigned long long m = __ballot(got[j] == s);
+                if (got[j] == s) mine[n + __popcll(m & ((1ull << threadIdx.x) - 1ull))] = p0 + j * kWave;
+                n += __popcll(m);
+            }
         }
-        if (threadIdx.x == 0) *mine_cnt = n;
+        if (threadIdx.x == 0) hits = n;
     }
     __syncthreads();
     rs.r0 = 0;
-    rs.cnt = *mine_cnt;
+    rs.cnt = by_pair && mine[0] != (int)blockIdx.y ? 0 : hits;
     rs.mine = mine;
     return rs;
 }
@@ -119,7 +133,7 @@ template <int NW, int MODE, bool SPLITK>
 __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(const float* __restrict__ A,
                                                             const int32_t* __restrict__ perm, int kdiv,
                                                             const int32_t* __restrict__ offsets,
-                                                            const int32_t* __restrict__ slot_of_pair, int P,
+                                                            const int32_t* __restrict__ slot_of_pair, int P, int by_pair,
                                                             const float* __restrict__ W0, const float* __restrict__ W1,
                                                             float* __restrict__ out, int K, int N, SlotFilter filt,
                                                             const int32_t* __restrict__ sink_perm,
@@ -129,10 +143,9 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
     static_assert(sizeof(rows) >= sizeof(float) * kSkWaves * kSkMB * NW * kWave * 4, "one array for the partial sums too");
     float(*red)[kSkMB][NW][kWave][4] = reinterpret_cast<float(*)[kSkMB][NW][kWave][4]>(&rows[0][0]);
     __shared__ int mine[kSelfMaxP];
-    __shared__ int mine_cnt;
 
-    const int s = blockIdx.y;
-    const RowSet rs = slot_rows(offsets, perm, kdiv, slot_of_pair, P, s, mine, &mine_cnt, filt);
+    const int s = slot_of_block(slot_of_pair, by_pair);
+    const RowSet rs = slot_rows(offsets, perm, kdiv, slot_of_pair, P, s, by_pair, mine, filt);
     const int cnt = rs.cnt;
     if (cnt <= 0) return;  // uniform over the workgroup
 
@@ -160,6 +173,14 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
         src[i] = li * kRunRow + (((4 * i + g) ^ li) << 4);
     }
 
+    f32x4 wraw[NW][kRunLoads];  // a run's weights as loaded
+    auto load_w = [&](int run) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int i = 0; i < kRunLoads; ++i) wraw[w][i] = *reinterpret_cast<const f32x4*>(wrow[w][i] + (size_t)run * kRun);
+    };
+
     auto pass = [&](int pass0, auto mbc) {
         constexpr int MB = decltype(mbc)::value;  // 16-row blocks of this pass that hold rows
         const float* arow[MB][kRunLoads];
@@ -176,15 +197,12 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
 #pragma unroll
             for (int w = 0; w < NW; ++w) tot[mb][w] = acc[mb][w] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-        f32x4 wraw[NW][kRunLoads], traw[MB][kRunLoads];  // a run's rows as loaded
-        auto load = [&](int run) {
+        f32x4 traw[MB][kRunLoads];  // a run's tokens as loaded
+        auto load_t = [&](int run) {
 #pragma unroll
-            for (int i = 0; i < kRunLoads; ++i) {
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) traw[mb][i] = *reinterpret_cast<const f32x4*>(arow[mb][i] + (size_t)run * kRun);
-#pragma unroll
-                for (int w = 0; w < NW; ++w) wraw[w][i] = *reinterpret_cast<const f32x4*>(wrow[w][i] + (size_t)run * kRun);
-            }
+                for (int i = 0; i < kRunLoads; ++i) traw[mb][i] = *reinterpret_cast<const f32x4*>(arow[mb][i] + (size_t)run * kRun);
         };
         // A wavefront's LDS operations execute in program order; the fences keep the compiler from moving them.
         auto fence = [] {
@@ -201,7 +219,10 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
                 for (int w = 0; w < NW; ++w) *reinterpret_cast<f32x4*>(myrows + w * kRunBlock + dst[i]) = wraw[w][i];
             }
             fence();
-            if (next >= 0) load(next);
+            if (next >= 0) {
+                load_t(next);
+                load_w(next);
+            }
 #pragma unroll
             for (int q = 0; q < kRunLoads; ++q) {
                 f32x4 x[MB], wf[NW];
@@ -229,7 +250,8 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
                 }
         };
         int run = first, chain = 0;  // a wavefront has at least one run: K >= 256
-        load(run);
+        load_t(run);
+        load_w(run);
         for (; run + kStride < nrun; run += kStride) {
             step(run + kStride);
             if (++chain % kChainRuns == 0) end_chain();  // uniform
@@ -312,7 +334,7 @@ template <int NW, int KU, int MODE>
 __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t* __restrict__ A,
                                                                  const int32_t* __restrict__ perm, int kdiv,
                                                                  const int32_t* __restrict__ offsets,
-                                                                 const int32_t* __restrict__ slot_of_pair, int P,
+                                                                 const int32_t* __restrict__ slot_of_pair, int P, int by_pair,
                                                                  const uint16_t* __restrict__ W0,
                                                                  const uint16_t* __restrict__ W1,
                                                                  void* __restrict__ out, int K, int N,
@@ -322,11 +344,10 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
 {
     __shared__ float red[kSkWaves][NW][kWave][16];  // 16 KB per matrix
     __shared__ int mine[kSelfMaxP];
-    __shared__ int mine_cnt;
 
-    const int s = blockIdx.y;
+    const int s = slot_of_block(slot_of_pair, by_pair);
     const int nb = blockIdx.x;
-    const RowSet rs = slot_rows(offsets, perm, kdiv, slot_of_pair, P, s, mine, &mine_cnt, filt);
+    const RowSet rs = slot_rows(offsets, perm, kdiv, slot_of_pair, P, s, by_pair, mine, filt);
     const int cnt = rs.cnt;
     if (cnt <= 0) return;  // uniform over the workgroup
 
@@ -341,6 +362,17 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
     wrow[0] = W0 + blk;
     if (NW == 2) wrow[NW - 1] = W1 + blk;
 
+    u32x4 wcur[NW][KU][4], wnxt[NW][KU][4];
+    auto load_w = [&](u32x4 (&to)[NW][KU][4], int it) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int u = 0; u < KU; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    to[w][u][q] = *reinterpret_cast<const u32x4*>(wrow[w] + ((size_t)(it * KU + u) * 4 + q) * 512);
+    };
+
     for (int pass0 = 0; pass0 < cnt; pass0 += 32) {
         const int rr = min(pass0 + tok, cnt - 1);  // tokens past the end re-read the last one; never stored
         const uint16_t* arow = A + (size_t)rs.in_row(rr) * K + h * 32;
@@ -350,18 +382,8 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[w][e] = 0.0f;
 
-        u32x4 wcur[NW][KU][4], wnxt[NW][KU][4];
         int it = wave;
-        if (it < nit) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-#pragma unroll
-                for (int u = 0; u < KU; ++u)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        wcur[w][u][q] =
-                            *reinterpret_cast<const u32x4*>(wrow[w] + ((size_t)(it * KU + u) * 4 + q) * 512);
-        }
+        if (it < nit) load_w(wcur, it);
         for (; it < nit; it += kSkWaves) {
             u32x4 xa[KU][4];
 #pragma unroll
@@ -370,16 +392,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
                 for (int q = 0; q < 4; ++q)
                     xa[u][q] = *reinterpret_cast<const u32x4*>(arow + (size_t)(it * KU + u) * 64 + q * 8);
             const int itn = it + kSkWaves;
-            if (itn < nit) {  // the next weights: the youngest loads, still in flight during the math below
-#pragma unroll
-                for (int w = 0; w < NW; ++w)
-#pragma unroll
-                    for (int u = 0; u < KU; ++u)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            wnxt[w][u][q] =
-                                *reinterpret_cast<const u32x4*>(wrow[w] + ((size_t)(itn * KU + u) * 4 + q) * 512);
-            }
+            if (itn < nit) load_w(wnxt, itn);  // the next weights: the youngest loads, still in flight during the math below
 #pragma unroll
             for (int u = 0; u < KU; ++u)
 #pragma unroll
@@ -452,25 +465,27 @@ static int run_skinny_bf16(const mmoe_shape& s, const void* rows, const int32_t*
     const int32_t* noperm = nullptr;
     const int d = s.d_model, f = s.d_ff, P = s.T * s.top_k;
     dim3 block(kSkThreads);
-    dim3 g1(f / 32, s.S), g2(d / 32, s.S);
+    const int by_pair = slot_of_pair && P < s.S;  // a workgroup row per pair, not per slot
+    const int ny = by_pair ? P : s.S;
+    dim3 g1(f / 32, ny), g2(d / 32, ny);
     const uint16_t* nul = nullptr;
     if (s.act == MMOE_SWIGLU)
         hipLaunchKernelGGL((skinny_frag_kernel<2, 1, kModeSwigluH>), g1, block, 0, st, (const uint16_t*)rows, perm,
-                           s.top_k, offsets, slot_of_pair, P, (const uint16_t*)W1p, (const uint16_t*)W3p, H, d, f, filt,
+                           s.top_k, offsets, slot_of_pair, P, by_pair, (const uint16_t*)W1p, (const uint16_t*)W3p, H, d, f, filt,
                            nosink, now);
     else if (s.act == MMOE_GELU)
         hipLaunchKernelGGL((skinny_frag_kernel<1, 2, kModeGeluH>), g1, block, 0, st, (const uint16_t*)rows, perm,
-                           s.top_k, offsets, slot_of_pair, P, (const uint16_t*)W1p, nul, H, d, f, filt, nosink, now);
+                           s.top_k, offsets, slot_of_pair, P, by_pair, (const uint16_t*)W1p, nul, H, d, f, filt, nosink, now);
     else
         hipLaunchKernelGGL((skinny_frag_kernel<1, 2, kModeReluH>), g1, block, 0, st, (const uint16_t*)rows, perm,
-                           s.top_k, offsets, slot_of_pair, P, (const uint16_t*)W1p, nul, H, d, f, filt, nosink, now);
+                           s.top_k, offsets, slot_of_pair, P, by_pair, (const uint16_t*)W1p, nul, H, d, f, filt, nosink, now);
     if (mid && hipEventRecord(mid, st) != hipSuccess) return MMOE_ERR_LAUNCH;
     if (sink.w)
         hipLaunchKernelGGL((skinny_frag_kernel<1, 2, kModeGatedY>), g2, block, 0, st, (const uint16_t*)H, noperm, 1,
-                           offsets, slot_of_pair, P, (const uint16_t*)W2p, nul, sink.Y, f, d, filt, sink.perm, sink.w);
+                           offsets, slot_of_pair, P, by_pair, (const uint16_t*)W2p, nul, sink.Y, f, d, filt, sink.perm, sink.w);
     else
         hipLaunchKernelGGL((skinny_frag_kernel<1, 2, kModePlainF32>), g2, block, 0, st, (const uint16_t*)H, noperm, 1,
-                           offsets, slot_of_pair, P, (const uint16_t*)W2p, nul, (void*)Yg, f, d, filt, nosink, now);
+                           offsets, slot_of_pair, P, by_pair, (const uint16_t*)W2p, nul, (void*)Yg, f, d, filt, nosink, now);
     return launch_status();
 }
 
@@ -486,26 +501,28 @@ static void launch_skinny_products(const mmoe_shape& s, const void* rows, const 
     const int d = s.d_model, f = s.d_ff, P = s.T * s.top_k;
     constexpr int kFeat = SPLITK ? 16 : 16 * kSkWaves;  // output features per workgroup
     dim3 block(kSkThreads);
-    dim3 g1(f / kFeat, s.S), g2(d / kFeat, s.S);
+    const int by_pair = slot_of_pair && P < s.S;  // a workgroup row per pair, not per slot
+    const int ny = by_pair ? P : s.S;
+    dim3 g1(f / kFeat, ny), g2(d / kFeat, ny);
     const float* nul = nullptr;
     if (up) {
         if (s.act == MMOE_SWIGLU)
             hipLaunchKernelGGL((skinny_kernel<2, kModeSwigluH, SPLITK>), g1, block, 0, st, (const float*)rows, perm,
-                               s.top_k, offsets, slot_of_pair, P, (const float*)W1p, (const float*)W3p, (float*)H, d, f, filt,
+                               s.top_k, offsets, slot_of_pair, P, by_pair, (const float*)W1p, (const float*)W3p, (float*)H, d, f, filt,
                                nosink, now);
         else if (s.act == MMOE_GELU)
             hipLaunchKernelGGL((skinny_kernel<1, kModeGeluH, SPLITK>), g1, block, 0, st, (const float*)rows, perm,
-                               s.top_k, offsets, slot_of_pair, P, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
+                               s.top_k, offsets, slot_of_pair, P, by_pair, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
         else
             hipLaunchKernelGGL((skinny_kernel<1, kModeReluH, SPLITK>), g1, block, 0, st, (const float*)rows, perm,
-                               s.top_k, offsets, slot_of_pair, P, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
+                               s.top_k, offsets, slot_of_pair, P, by_pair, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
     }
     if (down && sink.w)
         hipLaunchKernelGGL((skinny_kernel<1, kModeGatedY, SPLITK>), g2, block, 0, st, (const float*)H, noperm, 1,
-                           offsets, slot_of_pair, P, (const float*)W2p, nul, (float*)sink.Y, f, d, filt, sink.perm, sink.w);
+                           offsets, slot_of_pair, P, by_pair, (const float*)W2p, nul, (float*)sink.Y, f, d, filt, sink.perm, sink.w);
     else if (down)
         hipLaunchKernelGGL((skinny_kernel<1, kModePlainF32, SPLITK>), g2, block, 0, st, (const float*)H, noperm, 1,
-                           offsets, slot_of_pair, P, (const float*)W2p, nul, Yg, f, d, filt, nosink, now);
+                           offsets, slot_of_pair, P, by_pair, (const float*)W2p, nul, Yg, f, d, filt, nosink, now);
     (void)mid;
 }
 
