@@ -455,12 +455,29 @@ static int planned_nb(const mmoe_shape& s, int bm, int N, bool gated)
     return ((P + bm - 1) / bm) * (N / kBN) < kNb1Room ? 1 : 2;
 }
 
+// fp32: does a product with N outputs (of each matrix) run on bf16 parts (ffn_split_f32.hip)?  Its tiles have twice the
+// features, so it needs rows that fill tiles and tiles that fill the chip: about as many as half the compute units,
+// counted as if every slot had one tile more than its share of full ones.  Measured for both products by each kernel and
+// with this rule, us: 768 x 3072, 13 slots 116 : 134 : 116 at 54 rows per slot, 125 : 136 : 120 at 65, 132 : 137 : 119 at 77,
+// 173 : 157 : 158 at 90, 229 : 173 : 172 at 154; 256 x 8192 (2 wide tiles down) 245 : 262 : 228 at 115, 284 : 281 : 242 at
+// 192; 4096 x 512 139 : 146 : 122 at 62, 284 : 206 : 205 at 192; 2048 x 4096, 6 slots 160 : 166 : 154 at 50; 768 x 768, 4 slots
+// 53 : 57 : 53 at 250, 119 : 87 : 86 at 1000; SwiGLU 1024 x 2048 123 : 118 : 119 at 46, 131 : 121 : 121 at 65; 2048 x 4096
+// 218 : 205 : 191 at 43.
+constexpr int kPartsRows = 40, kPartsTiles = 150;
+static bool f32_in_parts(const mmoe_shape& s, int N, bool gated)
+{
+    const int64_t P = (int64_t)s.T * s.top_k;
+    if (P < (int64_t)kPartsRows * s.S) return false;
+    return gated || (P / kFRows + s.S) * (N / (2 * kFeatF32)) >= kPartsTiles;
+}
+
 static void tiled_nts(const mmoe_shape& s, int bm, int& nt_up, int& nt_down, int& nb_up, int& nb_down)
 {
     if (s.dtype == MMOE_F32) {
-        nb_up = nb_down = 1;
-        nt_up = s.d_ff / kFeatF32;
-        nt_down = s.d_model / kFeatF32;
+        nb_up = f32_in_parts(s, s.d_ff, s.act == MMOE_SWIGLU) ? 2 : 1;
+        nb_down = f32_in_parts(s, s.d_model, false) ? 2 : 1;
+        nt_up = s.d_ff / (kFeatF32 * (s.act == MMOE_SWIGLU ? 1 : nb_up));
+        nt_down = s.d_model / (kFeatF32 * nb_down);
         return;
     }
     nb_up = planned_nb(s, bm, s.d_ff, s.act == MMOE_SWIGLU);
@@ -517,15 +534,17 @@ size_t tiled_table_bytes(const mmoe_shape& s)
 size_t tiled_table_most(const mmoe_shape& s)
 {
     const int P = s.T * s.top_k;
-    if (s.dtype == MMOE_F32) return align256(tiled_plan(s).L.bytes);  // one height, one feature tile
-    // Fewer pairs may get the other height and narrower feature tiles (planned_tile_rows, planned_nb); with each of
-    // them fixed the lists only grow with P.
     size_t most = 0;
-    for (int bm : {kBMSmall, kBMBig})
+    // Fewer pairs may get the other height and narrower feature tiles (planned_tile_rows, planned_nb, f32_in_parts); with
+    // each of them fixed the lists only grow with P.  (Wider feature tiles can make the longer lists: a number of
+    // them that is no multiple of 8 takes a list per XCD.)
+    const bool f32 = s.dtype == MMOE_F32;
+    const int wide = f32 ? kFeatF32 : 128;  // features of a tile with one weight block per wavefront
+    for (int bm : {f32 ? kFRows : kBMSmall, f32 ? kFRows : kBMBig})
         for (int nb_up : {1, 2})
             for (int nb_down : {1, 2}) {
-                const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / (kBN / 2) : s.d_ff / (128 * nb_up);
-                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (128 * nb_down), bm / 32, bm / 32, bm, false);
+                const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb_up);
+                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (wide * nb_down), bm / 32, bm / 32, bm, f32);
                 most = L.bytes > most ? L.bytes : most;
             }
     return align256(most);
@@ -580,7 +599,12 @@ int launch_ffn_tiled(const mmoe_shape& s, const void* rows, const int32_t* perm,
     if (sink.w && (s.top_k != 1 || !sink.perm || !sink.Y)) return MMOE_ERR_DIM;
     const TiledPlan p = tiled_plan(s);
     if (!tab_ready) launch_tile_lists(s, offsets, tab, st, filt);
-    if (s.dtype == MMOE_F32) return launch_products_f32(s, p, rows, perm, tab, W1p, W3p, W2p, H, Yg, st, mid, sink);
+    if (s.dtype == MMOE_F32) {
+        (p.nb_up == 2 ? launch_up_split : launch_up_f32)(s, p, rows, perm, tab, W1p, W3p, H, st);
+        if (mid && hipEventRecord(mid, st) != hipSuccess) return MMOE_ERR_LAUNCH;
+        (p.nb_down == 2 ? launch_down_split : launch_down_f32)(s, p, tab, W2p, H, Yg, st, sink);
+        return launch_status();
+    }
     if (s.act == MMOE_SWIGLU) {
         if (p.bm == kBMBig)
             launch_product<kTModeSwigluH, kBMBig, 2>(p, 0, rows, perm, s.top_k, tab, W1p, W3p, H, d, f, st);

@@ -3,6 +3,8 @@
 //
 // Both products are  out[r, n] = sum_k A[r, k] * W[s][n][k]  over the transposed pool [S, N, K].
 //
+// Products with many rows per slot and enough tiles run on bf16 parts instead (ffn_split_f32.hip).
+//
 // What bounds it: the fp32 matrix rate (256 flop per cycle and compute unit), a sixteenth of bf16's, so a
 // tile moves little per flop and the design is plain.  Tile: up to 96 token rows x 64 output features x
 // 32 k per step, four wavefronts, 16 features each (of both weight matrices for the gated product, so that
@@ -218,18 +220,21 @@ static void launch_product(const TiledPlan& p, int prod, const void* A, const in
                        (const float*)W1, (float*)out, K, N, sink.perm, sink.w);
 }
 
-int launch_products_f32(const mmoe_shape& s, const TiledPlan& p, const void* rows, const int32_t* perm, const int32_t* tab,
-                        const void* W1p, const void* W3p, const void* W2p, void* H, float* Yg, hipStream_t st,
-                        hipEvent_t mid, GateSink sink)
+void launch_up_f32(const mmoe_shape& s, const TiledPlan& p, const void* rows, const int32_t* perm, const int32_t* tab,
+                   const void* W1p, const void* W3p, void* H, hipStream_t st)
 {
     const int d = s.d_model, f = s.d_ff;
     if (s.act == MMOE_SWIGLU) launch_product<kModeSwigluH>(p, 0, rows, perm, s.top_k, tab, W1p, W3p, H, d, f, st);
     else if (s.act == MMOE_GELU) launch_product<kModeGeluH>(p, 0, rows, perm, s.top_k, tab, W1p, nullptr, H, d, f, st);
     else launch_product<kModeReluH>(p, 0, rows, perm, s.top_k, tab, W1p, nullptr, H, d, f, st);
-    if (mid && hipEventRecord(mid, st) != hipSuccess) return MMOE_ERR_LAUNCH;
+}
+
+void launch_down_f32(const mmoe_shape& s, const TiledPlan& p, const int32_t* tab, const void* W2p, const void* H, float* Yg,
+                     hipStream_t st, GateSink sink)
+{
+    const int d = s.d_model, f = s.d_ff;
     if (sink.w) launch_product<kModeGatedY>(p, 1, H, nullptr, 1, tab, W2p, nullptr, sink.Y, f, d, st, sink);
     else launch_product<kModePlainF32>(p, 1, H, nullptr, 1, tab, W2p, nullptr, Yg, f, d, st);
-    return launch_status();
 }
 
 }  // namespace mmoe

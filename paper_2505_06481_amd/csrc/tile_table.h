@@ -263,11 +263,17 @@ struct TiledPlan {
     TileLists L;
 };
 
-// fp32 (ffn_tiled_f32.hip): tiles of up to 96 rows x 64 features.
+// fp32: tiles of up to 96 rows; 64 features on the fp32 instruction (ffn_tiled_f32.hip: plan with one weight block per
+// wavefront), 128 (gated: 64) on bf16 parts (ffn_split_f32.hip: two weight blocks).
 constexpr int kFRows = 96, kFeatF32 = 64;
-int launch_products_f32(const mmoe_shape& s, const TiledPlan& p, const void* rows, const int32_t* perm, const int32_t* tab,
-                        const void* W1p, const void* W3p, const void* W2p, void* H, float* Yg, hipStream_t st,
-                        hipEvent_t mid, GateSink sink);
+void launch_up_f32(const mmoe_shape& s, const TiledPlan& p, const void* rows, const int32_t* perm, const int32_t* tab,
+                   const void* W1p, const void* W3p, void* H, hipStream_t st);
+void launch_down_f32(const mmoe_shape& s, const TiledPlan& p, const int32_t* tab, const void* W2p, const void* H, float* Yg,
+                     hipStream_t st, GateSink sink);
+void launch_up_split(const mmoe_shape& s, const TiledPlan& p, const void* rows, const int32_t* perm, const int32_t* tab,
+                     const void* W1p, const void* W3p, void* H, hipStream_t st);
+void launch_down_split(const mmoe_shape& s, const TiledPlan& p, const int32_t* tab, const void* W2p, const void* H, float* Yg,
+                       hipStream_t st, GateSink sink);
 
 // What the grouping kernels need to write the lists themselves (null `tab`: they do not).
 struct TileJob {

@@ -157,6 +157,81 @@ def test_tiled_f32_row_remainders(mm, gc, oracle, act, k, d, f):
         assert mm.expert_plan(case.shape) == (False, 96)
 
 
+def _parts_case(mm, oracle, act, d, f, seed):
+    """A grouped batch in fp32 whose slots hold every number of rows at which a tile's fragments change; both
+    products of 768 outputs and the gated one run on bf16 parts, those of 256 and 512 on the fp32 instruction."""
+    counts = [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 79, 80, 81, 95, 96, 97, 0, 129, 191, 193, 289]
+    rng = np.random.default_rng(seed)
+    S, P = len(counts), sum(counts)
+    assert P >= 40 * S
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    Xg = rng.standard_normal((P, d)).astype(np.float32)
+    W1, W2 = (0.05 * rng.standard_normal((S, a, b)).astype(np.float32) for a, b in ((d, f), (f, d)))
+    W3 = 0.05 * rng.standard_normal((S, d, f)).astype(np.float32) if act == "swiglu" else None
+    shape = mm.make_shape(P, d, f, 1, S, S, 1, "f32", act)
+    assert mm.expert_plan(shape) == (False, 96)
+    return shape, offsets, Xg, W1, W3, W2
+
+
+def _parts_run(mm, shape, offsets, Xg, W1, W3, W2):
+    dev = lambda a: None if a is None else torch.from_numpy(a).cuda()
+    packed = mm.pack_weights(shape, dev(W1), dev(W3), dev(W2))
+    Y = mm.expert_ffn(shape, dev(Xg), dev(offsets), *packed, mm.alloc_workspace(shape))
+    torch.cuda.synchronize()
+    return Y.cpu().numpy()
+
+
+@pytest.mark.parametrize("act,d,f", [("relu", 256, 768), ("gelu", 768, 256), ("swiglu", 512, 768), ("swiglu", 768, 1024),
+                                     ("relu", 768, 2560)])
+def test_f32_products_on_bf16_parts(mm, gc, oracle, act, d, f):
+    """Rows at the edges of the tiles, one and several chains of the reduction, either product on either kernel.
+    The tolerance on the 2-norm is what the fp32 instruction gives (measured: 2.2e-7 to 2.9e-7 here, 3.5e-7 to 5.2e-7
+    there), so that parts of too few bits, or a missing one (2^-16), do not pass."""
+    shape, offsets, Xg, W1, W3, W2 = _parts_case(mm, oracle, act, d, f, seed=d + f)
+    got = _parts_run(mm, shape, offsets, Xg, W1, W3, W2).astype(np.float64)
+    ref = oracle.expert_ffn(Xg, offsets, W1, W3, W2, "f32", act)
+    gc.assert_close(got, ref, "f32", "Yg")
+    assert np.linalg.norm(got - ref) <= 6e-7 * np.linalg.norm(ref)
+
+
+def test_f32_parts_of_numbers_that_are_not_finite(mm, gc, oracle):
+    """Infinities, NaN and numbers that round to an infinity in bf16 give what fp32 gives, and only in their own
+    rows and features."""
+    shape, offsets, Xg, W1, _, W2 = _parts_case(mm, oracle, "gelu", 768, 768, seed=5)
+    W1[:, 700, :] = np.abs(W1[:, 700, :]) * 1e-3 + 1e-6  # the large entry's products: finite, of one sign
+    rows = [3, 40, 200, len(Xg) - 1]
+    others = ~np.isin(np.arange(len(Xg)), rows)
+    clean = np.where(others[:, None], Xg, np.float32(0))
+    Xg[rows, 700] = np.inf, -np.inf, np.nan, np.finfo(np.float32).max
+    got = _parts_run(mm, shape, offsets, Xg, W1, None, W2)
+    assert np.array_equal(got[others], _parts_run(mm, shape, offsets, clean, W1, None, W2)[others])
+    with np.errstate(over="ignore", invalid="ignore"):
+        want = oracle.expert_ffn(Xg, offsets, W1, None, W2, "f32", "gelu").astype(np.float32)
+    for r in rows:
+        nan, fin = np.isnan(want[r]), np.isfinite(want[r])
+        assert np.array_equal(np.isnan(got[r]), nan), r
+        assert np.array_equal(got[r][~nan & ~fin], want[r][~nan & ~fin]), r
+        assert np.allclose(got[r][fin], want[r][fin], rtol=1e-4), r
+    W2[5, 10, 100] = np.inf  # one feature of one slot, on the other operand
+    got = _parts_run(mm, shape, offsets, clean, W1, None, W2)
+    hit = np.zeros(got.shape, bool)
+    hit[offsets[5]:offsets[6], 100] = True
+    assert np.isfinite(got[~hit]).all() and not np.isfinite(got[hit]).any()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_streaming_grid_by_pair(mm, gc, oracle, dtype):
+    """Batches of fewer pairs than slots (a row of workgroups per pair), as many and one more, with slots picked by
+    several pairs; and numbers of pairs around the rounds in which a slot's list is made."""
+    for T, V, E, k, d, f in ((1, 4, 8, 1, 256, 1280), (2, 1, 4, 2, 512, 256), (7, 4, 4, 2, 256, 512), (31, 4, 8, 1, 1280, 256),
+                             (32, 4, 8, 1, 256, 512), (33, 4, 8, 1, 256, 512), (16, 1, 33, 2, 256, 512), (64, 8, 9, 1, 256, 256),
+                             (65, 8, 9, 1, 256, 256), (255, 4, 8, 1, 256, 256), (128, 4, 8, 2, 256, 256), (257, 4, 8, 1, 256, 256)):
+        cfg = synth.Config(f"by_pair_{dtype}_{T}", T, d, f, V, E, k, dtype, "gelu" if k == 1 else "swiglu", seed=1200 + T,
+                           share_prob=0.0, bias_alpha=1.0)
+        case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
+        assert mm.expert_plan(case.shape) == (True, 32)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d", [256, 768, 1024, 1280, 2048, 2304, 4096, 4352])
 def test_router_row_lengths(mm, gc, oracle, dtype, d):
