@@ -14,7 +14,7 @@
 //   3.1 / 2.3 and 2.2 / 2.2.  (Chains of 256 k: 2.3 to 2.6, not below the fp32 instruction's after a ReLU.)
 //   Range: bf16 has fp32's exponents.  Parts below 2^-126 are lost, so numbers below 2^-101 count with fewer than 24
 //   bits.  Numbers that are not finite, or round to an infinity in bf16, make the result a NaN: results that are
-//   not finite are computed again in plain fp32 in the epilogue, so that they are what fp32 gives.
+//   not finite are computed again on the fp32 instruction in the epilogue, so that they are what fp32 gives.
 //
 // What bounds it: matrix instructions, the splitting of the operands (11 vector instructions for two numbers) and the
 // loads of the weights in operand order (65 cycles of a compute unit's memory pipeline for each KB, 1040 a step; the
@@ -101,16 +101,14 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
     const int n0 = nt * (kFeatF32 * kOut) + wave * (16 * kOut);
 
     // Lane (li, g) of an operand holds, of a step's 32 k, the four from 4 g on and the four from 16 + 4 g on.
-    auto weight_row = [&](int i, int row) {  // of the wavefront's block i
-        return (kGated && i == 1 ? W1 : W0) + ((size_t)s * N + n0 + (kGated ? 0 : 16 * i) + row) * K;
-    };
     auto token_row = [&](int row) {  // input row of the tile's row
         const int r = r0 + row;
         return A + (size_t)(perm ? perm[r] / kdiv : r) * K;
     };
     const float* wrow[kNB];
 #pragma unroll
-    for (int i = 0; i < kNB; ++i) wrow[i] = weight_row(i, li) + 4 * g;
+    for (int i = 0; i < kNB; ++i)
+        wrow[i] = (kGated && i == 1 ? W1 : W0) + ((size_t)s * N + n0 + (kGated ? 0 : 16 * i) + li) * K + 4 * g;
 
     auto run = [&](auto njc) {
         constexpr int NJ = decltype(njc)::value;  // 16-row fragments of the tile that hold rows
@@ -247,17 +245,24 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
         if (__any(odd)) {
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
-                const float* a = token_row(min(j * 16 + li, cnt - 1));
+                const float* a = token_row(min(j * 16 + li, cnt - 1)) + 4 * g;
+                f32x4 c[kNB];
+#pragma unroll
+                for (int i = 0; i < kNB; ++i) c[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int k = 0; k < K; k += 16) {
+                    const f32x4 xv = *reinterpret_cast<const f32x4*>(a + k);
+#pragma unroll
+                    for (int i = 0; i < kNB; ++i) {
+                        const f32x4 wv = *reinterpret_cast<const f32x4*>(wrow[i] + k);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) c[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], c[i], 0, 0, 0);
+                    }
+                }
 #pragma unroll
                 for (int i = 0; i < kNB; ++i)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (fabsf(tot[j][i][e]) < INFINITY) continue;
-                        const float* w = weight_row(i, 4 * g + e);
-                        float v = 0.0f;
-                        for (int k = 0; k < K; ++k) v = __builtin_fmaf(a[k], w[k], v);
-                        tot[j][i][e] = v;
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if (!(fabsf(tot[j][i][e]) < INFINITY)) tot[j][i][e] = c[i][e];
             }
         }
 
