@@ -27,8 +27,9 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
                                                         int C)
 {
     __shared__ T tile[kTile][kTile + 2];
-    const size_t mat = (size_t)blockIdx.z * R * C;
-    const int c0 = blockIdx.x * kTile, r0 = blockIdx.y * kTile;
+    // backwards and past the caches, as the fragment packing below
+    const size_t mat = (size_t)(gridDim.z - 1 - blockIdx.z) * R * C;
+    const int c0 = (gridDim.x - 1 - blockIdx.x) * kTile, r0 = (gridDim.y - 1 - blockIdx.y) * kTile;
     const int tx = threadIdx.x % kTile, ty = threadIdx.x / kTile;  // 64 x 4
     for (int i = ty; i < kTile; i += 4) {
         int r = r0 + i, c = c0 + tx;
@@ -37,37 +38,50 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in
     __syncthreads();
     for (int i = ty; i < kTile; i += 4) {
         int c = c0 + i, r = r0 + tx;
-        if (r < R && c < C) out[mat + (size_t)c * R + r] = tile[tx][i];
+        if (r < R && c < C) __builtin_nontemporal_store(tile[tx][i], &out[mat + (size_t)c * R + r]);
     }
 }
 
-// bf16 fragment packing: one thread writes one 16-byte piece.
-__global__ __launch_bounds__(256) void pack_fragments_kernel(const uint16_t* __restrict__ in,
-                                                             u32x4* __restrict__ out, int K, int N)
+// bf16 fragment packing.  Bound by HBM.  A workgroup packs 64 k x 256 n: rows are read 512 bytes at a time into LDS, a
+// thread then gathers the 8 k of a piece from LDS and writes it, a wavefront the pieces of a fragment (1 KB).  A program
+// packs the pool that it has just assembled, so the pool is walked backwards, last matrix first, and the packed copy,
+// which nobody reads soon, is written past the caches: the end of the pool is then still in the last-level cache.
+// (768 x 3072, 12 layers of 20 slots on average, assembly and packing of 2.26 GB: 1749 us with a 16-byte piece gathered
+// by eight 2-byte loads, forwards; 1570 backwards and past the caches; 1500 with rows read into LDS.)
+constexpr int kPackN = 256, kPackK = 64;
+__global__ __launch_bounds__(256) void pack_fragments_kernel(const uint16_t* __restrict__ in, u32x4* __restrict__ out, int K, int N)
 {
-    // `in` is [S, K, N]; piece index = ((s*(N/32) + nb) * (K/16) + ks) * 64 + lane
-    const size_t piece = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const int lane = (int)(piece & 63);
-    const size_t frag = piece >> 6;
-    const int ks = (int)(frag % (size_t)(K / 16));
-    const size_t blk = frag / (size_t)(K / 16);  // s*(N/32) + nb
-    const int nb = (int)(blk % (size_t)(N / 32));
-    const size_t s = blk / (size_t)(N / 32);
-    const int n = nb * 32 + (lane & 31);
-    const int k0 = (ks >> 2) * 64 + (lane >> 5) * 32 + (ks & 3) * 8;
-    const uint16_t* src = in + (s * K + k0) * (size_t)N + n;
-    uint32_t w[4];
+    __shared__ __attribute__((aligned(16))) uint16_t tile[kPackK][kPackN];
+    // workgroup -> (slot, block of 256 n, block of 64 k), `in` is [S, K, N]
+    const unsigned b = gridDim.x - 1 - blockIdx.x;
+    const unsigned km = K / kPackK, nn = N / kPackN;
+    const unsigned m = b % km, rest = b / km, nb8 = rest % nn;
+    const size_t s = rest / nn;
+    const int tid = threadIdx.x;
+    const uint16_t* src = in + (s * K + (size_t)m * kPackK) * N + nb8 * kPackN;
+    u32x4 v[8];
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        w[e] = (uint32_t)src[(size_t)(2 * e) * N] | ((uint32_t)src[(size_t)(2 * e + 1) * N] << 16);
-    out[piece] = u32x4{w[0], w[1], w[2], w[3]};
+    for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const u32x4*>(src + (size_t)(i * 8 + tid / 32) * N + (tid % 32) * 8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(&tile[i * 8 + tid / 32][((tid % 32) * 8) ^ (i < 4 ? 0 : 32)]) = v[i];  // the upper 32 k in other banks
+    __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6;  // wave = fragment kk of the 64-k step; i = block of 32 n
+    const int k0 = (lane >> 5) * 32 + wave * 8;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int n = (i * 32 + (lane & 31)) ^ (lane & 32);
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = (uint32_t)tile[k0 + 2 * e][n] | ((uint32_t)tile[k0 + 2 * e + 1][n] << 16);
+        const size_t frag = (s * (N / 32) + nb8 * 8 + i) * (K / 16) + m * 4 + wave;
+        __builtin_nontemporal_store((u32x4{w[0], w[1], w[2], w[3]}), &out[frag * 64 + lane]);
+    }
 }
 
 static void pack_fragments(const void* in, void* out, int S, int K, int N, hipStream_t st)
 {
-    const size_t pieces = (size_t)S * (N / 32) * (K / 16) * 64;  // a multiple of 256: K, N are multiples of 256
-    hipLaunchKernelGGL(pack_fragments_kernel, dim3((unsigned)(pieces / 256)), dim3(256), 0, st, (const uint16_t*)in,
-                       (u32x4*)out, K, N);
+    const size_t blocks = (size_t)S * (N / kPackN) * (K / kPackK);
+    hipLaunchKernelGGL(pack_fragments_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)in, (u32x4*)out, K, N);
 }
 
 static void transpose(const void* in, void* out, int S, int R, int C, int dtype, hipStream_t st)
@@ -83,13 +97,13 @@ int launch_pack(const mmoe_shape& s, const void* W1, const void* W3, const void*
                 void* W2p, hipStream_t st)
 {
     if (s.dtype == MMOE_BF16) {
-        pack_fragments(W1, W1p, s.S, s.d_model, s.d_ff, st);
-        if (W3) pack_fragments(W3, W3p, s.S, s.d_model, s.d_ff, st);
         pack_fragments(W2, W2p, s.S, s.d_ff, s.d_model, st);
+        if (W3) pack_fragments(W3, W3p, s.S, s.d_model, s.d_ff, st);
+        pack_fragments(W1, W1p, s.S, s.d_model, s.d_ff, st);
     } else {
-        transpose(W1, W1p, s.S, s.d_model, s.d_ff, s.dtype, st);
-        if (W3) transpose(W3, W3p, s.S, s.d_model, s.d_ff, s.dtype, st);
         transpose(W2, W2p, s.S, s.d_ff, s.d_model, s.dtype, st);
+        if (W3) transpose(W3, W3p, s.S, s.d_model, s.d_ff, s.dtype, st);
+        transpose(W1, W1p, s.S, s.d_model, s.d_ff, s.dtype, st);
     }
     return launch_status();
 }
