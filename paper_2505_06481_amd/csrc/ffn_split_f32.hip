@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
     const int n_mine = tab[hdr + xcd];
     const int4 ent = list[local];  // in bounds for every workgroup of the grid
     if (local >= n_mine) return;   // uniform over the workgroup
-    const int s = ent.x;
+    const int s = ent.x & kSlotMask;
     const int nt = list_stride ? ent.y : ent.y * kXcds + xcd;
     const int r0 = ent.z, cnt = ent.w;  // first row, rows (1..96)
 

@@ -72,15 +72,16 @@ __global__ __launch_bounds__(kListThreads) void tile_table_kernel(const int32_t*
     build_tile_lists(off, tab, S, p, p == 0 ? nt_up : nt_down, L, first, filt);
 }
 
-template <int MODE, int BM, int NB>
-__global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const uint16_t* __restrict__ A,
-                                                       const int32_t* __restrict__ perm, int kdiv,
-                                                            const int32_t* __restrict__ tab, int hdr, int list_at,
-                                                            int list_stride, const uint16_t* __restrict__ W0,
-                                                            const uint16_t* __restrict__ W1,
-                                                            void* __restrict__ out, int K, int N,
-                                                            const int32_t* __restrict__ sink_perm,
-                                                            const float* __restrict__ sink_w)
+// LONE: a tile that holds all rows of its slot is the only reader of its weight panels and reads them past the caches,
+// which streams faster (4096 x 14336, 18 slots, 777 tokens 1227 -> 1200 us; 4096 x 2048, 64 slots, 4800 pairs 737 -> 717;
+// 2560 x 2560 GELU, 20 slots, 2000 pairs 179 -> 171).  A panel with several readers has to stay in L2 (8192 tokens 4486 ->
+// 5087 us with every panel past the caches).
+template <int MODE, int BM, int NB, bool LONE>
+__device__ __forceinline__ void tiled_body(const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv,
+                                           const int32_t* __restrict__ tab, int hdr, int list_at, int list_stride,
+                                           const uint16_t* __restrict__ W0, const uint16_t* __restrict__ W1,
+                                           void* __restrict__ out, int K, int N, const int32_t* __restrict__ sink_perm,
+                                           const float* __restrict__ sink_w)
 {
     constexpr int kTileBytes = BM * kBK * 2;  // one step of the token operand (32 KB for 256 rows)
     __shared__ __attribute__((aligned(1024))) char lds_a[kStagesA * kTileBytes];
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     const int n_mine = tab[hdr + xcd];
     const int4 ent = list[local];                     // in bounds for every workgroup of the grid
     if (local >= n_mine) return;                      // uniform over the workgroup
-    const int s = ent.x;
+    const int s = ent.x & kSlotMask;
     const int nt = list_stride ? ent.y : ent.y * kXcds + xcd;
     const int r0 = ent.z;                             // first row of the tile
     const int cnt = ent.w;                            // rows of the tile that exist (1..256)
@@ -244,8 +245,9 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
     const int last = nkt - 1;
     const int last_slice = K / 32 - 1;
     constexpr int kUnroll = (BM == kBMBig || NB == 1) ? 4 : 2;
-    auto run = [&](auto njc) {
+    auto run = [&](auto njc, auto ntc) {
         constexpr int NJ = decltype(njc)::value;
+        constexpr bool NT = decltype(ntc)::value;  // weights past the caches
         // ring of weight slices in registers (four steps, two steps): what the accumulators leave room for
         constexpr int kSlices = NB == 1 || (BM == kBMBig && NJ <= 4) ? 8 : 4;
         constexpr int kDeep = kNP / NJ;
@@ -264,7 +266,8 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
         BFrags bq[kSlices];
         auto load_bf = [&](BFrags& fr, int g, int i) {
             const size_t o = (size_t)min(g, last_slice) * 2048;  // past the end: a harmless reload
-            fr.b[i] = *reinterpret_cast<const u32x4*>(wb[i >> 1] + o + (w_off + (i & 1) * 256));
+            const u32x4* src = reinterpret_cast<const u32x4*>(wb[i >> 1] + o + (w_off + (i & 1) * 256));
+            fr.b[i] = NT ? __builtin_nontemporal_load(src) : *src;
         };
         // prologue: copies of steps 0 .. kStages-2, then the first weight slices; the wait leaves at most
         // the copies of the last kDeep of those steps in flight
@@ -368,15 +371,23 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
         // results are there before the accumulators are read
         asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     };
-    switch (min(BM / 32, (cnt + 31) / 32)) {  // uniform over the workgroup
-        case 8: if constexpr (BM == kBMBig) run(std::integral_constant<int, 8>{}); break;
-        case 7: if constexpr (BM == kBMBig) run(std::integral_constant<int, 7>{}); break;
-        case 6: if constexpr (BM == kBMBig) run(std::integral_constant<int, 6>{}); break;
-        case 5: if constexpr (BM == kBMBig) run(std::integral_constant<int, 5>{}); break;
-        case 4: run(std::integral_constant<int, 4>{}); break;
-        case 3: run(std::integral_constant<int, 3>{}); break;
-        case 2: run(std::integral_constant<int, 2>{}); break;
-        default: run(std::integral_constant<int, 1>{}); break;
+    auto sized = [&](auto ntc) {
+        switch (min(BM / 32, (cnt + 31) / 32)) {  // uniform over the workgroup
+            case 8: if constexpr (BM == kBMBig) run(std::integral_constant<int, 8>{}, ntc); break;
+            case 7: if constexpr (BM == kBMBig) run(std::integral_constant<int, 7>{}, ntc); break;
+            case 6: if constexpr (BM == kBMBig) run(std::integral_constant<int, 6>{}, ntc); break;
+            case 5: if constexpr (BM == kBMBig) run(std::integral_constant<int, 5>{}, ntc); break;
+            case 4: run(std::integral_constant<int, 4>{}, ntc); break;
+            case 3: run(std::integral_constant<int, 3>{}, ntc); break;
+            case 2: run(std::integral_constant<int, 2>{}, ntc); break;
+            default: run(std::integral_constant<int, 1>{}, ntc); break;
+        }
+    };
+    if constexpr (LONE) {
+        if (ent.x & kOnlyTile) sized(std::true_type{});  // uniform over the workgroup
+        else sized(std::false_type{});
+    } else {
+        sized(std::false_type{});
     }
     // the accumulators stay where the matrix instructions left them until the epilogue reads them
 #pragma unroll
@@ -442,6 +453,25 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(const 
         }
         __builtin_amdgcn_sched_barrier(0);  // one fragment at a time: few registers
     }
+}
+
+template <int MODE, int BM, int NB>
+__global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv, const int32_t* __restrict__ tab, int hdr,
+    int list_at, int list_stride, const uint16_t* __restrict__ W0, const uint16_t* __restrict__ W1, void* __restrict__ out,
+    int K, int N, const int32_t* __restrict__ sink_perm, const float* __restrict__ sink_w)
+{
+    tiled_body<MODE, BM, NB, false>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
+}
+
+// 256-row tiles of a batch in which slots may be one tile.
+template <int MODE>
+__global__ __launch_bounds__(256, 1) void tiled_lone_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv, const int32_t* __restrict__ tab, int hdr,
+    int list_at, int list_stride, const uint16_t* __restrict__ W0, const uint16_t* __restrict__ W1, void* __restrict__ out,
+    int K, int N, const int32_t* __restrict__ sink_perm, const float* __restrict__ sink_w)
+{
+    tiled_body<MODE, kBMBig, 2, true>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
 }
 
 // Weight blocks per wavefront of a product with N output features: 2, or 1 (tiles of 128 weight
@@ -512,6 +542,8 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
 {
     TiledPlan p;
     p.bm = planned_tile_rows(s);
+    // slots of one 256-row tile are likely (at 244 and 306 rows per slot on average both are within 1 %)
+    p.lone = (int64_t)s.T * s.top_k <= (int64_t)kBMBig * s.S;
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm), planned_upt(s, p.bm), p.bm,
                      s.dtype == MMOE_F32);
@@ -555,9 +587,17 @@ static void launch_product(const TiledPlan& p, int prod, const void* A, const in
                            const void* W0, const void* W1, void* out, int K, int N, hipStream_t st,
                            GateSink sink = GateSink())
 {
-    hipLaunchKernelGGL((tiled_kernel<MODE, BM, NB>), dim3(p.L.len[prod] * kXcds), dim3(256), 0, st, (const uint16_t*)A,
-                       perm, kdiv, tab, kXcds * prod, p.L.list[prod], p.L.lists[prod] == 1 ? 0 : p.L.len[prod],
-                       (const uint16_t*)W0, (const uint16_t*)W1, out, K, N, sink.perm, sink.w);
+    const dim3 grid(p.L.len[prod] * kXcds), block(256);
+    const int stride = p.L.lists[prod] == 1 ? 0 : p.L.len[prod];
+    if constexpr (BM == kBMBig) {
+        if (p.lone) {
+            hipLaunchKernelGGL((tiled_lone_kernel<MODE>), grid, block, 0, st, (const uint16_t*)A, perm, kdiv, tab, kXcds * prod,
+                               p.L.list[prod], stride, (const uint16_t*)W0, (const uint16_t*)W1, out, K, N, sink.perm, sink.w);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((tiled_kernel<MODE, BM, NB>), grid, block, 0, st, (const uint16_t*)A, perm, kdiv, tab, kXcds * prod,
+                       p.L.list[prod], stride, (const uint16_t*)W0, (const uint16_t*)W1, out, K, N, sink.perm, sink.w);
 }
 
 // one weight block per wavefront exists for 128-row tiles only (planned_nb)

@@ -29,7 +29,7 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // as square as the slot allows (8 x 4 for a slot of 8 row tiles, 4 x 8 for one of 4).
 //
 // XCDs.  Workgroup id 8*local + x runs on XCD x and computes entry `local` of the XCD's list, an int4
-// {slot, feature tile, first row, rows}; tab[8 p + x] = number of entries of product p's list for XCD x.
+// {slot (and kOnlyTile), feature tile, first row, rows}; tab[8 p + x] = number of entries of product p's list for XCD x.
 // The weight panels of the batch -- the feature tiles of the slots that hold rows, slot after slot -- are
 // dealt to the XCDs in turn: panel c to XCD c mod 8, with all its row tiles, so a weight panel is read
 // by one XCD and every XCD has the same number of panels to within one.  Where NT is a multiple of 8 this
@@ -45,6 +45,10 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // bound by what they move).  fp32: one sub-tile (the matrix rate bounds tiles of any height, and short
 // ones share out a product of few tiles evenly).
 constexpr int kMaxHeightCands = 16;
+
+// In an entry's first word: the slot, and whether the tile holds all rows of the slot.
+constexpr int kSlotMask = 0xFFFF, kOnlyTile = 1 << 16;
+static_assert(kMaxS <= kSlotMask, "slot ids");
 
 struct TileLists {
     int list[2];    // [product: up, down] -> int4 index into tab of XCD 0's list
@@ -251,7 +255,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
         const int u = units_of(s), h = div24(u, mt), extra = u - h * mt;
         const int row0 = 32 * (i * h + min(i, extra));
         const int rows = 32 * (h + (i < extra ? 1 : 0));
-        lists[L.list[p] + x * L.len[p] + e] = make_int4(s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
+        lists[L.list[p] + x * L.len[p] + e] = make_int4(mt == 1 ? s | kOnlyTile : s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
     }
 }
 
@@ -260,6 +264,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
 // tiles of both products, and the tile lists' layout.
 struct TiledPlan {
     int bm, nt_up, nt_down, nb_up, nb_down;
+    bool lone;  // 256-row tiles: the kernel that reads the panels of one-tile slots past the caches
     TileLists L;
 };
 

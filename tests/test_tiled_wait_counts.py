@@ -195,6 +195,17 @@ def test_every_written_out_wait_of_the_tiled_kernel_is_covered():
         print(f"{fn.name}: {len(res)} waits, smallest margin {min(i - n for n, _, i in res)}")
 
 
+def test_waits_of_the_kernel_for_slots_of_one_tile():
+    """The same main loops, each twice: weights through the caches and past them."""
+    fns = functions(device_assembly(), "_ZN4mmoe17tiled_lone_kernel")
+    assert len(fns) == 5, [f.name for f in fns]
+    for fn in fns:
+        mode = re.search(r"kernelILi(\d)E", fn.name).group(1)
+        res = check_function(fn)
+        want = sorted(k for _, k, waits in variants(f"_ZN4mmoe12tiled_kernelILi{mode}ELi256ELi2EE") for _ in range(2 * waits))
+        assert sorted(k for _, k, _ in res) == want, fn.name
+
+
 def test_loads_moved_across_a_wait_are_flagged():
     """A mistake planted in the assembly text: the waits with one number of copies in flight (tiles of 3, 5, 6 and 7
     sub-tiles have their own) leave three more instructions outstanding than the kernel asks for, as if three loads had
