@@ -120,19 +120,21 @@ def workspace_bytes(shape: Shape) -> int:
 def _ptr(t: Optional[torch.Tensor], dtype=None, numel=None, name="tensor"):
     if t is None:
         return None
+    if t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype) and (numel is None or t.numel() >= numel):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name} must live on the GPU")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
-    if numel is not None and t.numel() < numel:
-        raise ValueError(f"{name}: needs {numel} elements, has {t.numel()}")
-    return t.data_ptr()
+    raise ValueError(f"{name}: needs {numel} elements, has {t.numel()}")
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    """Raw handle of the current device's current stream (what torch.cuda.current_stream().cuda_stream is,
+    without the Stream object: 2.7 -> 0.3 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(rc: int, where: str):
@@ -219,16 +221,15 @@ EV_START, EV_ROUTE, EV_PERMUTE, EV_FFN_UP, EV_FFN_DOWN, EV_COMBINE = range(NUM_E
 def layer_forward(shape: Shape, X, vid, Wr, br, M, W1p, W3p, W2p, ws, Y=None, events=None):
     """``events``: optional ctypes array of NUM_EVENTS hipEvent_t handles (c_void_p); null entries are skipped."""
     dt = _TORCH_DT[shape.dtype]
-    S, d, f = shape.S, shape.d_model, shape.d_ff
+    T, V, E, d = shape.T, shape.V, shape.E, shape.d_model
+    n = shape.S * d * shape.d_ff
+    i32 = torch.int32
     if Y is None:
-        Y = torch.empty((shape.T, d), dtype=dt, device=X.device)
-    rc = lib().mmoe_layer_forward_events(ctypes.byref(shape), _ptr(X, dt, shape.T * d, "X"),
-                                  _ptr(vid, torch.int32, shape.T, "vid"), _ptr(Wr, dt, shape.V * shape.E * d, "Wr"),
-                                  _ptr(br, torch.float32, shape.V * shape.E, "br"),
-                                  _ptr(M, torch.int32, shape.V * shape.E, "M"), _ptr(W1p, dt, S * d * f, "W1p"),
-                                  _ptr(W3p, dt, S * d * f, "W3p"), _ptr(W2p, dt, S * d * f, "W2p"),
-                                  _ptr(Y, dt, shape.T * d, "Y"), _ptr(ws, torch.uint8, None, "ws"), ws.numel(),
-                                  _stream(), events)
+        Y = torch.empty((T, d), dtype=dt, device=X.device)
+    rc = (_lib or lib()).mmoe_layer_forward_events(
+        ctypes.byref(shape), _ptr(X, dt, T * d, "X"), _ptr(vid, i32, T, "vid"), _ptr(Wr, dt, V * E * d, "Wr"),
+        _ptr(br, torch.float32, V * E, "br"), _ptr(M, i32, V * E, "M"), _ptr(W1p, dt, n, "W1p"), _ptr(W3p, dt, n, "W3p"),
+        _ptr(W2p, dt, n, "W2p"), _ptr(Y, dt, T * d, "Y"), _ptr(ws, torch.uint8, None, "ws"), ws.numel(), _stream(), events)
     _check(rc, "mmoe_layer_forward")
     return Y
 
