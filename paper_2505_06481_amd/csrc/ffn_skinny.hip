@@ -132,8 +132,8 @@ static bool past_the_caches(const mmoe_shape& s)
 
 // SPLITK: the four wavefronts split the reduction dimension of one 16-feature block and meet in
 // LDS (long reductions).  !SPLITK: every wavefront owns a 16-feature block of its own and walks the
-// whole reduction dimension (short reductions, where a quarter of K is one or two iterations: all
-// latency, no pipelining): 64 features per workgroup, no LDS reduction.
+// whole reduction dimension (K = 256, of which a quarter is a single run: see whole_k): 64 features per workgroup, no
+// LDS reduction.
 //
 // What bounds it is the memory pipeline of a compute unit.  A 1 KB load instruction takes 18 to 20 of its cycles
 // where four neighbouring lanes read 64 contiguous bytes and 65 where neighbouring lanes are in different rows, as
@@ -141,8 +141,8 @@ static bool past_the_caches(const mmoe_shape& s)
 // lanes to the 256 bytes of a run of 64 k, and pass through LDS of the wavefront's own to get into operand order.
 // One run is in flight per wavefront, twelve wavefronts on a compute unit (eight of the gated product): with two
 // runs in flight the registers (over 168) leave eight, or spill.
-// Measured against reading both operands in operand order (768 x 3072 top-1, 13 slots, layer): 4 tokens 36.3 -> 31.5 us,
-// 24 tokens 66.6 -> 52.6, 128 tokens 79.3 -> 64.5 (246 MB of weights); 1024 x 2048 SwiGLU top-2, 64 tokens 97.3 -> 88.9;
+// Measured against reading both operands in operand order (768 x 3072 top-1, 13 slots, layer): 4 tokens 36.0 -> 25.6 us,
+// 24 tokens 66.9 -> 49.2, 128 tokens 79.2 -> 61.1 (246 MB of weights); 1024 x 2048 SwiGLU top-2, 64 tokens 97.3 -> 88.9;
 // 4096 x 1024 GELU 120.1 -> 118.3.
 constexpr int kRun = 64;              // k per run
 constexpr int kRunRow = kRun * 4;     // bytes of a row per run
@@ -548,9 +548,12 @@ static void launch_skinny_products(const mmoe_shape& s, const void* rows, const 
     (void)mid;
 }
 
-// A product whose reduction dimension gives a wavefront fewer than three iterations when split four
-// ways keeps it whole (K <= 1024 for fp32).
-static bool whole_k(int K) { return K <= 1024; }
+// Split four ways a product has four times the workgroups, so slots with many rows (passes of 32 that one workgroup
+// does one after the other) and the last round leave less of the chip idle.  Whole : split, us: 1024 x 1024, 8 slots, 12
+// tokens 35.0 : 23.7; 768 x 3072, 13 slots, 4 tokens 30.1 : 25.6, 128 tokens 59.6 : 61.1; 16 slots, 47 tokens 52.0 : 40.2; 32
+// slots, 200 tokens 113 : 121; 512 x 512, 110 slots of unequal use, 802 tokens 259 : 103; SwiGLU 512 x 4864, 9 slots 52.0 :
+// 55.6.  K = 256 split is one run per wavefront, all latency: 256 x 4096 45.0 : 48.8, 256 x 1024, 60 slots 51.6 : 59.2.
+static bool whole_k(int K) { return K <= 256; }
 
 template <bool NT>
 static int run_skinny_f32(const mmoe_shape& s, const void* rows, const int32_t* perm, const int32_t* offsets,
