@@ -33,12 +33,12 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # to one version of the kernel's sources (the kernel file and the tile-list builder that decides
 # which tiles it runs); with any other version `traffic` is null.
 TRAFFIC = {
-    "ffn_tiled.hip": {"sources": ("ffn_tiled.hip", "tile_table.h"), "sha256": "43b709161827d2e82d2e9eec64b11a7e185f5a0bacb98c748417206da8ef4ae3",
+    "ffn_tiled.hip": {"sources": ("ffn_tiled.hip", "tile_table.h"), "sha256": "cf63497284a31a41bbbae61a5f4f2fac26af0b201187a424337ddca256406639",
                       "workload": "mixtral_prefill_bf16_v2_t8192",
-                      "fetch_bytes": 11760644462, "write_bytes": 469763470},
-    "ffn_skinny.hip": {"sources": ("ffn_skinny.hip",), "sha256": "6251fdfca2475672fcf8c0de351e5d1c7ea8df1bf17f56ce71ef8f3fdd6a3716",
+                      "fetch_bytes": 11594622537, "write_bytes": 469763296},
+    "ffn_skinny.hip": {"sources": ("ffn_skinny.hip",), "sha256": "6ab2ae25ad8c5c4defb664d6cd63d8e5aec0408c558ece62b8a576408c394f35",
                        "workload": "mixtral_decode_bf16_v2_t64",
-                       "fetch_bytes": 3068027183, "write_bytes": 3670794},
+                       "fetch_bytes": 3057711718, "write_bytes": 3670426},
 }
 
 
