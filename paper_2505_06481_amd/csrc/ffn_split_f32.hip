@@ -12,11 +12,17 @@
 //   tiles of 16 x 16; normal inputs / inputs after a ReLU) of the fp32 instruction in chains of 256 k and of this:
 //   K = 256 2.9e-7 / 2.0e-7 and 1.5e-7 / 1.5e-7; 768 2.9 / 2.1 and 1.6 / 1.6; 3072 3.0 / 2.1 and 1.8 / 1.8; 8192
 //   3.1 / 2.3 and 2.2 / 2.2.  (Chains of 256 k: 2.3 to 2.6, not below the fp32 instruction's after a ReLU.)
-//   Range: bf16 has fp32's exponents.  Parts below 2^-126 are lost, so numbers below 2^-101 count with fewer than 24
-//   bits.  Numbers that are not finite, or round to an infinity in bf16, make the result a NaN: results that are
-//   not finite are computed again on the fp32 instruction in the epilogue, so that they are what fp32 gives.
+//   Range: bf16 has fp32's exponents, but parts and products below 2^-126 may be lost (2-norm error with operands around
+//   2^-110 2.7e-6, around 2^-118 1.4e-3).  So both operands are multiplied by 2^24 before they are split: the last bit of
+//   the smallest fp32 number is then 2^-125, no part of any number is subnormal, and a product that fp32 can hold is
+//   at least 2^-101.  The total is multiplied by 2^-48.  At the other end the scaled numbers overflow: operands above 2^103,
+//   sums above 2^80 and what was not finite before make the scaled total infinite or NaN, and such results are
+//   computed again on the fp32 instruction in the epilogue, so that they are what fp32 gives.
+//   Few terms: where less than some 64 of a sum's terms are not zero, the rounding of the six products shows.
+//   2-norm error, parts against fp32 instruction: 2.6e-8 : 2.5e-8 with one term, 5.2e-8 : 4.3e-8 with four, 9.0e-8 : 8.9e-8
+//   with 64, 9.3e-8 : 13.5e-8 with 256 (of K = 768, simulated).
 //
-// What bounds it: matrix instructions, the splitting of the operands (11 vector instructions for two numbers) and the
+// What bounds it: matrix instructions, the splitting of the operands (13 vector instructions for two numbers) and the
 // loads of the weights in operand order (65 cycles of a compute unit's memory pipeline for each KB, 1040 a step; the
 // step's matrix instructions take 1152).  Reading them along the rows and rearranging them in LDS costs less of the
 // memory pipeline but fills LDS (2000 tokens of 768 x 3072: 172 -> 185 us).  Tile: up to 96 token rows x 128 output
@@ -27,9 +33,9 @@
 //   tokens    global -> registers two steps ahead, split once for the workgroup one step ahead, three bf16 planes -> LDS
 //             (two stages, 16-byte pieces swizzled, f32_piece) -> fragments.  The one barrier of a step stands before
 //             its last fragment, so the next step's first fragment is fetched while matrix instructions run.
-// Measured against the fp32 instruction (ffn_tiled_f32.hip), layer: 768 x 3072 top-1, 13 slots, 2000 tokens 231 -> 172 us,
-// 4096 tokens 432 -> 299; 1024 x 2048 SwiGLU top-2, 13 slots, 1200 tokens 349 -> 220, 3000 tokens 767 -> 460.  Error of
-// those layers against float64: 3.6e-7 -> 2.4e-7 and 5.1e-7 -> 2.8e-7.
+// Measured against the fp32 instruction (ffn_tiled_f32.hip), layer: 768 x 3072 top-1, 13 slots, 2000 tokens 234 -> 176 us,
+// 4096 tokens 437 -> 346; 1024 x 2048 SwiGLU top-2, 13 slots, 1200 tokens 357 -> 232, 3000 tokens 780 -> 489 (of which the
+// multiplication by 2^24 is 2 to 4 %).  Error of those layers against float64: 3.6e-7 -> 2.4e-7 and 5.1e-7 -> 2.8e-7.
 #include <type_traits>
 
 #include "mmoe_internal.h"
@@ -43,6 +49,7 @@ enum { kModeReluH = 0, kModeSwigluH = 1, kModePlainF32 = 2, kModeGeluH = 3, kMod
 constexpr int kFThreads = 256;
 constexpr int kFK = 32;            // k per step
 constexpr int kChain = 128;        // k per chain of matrix instructions
+constexpr int kChainF32 = 64;      // and on the fp32 instruction
 constexpr int kFUnroll = kChain / kFK;
 constexpr int kNB = 2;             // 16-row weight blocks per wavefront
 static_assert(256 % kChain == 0 && kFUnroll % 2 == 0, "K is a multiple of 256; two sets of registers in turn");
@@ -50,12 +57,14 @@ static_assert(256 % kChain == 0 && kFUnroll % 2 == 0, "K is a multiple of 256; t
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 
-// Three bf16 parts of each of four numbers, part 0 the largest: 22 vector instructions.
+constexpr float kUp = 0x1p24f, kBack = 0x1p-48f;  // of an operand, of a result: powers of two, exact
+
+// Three bf16 parts of each of four numbers times kUp, part 0 the largest: 26 vector instructions.
 __device__ __forceinline__ void split4(f32x4 v, u32x2 (&part)[3])
 {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        float x = v[2 * i], y = v[2 * i + 1];
+        float x = v[2 * i] * kUp, y = v[2 * i + 1] * kUp;
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
             const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));  // to nearest even
@@ -234,7 +243,7 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
 #pragma unroll
             for (int i = 0; i < kNB; ++i) tot[j][i] += acc[j][i];
 
-        // Results that are not finite: again in fp32.  (Never taken on finite inputs whose results are finite.)
+        // Scaled results that are not finite: again in fp32.  (Never taken where operands are below 2^103 and sums below 2^80.)
         bool odd = false;
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
@@ -246,24 +255,36 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
                 const float* a = token_row(min(j * 16 + li, cnt - 1)) + 4 * g;
-                f32x4 c[kNB];
+                f32x4 sum[kNB];
 #pragma unroll
-                for (int i = 0; i < kNB; ++i) c[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-                for (int k = 0; k < K; k += 16) {
-                    const f32x4 xv = *reinterpret_cast<const f32x4*>(a + k);
+                for (int i = 0; i < kNB; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int k0 = 0; k0 < K; k0 += kChainF32) {
+                    f32x4 c[kNB];
 #pragma unroll
-                    for (int i = 0; i < kNB; ++i) {
-                        const f32x4 wv = *reinterpret_cast<const f32x4*>(wrow[i] + k);
+                    for (int i = 0; i < kNB; ++i) c[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    for (int k = k0; k < k0 + kChainF32; k += 16) {
+                        const f32x4 xv = *reinterpret_cast<const f32x4*>(a + k);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) c[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], c[i], 0, 0, 0);
+                        for (int i = 0; i < kNB; ++i) {
+                            const f32x4 wv = *reinterpret_cast<const f32x4*>(wrow[i] + k);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) c[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], xv[e], c[i], 0, 0, 0);
+                        }
                     }
+#pragma unroll
+                    for (int i = 0; i < kNB; ++i) sum[i] += c[i];
                 }
 #pragma unroll
                 for (int i = 0; i < kNB; ++i)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (!(fabsf(tot[j][i][e]) < INFINITY)) tot[j][i][e] = c[i][e];
+                        tot[j][i][e] = fabsf(tot[j][i][e]) < INFINITY ? tot[j][i][e] * kBack : sum[i][e];
             }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int i = 0; i < kNB; ++i) tot[j][i] *= kBack;
         }
 
         // accumulator element e of lane (li, g): feature 4 g + e of the block, token row li of the fragment

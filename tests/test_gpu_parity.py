@@ -219,6 +219,24 @@ def test_f32_parts_of_numbers_that_are_not_finite(mm, gc, oracle):
     assert np.isfinite(got[~hit]).all() and not np.isfinite(got[hit]).any()
 
 
+@pytest.mark.parametrize("act,d,f,x_exp,w1_exp,w2_exp", [
+    ("relu", 768, 768, -110, 0, 0), ("gelu", 768, 768, -118, 0, 0), ("relu", 768, 768, 0, -118, 0),
+    ("relu", 768, 768, 0, 0, -118), ("relu", 768, 768, -58, -55, 0), ("relu", 768, 768, 0, -60, -55),
+    ("relu", 768, 768, -118, 110, 0), ("swiglu", 512, 768, -58, -4, 0), ("swiglu", 512, 768, 0, 0, -118),
+    ("relu", 768, 768, 106, -100, 0), ("relu", 768, 768, 60, 40, -90)])
+def test_f32_parts_keep_the_range_of_fp32(mm, gc, oracle, act, d, f, x_exp, w1_exp, w2_exp):
+    """Operands and products of any size that fp32 holds with all its bits, in either operand of either product, keep
+    the accuracy of ordinary ones: the bound is test_f32_products_on_bf16_parts's.  (The last two: operands and sums beyond
+    what the scaled parts hold, on the fp32 instruction, whose relative error does not depend on the scale.)"""
+    shape, offsets, Xg, W1, W3, W2 = _parts_case(mm, oracle, act, d, f, seed=31)
+    Xg, W1, W2 = (a * np.float32(2.0 ** e) for a, e in ((Xg, x_exp), (W1, w1_exp), (W2, w2_exp)))
+    W3 = None if W3 is None else W3 * np.float32(2.0 ** w1_exp)
+    got = _parts_run(mm, shape, offsets, Xg, W1, W3, W2).astype(np.float64)
+    ref = oracle.expert_ffn(Xg, offsets, W1, W3, W2, "f32", act)
+    scale = 1.0 / np.abs(ref).max()
+    assert np.linalg.norm((got - ref) * scale) <= 6e-7 * np.linalg.norm(ref * scale)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_streaming_grid_by_pair(mm, gc, oracle, dtype):
     """Batches of fewer pairs than slots (a row of workgroups per pair), as many and one more, with slots picked by
