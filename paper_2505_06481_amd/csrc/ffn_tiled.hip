@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kListThreads) void tile_table_kernel(const int32_t*
 }
 
 // LONE: a tile that holds all rows of its slot is the only reader of its weight panels and reads them past the caches,
-// which streams faster (4096 x 14336, 18 slots, 777 tokens 1227 -> 1200 us; 4096 x 2048, 64 slots, 4800 pairs 737 -> 717;
+// which streams faster where the pool is large (lone_tiles; 4096 x 14336, 18 slots, 777 tokens 1227 -> 1200 us; 4096 x 2048, 64 slots, 4800 pairs 737 -> 717;
 // 2560 x 2560 GELU, 20 slots, 2000 pairs 179 -> 171).  A panel with several readers has to stay in L2 (8192 tokens 4486 ->
 // 5087 us with every panel past the caches).
 template <int MODE, int BM, int NB, bool LONE>
@@ -538,12 +538,23 @@ int planned_tile_rows(const mmoe_shape& s)
 // copies in flight, before short tiles had several.)
 static int planned_upt(const mmoe_shape&, int bm) { return bm / 32; }
 
+// Are panels read past the caches where a 256-row tile is the only one of its slot?  Where slots of one tile are likely, and
+// the pool is larger than the last-level cache: a smaller one may still be there from an earlier call, and the few
+// tiles of a small layer wait longer for each load.  Through the caches : past them, us, one pool again and again / three in
+// turn: 2304 x 768 SwiGLU, 6 slots (64 MB), 180 rows per slot 72.2 : 82.9 / 72.3 : 83.2; 4096 x 512, 5 slots (42 MB) 80.9 :
+// 95.4 / 80.0 : 95.4; 4096 x 1024 SwiGLU, 8 slots (201 MB), 110 rows 88.3 : 109.0 / 111.6 : 109.1; 2560 x 2560, 20 slots (524 MB)
+// 182.7 : 172.3 / 183.2 : 174.1; 4096 x 2048 SwiGLU, 13 slots (654 MB) 178.9 : 161.1 / 180.0 : 166.2.  (At 244 and 306 rows
+// per slot on average both are within 1 %.)
+bool lone_tiles(const mmoe_shape& s)
+{
+    return (int64_t)s.T * s.top_k <= (int64_t)kBMBig * s.S && s.S * slot_bytes(s) > kLastLevelCache;
+}
+
 static TiledPlan tiled_plan(const mmoe_shape& s)
 {
     TiledPlan p;
     p.bm = planned_tile_rows(s);
-    // slots of one 256-row tile are likely (at 244 and 306 rows per slot on average both are within 1 %)
-    p.lone = (int64_t)s.T * s.top_k <= (int64_t)kBMBig * s.S;
+    p.lone = lone_tiles(s);
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm), planned_upt(s, p.bm), p.bm,
                      s.dtype == MMOE_F32);

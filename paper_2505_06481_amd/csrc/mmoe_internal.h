@@ -37,6 +37,12 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float x)
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 inline size_t elem_size(int dtype) { return dtype == MMOE_BF16 ? 2 : 4; }
 
+constexpr int64_t kLastLevelCache = (int64_t)256 << 20;  // bytes
+inline int64_t slot_bytes(const mmoe_shape& s)
+{
+    return (int64_t)s.d_model * s.d_ff * (int64_t)elem_size(s.dtype) * (s.act == MMOE_SWIGLU ? 3 : 2);
+}
+
 // Which slots one launch of the expert stage works on: all of them (`flag` null), or those whose
 // flag equals `want` (a launch for the resident slots, a later one for the slots just fetched).
 struct SlotFilter {

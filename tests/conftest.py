@@ -1,3 +1,4 @@
+import ctypes
 import os
 import sys
 
@@ -18,3 +19,17 @@ def oracle():
 
     orc.build()
     return orc
+
+
+@pytest.fixture(scope="session")
+def dispatch_rule():
+    """bool mmoe::name(const mmoe_shape&[, int, bool]): a rule of the library's dispatch, by its C++ symbol."""
+    from paper_2505_06481_amd import mmoe
+
+    def rule(name, shape, *args):
+        f = getattr(mmoe.lib(), f"_ZN4mmoe{len(name)}{name}ERK10mmoe_shape" + "ib"[:len(args)])
+        f.restype = ctypes.c_bool
+        f.argtypes = [ctypes.c_void_p] + [ctypes.c_int, ctypes.c_bool][:len(args)]
+        return f(ctypes.addressof(shape), *args)
+
+    return rule

@@ -276,3 +276,14 @@ def test_static_entry_point_size_limit(mm, d, f, S, E, k, dtype, act, largest):
         assert not static_refuses(mm, shape(T)), T
     for T in range(largest + 1, largest + 300):
         assert static_refuses(mm, shape(T)), T
+
+
+def test_one_tile_slots_leave_the_caches_only_with_large_pools(mm, dispatch_rule):
+    """A pool that the last-level cache (256 MB) holds is read through it, whatever the rows per slot."""
+    for T, d, f, S, act, want in ((540, 2304, 768, 6, "swiglu", False), (450, 4096, 512, 5, "relu", False),
+                                  (440, 4096, 1024, 8, "swiglu", False), (1100, 2560, 2560, 20, "gelu", True),
+                                  (715, 4096, 2048, 13, "swiglu", True), (777, 4096, 14336, 18, "swiglu", True),
+                                  (8192, 4096, 14336, 13, "swiglu", False)):
+        shape = mm.make_shape(T, d, f, 4, 8, S, 2, "bf16", act)
+        assert mm.expert_plan(shape) == (False, 256)
+        assert dispatch_rule("lone_tiles", shape) is want, (d, f, S)
