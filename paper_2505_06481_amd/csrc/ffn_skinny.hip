@@ -109,9 +109,11 @@ __device__ __forceinline__ RowSet slot_rows(const int32_t* __restrict__ offsets,
     return rs;
 }
 
-// Weights are read once per pass.  NT: past the caches, at 6.5 to 6.9 TB/s instead of 5.9 (4096 x 14336, 13 slots: 64 tokens
-// 768 -> 698 us, one token 135 -> 121; 2048 x 1280, 90 slots, 60 tokens 200 -> 179; fp32 768 x 3072, 13 slots, 128 tokens
-// 62.7 -> 59.1).
+// NT: the weights of a slot with one pass are read past the caches, at 6.5 to 6.9 TB/s instead of 5.9 (4096 x 14336, 13
+// slots: 64 tokens 768 -> 698 us, one token 135 -> 121; 2048 x 1280, 90 slots, 60 tokens 200 -> 179; fp32 768 x 3072, 13 slots,
+// 128 tokens 62.7 -> 59.1).  A slot with more rows than a pass takes has its weights read again by every pass, from L2 if
+// they came through it (unequal slots: 2048 x 2048 SwiGLU, 13 slots, 200 tokens 109.4 us past the caches in every pass, 92.5
+// with several passes through them; 4096 x 14336, 100 tokens 865 : 798; fp32 768 x 3072, 150 tokens 117 : 100).
 template <bool NT, typename T>
 __device__ __forceinline__ T load_weights(const T* p)
 {
@@ -123,7 +125,7 @@ __device__ __forceinline__ T load_weights(const T* p)
 // 21.4 : 23.8 with 10, 27.9 : 31.2 with 16, 36.8 : 34.9 with 40.  (P S / (P + S) is a little below the number of
 // slots that P picks touch.)
 constexpr int64_t kCachedBytes = (int64_t)96 << 20;
-static bool past_the_caches(const mmoe_shape& s)
+bool past_the_caches(const mmoe_shape& s)
 {
     const int64_t P = (int64_t)s.T * s.top_k;
     const int64_t slot_bytes = (int64_t)s.d_model * s.d_ff * (int64_t)elem_size(s.dtype) * (s.act == MMOE_SWIGLU ? 3 : 2);
@@ -195,14 +197,14 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
     }
 
     f32x4 wraw[NW][kRunLoads];  // a run's weights as loaded
-    auto load_w = [&](int run) {
+    auto load_w = [&](int run, auto ntc) {
 #pragma unroll
         for (int w = 0; w < NW; ++w)
 #pragma unroll
-            for (int i = 0; i < kRunLoads; ++i) wraw[w][i] = load_weights<NT>(reinterpret_cast<const f32x4*>(wrow[w][i] + (size_t)run * kRun));
+            for (int i = 0; i < kRunLoads; ++i) wraw[w][i] = load_weights<decltype(ntc)::value>(reinterpret_cast<const f32x4*>(wrow[w][i] + (size_t)run * kRun));
     };
 
-    auto pass = [&](int pass0, auto mbc) {
+    auto pass = [&](int pass0, auto mbc, auto ntc) {
         constexpr int MB = decltype(mbc)::value;  // 16-row blocks of this pass that hold rows
         const float* arow[MB][kRunLoads];
 #pragma unroll
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
             fence();
             if (next >= 0) {
                 load_t(next);
-                load_w(next);
+                load_w(next, ntc);
             }
 #pragma unroll
             for (int q = 0; q < kRunLoads; ++q) {
@@ -272,7 +274,7 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
         };
         int run = first, chain = 0;  // a wavefront has at least one run: K >= 256
         load_t(run);
-        load_w(run);
+        load_w(run, ntc);
         for (; run + kStride < nrun; run += kStride) {
             step(run + kStride);
             if (++chain % kChainRuns == 0) end_chain();  // uniform
@@ -337,10 +339,14 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
         }
         __syncthreads();
     };
-    for (int pass0 = 0; pass0 < cnt; pass0 += 16 * kSkMB) {  // uniform over the workgroup
-        if (cnt - pass0 > 16) pass(pass0, std::integral_constant<int, 2>{});
-        else pass(pass0, std::integral_constant<int, 1>{});
-    }
+    auto passes = [&](auto ntc) {
+        for (int pass0 = 0; pass0 < cnt; pass0 += 16 * kSkMB) {  // uniform over the workgroup
+            if (cnt - pass0 > 16) pass(pass0, std::integral_constant<int, 2>{}, ntc);
+            else pass(pass0, std::integral_constant<int, 1>{}, ntc);
+        }
+    };
+    if (NT && cnt <= 16 * kSkMB) passes(std::true_type{});  // uniform
+    else passes(std::false_type{});
 }
 
 // ---- bf16 on the fragment-packed pool ----------------------------------------------------
@@ -384,17 +390,17 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
     if (NW == 2) wrow[NW - 1] = W1 + blk;
 
     u32x4 wcur[NW][KU][4], wnxt[NW][KU][4];
-    auto load_w = [&](u32x4 (&to)[NW][KU][4], int it) {
+    auto load_w = [&](u32x4 (&to)[NW][KU][4], int it, auto ntc) {
 #pragma unroll
         for (int w = 0; w < NW; ++w)
 #pragma unroll
             for (int u = 0; u < KU; ++u)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    to[w][u][q] = load_weights<NT>(reinterpret_cast<const u32x4*>(wrow[w] + ((size_t)(it * KU + u) * 4 + q) * 512));
+                    to[w][u][q] = load_weights<decltype(ntc)::value>(reinterpret_cast<const u32x4*>(wrow[w] + ((size_t)(it * KU + u) * 4 + q) * 512));
     };
 
-    for (int pass0 = 0; pass0 < cnt; pass0 += 32) {
+    auto pass = [&](int pass0, auto ntc) {
         const int rr = min(pass0 + tok, cnt - 1);  // tokens past the end re-read the last one; never stored
         const uint16_t* arow = A + (size_t)rs.in_row(rr) * K + h * 32;
         f32x16 acc[NW];
@@ -404,7 +410,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
             for (int e = 0; e < 16; ++e) acc[w][e] = 0.0f;
 
         int it = wave;
-        if (it < nit) load_w(wcur, it);
+        if (it < nit) load_w(wcur, it, ntc);
         for (; it < nit; it += kSkWaves) {
             u32x4 xa[KU][4];
 #pragma unroll
@@ -413,7 +419,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
                 for (int q = 0; q < 4; ++q)
                     xa[u][q] = *reinterpret_cast<const u32x4*>(arow + (size_t)(it * KU + u) * 64 + q * 8);
             const int itn = it + kSkWaves;
-            if (itn < nit) load_w(wnxt, itn);  // the next weights: the youngest loads, still in flight during the math below
+            if (itn < nit) load_w(wnxt, itn, ntc);  // the next weights: the youngest loads, still in flight during the math below
 #pragma unroll
             for (int u = 0; u < KU; ++u)
 #pragma unroll
@@ -474,6 +480,11 @@ __global__ __launch_bounds__(kSkThreads) void skinny_frag_kernel(const uint16_t*
             }
         }
         __syncthreads();
+    };
+    if (NT && cnt <= 32) {  // uniform
+        pass(0, std::true_type{});
+    } else {
+        for (int pass0 = 0; pass0 < cnt; pass0 += 32) pass(pass0, std::false_type{});  // uniform over the workgroup
     }
 }
 

@@ -237,6 +237,16 @@ def test_f32_parts_keep_the_range_of_fp32(mm, gc, oracle, act, d, f, x_exp, w1_e
     assert np.linalg.norm((got - ref) * scale) <= 6e-7 * np.linalg.norm(ref * scale)
 
 
+@pytest.mark.parametrize("dtype,act,k,T,d,f", [("bf16", "relu", 1, 100, 2048, 2048), ("bf16", "swiglu", 2, 60, 2048, 1536),
+                                               ("f32", "gelu", 1, 95, 1024, 2304), ("f32", "swiglu", 2, 47, 1536, 1024)])
+def test_streaming_slots_of_several_passes_in_large_pools(mm, gc, oracle, dispatch_rule, dtype, act, k, T, d, f):
+    """Where weights are read past the caches, beside slots of one pass: slots of two passes and more, read through them."""
+    cfg = synth.Config(f"passes_{dtype}_{act}", T, d, f, 1, 8, k, dtype, act, seed=90, bias_alpha=2.0)
+    case, ref = staged_vs_oracle(mm, gc, oracle, cfg)
+    assert mm.expert_plan(case.shape) == (True, 32) and dispatch_rule("past_the_caches", case.shape)
+    assert ref["counts"].max() > 32 and (ref["counts"] > 0).sum() > (ref["counts"] > 32).sum()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_streaming_grid_by_pair(mm, gc, oracle, dtype):
     """Batches of fewer pairs than slots (a row of workgroups per pair), as many and one more, with slots picked by
