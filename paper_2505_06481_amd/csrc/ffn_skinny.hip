@@ -122,14 +122,14 @@ __device__ __forceinline__ T load_weights(const T* p)
 
 // Unless the batch is expected to touch so little of the pool that the 256 MB last-level cache may still hold it from an
 // earlier step: 768 x 3072, 16 slots of 9.4 MB, three pools in turn, cached : past the caches, us: 18.1 : 20.0 with 5 tokens,
-// 21.4 : 23.8 with 10, 27.9 : 31.2 with 16, 36.8 : 34.9 with 40.  (P S / (P + S) is a little below the number of
-// slots that P picks touch.)
+// 21.4 : 23.8 with 10, 27.9 : 31.2 with 16, 36.8 : 34.9 with 40; slots of 101 MB, 8 of them, one pick 35.6 : 34.9, two picks
+// 48.4 : 42.9; of 235 MB, 9 of them, one pick 59.6 : 52.5.  (P S / (P + S), fractions and all, is a little below the number
+// of slots that P picks touch.)
 constexpr int64_t kCachedBytes = (int64_t)96 << 20;
 bool past_the_caches(const mmoe_shape& s)
 {
-    const int64_t P = (int64_t)s.T * s.top_k;
-    const int64_t slot_bytes = (int64_t)s.d_model * s.d_ff * (int64_t)elem_size(s.dtype) * (s.act == MMOE_SWIGLU ? 3 : 2);
-    return P * s.S / (P + s.S) * slot_bytes > kCachedBytes;
+    const double P = (double)s.T * s.top_k;
+    return P * s.S / (P + s.S) * (double)slot_bytes(s) > (double)kCachedBytes;
 }
 
 // SPLITK: the four wavefronts split the reduction dimension of one 16-feature block and meet in

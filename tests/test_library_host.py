@@ -278,6 +278,16 @@ def test_static_entry_point_size_limit(mm, d, f, S, E, k, dtype, act, largest):
         assert static_refuses(mm, shape(T)), T
 
 
+def test_few_picks_of_large_experts_leave_the_caches(mm, dispatch_rule):
+    """One pick touches one slot of S, or nearly: an expert of hundreds of MB streams past the caches for it."""
+    for T, k, d, f, S, act, dtype, want in ((1, 1, 4096, 14336, 8, "relu", "bf16", True), (1, 1, 4096, 14336, 9, "swiglu", "bf16", True),
+                                            (1, 1, 4096, 4096, 8, "swiglu", "bf16", False), (2, 1, 4096, 4096, 8, "swiglu", "bf16", True),
+                                            (1, 2, 4096, 4096, 13, "swiglu", "bf16", True), (1, 1, 4096, 8192, 9, "relu", "f32", True),
+                                            (3, 1, 768, 3072, 16, "gelu", "bf16", False), (40, 1, 768, 3072, 16, "gelu", "bf16", True)):
+        shape = mm.make_shape(T, d, f, 2, 8, S, k, dtype, act)
+        assert dispatch_rule("past_the_caches", shape) is want, (T, k, d, f, S)
+
+
 def test_one_tile_slots_leave_the_caches_only_with_large_pools(mm, dispatch_rule):
     """A pool that the last-level cache (256 MB) holds is read through it, whatever the rows per slot."""
     for T, d, f, S, act, want in ((540, 2304, 768, 6, "swiglu", False), (450, 4096, 512, 5, "relu", False),
