@@ -132,8 +132,10 @@ bool past_the_caches(const mmoe_shape& s)
     return P * s.S / (P + s.S) * (double)slot_bytes(s) > (double)kCachedBytes;
 }
 
-// SPLITK: the four wavefronts split the reduction dimension of one 16-feature block and meet in
-// LDS (long reductions).  !SPLITK: every wavefront owns a 16-feature block of its own and walks the
+constexpr int skinny_threads(int split) { return split == 8 ? 8 * kWave : kSkThreads; }
+
+// SPLIT 4, 8: so many wavefronts split the reduction dimension of one 16-feature block and meet in
+// LDS (long reductions).  1: every wavefront of four owns a 16-feature block of its own and walks the
 // whole reduction dimension (K = 256, of which a quarter is a single run: see whole_k): 64 features per workgroup, no
 // LDS reduction.
 //
@@ -152,8 +154,8 @@ constexpr int kRunBlock = 16 * kRunRow;  // bytes of 16 rows
 constexpr int kRunLoads = 4;          // load instructions per 16 rows; pieces of an operand per run
 constexpr int kChainRuns = 4;         // runs per chain of matrix instructions: rounding errors do not build up over all of K
 
-template <int NW, int MODE, bool SPLITK, bool NT>
-__global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(const float* __restrict__ A,
+template <int NW, int MODE, int SPLIT, bool NT>
+__global__ __launch_bounds__(skinny_threads(SPLIT), SPLIT == 8 ? 1 : NW == 1 ? 3 : 2) void skinny_kernel(const float* __restrict__ A,
                                                             const int32_t* __restrict__ perm, int kdiv,
                                                             const int32_t* __restrict__ offsets,
                                                             const int32_t* __restrict__ slot_of_pair, int P, int by_pair,
@@ -162,8 +164,9 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
                                                             const int32_t* __restrict__ sink_perm,
                                                             const float* __restrict__ sink_w)
 {
-    __shared__ __attribute__((aligned(256))) char rows[kSkWaves][(NW + kSkMB) * kRunBlock];  // of a run: weights, tokens
-    static_assert(sizeof(rows) >= sizeof(float) * kSkWaves * kSkMB * NW * kWave * 4, "one array for the partial sums too");
+    constexpr int kWaves = skinny_threads(SPLIT) / kWave;
+    __shared__ __attribute__((aligned(256))) char rows[kWaves][(NW + kSkMB) * kRunBlock];  // of a run: weights, tokens
+    static_assert(sizeof(rows) >= sizeof(float) * kWaves * kSkMB * NW * kWave * 4, "one array for the partial sums too");
     float(*red)[kSkMB][NW][kWave][4] = reinterpret_cast<float(*)[kSkMB][NW][kWave][4]>(&rows[0][0]);
     __shared__ int mine[kSelfMaxP];
 
@@ -174,10 +177,10 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int n0 = SPLITK ? blockIdx.x * 16 : (blockIdx.x * kSkWaves + wave) * 16;
+    const int n0 = SPLIT > 1 ? blockIdx.x * 16 : (blockIdx.x * kWaves + wave) * 16;
     const int li = lane & 15, g = lane >> 4;
-    constexpr int kStride = SPLITK ? kSkWaves : 1;  // runs between two of one wavefront
-    const int first = SPLITK ? wave : 0;
+    constexpr int kStride = SPLIT;  // runs between two of one wavefront
+    const int first = SPLIT > 1 ? wave : 0;
     const int nrun = K / kRun;
 
     // Load i of a 16-row block: row 4 i + g, 16 bytes (li) of its 256.  In LDS piece q of row r stands at q ^ r: the
@@ -272,7 +275,7 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
                     acc[mb][w] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
         };
-        int run = first, chain = 0;  // a wavefront has at least one run: K >= 256
+        int run = first, chain = 0;  // a wavefront has at least one run: K >= 256, or 512 with eight of them
         load_t(run);
         load_w(run, ntc);
         for (; run + kStride < nrun; run += kStride) {
@@ -301,7 +304,7 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
             }
             *reinterpret_cast<f32x4*>(out + (size_t)orow * N + n0 + 4 * (l >> 4)) = f32x4{o[0], o[1], o[2], o[3]};
         };
-        if (!SPLITK) {  // every wavefront finishes its own 16 features straight from its accumulators
+        if (SPLIT == 1) {  // every wavefront finishes its own 16 features straight from its accumulators
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
                 const int row = pass0 + mb * 16 + (lane & 15);
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
 #pragma unroll
                 for (int i = 0; i < 4; ++i) red[wave][mb][w][lane][i] = tot[mb][w][i];
         __syncthreads();
-        for (int idx = threadIdx.x; idx < MB * kWave; idx += kSkThreads) {
+        for (int idx = threadIdx.x; idx < MB * kWave; idx += skinny_threads(SPLIT)) {
             const int mb = idx / kWave, l = idx % kWave;
             const int row = pass0 + mb * 16 + (l & 15);
             if (row < cnt) {
@@ -333,7 +336,11 @@ __global__ __launch_bounds__(kSkThreads, NW == 1 ? 3 : 2) void skinny_kernel(con
                 for (int w = 0; w < NW; ++w)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
+                    {
                         v[w][i] = (red[0][mb][w][l][i] + red[1][mb][w][l][i]) + (red[2][mb][w][l][i] + red[3][mb][w][l][i]);
+                        if constexpr (SPLIT == 8)
+                            v[w][i] += (red[4][mb][w][l][i] + red[5][mb][w][l][i]) + (red[6][mb][w][l][i] + red[7][mb][w][l][i]);
+                    }
                 finish(row, l, v);
             }
         }
@@ -534,7 +541,7 @@ static int run_skinny_bf16(const mmoe_shape& s, const void* rows, const int32_t*
     return launch_status();
 }
 
-template <bool SPLITK, bool NT>
+template <int SPLIT, bool NT>
 static void launch_skinny_products(const mmoe_shape& s, const void* rows, const int32_t* perm, const int32_t* offsets,
                                    const int32_t* slot_of_pair, const void* W1p, const void* W3p, const void* W2p,
                                    void* H, float* Yg, hipStream_t st, hipEvent_t mid, SlotFilter filt, bool up,
@@ -544,29 +551,29 @@ static void launch_skinny_products(const mmoe_shape& s, const void* rows, const 
     const float* now = nullptr;
     const int32_t* noperm = nullptr;
     const int d = s.d_model, f = s.d_ff, P = s.T * s.top_k;
-    constexpr int kFeat = SPLITK ? 16 : 16 * kSkWaves;  // output features per workgroup
-    dim3 block(kSkThreads);
+    constexpr int kFeat = SPLIT > 1 ? 16 : 16 * kSkWaves;  // output features per workgroup
+    dim3 block(skinny_threads(SPLIT));
     const int by_pair = slot_of_pair && P < s.S;  // a workgroup row per pair, not per slot
     const int ny = by_pair ? P : s.S;
     dim3 g1(f / kFeat, ny), g2(d / kFeat, ny);
     const float* nul = nullptr;
     if (up) {
         if (s.act == MMOE_SWIGLU)
-            hipLaunchKernelGGL((skinny_kernel<2, kModeSwigluH, SPLITK, NT>), g1, block, 0, st, (const float*)rows, perm,
+            hipLaunchKernelGGL((skinny_kernel<2, kModeSwigluH, SPLIT, NT>), g1, block, 0, st, (const float*)rows, perm,
                                s.top_k, offsets, slot_of_pair, P, by_pair, (const float*)W1p, (const float*)W3p, (float*)H, d, f, filt,
                                nosink, now);
         else if (s.act == MMOE_GELU)
-            hipLaunchKernelGGL((skinny_kernel<1, kModeGeluH, SPLITK, NT>), g1, block, 0, st, (const float*)rows, perm,
+            hipLaunchKernelGGL((skinny_kernel<1, kModeGeluH, SPLIT, NT>), g1, block, 0, st, (const float*)rows, perm,
                                s.top_k, offsets, slot_of_pair, P, by_pair, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
         else
-            hipLaunchKernelGGL((skinny_kernel<1, kModeReluH, SPLITK, NT>), g1, block, 0, st, (const float*)rows, perm,
+            hipLaunchKernelGGL((skinny_kernel<1, kModeReluH, SPLIT, NT>), g1, block, 0, st, (const float*)rows, perm,
                                s.top_k, offsets, slot_of_pair, P, by_pair, (const float*)W1p, nul, (float*)H, d, f, filt, nosink, now);
     }
     if (down && sink.w)
-        hipLaunchKernelGGL((skinny_kernel<1, kModeGatedY, SPLITK, NT>), g2, block, 0, st, (const float*)H, noperm, 1,
+        hipLaunchKernelGGL((skinny_kernel<1, kModeGatedY, SPLIT, NT>), g2, block, 0, st, (const float*)H, noperm, 1,
                            offsets, slot_of_pair, P, by_pair, (const float*)W2p, nul, (float*)sink.Y, f, d, filt, sink.perm, sink.w);
     else if (down)
-        hipLaunchKernelGGL((skinny_kernel<1, kModePlainF32, SPLITK, NT>), g2, block, 0, st, (const float*)H, noperm, 1,
+        hipLaunchKernelGGL((skinny_kernel<1, kModePlainF32, SPLIT, NT>), g2, block, 0, st, (const float*)H, noperm, 1,
                            offsets, slot_of_pair, P, by_pair, (const float*)W2p, nul, Yg, f, d, filt, nosink, now);
     (void)mid;
 }
@@ -578,24 +585,29 @@ static void launch_skinny_products(const mmoe_shape& s, const void* rows, const 
 // 55.6.  K = 256 split is one run per wavefront, all latency: 256 x 4096 45.0 : 48.8, 256 x 1024, 60 slots 51.6 : 59.2.
 static bool whole_k(int K) { return K <= 256; }
 
+// With at most one workgroup for each of the 256 compute units, eight wavefronts instead of four: each has one run of 4 KB
+// of weights in flight, and four of them do not cover the latency of memory.  Four : eight, us, workgroups of up, down: one
+// token, top-1, 4096 x 14336 (896, 256) 123 : 98; 4096 x 4096 (256, 256) 48.2 : 42.3; 256 x 4096 (up whole, 16) 24.9 : 19.9; 768 x
+// 3072 (192, 48) 22.3 : 17.3.  With more of them a compute unit has its wavefronts anyway: top-2, 4096 x 4096 (512, 512)
+// 69.4 : 76.9; two tokens 2048 x 8192 (2048, 512) 99.5 : 111.1; 4 tokens 768 x 3072 (1536, 384) 41.7 : 48.1.
+bool eight_waves(const mmoe_shape& s, int N)
+{
+    const int64_t P = (int64_t)s.T * s.top_k;
+    return (P < s.S ? P : s.S) * (N / 16) <= 256;
+}
+
 template <bool NT>
 static int run_skinny_f32(const mmoe_shape& s, const void* rows, const int32_t* perm, const int32_t* offsets,
                       const int32_t* slot_of_pair, const void* W1p, const void* W3p, const void* W2p, void* H, float* Yg,
                       hipStream_t st, hipEvent_t mid, SlotFilter filt, GateSink sink)
 {
-    if (whole_k(s.d_model))
-        launch_skinny_products<false, NT>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, true,
-                                         false, sink);
-    else
-        launch_skinny_products<true, NT>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, true,
-                                        false, sink);
+    const auto product = [&](int K, int N, bool up) {
+        const auto go = whole_k(K) ? launch_skinny_products<1, NT> : eight_waves(s, N) ? launch_skinny_products<8, NT> : launch_skinny_products<4, NT>;
+        go(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, up, !up, sink);
+    };
+    product(s.d_model, s.d_ff, true);
     if (mid && hipEventRecord(mid, st) != hipSuccess) return MMOE_ERR_LAUNCH;
-    if (whole_k(s.d_ff))
-        launch_skinny_products<false, NT>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, false,
-                                         true, sink);
-    else
-        launch_skinny_products<true, NT>(s, rows, perm, offsets, slot_of_pair, W1p, W3p, W2p, H, Yg, st, mid, filt, false,
-                                        true, sink);
+    product(s.d_ff, s.d_model, false);
     return launch_status();
 }
 

@@ -247,6 +247,19 @@ def test_streaming_slots_of_several_passes_in_large_pools(mm, gc, oracle, dispat
     assert ref["counts"].max() > 32 and (ref["counts"] > 0).sum() > (ref["counts"] > 32).sum()
 
 
+@pytest.mark.parametrize("act,k", [("relu", 1), ("swiglu", 2)])
+def test_f32_streaming_split_over_eight_wavefronts(mm, gc, oracle, act, k):
+    """Reductions of one run, of an uneven number of runs and of several chains per wavefront, grids at both sides of
+    the line (256 workgroups), slots of one 16-row block and of two."""
+    for T, V, E, d, f, alpha in ((1, 2, 8, 512, 256, 0.0), (3, 2, 8, 768, 512, 0.0), (1, 2, 8, 1280, 4096, 0.0), (1, 2, 8, 512, 4352, 0.0),
+                                 (20, 1, 4, 768, 1024, 0.0), (45, 1, 4, 2304, 512, 2.5), (24, 1, 2, 512, 768, 0.0)):
+        cfg = synth.Config(f"eight_{act}_{T}_{d}", T // k or 1, d, f, V, E, k, "f32", act, seed=1300 + T + d, bias_alpha=alpha)
+        case, ref = staged_vs_oracle(mm, gc, oracle, cfg)
+        assert mm.expert_plan(case.shape) == (True, 32)
+        if alpha:
+            assert ref["counts"].max() > 16
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_streaming_grid_by_pair(mm, gc, oracle, dtype):
     """Batches of fewer pairs than slots (a row of workgroups per pair), as many and one more, with slots picked by
