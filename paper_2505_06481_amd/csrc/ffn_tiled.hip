@@ -494,7 +494,7 @@ static int planned_nb(const mmoe_shape& s, int bm, int N, bool gated)
 // 53 : 57 : 53 at 250, 119 : 87 : 86 at 1000; SwiGLU 1024 x 2048 123 : 118 : 119 at 46, 131 : 121 : 121 at 65; 2048 x 4096
 // 218 : 205 : 191 at 43.
 constexpr int kPartsRows = 40, kPartsTiles = 150;
-static bool f32_in_parts(const mmoe_shape& s, int N, bool gated)
+bool f32_in_parts(const mmoe_shape& s, int N, bool gated)
 {
     const int64_t P = (int64_t)s.T * s.top_k;
     if (P < (int64_t)kPartsRows * s.S) return false;

@@ -92,6 +92,8 @@ CASES = [
     # fp32 matrix-core tiles: one table of tiles, rewritten for the second pass
     (synth.Config("p_tiled_f32_k1", 300, 256, 512, 2, 4, 1, "f32", "gelu", seed=67), every_other),
     (synth.Config("p_tiled_f32_k2", 260, 512, 768, 2, 4, 2, "f32", "swiglu", seed=68), none_resident),
+    # the same on bf16 parts
+    (synth.Config("p_tiled_f32_parts", 900, 768, 1024, 2, 8, 1, "f32", "gelu", seed=69, share_prob=0.0), every_other),
     (synth.Config("p_all_resident", 64, 256, 256, 2, 4, 2, "bf16", "swiglu", seed=65), all_resident),
     # a pool with slots that no token touches: those are never fetched
     (synth.Config("p_untouched", 6, 256, 256, 4, 8, 1, "bf16", "relu", seed=66), none_resident),
@@ -99,12 +101,13 @@ CASES = [
 
 
 @pytest.mark.parametrize("cfg,resident_of", CASES, ids=lambda c: getattr(c, "name", None))
-def test_paged_layer(mm, oracle, cfg, resident_of):
+def test_paged_layer(mm, oracle, dispatch_rule, cfg, resident_of):
     import gpu_common as gc
     if "_tiled_" in cfg.name or "_stream_" in cfg.name:
         S = int(synth.make_inputs(cfg, weights=False)["S"])
         shape = mm.make_shape(cfg.T, cfg.d_model, cfg.d_ff, cfg.V, cfg.E, S, cfg.top_k, cfg.dtype, cfg.act)
         assert mm.expert_plan(shape)[0] == ("_stream_" in cfg.name)
+        assert dispatch_rule("f32_in_parts", shape, cfg.d_model, False) == ("parts" in cfg.name)
     n = paged_case(mm, gc, oracle, cfg, resident_of)
     if resident_of is all_resident:
         assert n == 0

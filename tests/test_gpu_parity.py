@@ -158,8 +158,8 @@ def test_tiled_f32_row_remainders(mm, gc, oracle, act, k, d, f):
 
 
 def _parts_case(mm, oracle, act, d, f, seed):
-    """A grouped batch in fp32 whose slots hold every number of rows at which a tile's fragments change; both
-    products of 768 outputs and the gated one run on bf16 parts, those of 256 and 512 on the fp32 instruction."""
+    """A grouped batch in fp32 whose slots hold every number of rows at which a tile's fragments change; products of 512
+    outputs and more and the gated one run on bf16 parts, those of 256 on the fp32 instruction."""
     counts = [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 79, 80, 81, 95, 96, 97, 0, 129, 191, 193, 289]
     rng = np.random.default_rng(seed)
     S, P = len(counts), sum(counts)
@@ -183,11 +183,13 @@ def _parts_run(mm, shape, offsets, Xg, W1, W3, W2):
 
 @pytest.mark.parametrize("act,d,f", [("relu", 256, 768), ("gelu", 768, 256), ("swiglu", 512, 768), ("swiglu", 768, 1024),
                                      ("relu", 768, 2560)])
-def test_f32_products_on_bf16_parts(mm, gc, oracle, act, d, f):
+def test_f32_products_on_bf16_parts(mm, gc, oracle, dispatch_rule, act, d, f):
     """Rows at the edges of the tiles, one and several chains of the reduction, either product on either kernel.
     The tolerance on the 2-norm is what the fp32 instruction gives (measured: 2.2e-7 to 2.9e-7 here, 3.5e-7 to 5.2e-7
     there), so that parts of too few bits, or a missing one (2^-16), do not pass."""
     shape, offsets, Xg, W1, W3, W2 = _parts_case(mm, oracle, act, d, f, seed=d + f)
+    assert dispatch_rule("f32_in_parts", shape, f, act == "swiglu") == (f > 256 or act == "swiglu")
+    assert dispatch_rule("f32_in_parts", shape, d, False) == (d > 256)
     got = _parts_run(mm, shape, offsets, Xg, W1, W3, W2).astype(np.float64)
     ref = oracle.expert_ffn(Xg, offsets, W1, W3, W2, "f32", act)
     gc.assert_close(got, ref, "f32", "Yg")
@@ -217,6 +219,58 @@ def test_f32_parts_of_numbers_that_are_not_finite(mm, gc, oracle):
     hit = np.zeros(got.shape, bool)
     hit[offsets[5]:offsets[6], 100] = True
     assert np.isfinite(got[~hit]).all() and not np.isfinite(got[hit]).any()
+
+
+PARTS_LAYERS = [
+    # one pick per token (the down product on parts writes the layer's rows), either gate; several picks; token rows read
+    # through the permutation by every up product
+    synth.Config("parts_k1_relu", 900, 768, 1024, 2, 8, 1, "f32", "relu", seed=95, share_prob=0.0),
+    synth.Config("parts_k1_gelu_all", 1001, 1024, 768, 2, 8, 1, "f32", "gelu", seed=96, share_prob=0.0, gate="all"),
+    synth.Config("parts_k1_swiglu", 1500, 768, 512, 2, 6, 1, "f32", "swiglu", seed=97, share_prob=0.0, bias_alpha=0.5),
+    synth.Config("parts_k2_relu", 620, 1024, 1280, 2, 8, 2, "f32", "relu", seed=98, share_prob=0.0),
+]
+
+
+@pytest.mark.parametrize("cfg", PARTS_LAYERS, ids=lambda c: c.name)
+def test_f32_layers_on_bf16_parts(mm, gc, oracle, dispatch_rule, cfg):
+    """Every stage and the fused call; both products on parts."""
+    case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
+    assert dispatch_rule("f32_in_parts", case.shape, cfg.d_ff, cfg.act == "swiglu")
+    assert dispatch_rule("f32_in_parts", case.shape, cfg.d_model, False)
+
+
+@pytest.mark.parametrize("cfg", PARTS_LAYERS[1:3], ids=lambda c: c.name)
+def test_f32_layers_on_bf16_parts_with_weights_that_are_not_finite(mm, gc, oracle, cfg):
+    """Infinite weights, and large ones that are finite in fp32 only, in the plain factor of the gated product and in the
+    down product that writes the layer's rows: what fp32 gives, and only in the tokens and features they reach."""
+    inp = synth.make_inputs(cfg)
+    clean = gc.DeviceCase(cfg, inp).forward()
+    torch.cuda.synchronize()
+    inp = dict(inp, W2=inp["W2"].copy())
+    inp["W2"][5, 10, 100] = np.inf
+    inp["W2"][6, 20, 200] = -np.finfo(np.float32).max
+    if cfg.act == "swiglu":
+        inp["W3"] = inp["W3"].copy()
+        inp["W3"][4, 30, 300] = -np.inf
+    case = gc.DeviceCase(cfg, inp)
+    got = case.forward()
+    torch.cuda.synchronize()
+    got, clean = got.cpu().numpy(), clean.cpu().numpy()
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref = oracle.layer_forward(inp, 1, "f32", cfg.act, gate=cfg.gate)
+        want = (ref["Yg"].astype(np.float32)[ref["inv_perm"]] * ref["topk_w"]).astype(np.float32)  # Yg is fp32
+    slot = ref["slot"]
+    hit = np.zeros(got.shape, bool)
+    hit[slot == 5, 100] = hit[slot == 6, 200] = True
+    if cfg.act == "swiglu":
+        hit[slot == 4] = True
+    assert hit.any() and np.array_equal(got[~hit], clean[~hit])
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    inf = np.isinf(want)
+    assert inf.any() and np.array_equal(got[inf], want[inf])
+    fin = hit & np.isfinite(want)
+    assert fin.any()
+    gc.assert_close_f32(got[fin].astype(np.float64), want[fin].astype(np.float64), "features of the large weight")
 
 
 @pytest.mark.parametrize("act,d,f,x_exp,w1_exp,w2_exp", [
@@ -636,6 +690,24 @@ def _random_configs(n, seed):
 @pytest.mark.parametrize("cfg", _random_configs(24, seed=2024), ids=lambda c: c.name)
 def test_random_shapes(mm, gc, oracle, cfg):
     staged_vs_oracle(mm, gc, oracle, cfg)
+
+
+def test_calls_run_on_the_current_stream(mm):
+    """The raw handle that the binding passes on is torch's current stream: the default one, a stream of a context, of a
+    nested one, and the default one again."""
+    torch.zeros(1, device="cuda")
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def same(stream):
+        return mm._stream() == torch.cuda.current_stream().cuda_stream == stream.cuda_stream
+
+    assert same(torch.cuda.default_stream())
+    with torch.cuda.stream(a):
+        assert same(a)
+        with torch.cuda.stream(b):
+            assert same(b)
+        assert same(a)
+    assert same(torch.cuda.default_stream()) and a.cuda_stream != b.cuda_stream
 
 
 def test_ceiling_probe_reports_plausible_rates(mm):
