@@ -22,11 +22,10 @@ namespace mmoe {
 
 constexpr int kTile = 64;
 
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T* __restrict__ in, T* __restrict__ out, int R,
+__global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict__ in, float* __restrict__ out, int R,
                                                         int C)
 {
-    __shared__ T tile[kTile][kTile + 2];
+    __shared__ float tile[kTile][kTile + 2];
     // backwards and past the caches, as the fragment packing below
     const size_t mat = (size_t)(gridDim.z - 1 - blockIdx.z) * R * C;
     const int c0 = (gridDim.x - 1 - blockIdx.x) * kTile, r0 = (gridDim.y - 1 - blockIdx.y) * kTile;
@@ -84,13 +83,10 @@ static void pack_fragments(const void* in, void* out, int S, int K, int N, hipSt
     hipLaunchKernelGGL(pack_fragments_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const uint16_t*)in, (u32x4*)out, K, N);
 }
 
-static void transpose(const void* in, void* out, int S, int R, int C, int dtype, hipStream_t st)
+static void transpose(const void* in, void* out, int S, int R, int C, hipStream_t st)
 {
     dim3 grid((C + kTile - 1) / kTile, (R + kTile - 1) / kTile, S), block(256);
-    if (dtype == MMOE_BF16)
-        hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, block, 0, st, (const uint16_t*)in, (uint16_t*)out, R, C);
-    else
-        hipLaunchKernelGGL(transpose_kernel<float>, grid, block, 0, st, (const float*)in, (float*)out, R, C);
+    hipLaunchKernelGGL(transpose_kernel, grid, block, 0, st, (const float*)in, (float*)out, R, C);
 }
 
 int launch_pack(const mmoe_shape& s, const void* W1, const void* W3, const void* W2, void* W1p, void* W3p,
@@ -101,9 +97,9 @@ int launch_pack(const mmoe_shape& s, const void* W1, const void* W3, const void*
         if (W3) pack_fragments(W3, W3p, s.S, s.d_model, s.d_ff, st);
         pack_fragments(W1, W1p, s.S, s.d_model, s.d_ff, st);
     } else {
-        transpose(W2, W2p, s.S, s.d_ff, s.d_model, s.dtype, st);
-        if (W3) transpose(W3, W3p, s.S, s.d_model, s.d_ff, s.dtype, st);
-        transpose(W1, W1p, s.S, s.d_model, s.d_ff, s.dtype, st);
+        transpose(W2, W2p, s.S, s.d_ff, s.d_model, st);
+        if (W3) transpose(W3, W3p, s.S, s.d_model, s.d_ff, st);
+        transpose(W1, W1p, s.S, s.d_model, s.d_ff, st);
     }
     return launch_status();
 }
