@@ -19,7 +19,10 @@
  *   T tokens, d = d_model, f = d_ff, V variants, E experts per variant,
  *   k = top_k, S pool slots, P = T*k (token, pick) pairs, pair id p = t*k + j.
  *   All tensors are dense and row-major.  "dtype" is the storage type of X, Wr,
- *   the pool, H and Y; every product is accumulated in fp32.
+ *   the pool, H and Y; every product is accumulated in fp32.  (fp32 batches with many rows per
+ *   slot may run on the bf16 matrix instruction, every number as three bf16 parts that together
+ *   hold all of its 24 bits over the whole range of fp32; products of the parts below 2^-24 of
+ *   the term are left out.)
  *
  * Pointers
  *   Every pointer except mmoe_shape* is a DEVICE pointer owned by the caller.

@@ -145,9 +145,9 @@ constexpr int skinny_threads(int split) { return split == 8 ? 8 * kWave : kSkThr
 // lanes to the 256 bytes of a run of 64 k, and pass through LDS of the wavefront's own to get into operand order.
 // One run is in flight per wavefront, twelve wavefronts on a compute unit (eight of the gated product): with two
 // runs in flight the registers (over 168) leave eight, or spill.
-// Measured against reading both operands in operand order (768 x 3072 top-1, 13 slots, layer): 4 tokens 36.0 -> 25.6 us,
-// 24 tokens 66.9 -> 49.2, 128 tokens 79.2 -> 61.1 (246 MB of weights); 1024 x 2048 SwiGLU top-2, 64 tokens 97.3 -> 88.9;
-// 4096 x 1024 GELU 120.1 -> 118.3.
+// Measured against reading both operands in operand order (768 x 3072 top-1, 13 slots, layer): 4 tokens 36.0 -> 25.6 us
+// (21.9 with eight wavefronts in the down product), 24 tokens 66.9 -> 49.2, 128 tokens 79.2 -> 60.5 (246 MB of weights);
+// 1024 x 2048 SwiGLU top-2, 64 tokens 97.3 -> 86.
 constexpr int kRun = 64;              // k per run
 constexpr int kRunRow = kRun * 4;     // bytes of a row per run
 constexpr int kRunBlock = 16 * kRunRow;  // bytes of 16 rows
@@ -579,10 +579,13 @@ static void launch_skinny_products(const mmoe_shape& s, const void* rows, const 
 }
 
 // Split four ways a product has four times the workgroups, so slots with many rows (passes of 32 that one workgroup
-// does one after the other) and the last round leave less of the chip idle.  Whole : split, us: 1024 x 1024, 8 slots, 12
-// tokens 35.0 : 23.7; 768 x 3072, 13 slots, 4 tokens 30.1 : 25.6, 128 tokens 59.6 : 61.1; 16 slots, 47 tokens 52.0 : 40.2; 32
-// slots, 200 tokens 113 : 121; 512 x 512, 110 slots of unequal use, 802 tokens 259 : 103; SwiGLU 512 x 4864, 9 slots 52.0 :
-// 55.6.  K = 256 split is one run per wavefront, all latency: 256 x 4096 45.0 : 48.8, 256 x 1024, 60 slots 51.6 : 59.2.
+// does one after the other) and the last round leave less of the chip idle.  Whole : split, us, rows spread evenly / unequally
+// (router bias 1): 1024 x 1024, 8 slots, 12 tokens 35.1 : 24.1 / 34.9 : 19.3; 768 x 3072, 13 slots, 4 tokens 26.3 : 21.9, 64 tokens
+// 52.7 : 55.4 / 70.6 : 58.0, 128 tokens 59.3 : 60.4 / 111 : 82; 32 slots, 200 tokens 113 : 121 / 125 : 103; 512 x 512, 110 slots,
+// 802 tokens 75.8 : 81.9 / 429 : 166; SwiGLU 512 x 4864, 9 slots 71.8 : 70.7, 1024 x 1024, 24 slots, 160 pairs 68.1 : 83.3 /
+// 145 : 66.  Evenly spread rows are up to a fifth faster whole, unequal ones up to 2.6 times as fast split; the host does not know
+// the counts.  K = 256 split is one run per wavefront, all latency: 256 x 4096, 30 tokens 27.5 : 33.1 / 29.6 : 28.7; 256 x 1024,
+// 60 slots, 240 pairs 46.4 : 51.0 / 38.7 : 36.0.
 static bool whole_k(int K) { return K <= 256; }
 
 // With at most one workgroup for each of the 256 compute units, eight wavefronts instead of four: each has one run of 4 KB

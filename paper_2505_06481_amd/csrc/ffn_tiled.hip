@@ -487,12 +487,13 @@ static int planned_nb(const mmoe_shape& s, int bm, int N, bool gated)
 
 // fp32: does a product with N outputs (of each matrix) run on bf16 parts (ffn_split_f32.hip)?  Its tiles have twice the
 // features, so it needs rows that fill tiles and tiles that fill the chip: about as many as half the compute units,
-// counted as if every slot had one tile more than its share of full ones.  Measured for both products by each kernel and
-// with this rule, us: 768 x 3072, 13 slots 116 : 134 : 116 at 54 rows per slot, 125 : 136 : 120 at 65, 132 : 137 : 119 at 77,
-// 173 : 157 : 158 at 90, 229 : 173 : 172 at 154; 256 x 8192 (2 wide tiles down) 245 : 262 : 228 at 115, 284 : 281 : 242 at
-// 192; 4096 x 512 139 : 146 : 122 at 62, 284 : 206 : 205 at 192; 2048 x 4096, 6 slots 160 : 166 : 154 at 50; 768 x 768, 4 slots
-// 53 : 57 : 53 at 250, 119 : 87 : 86 at 1000; SwiGLU 1024 x 2048 123 : 118 : 119 at 46, 131 : 121 : 121 at 65; 2048 x 4096
-// 218 : 205 : 191 at 43.
+// counted as if every slot had one tile more than its share of full ones.  Measured for both products on the fp32
+// instruction : on parts : with this rule, us: 768 x 3072, 13 slots 117 : 125 : 108 at 54 rows per slot, 122 : 129 : 113 at 65,
+// 169 : 132 : 151 at 77, 172 : 149 : 147 at 90, 229 : 169 : 169 at 154; 256 x 8192 (2 wide tiles down) 238 : 260 : 221 at 115,
+// 286 : 289 : 252 at 192; 4096 x 512, 6 slots 80 : 110 : 78 at 62, 155 : 153 : 134 at 192; 768 x 768, 4 slots 50 : 60 : 50 at 250,
+// 129 : 90 : 89 at 1000; SwiGLU 1024 x 2048 123 : 123 : 123 at 46, 2048 x 4096 219 : 206 : 192 at 43.  It loses where slots of less than a
+// tile count as two: 2048 x 1024, 12 slots 95 : 101 : 102 at 60; 512 x 2048, 32 slots 99 : 110 : 109 at 40.  (With a line of 200
+// tiles below 64 rows per slot both take 89, but 768 x 3072, 16 slots of unequal use, at 59 rows 157 instead of 135.)
 constexpr int kPartsRows = 40, kPartsTiles = 150;
 bool f32_in_parts(const mmoe_shape& s, int N, bool gated)
 {

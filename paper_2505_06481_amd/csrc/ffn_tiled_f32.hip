@@ -18,14 +18,14 @@
 //             ones were, while matrix instructions run.
 // The streaming kernel (ffn_skinny.hip) reads the weights again, and every wavefront its own copy of the token
 // rows, for each 32 rows of a slot; here once for 96.
-// Measured with it against the streaming kernel (768 x 3072, top-1, 13 slots): 640 tokens 215 -> 115 us,
-// 2000 tokens 569 -> 236 us, 4096 tokens 1108 -> 430 us; 1024 x 2048 SwiGLU, top-2, 12 slots, 600 tokens:
-// 405 -> 195 us.  At 2000 tokens each product runs at 80 of 157 TFLOP/s; the matrix pipes are busy for 74 % of the
-// cycles in which their compute unit has work (SQ_VALU_MFMA_BUSY_CYCLES / 4 / SQ_BUSY_CU_CYCLES).
+// Measured against the streaming kernel, rows spread evenly (768 x 3072, top-1, 13 slots): 260 tokens 85 -> 70 us, 416 tokens
+// 117 -> 81; 1024 x 2048 SwiGLU, top-2, 13 slots, 208 tokens 141 -> 121; 2048 x 4096 SwiGLU, 8 slots, 128 tokens 281 -> 203.  At 2000
+// tokens of 768 x 3072 (which run on bf16 parts) each product reached 80 of 157 TFLOP/s with the matrix pipes busy for 74 % of
+// the cycles in which their compute unit had work (SQ_VALU_MFMA_BUSY_CYCLES / 4 / SQ_BUSY_CU_CYCLES).
 //
 // Summation: a chain of matrix instructions runs over kChain k values from zero and is then added to
-// the running total, so rounding errors do not build up over the whole reduction dimension (the
-// streaming kernel's chains are K or K/4 long).
+// the running total, so rounding errors do not build up over the whole reduction dimension (as in the
+// streaming kernel).
 #include <type_traits>
 
 #include "mmoe_internal.h"

@@ -36,9 +36,12 @@ static size_t counted_list_bytes(const mmoe_shape& s)
     return align256(256 + 32 * (tiles + (tiles + 7) / 8) * groups);
 }
 
-// fp32: most rows per slot, on average, for the streaming kernels.  Measured with each kernel forced:
-// 768 x 3072 top-1, 13 slots: 77 (streaming) against 83 us at 9.8 rows per slot, 90 against 84 at 15.4;
-// 1024 x 2048 SwiGLU top-2: 95 against 92 us at 8 rows, 115 against 91 at 17; 2048 x 4096 SwiGLU: equal at 10.
+// fp32: most rows per slot, on average, for the streaming kernels.  Measured with each kernel forced, streaming : tiles, us, rows
+// spread evenly / unequally (router bias 0.5): 768 x 3072 top-1, 13 slots: 10 rows per slot 61 : 69 / 69 : 68, 12 rows
+// 64 : 73 / 79 : 68, 16 rows 71 : 69 / 100 : 68; 1024 x 2048 SwiGLU top-2, 13 slots: 12 rows 84 : 88 / 89 : 91, 16 rows 98 : 96 /
+// 94 : 88; 2048 x 4096 SwiGLU, 8 slots: 12 rows 169 : 180 / 168 : 181, 20 rows 198 : 182 / 193 : 182; 4096 x 1024 14 rows 100 : 110 /
+// 113 : 113; 256 x 1024, 32 slots: 12 rows 35 : 38 / 62 : 38.  Evenly spread rows are level at 16 to 18, unequal ones below 8 (many
+// slots) to 14.
 constexpr int kF32StreamRows = 12;
 
 // Few rows per slot: the batch streams, and so does every smaller one.
@@ -48,15 +51,16 @@ static bool few_rows(const mmoe_shape& s)
     // read is the bound.  The streaming kernel takes 32 rows of a slot per pass over its weights, so it
     // only pays while the fullest slot stays near that, and each of its workgroups looks through all pairs
     // for its slot's, so it only pays while they are few.  Measured with each kernel forced, streaming
-    // against matrix-core tiles, us: 4096 x 14336 SwiGLU 777 : 793 at 12 rows per slot, 826 : 792 at 15;
-    // 2048 x 2048 SwiGLU 68 : 72 at 17, 82 : 73 at 25; 1280 x 2560 GELU 43 : 48 at 17, 52 : 51 at 25; 768 x 3072
-    // 37 : 39 at 15, 45 : 42 at 23; with many slots, 512 x 1024 SwiGLU 48 : 46 at 500 pairs, 57 : 49 at 800;
-    // 2048 x 1280 SwiGLU 284 : 279 at 800 pairs, 333 : 303 at 1800.
-    // In a pool of 4 to 11 slots the tiles' grouping launch (8 us) weighs more: 32 to 21 rows per slot.  Rows spread evenly / unequally (router bias
-    // 0.5): 768 x 3072, 4 slots, 24 rows per slot 25 : 34 / 30 : 36, 32 rows 29 : 35 / 38 : 37; 8 slots, 24 rows
-    // 30 : 43 / 46 : 45, 28 rows 36 : 44 / 51 : 46; 16 slots, 24 rows 56 : 57 / 71 : 58; 2048 x 2048 SwiGLU, 4 slots, 32 rows
-    // 44 : 60 / 45 : 60, 8 slots, 24 rows 56 : 66 / 62 : 68, 28 rows 63 : 67 / 68 : 68.  (With bias 2.5 one slot has half of
-    // the rows, 8 slots, 24 rows: 72 : 36 and 61 : 57.  The host does not know the counts.)
+    // against matrix-core tiles, us, rows spread evenly / unequally (router bias 0.5): 4096 x 14336 SwiGLU, 13 slots 746 : 844 /
+    // 780 : 839 at 17 rows per slot, 861 : 846 / 850 : 849 at 24; 2048 x 2048 SwiGLU, 13 slots 72 : 82 / 75 : 83 at 17, 80 : 81 /
+    // 82 : 79 at 20; 1280 x 2560 GELU, 16 slots 55 : 56 / 61 : 57 at 17, 62 : 57 / 68 : 59 at 24; 768 x 3072, 13 slots 38 : 40 /
+    // 56 : 43 at 17, 45 : 42 / 60 : 43 at 20; with many slots, 512 x 1024 SwiGLU 50 : 54 / 53 : 46 at 512 pairs, 55 : 55 / 65 : 51 at
+    // 768; 2048 x 1280 SwiGLU 253 : 290 / 253 : 272 at 720 pairs.
+    // In a pool of 4 to 11 slots the tiles' grouping launch (8 us) weighs more: 32 to 21 rows per slot.  768 x 3072, 4 slots,
+    // 24 rows per slot 21 : 31 / 28 : 35, 32 rows 27 : 35 / 36 : 36; 8 slots, 24 rows 25 : 35 / 43 : 39, 28 rows 31 : 37 /
+    // 49 : 39; 16 slots, 24 rows 48 : 43 / 66 : 47; 2048 x 2048 SwiGLU, 4 slots, 32 rows 38 : 44 / 39 : 44, 8 slots, 24 rows
+    // 49 : 54 / 54 : 55, 28 rows 54 : 53 / 55 : 56.  (With bias 2.5 one slot has half of the rows, 8 slots, 24 rows:
+    // 67 : 36 and 61 : 46.  The host does not know the counts.)
     const int64_t P = (int64_t)s.T * s.top_k;
     if (s.dtype == MMOE_F32) return P <= (int64_t)kF32StreamRows * s.S;
     const bool small_experts = (int64_t)s.d_model * s.d_ff <= ((int64_t)4 << 20);
