@@ -464,7 +464,7 @@ __global__ __launch_bounds__(256, BM == kBMBig ? 1 : 2) void tiled_kernel(
     tiled_body<MODE, BM, NB, false>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
 }
 
-// 256-row tiles of a batch in which slots may be one tile.
+// A batch in which slots may be one tile (lone_tiles): 256-row tiles.
 template <int MODE>
 __global__ __launch_bounds__(256, 1) void tiled_lone_kernel(
     const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv, const int32_t* __restrict__ tab, int hdr,
@@ -472,6 +472,16 @@ __global__ __launch_bounds__(256, 1) void tiled_lone_kernel(
     int K, int N, const int32_t* __restrict__ sink_perm, const float* __restrict__ sink_w)
 {
     tiled_body<MODE, kBMBig, 2, true>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
+}
+
+// And 128-row tiles.
+template <int MODE, int NB>
+__global__ __launch_bounds__(256, 2) void tiled_lone_small_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv, const int32_t* __restrict__ tab, int hdr,
+    int list_at, int list_stride, const uint16_t* __restrict__ W0, const uint16_t* __restrict__ W1, void* __restrict__ out,
+    int K, int N, const int32_t* __restrict__ sink_perm, const float* __restrict__ sink_w)
+{
+    tiled_body<MODE, kBMSmall, NB, true>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
 }
 
 // Weight blocks per wavefront of a product with N output features: 2, or 1 (tiles of 128 weight
@@ -539,13 +549,18 @@ int planned_tile_rows(const mmoe_shape& s)
 // copies in flight, before short tiles had several.)
 static int planned_upt(const mmoe_shape&, int bm) { return bm / 32; }
 
-// Are panels read past the caches where a 256-row tile is the only one of its slot?  Where slots of one tile are likely, and
+// Are panels read past the caches where a tile is the only one of its slot?  Where slots of one tile are likely, and
 // the pool is larger than the last-level cache: a smaller one may still be there from an earlier call, and the few
 // tiles of a small layer wait longer for each load.  Through the caches : past them, us, one pool again and again / three in
 // turn: 2304 x 768 SwiGLU, 6 slots (64 MB), 180 rows per slot 72.2 : 82.9 / 72.3 : 83.2; 4096 x 512, 5 slots (42 MB) 80.9 :
 // 95.4 / 80.0 : 95.4; 4096 x 1024 SwiGLU, 8 slots (201 MB), 110 rows 88.3 : 109.0 / 111.6 : 109.1; 2560 x 2560, 20 slots (524 MB)
 // 182.7 : 172.3 / 183.2 : 174.1; 4096 x 2048 SwiGLU, 13 slots (654 MB) 178.9 : 161.1 / 180.0 : 166.2.  (At 244 and 306 rows
 // per slot on average both are within 1 %.)
+// 128-row tiles, one pool: 2048 x 1280 SwiGLU, 90 slots, 46 rows 339 : 314 (three in turn 346 : 334), 16 rows 293 : 275; 4096 x 4096 SwiGLU, 24 slots, 33 rows
+// 457 : 425; 4096 x 14336, 39 rows 834 : 783; 1024 x 4096 GELU, 64 slots, 31 rows 244 : 228; 1280 x 2560 SwiGLU, 16 slots, 112 rows 114.9 :
+// 108.9; 1024 x 4096 SwiGLU, 60 slots, 80 rows 371 : 362, 133 rows 448 : 443, 200 rows 541 : 542; 768 x 3072, 40 slots, 110 rows 145 : 141, 200 rows
+// 204 : 205; a few of 200 slots much in use (router bias 2.5), 1024 x 1024, 16 rows 74.7 : 78.0.  A pool below the line, 2048 x 2048 GELU, 12 slots
+// (201 MB), 67 rows 72.6 : 81.5; 768 x 3072, 18 slots (170 MB) 95.8 : 101.7, three pools in turn 106.3 : 107.0.
 bool lone_tiles(const mmoe_shape& s)
 {
     return (int64_t)s.T * s.top_k <= (int64_t)kBMBig * s.S && s.S * slot_bytes(s) > kLastLevelCache;
@@ -601,14 +616,12 @@ static void launch_product(const TiledPlan& p, int prod, const void* A, const in
 {
     const dim3 grid(p.L.len[prod] * kXcds), block(256);
     const int stride = p.L.lists[prod] == 1 ? 0 : p.L.len[prod];
-    if constexpr (BM == kBMBig) {
-        if (p.lone) {
-            hipLaunchKernelGGL((tiled_lone_kernel<MODE>), grid, block, 0, st, (const uint16_t*)A, perm, kdiv, tab, kXcds * prod,
-                               p.L.list[prod], stride, (const uint16_t*)W0, (const uint16_t*)W1, out, K, N, sink.perm, sink.w);
-            return;
-        }
+    auto kernel = tiled_kernel<MODE, BM, NB>;
+    if (p.lone) {
+        if constexpr (BM == kBMBig) kernel = tiled_lone_kernel<MODE>;
+        else kernel = tiled_lone_small_kernel<MODE, NB>;
     }
-    hipLaunchKernelGGL((tiled_kernel<MODE, BM, NB>), grid, block, 0, st, (const uint16_t*)A, perm, kdiv, tab, kXcds * prod,
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, (const uint16_t*)A, perm, kdiv, tab, kXcds * prod,
                        p.L.list[prod], stride, (const uint16_t*)W0, (const uint16_t*)W1, out, K, N, sink.perm, sink.w);
 }
 

@@ -301,6 +301,16 @@ def test_streaming_slots_of_several_passes_in_large_pools(mm, gc, oracle, dispat
     assert ref["counts"].max() > 32 and (ref["counts"] > 0).sum() > (ref["counts"] > 32).sum()
 
 
+@pytest.mark.parametrize("act,k,E,d,f", [("gelu", 1, 16, 1024, 1536), ("swiglu", 2, 12, 1280, 1024)])
+def test_tiles_of_128_rows_in_large_pools(mm, gc, oracle, dispatch_rule, act, k, E, d, f):
+    """Slots of one tile, whose weights are read past the caches, of every height, beside slots of several tiles."""
+    cfg = synth.Config(f"lone128_{act}", 2600 // k, d, f, 3, E, k, "bf16", act, seed=91, share_prob=0.0, bias_alpha=0.6)
+    case, ref = staged_vs_oracle(mm, gc, oracle, cfg)
+    assert mm.expert_plan(case.shape) == (False, 128) and dispatch_rule("lone_tiles", case.shape)
+    heights = {-(-int(c) // 32) for c in ref["counts"]}
+    assert {1, 2, 3, 4} <= heights and max(heights) > 4
+
+
 @pytest.mark.parametrize("act,k", [("relu", 1), ("swiglu", 2)])
 def test_f32_streaming_split_over_eight_wavefronts(mm, gc, oracle, act, k):
     """Reductions of one run, of an uneven number of runs and of several chains per wavefront, grids at both sides of

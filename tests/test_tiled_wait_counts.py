@@ -206,6 +206,17 @@ def test_waits_of_the_kernel_for_slots_of_one_tile():
         assert sorted(k for _, k, _ in res) == want, fn.name
 
 
+def test_waits_of_the_128_row_kernel_for_slots_of_one_tile():
+    """As above: five products with two weight blocks per wavefront, the four without a gate with one too."""
+    fns = functions(device_assembly(), "_ZN4mmoe23tiled_lone_small_kernel")
+    assert len(fns) == 9, [f.name for f in fns]
+    for fn in fns:
+        mode, nb = re.search(r"kernelILi(\d)ELi(\d)E", fn.name).groups()
+        res = check_function(fn)
+        want = sorted(k for _, k, waits in variants(f"_ZN4mmoe12tiled_kernelILi{mode}ELi128ELi{nb}EE") for _ in range(2 * waits))
+        assert sorted(k for _, k, _ in res) == want, fn.name
+
+
 def test_loads_moved_across_a_wait_are_flagged():
     """A mistake planted in the assembly text: the waits with one number of copies in flight (tiles of 3, 5, 6 and 7
     sub-tiles have their own) leave three more instructions outstanding than the kernel asks for, as if three loads had
