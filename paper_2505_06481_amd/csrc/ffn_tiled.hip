@@ -566,6 +566,24 @@ bool lone_tiles(const mmoe_shape& s)
     return (int64_t)s.T * s.top_k <= (int64_t)kBMBig * s.S && s.S * slot_bytes(s) > kLastLevelCache;
 }
 
+// Do the XCDs take runs of neighbouring tiles of the down product (tile_table.h)?  What reaches an XCD's L2 from beyond it
+// bounds these products (5.7 TB/s; 768 x 3072, 18 slots, 4096 tokens: 251 MB, of which 151 token rows, each read by six
+// XCDs).  Panel by panel a slot's rows are read by min(8, NT) XCDs, a weight panel by one; in runs a slot's rows by one
+// or two, but the panels at the ends by two and the XCDs' shares of the weights differ.  So runs pay where token rows
+// are a good part of the traffic, min(8, NT) P against S N rows.  Panels : runs, layer, us, three pools in turn: ratio
+// 1.8 768 x 3072, 18 slots, 4096 tokens 106.2 : 100.7; 3.9 16 slots, 8000 tokens 148 : 131; 1.3 512 x 2048, 24 slots 96.1 : 82.8; 0.8 2560 x 7680,
+// 12 slots 442 : 360; 0.5 1024 x 1024, 64 slots 130.4 : 128.5; 0.4 768 x 3072, 40 slots 116.7 : 114.1; 0.26 18 slots 60.8 : 59.8; but 0.18
+// 2048 x 1280, 90 slots 324 : 329; 0.17 4096 x 14336, 777 tokens 1235 : 1289; 0.11 500 tokens 1157 : 1257.  256-row tiles of many
+// rows per slot are bound by the matrix cores, and runs of tiles drift apart: 417 rows per slot 2048 x 8192 440 : 428, 500 rows 4096 x 4096
+// 578 : 576, 615 rows 4096 x 14336 2487 : 2493, 833 rows 936 : 944, 1260 rows 4624 : 4690.  (The up product reads a few short rows of tokens for
+// each of its panels: 768 x 3072 equal, 1024 x 4096 210 : 219, 4096 x 14336 4690 : 4744.)
+static bool xcd_runs(const mmoe_shape& s, int bm, int nt_down)
+{
+    const int64_t P = (int64_t)s.T * s.top_k, readers = nt_down < kXcds ? nt_down : kXcds;
+    if (s.dtype == MMOE_F32 || (bm == kBMBig && P > (int64_t)512 * s.S)) return false;
+    return 4 * readers * P >= (int64_t)s.S * s.d_model;
+}
+
 static TiledPlan tiled_plan(const mmoe_shape& s)
 {
     TiledPlan p;
@@ -573,7 +591,7 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
     p.lone = lone_tiles(s);
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm), planned_upt(s, p.bm), p.bm,
-                     s.dtype == MMOE_F32);
+                     s.dtype == MMOE_F32, xcd_runs(s, p.bm, p.nt_down));
     return p;
 }
 
@@ -603,7 +621,7 @@ size_t tiled_table_most(const mmoe_shape& s)
         for (int nb_up : {1, 2})
             for (int nb_down : {1, 2}) {
                 const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb_up);
-                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (wide * nb_down), bm / 32, bm / 32, bm, f32);
+                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (wide * nb_down), bm / 32, bm / 32, bm, f32, !f32);
                 most = L.bytes > most ? L.bytes : most;
             }
     return align256(most);

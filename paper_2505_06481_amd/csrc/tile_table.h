@@ -37,8 +37,9 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // feature tiles count within the XCD (nt = 8*entry + x).  Dealing by nt mod 8 alone whatever NT gave 10
 // feature tiles to the XCDs as 2,2,1,1,1,1,1,1 (1.6 times an even share) and 6 as 1,1,1,1,1,1,0,0.
 // (64 experts of 2048 x 1280, 1037 tokens, 10 up panels a slot: up product 226 -> 179 us; 768 x 3072,
-// 4096 tokens, 6 down panels: 53 -> 47 us.)  Cutting the list into 8 contiguous runs instead was slower
-// where the tiles' costs differ, as they are not known here (4096 x 14336, 777 tokens: 1629 against 1310 us).
+// 4096 tokens, 6 down panels: 53 -> 47 us.)
+// With `runs` the list of all tiles is cut into eight contiguous runs of as many tiles each instead, so that a slot's
+// token rows are read by one or two XCDs and not by min(8, NT) of them (xcd_runs says where that pays).
 //
 // Target heights of a row tile that the table builder may choose from, in quarters of a 32-row
 // sub-tile: from a full tile (4 upt) down to hq_lo.  bf16: five eighths of a full tile (shorter tiles are
@@ -54,6 +55,7 @@ struct TileLists {
     int list[2];    // [product: up, down] -> int4 index into tab of XCD 0's list
     int lists[2];   // 1: the XCDs share one list; kXcds: one list each, `len` entries apart
     int len[2];     // entries reserved per list of each product: workgroups per XCD
+    int runs[2];    // 1: the XCDs take runs of neighbouring tiles, not panels in turn
     int upt[2];     // most 32-row sub-tiles of a row tile, per product
     int hq_lo[2];   // least target height, in quarters of a sub-tile
     int conc;       // workgroups that an XCD works on at a time, for the choice of the height
@@ -61,7 +63,7 @@ struct TileLists {
     size_t bytes;
 };
 
-inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down, int bm, bool f32)
+inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down, int bm, bool f32, bool runs_down)
 {
     TileLists L;
     L.upt[0] = upt_up;
@@ -82,7 +84,8 @@ inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, in
     int at = 16;  // int4 units; the header takes the first 256 bytes
     for (int p = 0; p < 2; ++p) {
         const int NT = p == 0 ? nt_up : nt_down;
-        L.lists[p] = NT % kXcds == 0 ? 1 : kXcds;
+        L.runs[p] = p == 1 && runs_down;
+        L.lists[p] = NT % kXcds == 0 && !L.runs[p] ? 1 : kXcds;
         L.len[p] = L.rows_cap[p] * ((NT + kXcds - 1) / kXcds);  // a slot's panels on one XCD: ceil(NT / 8) at most
         L.list[p] = at;
         at += L.lists[p] * L.len[p];
@@ -201,11 +204,14 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     }
     if (tid == 0) base[S] = total_m;
     __syncthreads();
-    const bool shared_list = L.lists[p] == 1;
+    const bool shared_list = L.lists[p] == 1, runs = L.runs[p];
+    const int share = (total_m * NT + kXcds - 1) / kXcds;  // tiles of an XCD's run
     // Panels of slot s (the r-th that holds rows) on XCD x: the c = r NT + nt with c mod 8 == x.
     // panels_before(x, c) of them lie before panel c.
     auto panels_before = [](int x, int c) { return (c + kXcds - 1 - x) / kXcds; };
-    if (!shared_list) {
+    if (runs) {
+        if (tid < kXcds) tab[kXcds * p + tid] = min(share, max(total_m * NT - tid * share, 0));
+    } else if (!shared_list) {
         // first entry of every slot in every XCD's list: an XCD to a wavefront, 64 slots at a time
         if (wave < kXcds) {
             const int x = wave;
@@ -230,12 +236,14 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     } else if (tid < kXcds) {
         tab[kXcds * p + tid] = total_m * (NT / kXcds);
     }
-    // the lists: all threads on the shared one, an eighth of them on each XCD's own
+    // the lists: all threads on the shared one (with runs: on the tiles of all XCDs in order), an eighth of them on each
+    // XCD's own
     constexpr int kPerXcd = kListThreads / kXcds;
-    const int x = shared_list ? 0 : tid / kPerXcd;
-    const int n = shared_list ? total_m * (NT / kXcds) : total[x];
-    for (int e = shared_list ? tid : tid % kPerXcd; e < n; e += shared_list ? kListThreads : kPerXcd) {
-        auto first_of = [&](int s) { return shared_list ? base[s] * (NT / kXcds) : first[x * kMaxS + s]; };
+    const bool all = shared_list || runs;
+    const int x = all ? 0 : tid / kPerXcd, nt_all = runs ? NT : NT / kXcds;  // panels of a slot in a list that all work on
+    const int n = all ? total_m * nt_all : total[x];
+    for (int e = all ? tid : tid % kPerXcd; e < n; e += all ? kListThreads : kPerXcd) {
+        auto first_of = [&](int s) { return all ? base[s] * nt_all : first[x * kMaxS + s]; };
         int lo = 0, hi = S;  // largest s with first_of(s) <= e (slots without entries have equal bounds)
         while (hi - lo > 1) {
             const int mid = (lo + hi) >> 1;
@@ -244,18 +252,19 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
         const int s = lo, mt = base[s + 1] - base[s];
         const int rem = e - first_of(s);
         const int c0 = pbase[s] * NT, j0 = panels_before(x, c0);
-        const int nt_x = shared_list ? NT / kXcds : panels_before(x, c0 + NT) - j0;  // the slot's panels on this XCD
+        const int nt_x = all ? nt_all : panels_before(x, c0 + NT) - j0;  // the slot's panels on this XCD
         // groups of g feature tiles; inside a group the feature tile runs fastest
         const int g = min(nt_x, max(kNtGroup, div24(conc, mt)));
         const int grp = div24(rem, g * mt), within = rem - grp * (g * mt);
         const int g_sz = min(g, nt_x - grp * g);
         const int i = div24(within, g_sz), j = grp * g + within - i * g_sz;  // j-th panel of the slot here
-        const int ntl = shared_list ? j : (j0 + j) * kXcds + x - c0;
+        const int ntl = all ? j : (j0 + j) * kXcds + x - c0;
         // row tile i of the slot: the first `extra` tiles are one sub-tile taller
         const int u = units_of(s), h = div24(u, mt), extra = u - h * mt;
         const int row0 = 32 * (i * h + min(i, extra));
         const int rows = 32 * (h + (i < extra ? 1 : 0));
-        lists[L.list[p] + x * L.len[p] + e] = make_int4(mt == 1 ? s | kOnlyTile : s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
+        const int to = runs ? div24(e, share) : x;
+        lists[L.list[p] + to * L.len[p] + e - (runs ? to * share : 0)] = make_int4(mt == 1 ? s | kOnlyTile : s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
     }
 }
 

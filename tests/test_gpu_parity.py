@@ -301,6 +301,17 @@ def test_streaming_slots_of_several_passes_in_large_pools(mm, gc, oracle, dispat
     assert ref["counts"].max() > 32 and (ref["counts"] > 0).sum() > (ref["counts"] > 32).sum()
 
 
+@pytest.mark.parametrize("rows", [256, 128])
+def test_down_tiles_in_runs(mm, gc, oracle, rows):
+    """Down products whose tiles go to the XCDs in runs: fewer tiles than XCDs, numbers that do not divide among them,
+    empty slots at either end, one panel per slot, and as many panels as XCDs or more."""
+    for T, V, E, k, d, f, alpha in ((65, 1, 1, 1, 256, 256, 0.0), (300, 1, 3, 1, 256, 512, 0.0), (900, 3, 16, 1, 768, 256, 3.0),
+                                    (800, 1, 40, 2, 512, 256, 2.0), (1300, 2, 6, 2, 2304, 256, 0.5), (1100, 1, 5, 1, 2048, 256, 0.0)):
+        cfg = synth.Config(f"runs_{T}_{d}", T, d, f, V, E, k, "bf16", "relu" if k == 1 else "swiglu", seed=1400 + T, bias_alpha=alpha)
+        case, _ = staged_vs_oracle(mm, gc, oracle, cfg, tile_rows=rows)
+        assert mm.expert_plan(case.shape) == (False, rows)
+
+
 @pytest.mark.parametrize("act,k,E,d,f", [("gelu", 1, 16, 1024, 1536), ("swiglu", 2, 12, 1280, 1024)])
 def test_tiles_of_128_rows_in_large_pools(mm, gc, oracle, dispatch_rule, act, k, E, d, f):
     """Slots of one tile, whose weights are read past the caches, of every height, beside slots of several tiles."""
