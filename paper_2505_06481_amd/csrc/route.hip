@@ -15,6 +15,8 @@
 // Coefficients: softmax over the selected logits, or (gate over all experts) each selected
 // expert's entry of the softmax over all E logits, whose normaliser is one more wavefront
 // reduction over the parked logits.
+#include <type_traits>
+
 #include "mmoe_internal.h"
 
 namespace mmoe {
@@ -37,6 +39,69 @@ template <> struct Raw4<uint16_t> {
 };
 
 constexpr int kNoExpert = 0x7FFFFFFF;  // a lane with no expert left to offer
+
+// Value of lane (lane ^ OFF), all 64 lanes taking part: vector instructions only, where __shfl_xor goes through the
+// LDS pipe with an address computed for it, six levels behind every dot product.  (One token of 4096 elements, 8 experts 5.3 ->
+// 5.0 us, three of 768 3.8 -> 3.4.)
+template <int OFF>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x)
+{
+    constexpr int kQuadSwap1 = 0xB1, kQuadSwap2 = 0x4E, kQuadReverse = 0x1B, kRor8 = 0x128, kHalfMirror = 0x141;
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "a power of two");
+    auto dpp = [](uint32_t v, auto ctrl) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, decltype(ctrl)::value, 0xF, 0xF, true); };
+    const int lane = threadIdx.x & (kWave - 1);
+    if constexpr (OFF == 1) return dpp(x, std::integral_constant<int, kQuadSwap1>{});
+    if constexpr (OFF == 2) return dpp(x, std::integral_constant<int, kQuadSwap2>{});
+    if constexpr (OFF == 4)  // 7 - lane of eight, then 3 - lane of four
+        return dpp(dpp(x, std::integral_constant<int, kHalfMirror>{}), std::integral_constant<int, kQuadReverse>{});
+    if constexpr (OFF == 8) return dpp(x, std::integral_constant<int, kRor8>{});
+    if constexpr (OFF == 16) {  // rows of 16 lanes {0,0,2,2} and {1,1,3,3}
+        const u32x2 r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return (lane & 16) ? r[0] : r[1];
+    }
+    if constexpr (OFF == 32) {
+        const u32x2 r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return (lane & 32) ? r[0] : r[1];
+    }
+}
+template <int OFF>
+__device__ __forceinline__ float lane_xor(float x) { return __uint_as_float(lane_xor<OFF>(__float_as_uint(x))); }
+template <int OFF>
+__device__ __forceinline__ int lane_xor(int x) { return (int)lane_xor<OFF>((uint32_t)x); }
+
+// f(offset) for the offsets 32, 16, ..., 1 that are below n.
+template <typename F>
+__device__ __forceinline__ void for_offsets_below(int n, F f)
+{
+    if (32 < n) f(std::integral_constant<int, 32>{});
+    if (16 < n) f(std::integral_constant<int, 16>{});
+    if (8 < n) f(std::integral_constant<int, 8>{});
+    if (4 < n) f(std::integral_constant<int, 4>{});
+    if (2 < n) f(std::integral_constant<int, 2>{});
+    if (1 < n) f(std::integral_constant<int, 1>{});
+}
+
+// The butterfly of one sum: every lane has it.
+__device__ __forceinline__ float butterfly(float p)
+{
+    for_offsets_below(kWave, [&](auto off) { p = p + lane_xor<decltype(off)::value>(p); });
+    return p;
+}
+
+// Two levels of four butterflies at once (one exchange and one addition for two sums), then the other four levels of all of them: what a lane adds is its partner's
+// partial sum either way, so every sum is the contract's.  Lanes 0-15 have the sum of a, 16-31 of b, 32-47 of c, 48-63 of d.
+__device__ __forceinline__ float butterfly4(float a, float b, float c, float d)
+{
+    auto swap32 = [](float x, float y) {  // x in lanes 0-31, y in lanes 32-63
+        const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    const float ac = swap32(a, c), bd = swap32(b, d);
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(ac), __float_as_uint(bd), false, false);
+    float p = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    for_offsets_below(16, [&](auto off) { p = p + lane_xor<decltype(off)::value>(p); });
+    return p;
+}
 
 // Expert e's bit among those of `lane`, which looks after experts lane, lane + 64, ...; 0 if it is another lane's.
 // kNoExpert is lane 63's by its low bits and has no bit: its shift count would be out of range.
@@ -83,15 +148,14 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
                     be = e;
                 }
             }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                if (off >= E) continue;
-                float ov = __shfl_xor(bv, off, kWave);
-                int oe = __shfl_xor(be, off, kWave);
-                bool other_valid = oe != kNoExpert, self_valid = be != kNoExpert;
-                bool take = other_valid && (!self_valid || ov > bv || (ov == bv && oe < be));
-                if (take) { bv = ov; be = oe; }
-            }
+            for_offsets_below(E, [&](auto off) {
+                const float ov = lane_xor<decltype(off)::value>(bv);
+                const int oe = lane_xor<decltype(off)::value>(be);
+                const bool other_valid = oe != kNoExpert, self_valid = be != kNoExpert;
+                const bool take = other_valid && (!self_valid || ov > bv || (ov == bv && oe < be));
+                bv = take ? ov : bv;
+                be = take ? oe : be;
+            });
             sel[j] = bv;
             seli[j] = be;
             taken |= expert_bit(be, lane);
@@ -104,9 +168,7 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
 #pragma unroll
         for (int q = 0; q < kPerLane; ++q)
             if (lane + q * kWave < E) all += expf(mine[q] - sel[0]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1)
-            if (off < E) all += __shfl_xor(all, off, kWave);
+        for_offsets_below(E, [&](auto off) { all += lane_xor<decltype(off)::value>(all); });
     }
     if (lane == 0) {
         float z[kMaxTopK];
@@ -177,9 +239,7 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
                         acc = __builtin_fmaf(Raw4<T>::get(xv[u], c), Raw4<T>::get(wv[u], c), acc);
                 }
         }
-        float p = acc;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) p = p + __shfl_xor(p, off, kWave);
+        float p = butterfly(acc);
         if (br) p = p + bias;
         if (lane == 0) lds_logit[e] = p;
     }
@@ -191,10 +251,9 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
 
 // Batches with much to score: a workgroup takes kRouteGroup tokens, so a router row is read once for
 // those of them that share a variant instead of once per token, and unpacked once.  Token rows in LDS as
-// stored; wavefront w of sixteen scores experts w, w+16, ... for all of the group's tokens.  The sums of the
-// group's tokens go through the butterfly together: at the first two levels half of the lanes keep one token
-// and half the other, and what a lane adds is its partner's partial sum either way, so every sum is the
-// contract's.  Bound by the chain of reads per expert at the small end, by vector issue at the large.
+// stored; wavefront w of sixteen scores experts w, w+16, ... for all of the group's tokens, whose sums share a
+// butterfly.  (Tried: rows in LDS in fp32, pairs of experts, the next rows requested a step ahead, with 4, 8 or 16
+// wavefronts: equal to a quarter slower, 6000 tokens of 2048, 32 experts 46 -> 48 to 57 us.)  Bound by the chain of reads per expert at the small end, by vector issue at the large.
 // 1024 tokens of 3072 elements, 64 experts, bf16: 39.1 (workgroup per token) -> 27.5 us, fp32 62.7 -> 25.5;
 // 8192 tokens of 4096, 64 experts: 237 (wavefront per token) -> 158 us; of 2304, 8 experts: 76.6 -> 35.7 us.
 constexpr int kRouteGroup = 4;
@@ -264,19 +323,11 @@ __global__ __launch_bounds__(kRouteGroupWaves* kWave) void route_group_kernel(
                     }
             }
         }
-        const bool hi = lane & 32, odd = lane & 16;
-        float a = hi ? acc[1] : acc[0], b = hi ? acc[3] : acc[2];
-        a = a + __shfl_xor(hi ? acc[0] : acc[1], 32, kWave);
-        b = b + __shfl_xor(hi ? acc[2] : acc[3], 32, kWave);
-        float p = odd ? b : a;
-        p = p + __shfl_xor(odd ? a : b, 16, kWave);
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) p = p + __shfl_xor(p, off, kWave);
-        const int tok = (hi ? 1 : 0) + (odd ? 2 : 0);
+        const float p = butterfly4(acc[0], acc[1], acc[2], acc[3]);
+        const int tok = lane / 16;
         if ((lane & 15) == 0) {
             const int vt = tok == 0 ? v[0] : tok == 1 ? v[1] : tok == 2 ? v[2] : v[3];
-            if (br) p = p + br[(size_t)vt * E + e];
-            lds_logit[tok][e] = p;
+            lds_logit[tok][e] = br ? p + br[(size_t)vt * E + e] : p;
         }
     }
     __syncthreads();
@@ -287,8 +338,10 @@ __global__ __launch_bounds__(kRouteGroupWaves* kWave) void route_group_kernel(
 // Throughput variant for large batches: one wavefront per token.  The token's elements
 // stay in registers (NC chunks of 256, d = 256*NC exactly, so that every load of a pass is
 // issued before the first one is waited for) and the wavefront walks the experts
-// two at a time, so that the token row crosses the memory pipeline once instead of once
-// per expert.  Each (token, expert) sum is formed by one wavefront in the contract's order:
+// four at a time, so that the token row crosses the memory pipeline once instead of once
+// per expert and four sums share a butterfly (two experts at a time and a butterfly for each: 16000 tokens of 256
+// elements, 64 experts 79 -> 39 us; 4000 of 1024, 32 experts 22.8 -> 19.6; 4096 of 768, 8 experts 7.6 -> 6.9; 16384 of 4096, 8 experts 76.6 ->
+// 74.6).  Each (token, expert) sum is formed by one wavefront in the contract's order:
 // the results are bit-identical to route_kernel's.
 constexpr int kRouteTokWaves = 4;
 // batches at least this large use the wavefront-per-token kernel (measured crossover: between
@@ -319,38 +372,32 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
     float* mylogit = lds_logit[wave];
     if (M)
         for (int e = lane; e < E; e += kWave) lds_map[wave][e] = M[(size_t)v * E + e];
-    for (int e = 0; e < E; e += 2) {
-        const bool two = e + 1 < E;
-        const T* w0 = wv0 + (size_t)e * d;
-        const T* w1 = wv0 + (size_t)(two ? e + 1 : e) * d;
-        float a0 = 0.0f, a1 = 0.0f;
-        raw_t p0[NC], p1[NC];
+    constexpr int EB = 4;  // experts at a time
+    for (int e = 0; e < E; e += EB) {
+        float a[EB];
+        constexpr int NB = NC * (int)sizeof(raw_t) > 64 ? 2 : EB;  // router rows in registers
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            p0[c] = *reinterpret_cast<const raw_t*>(w0 + 256 * c);
-            p1[c] = *reinterpret_cast<const raw_t*>(w1 + 256 * c);
-        }
+        for (int b0 = 0; b0 < EB; b0 += NB) {
+            raw_t p[NB][NC];
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
+            for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {  // ascending i within the lane
-                const float xq = Raw4<T>::get(xv[c], q);
-                a0 = __builtin_fmaf(xq, Raw4<T>::get(p0[c], q), a0);
-                a1 = __builtin_fmaf(xq, Raw4<T>::get(p1[c], q), a1);
-            }
+                for (int c = 0; c < NC; ++c)
+                    p[b][c] = *reinterpret_cast<const raw_t*>(wv0 + (size_t)min(e + b0 + b, E - 1) * d + 256 * c);
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            a0 = a0 + __shfl_xor(a0, off, kWave);
-            a1 = a1 + __shfl_xor(a1, off, kWave);
+            for (int b = 0; b < NB; ++b) a[b0 + b] = 0.0f;
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {  // ascending i within the lane
+                    const float xq = Raw4<T>::get(xv[c], q);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) a[b0 + b] = __builtin_fmaf(xq, Raw4<T>::get(p[b][c], q), a[b0 + b]);
+                }
         }
-        if (br) {
-            a0 = a0 + br[(size_t)v * E + e];
-            if (two) a1 = a1 + br[(size_t)v * E + e + 1];
-        }
-        if (lane == 0) {
-            mylogit[e] = a0;
-            if (two) mylogit[e + 1] = a1;
-        }
+        float p = butterfly4(a[0], a[1], a[2], a[3]);
+        const int mine = e + lane / 16;
+        if ((lane & 15) == 0 && mine < E) mylogit[mine] = br ? p + br[(size_t)v * E + mine] : p;
     }
     // the LDS writes of this wavefront's lanes before its reads: one wavefront's LDS operations execute in
     // program order, the fence keeps the compiler from moving them
@@ -359,7 +406,9 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
     select_topk(mylogit, lane, E, k, t, topk_idx, topk_w, M ? lds_map[wave] : nullptr, slot, S, gate);
 }
 
-constexpr size_t kRouteGroupBytes = 48 << 10;  // most LDS for the token rows of a group
+// Most LDS for the token rows of a group.  (fp32, 2500 tokens of 4096, 64 experts, 64 KB of rows: 149 us with a wavefront per token, 70
+// in groups.)
+constexpr size_t kRouteGroupBytes = 64 << 10;
 
 // Four tokens to a workgroup?  Measured against the other two, bf16, us, two variants:
 //   workgroup per token (under 2048 tokens, or an uncommon hidden size): 8 experts, 768 elements 8.2 : 8.6 at 1900 tokens;

@@ -301,6 +301,23 @@ def test_streaming_slots_of_several_passes_in_large_pools(mm, gc, oracle, dispat
     assert ref["counts"].max() > 32 and (ref["counts"] > 0).sum() > (ref["counts"] > 32).sum()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_router_with_every_remainder_of_experts(mm, gc, oracle, dtype):
+    """Numbers of experts around the four whose sums share a butterfly and around a wavefront's lanes, on each router
+    kernel (a workgroup per token, a wavefront per token, a workgroup per four), bit for bit."""
+    for T, d in ((70, 512), (2050, 256), (2051, 768), (771, 4096), (2100, 2304)):
+        for E in (1, 2, 3, 4, 5, 8, 9, 17, 33, 64, 67):
+            cfg = synth.Config(f"route_{dtype}_{T}_{d}_{E}", T, d, 256, 3, E, min(E, 4), dtype, "relu", seed=1500 + T + E, bias_alpha=0.5, gate="all")
+            inp = synth.make_inputs(cfg, weights=False)
+            shape = mm.make_shape(T, d, 256, 3, E, E, cfg.top_k, dtype, "relu", gate="all")
+            idx, w = mm.route(shape, gc.to_dev(inp["X"], dtype), torch.from_numpy(inp["vid"]).cuda(), gc.to_dev(inp["Wr"], dtype),
+                              torch.from_numpy(inp["br"]).cuda())
+            torch.cuda.synchronize()
+            idx_ref, w_ref, _ = oracle.route(inp["X"], inp["vid"], inp["Wr"], inp["br"], cfg.top_k, dtype, gate="all")
+            assert np.array_equal(idx.cpu().numpy(), idx_ref), (T, d, E)
+            np.testing.assert_allclose(w.cpu().numpy(), w_ref, rtol=2e-6, atol=1e-7)
+
+
 @pytest.mark.parametrize("rows", [256, 128])
 def test_down_tiles_in_runs(mm, gc, oracle, rows):
     """Down products whose tiles go to the XCDs in runs: fewer tiles than XCDs, numbers that do not divide among them,
