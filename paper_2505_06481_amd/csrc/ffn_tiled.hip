@@ -474,6 +474,16 @@ __global__ __launch_bounds__(256, 1) void tiled_lone_kernel(
     tiled_body<MODE, kBMBig, 2, true>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
 }
 
+// 256-row tiles of 128 features (few_wide_tiles).
+template <int MODE, bool LONE>
+__global__ __launch_bounds__(256, 1) void tiled_narrow_kernel(
+    const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv, const int32_t* __restrict__ tab, int hdr,
+    int list_at, int list_stride, const uint16_t* __restrict__ W0, const uint16_t* __restrict__ W1, void* __restrict__ out,
+    int K, int N, const int32_t* __restrict__ sink_perm, const float* __restrict__ sink_w)
+{
+    tiled_body<MODE, kBMBig, 1, LONE>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
+}
+
 // And 128-row tiles.
 template <int MODE, int NB>
 __global__ __launch_bounds__(256, 2) void tiled_lone_small_kernel(
@@ -484,13 +494,35 @@ __global__ __launch_bounds__(256, 2) void tiled_lone_small_kernel(
     tiled_body<MODE, kBMSmall, NB, true>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
 }
 
+constexpr int kCus = 256;  // compute units
+
+// Does an ungated product with N output features take 128 of them to a 256-row tile, not 256?  Twice the tiles, each with half of
+// the weights, pay where the wide ones leave compute units without work: fewer of them than half the units, or, where weights are
+// most of the traffic (few rows per slot), a second round that is nearly empty.  Tiles counted as if every slot held rows and its last tile were
+// half full.  Wide : narrow down products, layer, us, three pools in turn, rows spread evenly / unequally (router bias 1), tiles by that count: 60
+// 4096 x 8192, 4 slots 248 : 211 / 309 : 271; 72 2048 x 2048, 9 slots 96 : 87 / 96 : 89; 80 2048 x 8192, 10 slots 238 : 205 / 239 : 212; 96 4096 x 512 73.7 :
+// 69.9 / 72.0 : 67.9; 112 4096 x 14336, 7 slots 576 : 512 / 592 : 532; 120 2560 x 7680, 12 slots 257 : 220 / 257 : 245; from there on slots
+// that hold more than their share bring a second round: 128 4096 x 14336, 8 slots, 150 rows per slot 660 : 593 / 665 : 706; 144 to 256 4096 x
+// 14336, 9 slots 676 : 679 / 712 : 709, 2048 x 4096, 24 slots 217 : 229 / 222 : 238, 1.2 rounds of 250 rows 2560 x 7680 317 : 357 / 340 : 364.  A little over one round,
+// under 100 rows per slot: 280 2560 x 4096, 28 slots 290 : 282 / 304 : 301; 288 4096 x 14336, 18 slots 1229 : 1209 / 1257 : 1245; 304 4096 x 1024 150 : 145 /
+// 155 : 151; 320 4096 x 8192 782 : 775 / 838 : 829; with more rows 288 4096 x 4096, 18 slots, 133 rows 441 : 448.  (Past two rounds the narrow
+// tiles' second reading of the tokens costs more: 2200 tokens of 4096 x 14336 1818 : 1957.)
+bool few_wide_tiles(const mmoe_shape& s, int N)
+{
+    if (s.dtype == MMOE_F32 || planned_tile_rows(s) != kBMBig) return false;
+    const int64_t P = (int64_t)s.T * s.top_k, rows2 = s.S + P / 128;  // twice the row tiles
+    const int64_t narrow = (rows2 > 2 * s.S ? rows2 : 2 * s.S) * (N / kBN);
+    return narrow < kCus || (narrow > 2 * kCus && narrow <= 2 * kCus + 160 && P <= (int64_t)100 * s.S);
+}
+
 // Weight blocks per wavefront of a product with N output features: 2, or 1 (tiles of 128 weight
 // rows, twice as many of them) when 128-row token tiles are in use and the product would otherwise
-// have fewer tiles than the chip holds workgroups at a time.  Shape only.
-constexpr int kNb1Room = 512;  // two workgroups of 128-row tiles on each of 256 compute units
+// have fewer tiles than the chip holds workgroups at a time, and for 256-row tiles where few_wide_tiles says so.  Shape only.
+constexpr int kNb1Room = 2 * kCus;  // two workgroups of 128-row tiles on each of 256 compute units
 static int planned_nb(const mmoe_shape& s, int bm, int N, bool gated)
 {
-    if (gated || bm != kBMSmall) return 2;
+    if (gated) return 2;
+    if (bm != kBMSmall) return few_wide_tiles(s, N) ? 1 : 2;
     const int64_t P = (int64_t)s.T * s.top_k;
     return ((P + bm - 1) / bm) * (N / kBN) < kNb1Room ? 1 : 2;
 }
@@ -634,23 +666,23 @@ static void launch_product(const TiledPlan& p, int prod, const void* A, const in
 {
     const dim3 grid(p.L.len[prod] * kXcds), block(256);
     const int stride = p.L.lists[prod] == 1 ? 0 : p.L.len[prod];
-    auto kernel = tiled_kernel<MODE, BM, NB>;
-    if (p.lone) {
-        if constexpr (BM == kBMBig) kernel = tiled_lone_kernel<MODE>;
-        else kernel = tiled_lone_small_kernel<MODE, NB>;
-    }
+    void (*kernel)(const uint16_t*, const int32_t*, int, const int32_t*, int, int, int, const uint16_t*, const uint16_t*, void*, int, int,
+                   const int32_t*, const float*);
+    if constexpr (BM == kBMBig && NB == 1) kernel = p.lone ? tiled_narrow_kernel<MODE, true> : tiled_narrow_kernel<MODE, false>;
+    else if constexpr (BM == kBMBig) kernel = p.lone ? tiled_lone_kernel<MODE> : tiled_kernel<MODE, BM, NB>;
+    else kernel = p.lone ? tiled_lone_small_kernel<MODE, NB> : tiled_kernel<MODE, BM, NB>;
     hipLaunchKernelGGL(kernel, grid, block, 0, st, (const uint16_t*)A, perm, kdiv, tab, kXcds * prod,
                        p.L.list[prod], stride, (const uint16_t*)W0, (const uint16_t*)W1, out, K, N, sink.perm, sink.w);
 }
 
-// one weight block per wavefront exists for 128-row tiles only (planned_nb)
 template <int MODE>
 static void launch_plain_product(const TiledPlan& p, int prod, const void* A, const int32_t* perm, int kdiv,
                                  const int32_t* tab, const void* W0, void* out, int K, int N, hipStream_t st,
                                  GateSink sink = GateSink())
 {
     const int nb = prod == 0 ? p.nb_up : p.nb_down;
-    if (p.bm == kBMBig) launch_product<MODE, kBMBig, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
+    if (p.bm == kBMBig && nb == 1) launch_product<MODE, kBMBig, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
+    else if (p.bm == kBMBig) launch_product<MODE, kBMBig, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else if (nb == 2) launch_product<MODE, kBMSmall, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else launch_product<MODE, kBMSmall, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
 }

@@ -329,6 +329,19 @@ def test_down_tiles_in_runs(mm, gc, oracle, rows):
         assert mm.expert_plan(case.shape) == (False, rows)
 
 
+@pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,lone", [
+    (700, 3, 6, 1, 512, 768, "relu", 0.4, False), (1300, 1, 3, 1, 1024, 256, "gelu", 1.0, False), (900, 2, 5, 2, 256, 512, "gelu", 0.3, False),
+    (1500, 1, 16, 1, 256, 2048, "relu", 1.0, False), (1100, 1, 16, 2, 2048, 256, "gelu", 1.0, False),
+    (1700, 1, 16, 1, 1792, 2560, "relu", 0.5, True), (900, 1, 16, 2, 1792, 2560, "swiglu", 0.5, True)])
+def test_256_row_tiles_of_128_features(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f, act, alpha, lone):
+    """Products of few tiles beside ones of many (the larger sizes), tiles of every height, each activation and both outputs."""
+    cfg = synth.Config(f"narrow_{T}_{d}", T, d, f, V, E, k, "bf16", act, seed=1600 + T, bias_alpha=alpha)
+    case, ref = staged_vs_oracle(mm, gc, oracle, cfg, tile_rows=256)
+    assert mm.expert_plan(case.shape) == (False, 256) and dispatch_rule("lone_tiles", case.shape) == lone
+    assert dispatch_rule("few_wide_tiles", case.shape, d) == (d < 2048) and dispatch_rule("few_wide_tiles", case.shape, f) == (f < 2048)
+    assert len({-(-int(c) // 32) for c in ref["counts"]}) >= min(3, E - 2)
+
+
 @pytest.mark.parametrize("act,k,E,d,f", [("gelu", 1, 16, 1024, 1536), ("swiglu", 2, 12, 1280, 1024)])
 def test_tiles_of_128_rows_in_large_pools(mm, gc, oracle, dispatch_rule, act, k, E, d, f):
     """Slots of one tile, whose weights are read past the caches, of every height, beside slots of several tiles."""

@@ -217,6 +217,18 @@ def test_waits_of_the_128_row_kernel_for_slots_of_one_tile():
         assert sorted(k for _, k, _ in res) == want, fn.name
 
 
+def test_waits_of_the_256_row_kernel_of_128_features():
+    """The four products without a gate, each as for batches of many rows and (weights past the caches too) for slots of one tile."""
+    fns = functions(device_assembly(), "_ZN4mmoe19tiled_narrow_kernel")
+    assert len(fns) == 8, [f.name for f in fns]
+    for fn in fns:
+        mode, lone = re.search(r"kernelILi(\d)ELb([01])E", fn.name).groups()
+        res = check_function(fn)
+        times = 1 + int(lone)
+        want = sorted(k for _, k, waits in variants(f"_ZN4mmoe12tiled_kernelILi{mode}ELi256ELi1EE") for _ in range(times * waits))
+        assert sorted(k for _, k, _ in res) == want, fn.name
+
+
 def test_loads_moved_across_a_wait_are_flagged():
     """A mistake planted in the assembly text: the waits with one number of copies in flight (tiles of 3, 5, 6 and 7
     sub-tiles have their own) leave three more instructions outstanding than the kernel asks for, as if three loads had
