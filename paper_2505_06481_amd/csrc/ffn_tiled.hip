@@ -518,13 +518,20 @@ bool few_wide_tiles(const mmoe_shape& s, int N)
 // Weight blocks per wavefront of a product with N output features: 2, or 1 (tiles of 128 weight
 // rows, twice as many of them) when 128-row token tiles are in use and the product would otherwise
 // have fewer tiles than the chip holds workgroups at a time, and for 256-row tiles where few_wide_tiles says so.  Shape only.
-constexpr int kNb1Room = 2 * kCus;  // two workgroups of 128-row tiles on each of 256 compute units
+// Where slots have rows for more than a tile, half of the places filled are enough for wide tiles: one round of them reads the tokens once
+// where a round and a half of narrow ones reads them twice.  Narrow : wide up products, layer, us, three pools in turn: 768 x 3072, 4096 tokens, 9 slots 83.7 :
+// 80.3, 18 slots (228 rows per slot) 101.5 : 99.0, 24 slots (171) 110.0 : 107.8, but 30 slots (137) 115 : 118; 5000 tokens 112.5 : 109.0; 1024 x
+// 4096, 2500 tokens 108.8 : 105.3; 512 x 2048, 333 rows 97.4 : 94.6; 256 x 2048 50.7 : 48.5; 1280 x 5120, 100 rows 187.4 : 189.7; 1024 x 4096, 64
+// slots, 23 rows 222 : 232.  Down products, or both: 1536 x 1536, 7000 tokens 128.5 : 116.6; 1024 x 1024, 12000 tokens 107.8 : 98.0; 768 x 3072, 14000
+// tokens 204.9 : 198.6.  Unequal slots (router bias 1) of 768 x 3072, 4096 tokens, 18 slots 105.9 : 102.0, but 13 slots 97.9 : 102.5.
+constexpr int kNb1Room = 2 * kCus;  // two workgroups of 128-row tiles on each compute unit
+constexpr int kNb1RoomTall = 300, kTallRows = 160;
 static int planned_nb(const mmoe_shape& s, int bm, int N, bool gated)
 {
     if (gated) return 2;
     if (bm != kBMSmall) return few_wide_tiles(s, N) ? 1 : 2;
     const int64_t P = (int64_t)s.T * s.top_k;
-    return ((P + bm - 1) / bm) * (N / kBN) < kNb1Room ? 1 : 2;
+    return ((P + bm - 1) / bm) * (N / kBN) < (P >= (int64_t)kTallRows * s.S ? kNb1RoomTall : kNb1Room) ? 1 : 2;
 }
 
 // fp32: does a product with N outputs (of each matrix) run on bf16 parts (ffn_split_f32.hip)?  Its tiles have twice the
