@@ -274,7 +274,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
 bool lone_tiles(const mmoe_shape& s);
 struct TiledPlan {
     int bm, nt_up, nt_down, nb_up, nb_down;
-    bool lone;  // 256-row tiles: the kernel that reads the panels of one-tile slots past the caches
+    bool lone;  // the kernels that read the panels of one-tile slots past the caches (lone_tiles)
     TileLists L;
 };
 
