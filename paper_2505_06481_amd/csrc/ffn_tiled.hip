@@ -605,22 +605,33 @@ bool lone_tiles(const mmoe_shape& s)
     return (int64_t)s.T * s.top_k <= (int64_t)kBMBig * s.S && s.S * slot_bytes(s) > kLastLevelCache;
 }
 
-// Do the XCDs take runs of neighbouring tiles of the down product (tile_table.h)?  What reaches an XCD's L2 from beyond it
-// bounds these products (5.7 TB/s; 768 x 3072, 18 slots, 4096 tokens: 251 MB, of which 151 token rows, each read by six
-// XCDs).  Panel by panel a slot's rows are read by min(8, NT) XCDs, a weight panel by one; in runs a slot's rows by one
-// or two, but the panels at the ends by two and the XCDs' shares of the weights differ.  So runs pay where token rows
-// are a good part of the traffic, min(8, NT) P against S N rows.  Panels : runs, layer, us, three pools in turn: ratio
-// 1.8 768 x 3072, 18 slots, 4096 tokens 106.2 : 100.7; 3.9 16 slots, 8000 tokens 148 : 131; 1.3 512 x 2048, 24 slots 96.1 : 82.8; 0.8 2560 x 7680,
-// 12 slots 442 : 360; 0.5 1024 x 1024, 64 slots 130.4 : 128.5; 0.4 768 x 3072, 40 slots 116.7 : 114.1; 0.26 18 slots 60.8 : 59.8; but 0.18
-// 2048 x 1280, 90 slots 324 : 329; 0.17 4096 x 14336, 777 tokens 1235 : 1289; 0.11 500 tokens 1157 : 1257.  256-row tiles of many
-// rows per slot are bound by the matrix cores, and runs of tiles drift apart: 417 rows per slot 2048 x 8192 440 : 428, 500 rows 4096 x 4096
-// 578 : 576, 615 rows 4096 x 14336 2487 : 2493, 833 rows 936 : 944, 1260 rows 4624 : 4690.  (The up product reads a few short rows of tokens for
-// each of its panels: 768 x 3072 equal, 1024 x 4096 210 : 219, 4096 x 14336 4690 : 4744.)
-static bool xcd_runs(const mmoe_shape& s, int bm, int nt_down)
+// Do the XCDs take runs of neighbouring tiles of product `prod` (0 up, 1 down; RunsRule, tile_table.h)?
+// Down products.  What reaches an XCD's L2 from beyond it bounds them (5.7 TB/s; 768 x 3072, 18 slots, 4096 tokens: 251 MB,
+// of which 151 token rows, each read by six XCDs).  Panel by panel a slot's rows are read by min(8, NT) XCDs, a weight
+// panel by one; in runs the rows by one or two, but the panels at the ends by two.  So runs pay where token rows are a good
+// part of the traffic, min(8, NT) P against S N rows.
+// 128-row tiles: from a quarter on, NT a multiple of 8 from half on.  Panels : runs, layer, us, three pools in turn, slots
+// equally used / router bias 1 / 2.5: 768 x 3072, 13 slots of 300 rows 127 : 116 / 127 : 120 / 118 : 114; 24 of 80 106 : 105 /
+// 115 : 105 / 84 : 82; 1280 x 5120, 13 of 300 246 : 243 / 271 : 247 / 275 : 240; 1536 x 6144 323 : 325 / 342 : 319 / 335 : 312; 512 x
+// 2048 68 : 68 / 78 : 74 / 66 : 64; 1024 x 4096 172 : 170 / 179 : 178 / 171 : 166.  Below the lines: 2048 x 1280, 90 slots of 46
+// rows 324 : 329; 2048 x 3072 (NT 8 or 16), 13 of 80 138 : 141 / 137 : 139 / 128 : 131, 24 of 80 223 : 223 / 224 : 227 / 201 : 206.
+// 256-row tiles of up to 512 rows per slot: only for fewer rounds.  Always in runs they lose where panels need no more
+// rounds: panels : runs, 4096 x 14336, 18 slots (NT 16: panels are shared out evenly) of 130 rows 1311 : 1410 / 1318 : 1407 / 1440 :
+// 1486, of 250 1856 : 1870 / 1816 : 1869 / 1850 : 1918, of 450 2729 : 2815 / - / 2802 : 2845; 3584 x 7680, 12 of 420 842 : 879 /
+// 886 : 897; 3072 x 7680 747 : 777 / 769 : 793.  Panels : for fewer rounds, equally used / bias 1: 2304 x 7680, 12 of 420 644 : 563 /
+// 659 : 571, of 240 412 : 411 / 468 : 424; 2304 x 2304, 28 of 220 325 : 325 / 386 : 359; 2560 x 5120, 28 of 220 718 : 685 / 745 : 709; 3072
+// x 3072, 16 of 350 384 : 381 / 401 : 388.  Over 512 rows the matrix cores bound them (4096 x 14336, 1260 rows 4624 : 4690 always in runs).
+// Up products read a few short rows of tokens for each of their panels: never (1024 x 4096 210 : 219).
+int xcd_runs(const mmoe_shape& s, int prod)
 {
-    const int64_t P = (int64_t)s.T * s.top_k, readers = nt_down < kXcds ? nt_down : kXcds;
-    if (s.dtype == MMOE_F32 || (bm == kBMBig && P > (int64_t)512 * s.S)) return false;
-    return 4 * readers * P >= (int64_t)s.S * s.d_model;
+    if (s.dtype == MMOE_F32 || prod == 0) return kRunsNever;
+    const int bm = planned_tile_rows(s);
+    int nt_up, nt, nb_up, nb_down;
+    tiled_nts(s, bm, nt_up, nt, nb_up, nb_down);
+    const bool even = nt % kXcds == 0;  // panels divide among the XCDs
+    const int64_t P = (int64_t)s.T * s.top_k, rows = P * (nt < kXcds ? nt : kXcds), weights = (int64_t)s.S * s.d_model;
+    if (bm == kBMBig) return !even && P <= (int64_t)512 * s.S && 4 * rows >= weights ? kRunsForFewerRounds : kRunsNever;
+    return (even ? 2 : 4) * rows >= weights ? kRunsAlways : kRunsNever;
 }
 
 static TiledPlan tiled_plan(const mmoe_shape& s)
@@ -630,7 +641,7 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
     p.lone = lone_tiles(s);
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm), planned_upt(s, p.bm), p.bm,
-                     s.dtype == MMOE_F32, xcd_runs(s, p.bm, p.nt_down));
+                     s.dtype == MMOE_F32, xcd_runs(s, 0), xcd_runs(s, 1));
     return p;
 }
 
@@ -660,7 +671,8 @@ size_t tiled_table_most(const mmoe_shape& s)
         for (int nb_up : {1, 2})
             for (int nb_down : {1, 2}) {
                 const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb_up);
-                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (wide * nb_down), bm / 32, bm / 32, bm, f32, !f32);
+                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (wide * nb_down), bm / 32, bm / 32, bm, f32, kRunsNever,
+                                               f32 ? kRunsNever : kRunsAlways);
                 most = L.bytes > most ? L.bytes : most;
             }
     return align256(most);

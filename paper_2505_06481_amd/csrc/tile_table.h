@@ -38,8 +38,15 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // feature tiles to the XCDs as 2,2,1,1,1,1,1,1 (1.6 times an even share) and 6 as 1,1,1,1,1,1,0,0.
 // (64 experts of 2048 x 1280, 1037 tokens, 10 up panels a slot: up product 226 -> 179 us; 768 x 3072,
 // 4096 tokens, 6 down panels: 53 -> 47 us.)
-// With `runs` the list of all tiles is cut into eight contiguous runs of as many tiles each instead, so that a slot's
-// token rows are read by one or two XCDs and not by min(8, NT) of them (xcd_runs says where that pays).
+// In runs (RunsRule) the list of all tiles is cut into eight contiguous runs of as many tiles each instead: a slot's
+// token rows are read by one or two XCDs and not by min(8, NT) of them, and no XCD has more tiles than another
+// (xcd_runs says where that pays).  kRunsForFewerRounds: where panels in turn bring some XCD into a further round of
+// `conc` tiles and runs do not.  The target height is chosen so that the tiles just fill a round; the panels of unequal
+// slots, NT no multiple of 8, then put more than a round on some XCD.
+// Neighbouring tiles are of one height, so runs of tiles that differ in cost keep the XCDs busy for unequal times: the
+// up product of 4096 x 14336, 777 tokens, 1310 us by panels, 1629 in runs.  Runs of equal cost (half a sub-tile and the
+// height for each tile) are worse than runs of equal count: an XCD with more tiles than compute units begins another
+// round (layer, us, 2560 x 7680, 3200 pairs, 12 slots 496 : 561; 768 x 3072, 8000 tokens, 16 unequal slots 136 : 152).
 //
 // Target heights of a row tile that the table builder may choose from, in quarters of a 32-row
 // sub-tile: from a full tile (4 upt) down to hq_lo.  bf16: five eighths of a full tile (shorter tiles are
@@ -51,11 +58,13 @@ constexpr int kMaxHeightCands = 16;
 constexpr int kSlotMask = 0xFFFF, kOnlyTile = 1 << 16;
 static_assert(kMaxS <= kSlotMask, "slot ids");
 
+enum RunsRule { kRunsNever = 0, kRunsAlways = 1, kRunsForFewerRounds = 2 };
+
 struct TileLists {
     int list[2];    // [product: up, down] -> int4 index into tab of XCD 0's list
     int lists[2];   // 1: the XCDs share one list; kXcds: one list each, `len` entries apart
     int len[2];     // entries reserved per list of each product: workgroups per XCD
-    int runs[2];    // 1: the XCDs take runs of neighbouring tiles, not panels in turn
+    int runs[2];    // RunsRule
     int upt[2];     // most 32-row sub-tiles of a row tile, per product
     int hq_lo[2];   // least target height, in quarters of a sub-tile
     int conc;       // workgroups that an XCD works on at a time, for the choice of the height
@@ -63,7 +72,8 @@ struct TileLists {
     size_t bytes;
 };
 
-inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down, int bm, bool f32, bool runs_down)
+inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down, int bm, bool f32,
+                            int runs_up, int runs_down)
 {
     TileLists L;
     L.upt[0] = upt_up;
@@ -84,8 +94,8 @@ inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, in
     int at = 16;  // int4 units; the header takes the first 256 bytes
     for (int p = 0; p < 2; ++p) {
         const int NT = p == 0 ? nt_up : nt_down;
-        L.runs[p] = p == 1 && runs_down;
-        L.lists[p] = NT % kXcds == 0 && !L.runs[p] ? 1 : kXcds;
+        L.runs[p] = p == 0 ? runs_up : runs_down;
+        L.lists[p] = NT % kXcds == 0 && L.runs[p] == kRunsNever ? 1 : kXcds;
         L.len[p] = L.rows_cap[p] * ((NT + kXcds - 1) / kXcds);  // a slot's panels on one XCD: ceil(NT / 8) at most
         L.list[p] = at;
         at += L.lists[p] * L.len[p];
@@ -204,14 +214,13 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     }
     if (tid == 0) base[S] = total_m;
     __syncthreads();
-    const bool shared_list = L.lists[p] == 1, runs = L.runs[p];
+    const bool shared_list = L.lists[p] == 1;
+    bool runs = L.runs[p] == kRunsAlways;
     const int share = (total_m * NT + kXcds - 1) / kXcds;  // tiles of an XCD's run
     // Panels of slot s (the r-th that holds rows) on XCD x: the c = r NT + nt with c mod 8 == x.
     // panels_before(x, c) of them lie before panel c.
     auto panels_before = [](int x, int c) { return (c + kXcds - 1 - x) / kXcds; };
-    if (runs) {
-        if (tid < kXcds) tab[kXcds * p + tid] = min(share, max(total_m * NT - tid * share, 0));
-    } else if (!shared_list) {
+    if (!runs && !shared_list) {
         // first entry of every slot in every XCD's list: an XCD to a wavefront, 64 slots at a time
         if (wave < kXcds) {
             const int x = wave;
@@ -227,15 +236,18 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
                 if (s < S) first[x * kMaxS + s] = carry + inc - c;
                 carry += __shfl(inc, kWave - 1, kWave);
             }
-            if (lane == 0) {
-                tab[kXcds * p + x] = carry;
-                total[x] = carry;
-            }
+            if (lane == 0) total[x] = carry;
         }
         __syncthreads();
-    } else if (tid < kXcds) {
-        tab[kXcds * p + tid] = total_m * (NT / kXcds);
+        if (L.runs[p] == kRunsForFewerRounds) {
+            int most = 0;
+#pragma unroll
+            for (int x = 0; x < kXcds; ++x) most = max(most, total[x]);
+            runs = div24(most + conc - 1, conc) > div24(share + conc - 1, conc);
+        }
     }
+    if (tid < kXcds)
+        tab[kXcds * p + tid] = shared_list ? total_m * (NT / kXcds) : runs ? min(share, max(total_m * NT - tid * share, 0)) : total[tid];
     // the lists: all threads on the shared one (with runs: on the tiles of all XCDs in order), an eighth of them on each
     // XCD's own
     constexpr int kPerXcd = kListThreads / kXcds;
@@ -264,7 +276,8 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
         const int row0 = 32 * (i * h + min(i, extra));
         const int rows = 32 * (h + (i < extra ? 1 : 0));
         const int to = runs ? div24(e, share) : x;
-        lists[L.list[p] + to * L.len[p] + e - (runs ? to * share : 0)] = make_int4(mt == 1 ? s | kOnlyTile : s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
+        lists[L.list[p] + to * L.len[p] + e - (runs ? to * share : 0)] =
+            make_int4(mt == 1 ? s | kOnlyTile : s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
     }
 }
 

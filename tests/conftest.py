@@ -23,12 +23,12 @@ def oracle():
 
 @pytest.fixture(scope="session")
 def dispatch_rule():
-    """bool mmoe::name(const mmoe_shape&[, int, bool]): a rule of the library's dispatch, by its C++ symbol."""
+    """mmoe::name(const mmoe_shape&[, int, bool]), bool or as restype says: a rule of the library's dispatch, by its C++ symbol."""
     from paper_2505_06481_amd import mmoe
 
-    def rule(name, shape, *args):
+    def rule(name, shape, *args, restype=ctypes.c_bool):
         f = getattr(mmoe.lib(), f"_ZN4mmoe{len(name)}{name}ERK10mmoe_shape" + "ib"[:len(args)])
-        f.restype = ctypes.c_bool
+        f.restype = restype
         f.argtypes = [ctypes.c_void_p] + [ctypes.c_int, ctypes.c_bool][:len(args)]
         return f(ctypes.addressof(shape), *args)
 

@@ -8,6 +8,8 @@ permutation, gathered rows) must match bit for bit; floating-point outputs withi
 Small cases compare every element; the full benchmark shapes compare every integer output,
 every row of the smallest and the largest slot, and 512 seeded tokens.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -327,6 +329,52 @@ def test_down_tiles_in_runs(mm, gc, oracle, rows):
         cfg = synth.Config(f"runs_{T}_{d}", T, d, f, V, E, k, "bf16", "relu" if k == 1 else "swiglu", seed=1400 + T, bias_alpha=alpha)
         case, _ = staged_vs_oracle(mm, gc, oracle, cfg, tile_rows=rows)
         assert mm.expert_plan(case.shape) == (False, rows)
+
+
+def expert_lists(mm, gc, oracle, d, f, act, counts, tile_rows=0):
+    """The expert stage on slots of `counts` rows, against the oracle; its shape and the tile lists it has left in the
+    workspace behind H (int32)."""
+    rng = np.random.default_rng(sum(counts) + d)
+    S, P = len(counts), sum(counts)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    draw = lambda sigma, *shape: synth.f32_to_bf16_bits(sigma * rng.standard_normal(shape, dtype=np.float32))
+    Xg, W1, W2 = draw(1.0, P, d), draw(0.02, S, d, f), draw(0.02, S, f, d)
+    W3 = draw(0.02, S, d, f) if act == "swiglu" else None
+    shape = mm.make_shape(P, d, f, 1, S, S, 1, "bf16", act, tile_rows=tile_rows)
+    dev = lambda a: gc.to_dev(a, "bf16")
+    ws = mm.alloc_workspace(shape)
+    Yg = mm.expert_ffn(shape, dev(Xg), torch.from_numpy(offsets).cuda(), *mm.pack_weights(shape, dev(W1), dev(W3), dev(W2)), ws)
+    torch.cuda.synchronize()
+    gc.assert_close(gc.to_np64(Yg), oracle.expert_ffn(Xg, offsets, W1, W3, W2, "bf16", act), "bf16", "Yg")
+    at = -(-P * f * 2 // 256) * 256
+    return shape, ws[at:at + (ws.numel() - at) // 4 * 4].view(torch.int32).cpu().numpy()
+
+
+def rounds(tiles, conc):
+    """Rounds that an XCD takes for its tiles, so many at a time (32 of 256 rows, 64 of 128)."""
+    return -(-int(tiles) // conc)
+
+
+def in_runs(per_xcd):
+    share = -(-int(per_xcd.sum()) // 8)
+    return list(per_xcd) == [min(share, max(int(per_xcd.sum()) - x * share, 0)) for x in range(8)]
+
+
+@pytest.mark.parametrize("d,counts,runs", [
+    # nine panels a slot, unequal slots: panels in turn would give one XCD 34 tiles, 33 and 35 of 243
+    (2304, [76, 110, 90, 496, 70, 331, 62, 82, 993, 99, 198, 124, 141, 66, 165, 248], True),
+    (2304, [587, 223, 168, 115, 126, 182, 139, 111, 303, 200, 147, 255, 387, 132, 120, 157], True),
+    (2304, [165, 124, 198, 248, 99, 76, 141, 331, 496, 90, 993, 66, 82, 70, 110, 62], True),
+    # ten panels: 33 of 250
+    (2560, [159, 150, 241, 216, 328, 182, 169, 276, 197, 418, 634, 142], True),
+    # panels in turn take one round as well: nobody else reads a panel; empty slots at both ends
+    (2304, [211, 157, 362, 202, 260, 161, 223, 164, 194, 239, 294, 187, 168, 172, 176, 181], False),
+    (2560, [0, 0, 335, 1005, 111, 125, 502, 143, 251, 100, 167, 83, 91, 201, 0], False)])
+def test_256_row_down_tiles_in_the_fewest_rounds(mm, gc, oracle, dispatch_rule, d, counts, runs):
+    shape, tab = expert_lists(mm, gc, oracle, d, 256, "relu", counts)
+    assert mm.expert_plan(shape) == (False, 256) and dispatch_rule("xcd_runs", shape, 1, restype=ctypes.c_int) == 2
+    down = tab[8:16]
+    assert in_runs(down) == runs and rounds(down.max(), 32) == rounds(-(-down.sum() // 8), 32) == 1
 
 
 @pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,lone", [
