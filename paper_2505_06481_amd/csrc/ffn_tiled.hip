@@ -515,23 +515,35 @@ bool few_wide_tiles(const mmoe_shape& s, int N)
     return narrow < kCus || (narrow > 2 * kCus && narrow <= 2 * kCus + 160 && P <= (int64_t)100 * s.S);
 }
 
-// Weight blocks per wavefront of a product with N output features: 2, or 1 (tiles of 128 weight
-// rows, twice as many of them) when 128-row token tiles are in use and the product would otherwise
-// have fewer tiles than the chip holds workgroups at a time, and for 256-row tiles where few_wide_tiles says so.  Shape only.
-// Where slots have rows for more than a tile, half of the places filled are enough for wide tiles: one round of them reads the tokens once
-// where a round and a half of narrow ones reads them twice.  Narrow : wide up products, layer, us, three pools in turn: 768 x 3072, 4096 tokens, 9 slots 83.7 :
-// 80.3, 18 slots (228 rows per slot) 101.5 : 99.0, 24 slots (171) 110.0 : 107.8, but 30 slots (137) 115 : 118; 5000 tokens 112.5 : 109.0; 1024 x
-// 4096, 2500 tokens 108.8 : 105.3; 512 x 2048, 333 rows 97.4 : 94.6; 256 x 2048 50.7 : 48.5; 1280 x 5120, 100 rows 187.4 : 189.7; 1024 x 4096, 64
-// slots, 23 rows 222 : 232.  Down products, or both: 1536 x 1536, 7000 tokens 128.5 : 116.6; 1024 x 1024, 12000 tokens 107.8 : 98.0; 768 x 3072, 14000
-// tokens 204.9 : 198.6.  Unequal slots (router bias 1) of 768 x 3072, 4096 tokens, 18 slots 105.9 : 102.0, but 13 slots 97.9 : 102.5.
-constexpr int kNb1Room = 2 * kCus;  // two workgroups of 128-row tiles on each compute unit
+// Ungated products of 128-row tiles have one weight block per wavefront (128 features) where tiles of two would be fewer
+// than the chip holds workgroups, kNb1Room, and two from there on.  Counted as full row tiles of all pairs.
+constexpr int kNb1Room = 2 * kCus;
+// Two already from kNb1RoomTall on where slots have at least kTallRows rows on average, for more than a tile each: one round
+// of wide tiles reads the tokens once where a round and a half of narrow ones reads them twice.  With GELU, whose epilogue
+// is long, only if the tiles are one round with another half tile per slot.
+// Narrow : wide, up in runs where that is for fewer rounds, layer, us, three pools in turn, equally used / router bias 0.5 / 1: ReLU 768 x 3072,
+// 4096 tokens, 9 slots 87 : 85 / 89 : 86 / 98 : 98; 13 slots 93 : 92 / 103 : 101 / 99 : 96; 18 slots 102 : 99 / 103 : 101 / 105 : 104; 5000
+// tokens, 18 slots 111 : 110 / 116 : 116 / 115 : 118; 1280 x 3328, 4700 tokens, 13 slots 157 : 150 / 160 : 159 / 161 : 160; 1024 x 1536, 9000
+// tokens, 13 slots 112 : 104 / 116 : 108 / 118 : 110; both products wide, 1536 x 1536, 8000 tokens, 13 slots 136 : 122 / 144 : 124 / 148 :
+// 128.  GELU 768 x 3072, 4096 tokens, 13 slots 102 : 101 / 112 : 111 / 108 : 104; but past the round 5000 tokens, 18 slots 121 : 126 /
+// 124 : 129 / 126 : 131; 1280 x 3328, 4700 tokens, 13 slots 169 : 170 / 172 : 176 / 176 : 178.
+// Neither line is where both sides are level: 210 tiles of 768 x 3072, 267 rows 62 : 66 / - / 63 : 67, 178 rows 68 : 69 / - / 71 : 73; but 250
+// tiles, 180 rows 73 : 71 / - / 76 : 75, 140 rows 80 : 79 / - / 77 : 75, and 384 tiles, 140 rows are equal.
 constexpr int kNb1RoomTall = 300, kTallRows = 160;
-static int planned_nb(const mmoe_shape& s, int bm, int N, bool gated)
+bool wide_below_a_round(const mmoe_shape& s, int N, bool up)
 {
-    if (gated) return 2;
+    const int64_t P = (int64_t)s.T * s.top_k, nt = N / kBN, tiles = (P + kBMSmall - 1) / kBMSmall * nt;
+    if (P < (int64_t)kTallRows * s.S || tiles < kNb1RoomTall || tiles >= kNb1Room) return false;
+    return !up || s.act != MMOE_GELU || (2 * P / kBMSmall + s.S) * nt <= 2 * kNb1Room;
+}
+
+// Weight blocks per wavefront of a product with N output features: 2 (256 weight rows to a tile), or 1 (128).  Shape only.
+static int planned_nb(const mmoe_shape& s, int bm, int N, bool up)
+{
+    if (up && s.act == MMOE_SWIGLU) return 2;  // one block of each matrix
     if (bm != kBMSmall) return few_wide_tiles(s, N) ? 1 : 2;
     const int64_t P = (int64_t)s.T * s.top_k;
-    return ((P + bm - 1) / bm) * (N / kBN) < (P >= (int64_t)kTallRows * s.S ? kNb1RoomTall : kNb1Room) ? 1 : 2;
+    return (P + bm - 1) / bm * (N / kBN) >= kNb1Room || wide_below_a_round(s, N, up) ? 2 : 1;
 }
 
 // fp32: does a product with N outputs (of each matrix) run on bf16 parts (ffn_split_f32.hip)?  Its tiles have twice the
@@ -560,7 +572,7 @@ static void tiled_nts(const mmoe_shape& s, int bm, int& nt_up, int& nt_down, int
         nt_down = s.d_model / (kFeatF32 * nb_down);
         return;
     }
-    nb_up = planned_nb(s, bm, s.d_ff, s.act == MMOE_SWIGLU);
+    nb_up = planned_nb(s, bm, s.d_ff, true);
     nb_down = planned_nb(s, bm, s.d_model, false);
     nt_up = s.act == MMOE_SWIGLU ? s.d_ff / (kBN / 2) : s.d_ff / (128 * nb_up);
     nt_down = s.d_model / (128 * nb_down);
@@ -621,11 +633,19 @@ bool lone_tiles(const mmoe_shape& s)
 // 886 : 897; 3072 x 7680 747 : 777 / 769 : 793.  Panels : for fewer rounds, equally used / bias 1: 2304 x 7680, 12 of 420 644 : 563 /
 // 659 : 571, of 240 412 : 411 / 468 : 424; 2304 x 2304, 28 of 220 325 : 325 / 386 : 359; 2560 x 5120, 28 of 220 718 : 685 / 745 : 709; 3072
 // x 3072, 16 of 350 384 : 381 / 401 : 388.  Over 512 rows the matrix cores bound them (4096 x 14336, 1260 rows 4624 : 4690 always in runs).
-// Up products read a few short rows of tokens for each of their panels: never (1024 x 4096 210 : 219).
+// Up products read a few short rows of tokens for each of their panels (1024 x 4096 in runs 210 : 219).  Only for fewer rounds, and
+// where wide tiles were taken for being one (wide_below_a_round): 12 panels of unequal slots do not divide among the XCDs
+// as 24 narrow ones do.  Panels : runs where for fewer, layer, us, three pools in
+// turn, equally used / bias 0.5 / 1 / 2.5: 768 x 3072, 4096 tokens, 9 slots 84 : 84 / 96 : 88 / 97 : 92 / 82 : 76, 13 slots 86 : 86 / 102 : 97 /
+// 100 : 95 / 81 : 75, 18 slots 99 : 99 / 106 : 101 / 103 : 104 / 91 : 84; 1536 x 1536, 8000 tokens, 13 slots 133 : 122 / 139 : 124 / 142 : 128 / 133 : 118.
 int xcd_runs(const mmoe_shape& s, int prod)
 {
-    if (s.dtype == MMOE_F32 || prod == 0) return kRunsNever;
+    if (s.dtype == MMOE_F32) return kRunsNever;
     const int bm = planned_tile_rows(s);
+    if (prod == 0) {
+        const bool few = bm == kBMSmall && s.act != MMOE_SWIGLU && wide_below_a_round(s, s.d_ff, true);
+        return few && s.d_ff / kBN % kXcds != 0 ? kRunsForFewerRounds : kRunsNever;
+    }
     int nt_up, nt, nb_up, nb_down;
     tiled_nts(s, bm, nt_up, nt, nb_up, nb_down);
     const bool even = nt % kXcds == 0;  // panels divide among the XCDs

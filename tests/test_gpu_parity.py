@@ -377,6 +377,23 @@ def test_256_row_down_tiles_in_the_fewest_rounds(mm, gc, oracle, dispatch_rule, 
     assert in_runs(down) == runs and rounds(down.max(), 32) == rounds(-(-down.sum() // 8), 32) == 1
 
 
+@pytest.mark.parametrize("act,f,counts,runs", [
+    # twelve panels a slot, unequal slots: panels in turn would give four XCDs 71 tiles, 69 of 504
+    ("relu", 3072, [176, 201, 706, 353, 471, 282, 1413, 157, 235], True), ("gelu", 3072, [176, 201, 706, 353, 471, 282, 1413, 157, 235], True),
+    ("relu", 3072, [208, 195, 296, 185, 403, 167, 514, 175, 779, 339, 223, 242, 266], True),
+    # six: 66 and 68 of 456
+    ("relu", 1536, [733, 2201, 550, 220, 183, 200, 1100, 314, 275, 440, 169, 244, 366], True),
+    ("gelu", 1536, [366, 550, 169, 275, 733, 244, 220, 314, 440, 1100, 200, 2201, 183], True),
+    # panels in turn take one round as well; empty slots at both ends
+    ("relu", 3072, [492, 296, 414, 273, 628, 952, 254, 362, 325], False),
+    ("gelu", 1536, [0, 550, 169, 244, 314, 275, 2201, 440, 1100, 183, 200, 733, 366, 220, 0], False)])
+def test_128_row_up_tiles_in_the_fewest_rounds(mm, gc, oracle, dispatch_rule, act, f, counts, runs):
+    shape, tab = expert_lists(mm, gc, oracle, 256, f, act, counts)
+    assert mm.expert_plan(shape) == (False, 128) and dispatch_rule("xcd_runs", shape, 0, restype=ctypes.c_int) == 2
+    up = tab[:8]
+    assert in_runs(up) == runs and rounds(up.max(), 64) == rounds(-(-up.sum() // 8), 64) == 1
+
+
 @pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,lone", [
     (700, 3, 6, 1, 512, 768, "relu", 0.4, False), (1300, 1, 3, 1, 1024, 256, "gelu", 1.0, False), (900, 2, 5, 2, 256, 512, "gelu", 0.3, False),
     (1500, 1, 16, 1, 256, 2048, "relu", 1.0, False), (1100, 1, 16, 2, 2048, 256, "gelu", 1.0, False),

@@ -310,3 +310,21 @@ def test_down_products_take_runs_of_tiles(mm, dispatch_rule):
         shape = mm.make_shape(T, d, f, 4, 8, S, k, "bf16", "swiglu")
         assert dispatch_rule("xcd_runs", shape, 1, restype=ctypes.c_int) == want, (T, d, f, S)
         assert dispatch_rule("xcd_runs", mm.make_shape(T, d, f, 4, 8, S, k, "f32", "swiglu"), 1, restype=ctypes.c_int) == 0
+
+
+def test_up_products_of_less_than_a_round(mm, dispatch_rule):
+    """Wide 128-row tiles below a round of the chip, with GELU only where another half tile per slot leaves them one; and there
+    the XCDs may take runs (2) unless panels divide among them."""
+    for T, d, f, S, act, want, runs in ((4096, 768, 3072, 18, "relu", True, 2), (4096, 768, 3072, 13, "gelu", True, 2),
+                                        (4096, 768, 3072, 24, "gelu", False, 0), (4096, 768, 3072, 24, "relu", True, 2),
+                                        (5000, 768, 3072, 18, "relu", True, 2), (5000, 768, 3072, 18, "gelu", False, 0),
+                                        (5000, 768, 3072, 9, "gelu", False, 0), (4500, 768, 3072, 9, "gelu", True, 2),
+                                        (6000, 512, 2048, 13, "relu", True, 0), (6000, 512, 2048, 13, "gelu", True, 0),
+                                        (4096, 768, 3072, 30, "relu", False, 0), (3000, 768, 3072, 13, "relu", False, 0),
+                                        (5500, 768, 3072, 13, "relu", False, 0), (8000, 1536, 1536, 13, "relu", True, 2)):
+        shape = mm.make_shape(T, d, f, 4, 8, S, 1, "bf16", act)
+        assert mm.expert_plan(shape) == (False, 128)
+        assert dispatch_rule("wide_below_a_round", shape, f, True) is want, (T, d, f, S, act)
+        assert dispatch_rule("xcd_runs", shape, 0, restype=ctypes.c_int) == runs, (T, d, f, S, act)
+    assert dispatch_rule("wide_below_a_round", mm.make_shape(8000, 1536, 3072, 4, 8, 24, 1, "bf16", "gelu"), 1536, False)
+    assert dispatch_rule("xcd_runs", mm.make_shape(4096, 768, 3072, 4, 8, 18, 1, "bf16", "swiglu"), 0, restype=ctypes.c_int) == 0
