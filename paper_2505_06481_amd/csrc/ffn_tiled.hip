@@ -603,19 +603,24 @@ static int planned_upt(const mmoe_shape&, int bm) { return bm / 32; }
 // Are panels read past the caches where a tile is the only one of its slot?  Where slots of one tile are likely, and
 // the pool is larger than the last-level cache: a smaller one may still be there from an earlier call, and the few
 // tiles of a small layer wait longer for each load.  Through the caches : past them, us, one pool again and again / three in
-// turn: 2304 x 768 SwiGLU, 6 slots (64 MB), 180 rows per slot 72.2 : 82.9 / 72.3 : 83.2; 4096 x 512, 5 slots (42 MB) 80.9 :
-// 95.4 / 80.0 : 95.4; 4096 x 1024 SwiGLU, 8 slots (201 MB), 110 rows 88.3 : 109.0 / 111.6 : 109.1; 2560 x 2560, 20 slots (524 MB)
-// 182.7 : 172.3 / 183.2 : 174.1; 4096 x 2048 SwiGLU, 13 slots (654 MB) 178.9 : 161.1 / 180.0 : 166.2.  (At 244 and 306 rows
-// per slot on average both are within 1 %.)
-// 128-row tiles, one pool: 2048 x 1280 SwiGLU, 90 slots, 46 rows 339 : 314 (three in turn 346 : 334), 16 rows 293 : 275; 4096 x 4096 SwiGLU, 24 slots, 33 rows
-// 457 : 425; 4096 x 14336, 39 rows 834 : 783; 1024 x 4096 GELU, 64 slots, 31 rows 244 : 228; 1280 x 2560 SwiGLU, 16 slots, 112 rows 114.9 :
-// 108.9; 1024 x 4096 SwiGLU, 60 slots, 80 rows 371 : 362, 133 rows 448 : 443, 200 rows 541 : 542; 768 x 3072, 40 slots, 110 rows 145 : 141, 200 rows
-// 204 : 205; a few of 200 slots much in use (router bias 2.5), 1024 x 1024, 16 rows 74.7 : 78.0.  A pool below the line, 2048 x 2048 GELU, 12 slots
-// (201 MB), 67 rows 72.6 : 81.5; 768 x 3072, 18 slots (170 MB) 95.8 : 101.7, three pools in turn 106.3 : 107.0.
+// turn.  256-row tiles: 2304 x 768 SwiGLU, 6 slots (64 MB), 180 rows per slot 72.2 : 82.9 / 72.3 : 83.2; 4096 x 512, 5 slots (42
+// MB) 80.9 : 95.4 / 80.0 : 95.4; 4096 x 1024 SwiGLU, 8 slots (201 MB), 110 rows 88.3 : 109.0 / 111.6 : 109.1; 2560 x 2560, 20 slots
+// (524 MB) 182.7 : 172.3 / 183.2 : 174.1; 4096 x 2048 SwiGLU, 13 slots (654 MB) 178.9 : 161.1 / 180.0 : 166.2; at 244 and 306
+// rows per slot on average both are within 1 %.  128-row tiles: 2048 x 1280 SwiGLU, 90 slots, 46 rows 339 : 314 / 346 : 334;
+// 1024 x 1024 SwiGLU, 200 slots, 16 rows 271 : 260 / 272 : 260; 1024 x 4096 SwiGLU, 60 slots, 20 rows 300 : 286 / 305 : 287; 768 x 3072
+// SwiGLU, 40 slots, 50 rows 148 : 144 / 149 : 143, 110 rows 145 : 141, 200 rows 204 : 205; pools below the line 2048 x 2048 GELU, 12
+// slots (201 MB), 67 rows 72.6 : 81.5 / -; 768 x 3072, 18 slots (170 MB) 95.8 : 101.7 / 106.3 : 107.0.
 bool lone_tiles(const mmoe_shape& s)
 {
     return (int64_t)s.T * s.top_k <= (int64_t)kBMBig * s.S && s.S * slot_bytes(s) > kLastLevelCache;
 }
+
+// Of a large pool a batch may use few slots, which stay cached.  The list builder knows them: panels are read past the
+// caches from this many bytes on (the streaming kernels' line, past_the_caches).  Through : past, as above, by what is used: 57 MB 512
+// x 2048 SwiGLU, 150 slots, 800 tokens, router bias 3 57 : 59 / 56 : 58; 63 MB 57 : 60 / 56 : 60; 82 MB 57 : 61 / 60 : 60; above the line one
+// pool alone would rather stay cached, several not: 126 MB 63 : 65 / 66 : 63; 182 MB 1024 x 1024, 200 slots, 800 tokens 81 : 83 / 87 : 85;
+// 195 MB, 400 tokens 70 : 77 / 81 : 77; 267 MB 2048 x 1280, 90 slots, 1037 tokens 149 : 144 / 162 : 163.
+constexpr int64_t kLoneBytes = (int64_t)96 << 20;
 
 // Do the XCDs take runs of neighbouring tiles of product `prod` (0 up, 1 down; RunsRule, tile_table.h)?
 // Down products.  What reaches an XCD's L2 from beyond it bounds them (5.7 TB/s; 768 x 3072, 18 slots, 4096 tokens: 251 MB,
@@ -661,7 +666,7 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
     p.lone = lone_tiles(s);
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm), planned_upt(s, p.bm), p.bm,
-                     s.dtype == MMOE_F32, xcd_runs(s, 0), xcd_runs(s, 1));
+                     s.dtype == MMOE_F32, xcd_runs(s, 0), xcd_runs(s, 1), (int)(kLoneBytes / slot_bytes(s)) + 1);
     return p;
 }
 
@@ -692,7 +697,7 @@ size_t tiled_table_most(const mmoe_shape& s)
             for (int nb_down : {1, 2}) {
                 const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb_up);
                 const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (wide * nb_down), bm / 32, bm / 32, bm, f32, kRunsNever,
-                                               f32 ? kRunsNever : kRunsAlways);
+                                               f32 ? kRunsNever : kRunsAlways, 0);
                 most = L.bytes > most ? L.bytes : most;
             }
     return align256(most);

@@ -54,7 +54,7 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // ones share out a product of few tiles evenly).
 constexpr int kMaxHeightCands = 16;
 
-// In an entry's first word: the slot, and whether the tile holds all rows of the slot.
+// In an entry's first word: the slot, and whether the tile holds all rows of the slot (not set where few slots hold rows).
 constexpr int kSlotMask = 0xFFFF, kOnlyTile = 1 << 16;
 static_assert(kMaxS <= kSlotMask, "slot ids");
 
@@ -69,13 +69,15 @@ struct TileLists {
     int hq_lo[2];   // least target height, in quarters of a sub-tile
     int conc;       // workgroups that an XCD works on at a time, for the choice of the height
     int rows_cap[2]; // most row tiles of each product
+    int lone_slots; // least number of slots with rows for which kOnlyTile is set (lone_tiles)
     size_t bytes;
 };
 
 inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down, int bm, bool f32,
-                            int runs_up, int runs_down)
+                            int runs_up, int runs_down, int lone_slots)
 {
     TileLists L;
+    L.lone_slots = lone_slots;
     L.upt[0] = upt_up;
     L.upt[1] = upt_down;
     // fp32: the workgroups of a compute unit (three, two of the gated product) share its matrix pipes, which bound
@@ -199,7 +201,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
         ppart[wave] = pincl;
     }
     __syncthreads();
-    int before = 0, pbefore = 0, total_m = 0;
+    int before = 0, pbefore = 0, total_m = 0, touched = 0;
 #pragma unroll
     for (int w = 0; w < kListWaves; ++w) {
         if (w < wave) {
@@ -207,7 +209,9 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
             pbefore += ppart[w];
         }
         total_m += part[w];
+        touched += ppart[w];
     }
+    const bool lone = touched >= L.lone_slots;
     if (tid < S) {
         base[tid] = before + incl - mine;
         pbase[tid] = pbefore + pincl - pmine;
@@ -277,7 +281,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
         const int rows = 32 * (h + (i < extra ? 1 : 0));
         const int to = runs ? div24(e, share) : x;
         lists[L.list[p] + to * L.len[p] + e - (runs ? to * share : 0)] =
-            make_int4(mt == 1 ? s | kOnlyTile : s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
+            make_int4(lone && mt == 1 ? s | kOnlyTile : s, ntl, off[s] + row0, min(rows, off[s + 1] - off[s] - row0));
     }
 }
 

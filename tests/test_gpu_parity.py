@@ -407,6 +407,20 @@ def test_256_row_tiles_of_128_features(mm, gc, oracle, dispatch_rule, T, V, E, k
     assert len({-(-int(c) // 32) for c in ref["counts"]}) >= min(3, E - 2)
 
 
+@pytest.mark.parametrize("d,f,rows,want", [
+    # slots of 4 MiB (128-row tiles) and of 9 MiB (256-row ones), 73 and 34 of them in the pool: at 96 MiB used, and one slot more
+    (1024, 1024, [40] * 24, False), (1024, 1024, [40] * 25, True), (1024, 1024, [300] + [40] * 24, True),
+    (2304, 1024, [160] * 10, False), (2304, 1024, [160] * 11, True)])
+def test_few_used_slots_of_large_pools_stay_cached(mm, gc, oracle, dispatch_rule, d, f, rows, want):
+    """Tiles are marked as the only ones of their slots only where the batch uses more of the pool than 96 MiB."""
+    counts = rows + [0] * ((73 if d == 1024 else 34) - len(rows))
+    shape, tab = expert_lists(mm, gc, oracle, d, f, "relu", counts, tile_rows=128 if d == 1024 else 256)
+    assert not mm.expert_plan(shape)[0] and dispatch_rule("lone_tiles", shape)
+    entries = tab[64:64 + 4 * int(tab[0])].reshape(-1, 4)     # the up product's, of the first XCD
+    only = {int(s): bool(marked) for s, marked in zip(entries[:, 0] & 0xFFFF, entries[:, 0] >> 16)}
+    assert only == {s: want and rows[s] <= 256 for s in only} and len(only) > 4
+
+
 @pytest.mark.parametrize("act,k,E,d,f", [("gelu", 1, 16, 1024, 1536), ("swiglu", 2, 12, 1280, 1024)])
 def test_tiles_of_128_rows_in_large_pools(mm, gc, oracle, dispatch_rule, act, k, E, d, f):
     """Slots of one tile, whose weights are read past the caches, of every height, beside slots of several tiles."""
