@@ -406,9 +406,20 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
     select_topk(mylogit, lane, E, k, t, topk_idx, topk_w, M ? lds_map[wave] : nullptr, slot, S, gate);
 }
 
-// Most LDS for the token rows of a group.  (fp32, 2500 tokens of 4096, 64 experts, 64 KB of rows: 149 us with a wavefront per token, 70
-// in groups.)
-constexpr size_t kRouteGroupBytes = 64 << 10;
+// Most LDS for the token rows of a group: fp32 rows of 4096.  Over kRouteGroupLarge the rows, which have to arrive before the
+// first score, take long enough that there has to be something to score: fp32 rows of 3584 and 4096, two variants, other kernel : groups, us, caches warm / cold: 768 tokens, 1 expert 9.5 : 9.5 / 10.0 : 13.1, 4 9.5 : 9.5 / 12.6 : 13.7, 8 10.6 :
+// 9.4 / 16.2 : 14.9, 64 48 : 26 / 59 : 32; 1024 tokens, 1 9.5 : 9.5 / 12.5 : 14.3, 3 9.5 : 9.4 / 13.9 : 14.6, 4 9.5 : 9.5 / 14.9 : 14.8, 8 12.7 : 10.6 /
+// 19.4 : 16.3; 1536 tokens, 2 9.7 : 9.6 / 17.2 : 17.5, 3 10.5 : 9.8 / 18.3 : 17.7, 8 17.2 : 12.3 / 25.8 : 20.2; 2000 tokens, 1 11.0 : 9.6 /
+// 19.2 : 19.3, 2 12.2 : 9.9 / 20.4 : 19.6; and against a wavefront per token 2500 tokens of 4096, 16 37 : 25 / 60 : 36, 64 122 : 69 / 186 : 76.
+constexpr size_t kRouteGroupBytes = 64 << 10, kRouteGroupLarge = 48 << 10;
+constexpr int64_t kRouteLargeScores = 3500;  // tokens x experts
+
+// A wavefront per token, unless four tokens go to a workgroup?  Large batches of a common hidden size.
+static bool wavefront_per_token(const mmoe_shape& s)
+{
+    const int nc = s.d_model / 256;
+    return s.T >= kRouteTokMinT && (nc == 1 || nc == 2 || nc == 3 || nc == 4 || nc == 6 || nc == 8 || nc == 12 || nc == 16);
+}
 
 // Four tokens to a workgroup?  Measured against the other two, bf16, us, two variants:
 //   workgroup per token (under 2048 tokens, or an uncommon hidden size): 8 experts, 768 elements 8.2 : 8.6 at 1900 tokens;
@@ -416,10 +427,11 @@ constexpr size_t kRouteGroupBytes = 64 << 10;
 //   1024, 14.2 : 18.3 at 512;
 //   wavefront per token: 4096 tokens, 64 experts 768 27.5 : 42.4, 1536 51.0 : 43.9, 4096 123 : 84; 16 experts 2048 19.9 : 20.1,
 //   3072 28.1 : 26.6, 4096 35.7 : 29.5; 8 experts 4096 20.9 : 22.5.
-static bool route_in_groups(const mmoe_shape& s, bool token_per_wave)
+bool route_in_groups(const mmoe_shape& s)
 {
-    if ((size_t)kRouteGroup * s.d_model * elem_size(s.dtype) > kRouteGroupBytes) return false;
-    if (token_per_wave) return s.d_model >= 1536 && (int64_t)s.E * s.d_model >= 49152;
+    const size_t bytes = (size_t)kRouteGroup * s.d_model * elem_size(s.dtype);
+    if (bytes > kRouteGroupBytes || (bytes > kRouteGroupLarge && (int64_t)s.T * s.E < kRouteLargeScores)) return false;
+    if (wavefront_per_token(s)) return s.d_model >= 1536 && (int64_t)s.E * s.d_model >= 49152;
     // (inside a layer, whose weights push the router out of the L2s, 1037 tokens of 2048 and 64 experts take 348 : 350 us and
     // 1900 of 2048 and 8 154 : 155; 1900 of 2304 and 8 131 : 121, 1200 of 3072 and 64 243 : 237)
     return (s.d_model >= 2304 || s.T >= kRouteTokMinT) && s.T >= 768 && (int64_t)s.T * s.d_model >= ((int64_t)1 << 21);
@@ -432,10 +444,8 @@ int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const v
     // once); with more to score, a workgroup per four tokens; otherwise a workgroup per token (lower
     // latency, any d).
     const int nc = s.d_model / 256;
-    const bool tok_nc = nc == 1 || nc == 2 || nc == 3 || nc == 4 || nc == 6 || nc == 8 || nc == 12 || nc == 16;
-    const bool token_per_wave = s.T >= kRouteTokMinT && tok_nc;
-    const bool groups = route_in_groups(s, token_per_wave);
-    if (token_per_wave && !groups) {
+    const bool groups = route_in_groups(s);
+    if (wavefront_per_token(s) && !groups) {
         dim3 grid((s.T + kRouteTokWaves - 1) / kRouteTokWaves), block(kRouteTokWaves * kWave);
 #define MMOE_ROUTE_TOK(NC)                                                                                          \
     case NC:                                                                                                        \

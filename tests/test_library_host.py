@@ -328,3 +328,15 @@ def test_up_products_of_less_than_a_round(mm, dispatch_rule):
         assert dispatch_rule("xcd_runs", shape, 0, restype=ctypes.c_int) == runs, (T, d, f, S, act)
     assert dispatch_rule("wide_below_a_round", mm.make_shape(8000, 1536, 3072, 4, 8, 24, 1, "bf16", "gelu"), 1536, False)
     assert dispatch_rule("xcd_runs", mm.make_shape(4096, 768, 3072, 4, 8, 18, 1, "bf16", "swiglu"), 0, restype=ctypes.c_int) == 0
+
+
+def test_routers_of_few_scores_take_no_groups_of_long_rows(mm, dispatch_rule):
+    """fp32 rows of over 3072 elements go to groups of four tokens only with 3500 (token, expert) pairs to score; shorter
+    rows and bf16 as their own lines say."""
+    for T, d, E, dtype, want in ((768, 4096, 1, "f32", False), (768, 3584, 4, "f32", False), (768, 3328, 8, "f32", True),
+                                 (1024, 4096, 3, "f32", False), (1024, 4096, 4, "f32", True), (1536, 3840, 2, "f32", False),
+                                 (1536, 3840, 3, "f32", True), (2000, 4096, 1, "f32", False), (2000, 4096, 2, "f32", True), (2047, 3584, 64, "f32", True),
+                                 (767, 4096, 64, "f32", False), (2500, 4096, 64, "f32", True), (2500, 4096, 8, "f32", False),
+                                 (768, 3072, 1, "f32", True), (768, 4096, 1, "bf16", True), (768, 4352, 64, "f32", False)):
+        shape = mm.make_shape(T, d, 256, 2, E, E, 1, dtype, "relu")
+        assert dispatch_rule("route_in_groups", shape) is want, (T, d, E, dtype)
