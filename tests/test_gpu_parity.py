@@ -306,7 +306,7 @@ def test_streaming_slots_of_several_passes_in_large_pools(mm, gc, oracle, dispat
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_router_with_every_remainder_of_experts(mm, gc, oracle, dtype):
     """Numbers of experts around the four whose sums share a butterfly and around a wavefront's lanes, on each router
-    kernel (a workgroup per token, a wavefront per token, a workgroup per four), bit for bit."""
+    kernel (a workgroup per token, a wavefront per token, a workgroup per four): the oracle's picks, and its coefficients to rounding."""
     for T, d in ((70, 512), (2050, 256), (2051, 768), (771, 4096), (2100, 2304)):
         for E in (1, 2, 3, 4, 5, 8, 9, 17, 33, 64, 67):
             cfg = synth.Config(f"route_{dtype}_{T}_{d}_{E}", T, d, 256, 3, E, min(E, 4), dtype, "relu", seed=1500 + T + E, bias_alpha=0.5, gate="all")
@@ -320,15 +320,38 @@ def test_router_with_every_remainder_of_experts(mm, gc, oracle, dtype):
             np.testing.assert_allclose(w.cpu().numpy(), w_ref, rtol=2e-6, atol=1e-7)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_router_kernels_agree_bit_for_bit(mm, gc, dispatch_rule, dtype):
+    """Batches on a wavefront per token (rows of the router in registers four and two at a time) and on groups of four, and their
+    parts on a workgroup per token: the same picks and the same bits of every coefficient."""
+    for T, d, groups in ((2050, 256, False), (2049, 768, False), (2049, 2048, False), (2050, 3072, False), (2050, 4096, False),
+                         (771, 4096, True), (2053, 2304, True), (2051, 3072, True)):
+        for E in ((1, 2, 3, 5, 6, 7, 9) if not groups else (17, 66) if d == 3072 else (6, 7, 33)):
+            cfg = synth.Config(f"bits_{dtype}_{T}_{d}_{E}", T, d, 256, 3, E, min(E, 4), dtype, "relu", seed=1700 + T + E, bias_alpha=0.5, gate="all")
+            inp = synth.make_inputs(cfg, weights=False)
+            X, Wr, br = gc.to_dev(inp["X"], dtype), gc.to_dev(inp["Wr"], dtype), torch.from_numpy(inp["br"]).cuda()
+            vid = torch.from_numpy(inp["vid"]).cuda()
+            make = lambda n: mm.make_shape(n, d, 256, 3, E, E, cfg.top_k, dtype, "relu", gate="all")
+            assert dispatch_rule("route_in_groups", make(T)) is groups
+            idx, w = mm.route(make(T), X, vid, Wr, br)
+            for t0 in range(0, T, 700):
+                n = min(700, T - t0)
+                assert not dispatch_rule("route_in_groups", make(n))
+                part_idx, part_w = mm.route(make(n), X[t0:t0 + n], vid[t0:t0 + n], Wr, br)
+                assert torch.equal(part_idx, idx[t0:t0 + n]) and torch.equal(part_w, w[t0:t0 + n]), (T, d, E, t0)
+
+
 @pytest.mark.parametrize("rows", [256, 128])
-def test_down_tiles_in_runs(mm, gc, oracle, rows):
-    """Down products whose tiles go to the XCDs in runs: fewer tiles than XCDs, numbers that do not divide among them,
-    empty slots at either end, one panel per slot, and as many panels as XCDs or more."""
-    for T, V, E, k, d, f, alpha in ((65, 1, 1, 1, 256, 256, 0.0), (300, 1, 3, 1, 256, 512, 0.0), (900, 3, 16, 1, 768, 256, 3.0),
+def test_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, rows):
+    """Down products whose tiles may go to the XCDs in runs (128-row tiles: do): fewer tiles than XCDs, numbers that do not
+    divide among them, few and many slots, equally and unequally used, and as many panels as XCDs or more."""
+    for T, V, E, k, d, f, alpha in ((65, 1, 1, 1, 256, 256, 0.0), (300, 1, 3, 1, 256, 512, 0.0), (1100, 3, 16, 1, 768, 256, 3.0),
                                     (800, 1, 40, 2, 512, 256, 2.0), (1300, 2, 6, 2, 2304, 256, 0.5), (1100, 1, 5, 1, 2048, 256, 0.0)):
         cfg = synth.Config(f"runs_{T}_{d}", T, d, f, V, E, k, "bf16", "relu" if k == 1 else "swiglu", seed=1400 + T, bias_alpha=alpha)
         case, _ = staged_vs_oracle(mm, gc, oracle, cfg, tile_rows=rows)
         assert mm.expert_plan(case.shape) == (False, rows)
+        rule = dispatch_rule("xcd_runs", case.shape, 1, restype=ctypes.c_int)
+        assert rule == 1 if rows == 128 else rule in (0, 2)
 
 
 def expert_lists(mm, gc, oracle, d, f, act, counts, tile_rows=0):
@@ -358,6 +381,18 @@ def rounds(tiles, conc):
 def in_runs(per_xcd):
     share = -(-int(per_xcd.sum()) // 8)
     return list(per_xcd) == [min(share, max(int(per_xcd.sum()) - x * share, 0)) for x in range(8)]
+
+
+@pytest.mark.parametrize("d,counts", [
+    (256, [65]), (256, [0, 0, 40, 0, 200, 1, 0]),                                   # fewer tiles than XCDs; empty slots at either end
+    (768, [0, 1500, 3, 0, 40, 260, 90, 1, 33, 0, 0]), (1280, [5, 0, 700, 129, 64]),  # six and ten panels, very unequal slots
+    (1024, [300, 20, 0, 500, 31]), (2048, [0, 128, 400, 257, 90, 0]),                # panels that divide among the XCDs
+    (256, [9000, 17000, 300, 12500, 0])])                                            # one panel a slot
+def test_128_row_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, d, counts):
+    """Every XCD's list is a run of as many tiles, but for the last ones that hold any."""
+    shape, tab = expert_lists(mm, gc, oracle, d, 256, "relu", counts, tile_rows=128)
+    assert mm.expert_plan(shape) == (False, 128) and dispatch_rule("xcd_runs", shape, 1, restype=ctypes.c_int) == 1
+    assert in_runs(tab[8:16])
 
 
 @pytest.mark.parametrize("d,counts,runs", [
