@@ -632,7 +632,9 @@ constexpr int64_t kLoneBytes = (int64_t)96 << 20;
 // 115 : 105 / 84 : 82; 1280 x 5120, 13 of 300 246 : 243 / 271 : 247 / 275 : 240; 1536 x 6144 323 : 325 / 342 : 319 / 335 : 312; 512 x
 // 2048 68 : 68 / 78 : 74 / 66 : 64; 1024 x 4096 172 : 170 / 179 : 178 / 171 : 166.  Below the lines: 2048 x 1280, 90 slots of 46
 // rows 324 : 329; 2048 x 3072 (NT 8 or 16), 13 of 80 138 : 141 / 137 : 139 / 128 : 131, 24 of 80 223 : 223 / 224 : 227 / 201 : 206.
-// 256-row tiles of up to 512 rows per slot: only for fewer rounds.  Always in runs they lose where panels need no more
+// 256-row tiles of up to 512 rows per slot: only for fewer rounds, but always in short reductions (K to 1536, fewer than 16 wide
+// panels: by panels, but for fewer rounds : in runs, means of 10 to 17 layers, K = 1024 1 % more, at most 0.5 % less, K = 1536 0.3 %; 2048 x
+// 1536, 19 slots of 170 123 : 117, 1792 x 1536, 13 of 290 105 : 100; 4096 x 1536 0.9 % less).  In longer ones they drift apart and lose where panels need no more
 // rounds: panels : runs, 4096 x 14336, 18 slots (NT 16: panels are shared out evenly) of 130 rows 1311 : 1410 / 1318 : 1407 / 1440 :
 // 1486, of 250 1856 : 1870 / 1816 : 1869 / 1850 : 1918, of 450 2729 : 2815 / - / 2802 : 2845; 3584 x 7680, 12 of 420 842 : 879 /
 // 886 : 897; 3072 x 7680 747 : 777 / 769 : 793.  Panels : for fewer rounds, equally used / bias 1: 2304 x 7680, 12 of 420 644 : 563 /
@@ -655,7 +657,11 @@ int xcd_runs(const mmoe_shape& s, int prod)
     tiled_nts(s, bm, nt_up, nt, nb_up, nb_down);
     const bool even = nt % kXcds == 0;  // panels divide among the XCDs
     const int64_t P = (int64_t)s.T * s.top_k, rows = P * (nt < kXcds ? nt : kXcds), weights = (int64_t)s.S * s.d_model;
-    if (bm == kBMBig) return !even && P <= (int64_t)512 * s.S && 4 * rows >= weights ? kRunsForFewerRounds : kRunsNever;
+    if (bm == kBMBig) {
+        if (P > (int64_t)512 * s.S || 4 * rows < weights) return kRunsNever;
+        if (nb_down == 2 && nt < 2 * kXcds && s.d_ff <= 1536) return kRunsAlways;
+        return even ? kRunsNever : kRunsForFewerRounds;
+    }
     return (even ? 2 : 4) * rows >= weights ? kRunsAlways : kRunsNever;
 }
 

@@ -300,11 +300,12 @@ def test_one_tile_slots_leave_the_caches_only_with_large_pools(mm, dispatch_rule
 
 
 def test_down_products_take_runs_of_tiles(mm, dispatch_rule):
-    """Where panels divide among the XCDs 256-row tiles never do; elsewhere only where that takes fewer rounds (2); 128-row tiles
-    do (1) where token rows are a quarter of the traffic, or half where panels divide."""
+    """256-row tiles do (1) in short reductions with fewer than 16 panels; in long ones never where panels divide among the XCDs, else
+    only where that takes fewer rounds (2).  128-row tiles do where token rows are a quarter of the traffic, or half where panels divide."""
     for T, k, d, f, S, want in ((1170, 2, 4096, 14336, 18, 0), (2250, 2, 4096, 14336, 18, 0), (4050, 2, 4096, 14336, 18, 0),
                                 (2520, 2, 2048, 3072, 12, 0), (840, 2, 4096, 7680, 12, 0), (1600, 2, 2560, 7680, 12, 2),
-                                (2520, 2, 2304, 7680, 12, 2), (3600, 2, 2560, 7680, 12, 0), (500, 2, 2560, 7680, 16, 0),
+                                (2520, 2, 2304, 7680, 12, 2), (1440, 2, 2304, 1536, 12, 1),
+                                (1440, 2, 2304, 1792, 12, 2), (2520, 2, 2048, 1024, 12, 1), (1440, 2, 4096, 1024, 12, 0), (840, 2, 2304, 1024, 12, 2), (3600, 2, 2560, 7680, 12, 0), (500, 2, 2560, 7680, 16, 0),
                                 (4096, 1, 768, 3072, 18, 1), (200, 2, 768, 3072, 18, 0), (520, 2, 1024, 4096, 13, 1),
                                 (330, 2, 1024, 4096, 13, 0), (520, 2, 2048, 3072, 13, 0), (960, 2, 2048, 3072, 24, 0), (300, 2, 1280, 2560, 13, 1)):
         shape = mm.make_shape(T, d, f, 4, 8, S, k, "bf16", "swiglu")
