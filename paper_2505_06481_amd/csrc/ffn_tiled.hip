@@ -73,9 +73,9 @@ __global__ __launch_bounds__(kListThreads) void tile_table_kernel(const int32_t*
 }
 
 // LONE: a tile that holds all rows of its slot is the only reader of its weight panels and reads them past the caches,
-// which streams faster where the pool is large (lone_tiles; 4096 x 14336, 18 slots, 777 tokens 1227 -> 1200 us; 4096 x 2048, 64 slots, 4800 pairs 737 -> 717;
-// 2560 x 2560 GELU, 20 slots, 2000 pairs 179 -> 171).  A panel with several readers has to stay in L2 (8192 tokens 4486 ->
-// 5087 us with every panel past the caches).
+// which streams faster where the pool is large (lone_tiles; 4096 x 14336, 18 slots, 777 tokens 1227 -> 1200 us; 4096 x
+// 2048, 64 slots, 4800 pairs 737 -> 717; 2560 x 2560 GELU, 20 slots, 2000 pairs 179 -> 171).  A panel with several readers
+// has to stay in L2 (8192 tokens 4486 -> 5087 us with every panel past the caches).
 template <int MODE, int BM, int NB, bool LONE>
 __device__ __forceinline__ void tiled_body(const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv,
                                            const int32_t* __restrict__ tab, int hdr, int list_at, int list_stride,
@@ -212,7 +212,8 @@ __device__ __forceinline__ void tiled_body(const uint16_t* __restrict__ A, const
     // Short tiles (small NJ) are bound by the latency of memory instead: a step is over long before a load
     // issued in it has come back.  They copy only the 32 NJ rows they have (NJ instructions per wavefront and
     // step, not BM / 32), use the LDS and the registers that this leaves for more steps in flight, and so have as
-    // many bytes on the way as a full tile.  (4096 x 14336, 777 tokens, tiles of 1 to 4 sub-tiles: 1259 -> 1235 us; 768 x 3072 top-1, 543 tokens: 59.4 -> 55.9 us.)
+    // many bytes on the way as a full tile.  (4096 x 14336, 777 tokens, tiles of 1 to 4 sub-tiles: 1259 -> 1235 us; 768 x
+    // 3072 top-1, 543 tokens: 59.4 -> 55.9 us.)
     //
     // Pipeline (k step t = 64 k = two 32-k slices; step t's tokens live in LDS stage t mod kStages):
     //   weights   slice g is loaded straight into registers kSlices - 1 slices ahead of its use; these
@@ -496,17 +497,25 @@ __global__ __launch_bounds__(256, 2) void tiled_lone_small_kernel(
 
 constexpr int kCus = 256;  // compute units
 
-// Does an ungated product with N output features take 128 of them to a 256-row tile, not 256?  Twice the tiles, each with half of
-// the weights, pay where the wide ones leave compute units without work: fewer of them than half the units, or, where weights are
-// most of the traffic (few rows per slot), a second round that is nearly empty.  Tiles counted as if every slot held rows and its last tile were
-// half full.  Wide : narrow down products, layer, us, three pools in turn, rows spread evenly / unequally (router bias 1), tiles by that count: 60
-// 4096 x 8192, 4 slots 248 : 211 / 309 : 271; 72 2048 x 2048, 9 slots 96 : 87 / 96 : 89; 80 2048 x 8192, 10 slots 238 : 205 / 239 : 212; 96 4096 x 512 73.7 :
-// 69.9 / 72.0 : 67.9; 112 4096 x 14336, 7 slots 576 : 512 / 592 : 532; 120 2560 x 7680, 12 slots 257 : 220 / 257 : 245; from there on slots
-// that hold more than their share bring a second round: 128 4096 x 14336, 8 slots, 150 rows per slot 660 : 593 / 665 : 706; 144 to 256 4096 x
-// 14336, 9 slots 676 : 679 / 712 : 709, 2048 x 4096, 24 slots 217 : 229 / 222 : 238, 1.2 rounds of 250 rows 2560 x 7680 317 : 357 / 340 : 364.  A little over one round,
-// under 100 rows per slot: 280 2560 x 4096, 28 slots 290 : 282 / 304 : 301; 288 4096 x 14336, 18 slots 1229 : 1209 / 1257 : 1245; 304 4096 x 1024 150 : 145 /
-// 155 : 151; 320 4096 x 8192 782 : 775 / 838 : 829; with more rows 288 4096 x 4096, 18 slots, 133 rows 441 : 448.  (Past two rounds the narrow
-// tiles' second reading of the tokens costs more: 2200 tokens of 4096 x 14336 1818 : 1957.)
+// Does an ungated product with N output features take 128 of them to a 256-row tile, not 256?  Twice the tiles, each with
+// half of the weights, pay
+//   - where the wide ones leave half of the compute units without work: fewer than 128 of them;
+//   - where weights are most of the traffic, up to 100 rows per slot, and wide tiles are a little over one round: 257 to 336.
+// Tiles counted as if every slot held rows and its last tile were half full.
+// Wide : narrow down products, layer, us, three pools in turn, equally used slots / router bias 1, by that count:
+//   60   4096 x 8192, 4 slots       248 : 211 / 309 : 271      72   2048 x 2048, 9 slots       96 : 87 / 96 : 89
+//   80   2048 x 8192, 10 slots      238 : 205 / 239 : 212      96   4096 x 512                 73.7 : 69.9 / 72.0 : 67.9
+//   112  4096 x 14336, 7 slots      576 : 512 / 592 : 532      120  2560 x 7680, 12 slots      257 : 220 / 257 : 245
+//   128  4096 x 14336, 8 slots      660 : 593 / 665 : 706      144  4096 x 14336, 9 slots      676 : 679 / 712 : 709
+//   192  2048 x 4096, 24 slots      217 : 229 / 222 : 238      280  2560 x 4096, 28 slots      406 : 397 / 420 : 417
+//   288  4096 x 14336, 18 slots     1202 : 1188 / 1289 : 1280  304  4096 x 1024, 19 slots      148 : 143 / 141 : 136
+//   320  4096 x 8192, 19 slots      754 : 738 / 801 : 788      288  4096 x 4096, 133 rows      441 : 448 / -
+// (the down products of 280 to 320 themselves 146 : 136 / 141 : 138, 452 : 440 / 478 : 469, 49 : 45 / 48 : 44, 283 : 265 / 292 : 280).
+// Of 260 layers below the first line, random in width, depth, slots and use, narrow tiles take 14 % less from 70 to 90, 9 %
+// from 90 to 120, 5 % from there on, where unequal ones of which a few tiles are a second round lose up to 6 %.  From 120 on
+// with over 256 rows per slot 20 layers are level on average, from 2048 x 5888, 8 slots of 375 rows 276 : 253 to 2048 x 9984, 9
+// of 320 386 : 426; a line at 120 for those changed 9 % both ways.  Past two rounds the narrow tiles' second reading of the
+// tokens costs more: 2200 tokens of 4096 x 14336 1818 : 1957.
 bool few_wide_tiles(const mmoe_shape& s, int N)
 {
     if (s.dtype == MMOE_F32 || planned_tile_rows(s) != kBMBig) return false;
@@ -521,14 +530,19 @@ constexpr int kNb1Room = 2 * kCus;
 // Two already from kNb1RoomTall on where slots have at least kTallRows rows on average, for more than a tile each: one round
 // of wide tiles reads the tokens once where a round and a half of narrow ones reads them twice.  With GELU, whose epilogue
 // is long, only if the tiles are one round with another half tile per slot.
-// Narrow : wide, up in runs where that is for fewer rounds, layer, us, three pools in turn, equally used / router bias 0.5 / 1: ReLU 768 x 3072,
-// 4096 tokens, 9 slots 87 : 85 / 89 : 86 / 98 : 98; 13 slots 93 : 92 / 103 : 101 / 99 : 96; 18 slots 102 : 99 / 103 : 101 / 105 : 104; 5000
-// tokens, 18 slots 111 : 110 / 116 : 116 / 115 : 118; 1280 x 3328, 4700 tokens, 13 slots 157 : 150 / 160 : 159 / 161 : 160; 1024 x 1536, 9000
-// tokens, 13 slots 112 : 104 / 116 : 108 / 118 : 110; both products wide, 1536 x 1536, 8000 tokens, 13 slots 136 : 122 / 144 : 124 / 148 :
-// 128.  GELU 768 x 3072, 4096 tokens, 13 slots 102 : 101 / 112 : 111 / 108 : 104; but past the round 5000 tokens, 18 slots 121 : 126 /
-// 124 : 129 / 126 : 131; 1280 x 3328, 4700 tokens, 13 slots 169 : 170 / 172 : 176 / 176 : 178.
-// Neither line is where both sides are level: 210 tiles of 768 x 3072, 267 rows 62 : 66 / - / 63 : 67, 178 rows 68 : 69 / - / 71 : 73; but 250
-// tiles, 180 rows 73 : 71 / - / 76 : 75, 140 rows 80 : 79 / - / 77 : 75, and 384 tiles, 140 rows are equal.
+// Narrow : wide (up in runs where that is for fewer rounds), layer, us, three pools in turn, equally used slots / router
+// bias 0.5 / 1:
+//   ReLU  768 x 3072, 4096 tokens   9 slots   87 : 85 / 89 : 86 / 98 : 98         13 slots  93 : 92 / 103 : 101 / 99 : 96
+//                                   18 slots  102 : 99 / 103 : 101 / 105 : 104
+//         768 x 3072, 5000 tokens   18 slots  111 : 110 / 116 : 116 / 115 : 118
+//         1280 x 3328, 4700 tokens  13 slots  157 : 150 / 160 : 159 / 161 : 160
+//         1024 x 1536, 9000 tokens  13 slots  112 : 104 / 116 : 108 / 118 : 110
+//         1536 x 1536, 8000 tokens  13 slots  136 : 122 / 144 : 124 / 148 : 128 (both products wide)
+//   GELU  768 x 3072, 4096 tokens   13 slots  102 : 101 / 112 : 111 / 108 : 104
+//         past the round: 5000 tokens, 18 slots 121 : 126 / 124 : 129 / 126 : 131; 1280 x 3328 169 : 170 / 172 : 176 / 176 : 178
+// Unequal slots that take a round more than the host can see lose up to 5 % (GELU, 4096 tokens, 18 slots, bias 1 113 : 117).
+// Neither line is where both sides are level: 768 x 3072, equally used / bias 1, 210 tiles, 267 rows 62 : 66 / 63 : 67, 178
+// rows 68 : 69 / 71 : 73; but 250 tiles, 180 rows 73 : 71 / 76 : 75, 140 rows 80 : 79 / 77 : 75; 384 tiles, 140 rows are equal.
 constexpr int kNb1RoomTall = 300, kTallRows = 160;
 bool wide_below_a_round(const mmoe_shape& s, int N, bool up)
 {
@@ -616,35 +630,46 @@ bool lone_tiles(const mmoe_shape& s)
 }
 
 // Of a large pool a batch may use few slots, which stay cached.  The list builder knows them: panels are read past the
-// caches from this many bytes on (the streaming kernels' line, past_the_caches).  Through : past, as above, by what is used: 57 MB 512
-// x 2048 SwiGLU, 150 slots, 800 tokens, router bias 3 57 : 59 / 56 : 58; 63 MB 57 : 60 / 56 : 60; 82 MB 57 : 61 / 60 : 60; above the line one
-// pool alone would rather stay cached, several not: 126 MB 63 : 65 / 66 : 63; 182 MB 1024 x 1024, 200 slots, 800 tokens 81 : 83 / 87 : 85;
-// 195 MB, 400 tokens 70 : 77 / 81 : 77; 267 MB 2048 x 1280, 90 slots, 1037 tokens 149 : 144 / 162 : 163.
+// caches from this many bytes on (the streaming kernels' line, past_the_caches).  Through : past, us, one pool again and
+// again / three in turn, by what is used:
+//   57 MB   512 x 2048 SwiGLU, 150 slots, 800 tokens  57 : 59 / 56 : 58   63 MB  57 : 60 / 56 : 60   82 MB  57 : 61 / 60 : 60
+// and above the line, where one pool alone would rather stay cached and several lose by it:
+//   126 MB  the same                       63 : 65 / 66 : 63    157 MB  2560 x 1024, 24 slots, 379 tokens    64 : 73 / 78 : 74
+//   182 MB  1024 x 1024, 200 slots, 800    81 : 83 / 87 : 85    184 MB  1536 x 1536, 40 slots, 600 tokens    77 : 88 / 94 : 92
+//   195 MB  1024 x 1024, 200 slots, 400    70 : 77 / 81 : 77    267 MB  2048 x 1280, 90 slots, 1037 tokens   149 : 144 / 162 : 163
 constexpr int64_t kLoneBytes = (int64_t)96 << 20;
 
 // Do the XCDs take runs of neighbouring tiles of product `prod` (0 up, 1 down; RunsRule, tile_table.h)?
+//
 // Down products.  What reaches an XCD's L2 from beyond it bounds them (5.7 TB/s; 768 x 3072, 18 slots, 4096 tokens: 251 MB,
 // of which 151 token rows, each read by six XCDs).  Panel by panel a slot's rows are read by min(8, NT) XCDs, a weight
 // panel by one; in runs the rows by one or two, but the panels at the ends by two.  So runs pay where token rows are a good
-// part of the traffic, min(8, NT) P against S N rows.
-// 128-row tiles: from a quarter on, NT a multiple of 8 from half on.  Panels : runs, layer, us, three pools in turn, slots
-// equally used / router bias 1 / 2.5: 768 x 3072, 13 slots of 300 rows 127 : 116 / 127 : 120 / 118 : 114; 24 of 80 106 : 105 /
-// 115 : 105 / 84 : 82; 1280 x 5120, 13 of 300 246 : 243 / 271 : 247 / 275 : 240; 1536 x 6144 323 : 325 / 342 : 319 / 335 : 312; 512 x
-// 2048 68 : 68 / 78 : 74 / 66 : 64; 1024 x 4096 172 : 170 / 179 : 178 / 171 : 166.  Below the lines: 2048 x 1280, 90 slots of 46
-// rows 324 : 329; 2048 x 3072 (NT 8 or 16), 13 of 80 138 : 141 / 137 : 139 / 128 : 131, 24 of 80 223 : 223 / 224 : 227 / 201 : 206.
-// 256-row tiles of up to 512 rows per slot: only for fewer rounds, but always in short reductions (K to 1536, fewer than 16 wide
-// panels: by panels, but for fewer rounds : in runs, means of 10 to 17 layers, K = 1024 1 % more, at most 0.5 % less, K = 1536 0.3 %; 2048 x
-// 1536, 19 slots of 170 123 : 117, 1792 x 1536, 13 of 290 105 : 100; 4096 x 1536 0.9 % less).  In longer ones they drift apart and lose where panels need no more
-// rounds: panels : runs, 4096 x 14336, 18 slots (NT 16: panels are shared out evenly) of 130 rows 1311 : 1410 / 1318 : 1407 / 1440 :
-// 1486, of 250 1856 : 1870 / 1816 : 1869 / 1850 : 1918, of 450 2729 : 2815 / - / 2802 : 2845; 3584 x 7680, 12 of 420 842 : 879 /
-// 886 : 897; 3072 x 7680 747 : 777 / 769 : 793.  Panels : for fewer rounds, equally used / bias 1: 2304 x 7680, 12 of 420 644 : 563 /
-// 659 : 571, of 240 412 : 411 / 468 : 424; 2304 x 2304, 28 of 220 325 : 325 / 386 : 359; 2560 x 5120, 28 of 220 718 : 685 / 745 : 709; 3072
-// x 3072, 16 of 350 384 : 381 / 401 : 388.  Over 512 rows the matrix cores bound them (4096 x 14336, 1260 rows 4624 : 4690 always in runs).
-// Up products read a few short rows of tokens for each of their panels (1024 x 4096 in runs 210 : 219).  Only for fewer rounds, and
-// where wide tiles were taken for being one (wide_below_a_round): 12 panels of unequal slots do not divide among the XCDs
-// as 24 narrow ones do.  Panels : runs where for fewer, layer, us, three pools in
-// turn, equally used / bias 0.5 / 1 / 2.5: 768 x 3072, 4096 tokens, 9 slots 84 : 84 / 96 : 88 / 97 : 92 / 82 : 76, 13 slots 86 : 86 / 102 : 97 /
-// 100 : 95 / 81 : 75, 18 slots 99 : 99 / 106 : 101 / 103 : 104 / 91 : 84; 1536 x 1536, 8000 tokens, 13 slots 133 : 122 / 139 : 124 / 142 : 128 / 133 : 118.
+// part of the traffic, min(8, NT) P against S N rows: from a quarter on, 128-row tiles with NT a multiple of 8 from half on.
+// Panels : runs, layer, us, three pools in turn, equally used slots / router bias 1 / 2.5, 128-row tiles:
+//   768 x 3072    13 slots of 300 rows  127 : 116 / 127 : 120 / 118 : 114    24 of 80  106 : 105 / 115 : 105 / 84 : 82
+//   1280 x 5120   13 of 300  246 : 243 / 271 : 247 / 275 : 240   1536 x 6144  13 of 300  323 : 325 / 342 : 319 / 335 : 312
+//   512 x 2048    13 of 300  68 : 68 / 78 : 74 / 66 : 64         1024 x 4096  13 of 300  172 : 170 / 179 : 178 / 171 : 166
+//   below the lines 2048 x 1280, 90 of 46  324 : 329; 2048 x 3072 (NT 8, 16) 13 of 80  138 : 141 / 137 : 139 / 128 : 131
+// 256-row tiles of up to 512 rows per slot: always in short reductions with fewer than 16 wide panels, else for fewer
+// rounds, and not where panels divide among the XCDs.  Long runs drift apart.  Panels : always in runs, as above:
+//   4096 x 14336, 18 slots  130 rows  1311 : 1410 / 1318 : 1407 / 1440 : 1486   250  1856 : 1870 / 1816 : 1869 / 1850 : 1918
+//                           450 rows  2729 : 2815 / - / 2802 : 2845
+//   3584 x 7680, 12 of 420  842 : 879 / 886 : 897                               3072 x 7680  747 : 777 / 769 : 793
+//   short: 2048 x 1536, 19 of 170  123 : 117   1792 x 1536, 13 of 290  105 : 100   means of 10 to 17 layers of each width
+//   from 1792 to 3584 K = 1024 1 % less, K = 1536 0.3 % less, but 4096 x 1536 0.9 % more
+// Panels : for fewer rounds, equally used / bias 1:
+//   2304 x 7680   12 of 420  644 : 563 / 659 : 571    12 of 240  412 : 411 / 468 : 424
+//   2304 x 2304   28 of 220  325 : 325 / 386 : 359    2560 x 5120  28 of 220  718 : 685 / 745 : 709
+//   3072 x 3072   16 of 350  384 : 381 / 401 : 388
+// Over 512 rows the matrix cores bound them (4096 x 14336, 1260 rows, always in runs 4624 : 4690).
+//
+// Up products read a few short rows of tokens for each of their panels (1024 x 4096 in runs 210 : 219).  Only for fewer
+// rounds, and where wide tiles were taken for being one (wide_below_a_round): 12 panels of unequal slots do not divide
+// among the XCDs as 24 narrow ones do.  Panels : for fewer rounds, equally used / bias 0.5 / 1 / 2.5:
+//   768 x 3072, 4096 tokens   9 slots   84 : 84 / 96 : 88 / 97 : 92 / 82 : 76    13  86 : 86 / 102 : 97 / 100 : 95 / 81 : 75
+//                             18 slots  99 : 99 / 106 : 101 / 103 : 104 / 91 : 84
+//   1536 x 1536, 8000 tokens  13 slots  133 : 122 / 139 : 124 / 142 : 128 / 133 : 118
+constexpr int kShortReduction = 1536;
 int xcd_runs(const mmoe_shape& s, int prod)
 {
     if (s.dtype == MMOE_F32) return kRunsNever;
@@ -659,7 +684,7 @@ int xcd_runs(const mmoe_shape& s, int prod)
     const int64_t P = (int64_t)s.T * s.top_k, rows = P * (nt < kXcds ? nt : kXcds), weights = (int64_t)s.S * s.d_model;
     if (bm == kBMBig) {
         if (P > (int64_t)512 * s.S || 4 * rows < weights) return kRunsNever;
-        if (nb_down == 2 && nt < 2 * kXcds && s.d_ff <= 1536) return kRunsAlways;
+        if (nb_down == 2 && nt < 2 * kXcds && s.d_ff <= kShortReduction) return kRunsAlways;
         return even ? kRunsNever : kRunsForFewerRounds;
     }
     return (even ? 2 : 4) * rows >= weights ? kRunsAlways : kRunsNever;

@@ -88,8 +88,9 @@ __device__ __forceinline__ float butterfly(float p)
     return p;
 }
 
-// Two levels of four butterflies at once (one exchange and one addition for two sums), then the other four levels of all of them: what a lane adds is its partner's
-// partial sum either way, so every sum is the contract's.  Lanes 0-15 have the sum of a, 16-31 of b, 32-47 of c, 48-63 of d.
+// Two levels of four butterflies at once (one exchange and one addition for two sums), then the other four levels of all of
+// them: what a lane adds is its partner's partial sum either way, so every sum is the contract's.  Lanes 0-15 have the sum of
+// a, 16-31 of b, 32-47 of c, 48-63 of d.
 __device__ __forceinline__ float butterfly4(float a, float b, float c, float d)
 {
     auto swap32 = [](float x, float y) {  // x in lanes 0-31, y in lanes 32-63
@@ -253,7 +254,8 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
 // those of them that share a variant instead of once per token, and unpacked once.  Token rows in LDS as
 // stored; wavefront w of sixteen scores experts w, w+16, ... for all of the group's tokens, whose sums share a
 // butterfly.  (Tried: rows in LDS in fp32, pairs of experts, the next rows requested a step ahead, with 4, 8 or 16
-// wavefronts: equal to a quarter slower, 6000 tokens of 2048, 32 experts 46 -> 48 to 57 us.)  Bound by the chain of reads per expert at the small end, by vector issue at the large.
+// wavefronts: equal to a quarter slower, 6000 tokens of 2048, 32 experts 46 -> 48 to 57 us.)  Bound by the chain of reads per
+// expert at the small end, by vector issue at the large.
 // 1024 tokens of 3072 elements, 64 experts, bf16: 39.1 (workgroup per token) -> 27.5 us, fp32 62.7 -> 25.5;
 // 8192 tokens of 4096, 64 experts: 237 (wavefront per token) -> 158 us; of 2304, 8 experts: 76.6 -> 35.7 us.
 constexpr int kRouteGroup = 4;
@@ -407,10 +409,13 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
 }
 
 // Most LDS for the token rows of a group: fp32 rows of 4096.  Over kRouteGroupLarge the rows, which have to arrive before the
-// first score, take long enough that there has to be something to score: fp32 rows of 3584 and 4096, two variants, other kernel : groups, us, caches warm / cold: 768 tokens, 1 expert 9.5 : 9.5 / 10.0 : 13.1, 4 9.5 : 9.5 / 12.6 : 13.7, 8 10.6 :
-// 9.4 / 16.2 : 14.9, 64 48 : 26 / 59 : 32; 1024 tokens, 1 9.5 : 9.5 / 12.5 : 14.3, 3 9.5 : 9.4 / 13.9 : 14.6, 4 9.5 : 9.5 / 14.9 : 14.8, 8 12.7 : 10.6 /
-// 19.4 : 16.3; 1536 tokens, 2 9.7 : 9.6 / 17.2 : 17.5, 3 10.5 : 9.8 / 18.3 : 17.7, 8 17.2 : 12.3 / 25.8 : 20.2; 2000 tokens, 1 11.0 : 9.6 /
-// 19.2 : 19.3, 2 12.2 : 9.9 / 20.4 : 19.6; and against a wavefront per token 2500 tokens of 4096, 16 37 : 25 / 60 : 36, 64 122 : 69 / 186 : 76.
+// first score, take long enough that there has to be something to score.  fp32 rows of 3584 and 4096, two variants, us,
+// caches warm / cold, the other kernel : groups, by tokens and experts:
+//   768   1  9.5 : 9.5 / 10.0 : 13.1     4  9.5 : 9.5 / 12.6 : 13.7    8  10.6 : 9.4 / 16.2 : 14.9   64  48 : 26 / 59 : 32
+//   1024  1  9.5 : 9.5 / 12.5 : 14.3     3  9.5 : 9.4 / 13.9 : 14.6    4  9.5 : 9.5 / 14.9 : 14.8    8  12.7 : 10.6 / 19.4 : 16.3
+//   1536  2  9.7 : 9.6 / 17.2 : 17.5     3  10.5 : 9.8 / 18.3 : 17.7   8  17.2 : 12.3 / 25.8 : 20.2
+//   2000  1  11.0 : 9.6 / 19.2 : 19.3    2  12.2 : 9.9 / 20.4 : 19.6
+//   against a wavefront per token  2500 tokens of 4096  16  37 : 25 / 60 : 36   64  122 : 69 / 186 : 76
 constexpr size_t kRouteGroupBytes = 64 << 10, kRouteGroupLarge = 48 << 10;
 constexpr int64_t kRouteLargeScores = 3500;  // tokens x experts
 

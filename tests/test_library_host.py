@@ -341,3 +341,14 @@ def test_routers_of_few_scores_take_no_groups_of_long_rows(mm, dispatch_rule):
                                  (768, 3072, 1, "f32", True), (768, 4096, 1, "bf16", True), (768, 4352, 64, "f32", False)):
         shape = mm.make_shape(T, d, 256, 2, E, E, 1, dtype, "relu")
         assert dispatch_rule("route_in_groups", shape) is want, (T, d, E, dtype)
+
+
+def test_few_wide_tiles_are_cut_in_two(mm, dispatch_rule):
+    """Down products of 256-row tiles: fewer wide tiles than half of the compute units, and a little over one round of them up to
+    100 rows per slot."""
+    for T, k, d, S, want in ((400, 2, 4096, 4, True), (1000, 2, 2304, 12, True), (720, 4, 2048, 9, True), (820, 4, 2048, 9, False),
+                             (1070, 2, 2560, 8, True), (1200, 2, 2560, 8, False), (777, 2, 4096, 18, True), (1170, 2, 4096, 18, False),
+                             (777, 2, 4096, 24, False)):
+        shape = mm.make_shape(T, d, 4096, 4, 8, S, k, "bf16", "swiglu")
+        assert mm.expert_plan(shape) == (False, 256)
+        assert dispatch_rule("few_wide_tiles", shape, d) is want, (T, k, d, S)
