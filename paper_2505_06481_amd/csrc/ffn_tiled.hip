@@ -475,7 +475,7 @@ __global__ __launch_bounds__(256, 1) void tiled_lone_kernel(
     tiled_body<MODE, kBMBig, 2, true>(A, perm, kdiv, tab, hdr, list_at, list_stride, W0, W1, out, K, N, sink_perm, sink_w);
 }
 
-// 256-row tiles of 128 features (few_wide_tiles).
+// 256-row tiles of 128 features (few_wide_tiles, tile_share).
 template <int MODE, bool LONE>
 __global__ __launch_bounds__(256, 1) void tiled_narrow_kernel(
     const uint16_t* __restrict__ A, const int32_t* __restrict__ perm, int kdiv, const int32_t* __restrict__ tab, int hdr,
@@ -609,10 +609,45 @@ int planned_tile_rows(const mmoe_shape& s)
     return P < (int64_t)(s.d_model <= 2048 ? 100 : 64) * s.S ? kBMSmall : kBMBig;
 }
 
-// Most sub-tiles of a row tile: a full tile.  (Shorter tiles for products with few tiles were
-// measured on the Switch shape and lost: every tile streams its whole weight panel.  That was with one step's
-// copies in flight, before short tiles had several.)
-static int planned_upt(const mmoe_shape&, int bm) { return bm / 32; }
+// How a product with N output features and 128-row tiles of one weight block per wavefront shares its rows out.
+//
+// Two tiles on one compute unit take nearly twice the time of one (768 x 3072 down, 128 rows: 17 us of main loop alone on a
+// compute unit, 30 beside another; the matrix pipe bounds both), and a tile more than there are compute units puts two on
+// one: 258 tiles took 37 us where 252 take 24.  So up to kFillRounds rounds of kCus tiles, counted as a full tile and a part of
+// one for every slot, a target height is chosen that just fills whole rounds of one tile for each compute unit, down to one
+// sub-tile (kFill); and where 128 rows to a tile do not do, but 256 do, tiles are 256 rows by 128 features and one round
+// (kTall: tiled_narrow_kernel, one workgroup to a compute unit).  kPlain: rounds of two tiles for each compute unit.
+// Plain : as the rule says, layer, us, three pools in turn, equally used slots unless a router bias is given:
+//   kTall  768 x 3072, 18 slots  4096 tokens 99.1 : 90.4, bias 0.5 100.9 : 90.2   8000 132.7 : 128.2
+//          24 slots, 4096 tokens, bias 1 111.9 : 103.2, GELU bias 2.5 99.0 : 87.6   1280 x 3328 GELU, 13 slots, 9000 242.9 : 243.5
+//   kFill  768 x 3072   8 slots  4096 tokens 84.7 : 75.3   18 slots  600 60.5 : 58.2   1000 63.4 : 61.8   2000 76.7 : 72.7
+//          11 slots, 1500 63.3 : 56.7   12 slots, 3000 77.3 : 71.6   1280 x 2560, 16 slots, 1200, bias 0.5 82.2 : 78.1
+//          1536 x 2048, 16 slots, 3000 92.8 : 92.6   512 x 2048, 32 slots, 3000 62.3 : 62.4
+//   past the line, with kFill and with kTall  1024 x 4096, 30 slots, 5000 (560 tiles) 183.2 : 187.5 : 193.4
+//          2048 x 1280, 90 slots, 4148 pairs 328.4 : 331.0 : -   768 x 3072, 14 slots, 12000 (648) 180.3 : 176.4 : 169.8
+enum TileShare { kPlain, kFill, kTall };
+constexpr int kFillRounds = 2;
+int tile_share(const mmoe_shape& s, int N, bool up)
+{
+    if (s.dtype == MMOE_F32 || planned_tile_rows(s) != kBMSmall || planned_nb(s, kBMSmall, N, up) != 1) return kPlain;
+    const int64_t P = (int64_t)s.T * s.top_k, nt = N / 128, most = ((P + kBMSmall - 1) / kBMSmall + s.S) * nt;
+    // (slots of 256-row tiles counted as five eighths of a tile more than their rows fill)
+    if (most > kCus && (8 * P / kBMBig + 5 * s.S) * nt <= 8 * kCus && !s.tile_rows) return kTall;
+    return most <= kFillRounds * kCus ? kFill : kPlain;
+}
+
+// Heights of a product's row tiles.  Shorter ones than five eighths of a full tile are bound by what they move, unless they
+// fill a round that would be partly idle.  fp32: down to one sub-tile (the matrix rate bounds tiles of any height, and short
+// ones share out a product of few tiles evenly); the workgroups of a compute unit (three, two of the gated product) share
+// its matrix pipes, which bound them, so it counts as working on one tile at a time.
+static TileRows tile_rows_of(const mmoe_shape& s, int bm, int share)
+{
+    if (s.dtype == MMOE_F32) return {kFRows / 32, 4, 1, 32, false};
+    if (bm == kBMBig) return {8, 20, 1, 32, false};
+    if (share == kTall) return {8, 4, 2, 32, true};
+    if (share == kFill) return {4, 4, 1, 32, true};
+    return {4, 10, 1, 64, false};
+}
 
 // Are panels read past the caches where a tile is the only one of its slot?  Where slots of one tile are likely, and
 // the pool is larger than the last-level cache: a smaller one may still be there from an earlier call, and the few
@@ -696,7 +731,10 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
     p.bm = planned_tile_rows(s);
     p.lone = lone_tiles(s);
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
-    p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, planned_upt(s, p.bm), planned_upt(s, p.bm), p.bm,
+    const int up = tile_share(s, s.d_ff, true), down = tile_share(s, s.d_model, false);
+    p.tall[0] = up == kTall;
+    p.tall[1] = down == kTall;
+    p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, tile_rows_of(s, p.bm, up), tile_rows_of(s, p.bm, down),
                      s.dtype == MMOE_F32, xcd_runs(s, 0), xcd_runs(s, 1), (int)(kLoneBytes / slot_bytes(s)) + 1);
     return p;
 }
@@ -717,21 +755,25 @@ size_t tiled_table_bytes(const mmoe_shape& s)
 size_t tiled_table_most(const mmoe_shape& s)
 {
     const int P = s.T * s.top_k;
-    size_t most = 0;
-    // Fewer pairs may get the other height and narrower feature tiles (planned_tile_rows, planned_nb, f32_in_parts); with
-    // each of them fixed the lists only grow with P.  (Wider feature tiles can make the longer lists: a number of
-    // them that is no multiple of 8 takes a list per XCD.)
+    // Fewer pairs may get the other height and narrower feature tiles (planned_tile_rows, planned_nb, f32_in_parts,
+    // tile_share); with each of them fixed the lists only grow with P.  (Wider feature tiles can make the longer lists: a
+    // number of them that is no multiple of 8 takes a list per XCD.)
     const bool f32 = s.dtype == MMOE_F32;
     const int wide = f32 ? kFeatF32 : 128;  // features of a tile with one weight block per wavefront
-    for (int bm : {f32 ? kFRows : kBMSmall, f32 ? kFRows : kBMBig})
-        for (int nb_up : {1, 2})
-            for (int nb_down : {1, 2}) {
-                const int nt_up = s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb_up);
-                const TileLists L = tile_lists(P, s.S, nt_up, s.d_model / (wide * nb_down), bm / 32, bm / 32, bm, f32, kRunsNever,
-                                               f32 ? kRunsNever : kRunsAlways, 0);
-                most = L.bytes > most ? L.bytes : most;
-            }
-    return align256(most);
+    size_t at = kListHeader;
+    for (int prod = 0; prod < 2; ++prod) {
+        int64_t most = 0;
+        for (int bm : {kBMSmall, kBMBig})
+            for (int nb : {1, 2})
+                for (int share : {kPlain, kFill, kTall}) {
+                    const int NT = prod == 0 ? (s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb)) : s.d_model / (wide * nb);
+                    const int cap = row_tiles_cap(P, s.S, NT, tile_rows_of(s, bm, share), f32);
+                    const int64_t n = (int64_t)list_count(NT, prod == 0 || f32 ? kRunsNever : kRunsAlways) * list_len(cap, NT);
+                    most = n > most ? n : most;
+                }
+        at += most;
+    }
+    return align256(at * 16);
 }
 
 template <int MODE, int BM, int NB>
@@ -756,7 +798,7 @@ static void launch_plain_product(const TiledPlan& p, int prod, const void* A, co
                                  GateSink sink = GateSink())
 {
     const int nb = prod == 0 ? p.nb_up : p.nb_down;
-    if (p.bm == kBMBig && nb == 1) launch_product<MODE, kBMBig, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
+    if ((p.bm == kBMBig || p.tall[prod]) && nb == 1) launch_product<MODE, kBMBig, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else if (p.bm == kBMBig) launch_product<MODE, kBMBig, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else if (nb == 2) launch_product<MODE, kBMSmall, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else launch_product<MODE, kBMSmall, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);

@@ -49,9 +49,7 @@ constexpr int kNtGroup = 4;  // least number of feature tiles whose workgroups s
 // round (layer, us, 2560 x 7680, 3200 pairs, 12 slots 496 : 561; 768 x 3072, 8000 tokens, 16 unequal slots 136 : 152).
 //
 // Target heights of a row tile that the table builder may choose from, in quarters of a 32-row
-// sub-tile: from a full tile (4 upt) down to hq_lo.  bf16: five eighths of a full tile (shorter tiles are
-// bound by what they move).  fp32: one sub-tile (the matrix rate bounds tiles of any height, and short
-// ones share out a product of few tiles evenly).
+// sub-tile: from a full tile (4 upt) down to hq_lo, which the host gives with the tile kernels (tile_rows_of).
 constexpr int kMaxHeightCands = 16;
 
 // In an entry's first word: the slot, and whether the tile holds all rows of the slot (not set where few slots hold rows).
@@ -60,45 +58,61 @@ static_assert(kMaxS <= kSlotMask, "slot ids");
 
 enum RunsRule { kRunsNever = 0, kRunsAlways = 1, kRunsForFewerRounds = 2 };
 
+// Heights of a product's row tiles, and how many of its tiles a compute unit works on at a time.
+struct TileRows {
+    int upt;      // most 32-row sub-tiles of a row tile
+    int hq_lo;    // least target height, in quarters of a sub-tile
+    int hq_step;  // quarters between two target heights
+    int conc;     // tiles that an XCD works on in the time of one, for the choice of the height
+    bool fill;    // the lists have room for as many row tiles as fill whole rounds of the chip
+};
+
 struct TileLists {
     int list[2];    // [product: up, down] -> int4 index into tab of XCD 0's list
     int lists[2];   // 1: the XCDs share one list; kXcds: one list each, `len` entries apart
     int len[2];     // entries reserved per list of each product: workgroups per XCD
     int runs[2];    // RunsRule
-    int upt[2];     // most 32-row sub-tiles of a row tile, per product
-    int hq_lo[2];   // least target height, in quarters of a sub-tile
-    int conc;       // workgroups that an XCD works on at a time, for the choice of the height
+    TileRows rows[2];
     int rows_cap[2]; // most row tiles of each product
     int lone_slots; // least number of slots with rows for which kOnlyTile is set (lone_tiles)
     size_t bytes;
 };
 
-inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, int upt_up, int upt_down, int bm, bool f32,
+// Row tiles the lists have room for: an eighth more than full tiles can need (fp32: than tiles of two
+// sub-tiles), which is sum_s ceil(ceil(c_s / 32) / upt) <= P / (32 upt) + S.  The grid of a product is
+// sized by this bound (the host does not know the counts), and a workgroup without a tile still waits
+// for a compute unit before it can leave, so the room for lower target heights is kept small; with `fill` it
+// reaches to the end of the last round that full tiles can need.
+inline int row_tiles_cap(int P, int S, int NT, const TileRows& r, bool f32)
+{
+    const int u = f32 ? 2 : r.upt;
+    const int full = (P + 32 * u - 1) / (32 * u) + S, cap = full + (full + 7) / 8;
+    if (!r.fill) return cap;
+    const int round = kXcds * r.conc;  // tiles
+    const int64_t filled = ((int64_t)full * NT + round - 1) / round * round / NT;
+    return filled > cap ? (int)filled : cap;
+}
+
+// Lists of a product with NT feature tiles, and entries of each: a slot has at most ceil(NT / 8) panels on one XCD.
+inline int list_count(int NT, int runs) { return NT % kXcds == 0 && runs == kRunsNever ? 1 : kXcds; }
+inline int list_len(int cap, int NT) { return cap * ((NT + kXcds - 1) / kXcds); }
+constexpr int kListHeader = 16;  // int4 units: the first 256 bytes
+
+inline TileLists tile_lists(int P, int S, int nt_up, int nt_down, const TileRows& up, const TileRows& down, bool f32,
                             int runs_up, int runs_down, int lone_slots)
 {
     TileLists L;
     L.lone_slots = lone_slots;
-    L.upt[0] = upt_up;
-    L.upt[1] = upt_down;
-    // fp32: the workgroups of a compute unit (three, two of the gated product) share its matrix pipes, which bound
-    // them, so a compute unit counts as working on one tile at a time
-    L.conc = bm == kBMBig || f32 ? 32 : 64;
-    for (int p = 0; p < 2; ++p) {
-        // Row tiles the lists have room for: an eighth more than full tiles can need (fp32: than tiles of two
-        // sub-tiles), which is sum_s ceil(ceil(c_s / 32) / upt) <= P / (32 upt) + S.  The grid of a product is
-        // sized by this bound (the host does not know the counts), and a workgroup without a tile still waits
-        // for a compute unit before it can leave, so the room for lower target heights is kept small.
-        const int upt = L.upt[p], u = f32 ? 2 : upt;
-        const int full = (P + 32 * u - 1) / (32 * u) + S;
-        L.rows_cap[p] = full + (full + 7) / 8;
-        L.hq_lo[p] = f32 ? 4 : (5 * upt + 1) / 2;
-    }
-    int at = 16;  // int4 units; the header takes the first 256 bytes
+    L.rows[0] = up;
+    L.rows[1] = down;
+    L.runs[0] = runs_up;
+    L.runs[1] = runs_down;
+    int at = kListHeader;
     for (int p = 0; p < 2; ++p) {
         const int NT = p == 0 ? nt_up : nt_down;
-        L.runs[p] = p == 0 ? runs_up : runs_down;
-        L.lists[p] = NT % kXcds == 0 && L.runs[p] == kRunsNever ? 1 : kXcds;
-        L.len[p] = L.rows_cap[p] * ((NT + kXcds - 1) / kXcds);  // a slot's panels on one XCD: ceil(NT / 8) at most
+        L.rows_cap[p] = row_tiles_cap(P, S, NT, L.rows[p], f32);
+        L.lists[p] = list_count(NT, L.runs[p]);
+        L.len[p] = list_len(L.rows_cap[p], NT);
         L.list[p] = at;
         at += L.lists[p] * L.len[p];
     }
@@ -144,7 +158,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     __shared__ int total[kXcds];       // entries of every XCD's list
     __shared__ int units_all, chosen_hq;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int conc = L.conc, upt = L.upt[p];
+    const int conc = L.rows[p].conc, upt = L.rows[p].upt, hq_step = L.rows[p].hq_step;
     int4* lists = reinterpret_cast<int4*>(tab);
     auto units_of = [&](int s) { return s >= S || filt.skips(s) ? 0 : (off[s + 1] - off[s] + 31) >> 5; };
     auto tiles_at = [&](int u, int hq) { return max(div24(u + upt - 1, upt), div24(4 * u + hq - 1, hq)); };
@@ -155,7 +169,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     // (half a sub-tile's worth of time: prologue and epilogue) plus its height.  Lower targets also
     // bring the slots' tile heights closer together.  The cut decides where tiles begin, not what a
     // row's result is.
-    const int hq_hi = 4 * upt, ncand = hq_hi - L.hq_lo[p] + 1;  // <= kMaxHeightCands
+    const int hq_hi = 4 * upt, ncand = (hq_hi - L.rows[p].hq_lo) / hq_step + 1;  // <= kMaxHeightCands
     if (tid < kMaxHeightCands) cand[tid] = 0;
     if (tid == 0) units_all = 0;
     __syncthreads();
@@ -165,7 +179,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
         for (int s = tid / kMaxHeightCands; s < S; s += kListThreads / kMaxHeightCands) {
             const int u = units_of(s);
             units += u;
-            if (c < ncand) tiles += tiles_at(u, hq_hi - c);
+            if (c < ncand) tiles += tiles_at(u, hq_hi - hq_step * c);
         }
         if (tiles) atomicAdd(&cand[c], tiles);
         if (c == 0 && units) atomicAdd(&units_all, units);
@@ -189,7 +203,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
                 best = ob;
             }
         }
-        if (lane == 0) chosen_hq = hq_hi - best;
+        if (lane == 0) chosen_hq = hq_hi - hq_step * best;
     }
     __syncthreads();
     // exclusive prefix sums of the row tiles and of the slots that hold rows, a slot to a thread
@@ -291,6 +305,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
 bool lone_tiles(const mmoe_shape& s);
 struct TiledPlan {
     int bm, nt_up, nt_down, nb_up, nb_down;
+    bool tall[2];  // 256-row tiles beside a height of 128 (tile_share), per product
     bool lone;  // the kernels that read the panels of one-tile slots past the caches (lone_tiles)
     TileLists L;
 };

@@ -464,6 +464,29 @@ def test_few_used_slots_of_large_pools_stay_cached(mm, gc, oracle, dispatch_rule
     assert only == {s: want and rows[s] <= 256 for s in only} and len(only) > 4
 
 
+@pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,up,down", [
+    # a round that 128 rows to a tile do not fill evenly, tiles of every height up to 256 rows; either product, each output
+    (3500, 2, 14, 1, 768, 256, "relu", 0.5, 1, 2), (3300, 2, 12, 1, 256, 1024, "gelu", 1.0, 2, 1), (1800, 1, 16, 2, 768, 512, "swiglu", 0.6, 0, 2),
+    (700, 2, 8, 1, 1024, 1280, "relu", 2.0, 1, 1), (70, 1, 1, 1, 256, 256, "gelu", 0.0, 1, 1),     # rows that a round has room for
+    (2600, 1, 9, 1, 1280, 2048, "relu", 2.5, 2, 2), (2900, 1, 40, 1, 1280, 256, "relu", 1.0, 1, 0)])  # both tall; more than a round
+def test_row_tiles_that_fill_whole_rounds(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f, act, alpha, up, down):
+    """Row tiles of a height that gives every compute unit one (1), of up to 256 rows where 128 do not do (2), and plain ones."""
+    cfg = synth.Config(f"fill_{T}_{d}", T, d, f, V, E, k, "bf16", act, seed=1700 + T, bias_alpha=alpha)
+    case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
+    assert mm.expert_plan(case.shape) == (False, 128)
+    share = lambda n, is_up: dispatch_rule("tile_share", case.shape, n, is_up, restype=ctypes.c_int)
+    assert (share(f, True), share(d, False)) == (up, down)
+
+
+@pytest.mark.parametrize("d,counts", [
+    (768, [512, 540, 490, 515, 520, 500, 530, 489]),                                   # 128 rows: 43 row tiles, 258 tiles, in full height
+    (768, [350, 128, 360, 140, 330, 90, 129, 340, 100, 380, 128, 160, 350, 120, 345, 355, 110, 141]), (256, [3000, 1, 0, 900])])
+def test_one_tile_to_a_compute_unit(mm, gc, oracle, dispatch_rule, d, counts):
+    shape, tab = expert_lists(mm, gc, oracle, d, 256, "relu", counts)
+    assert mm.expert_plan(shape) == (False, 128) and dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) in (1, 2)
+    assert in_runs(tab[8:16]) and 24 < tab[8:16].max() <= 32
+
+
 @pytest.mark.parametrize("act,k,E,d,f", [("gelu", 1, 16, 1024, 1536), ("swiglu", 2, 12, 1280, 1024)])
 def test_tiles_of_128_rows_in_large_pools(mm, gc, oracle, dispatch_rule, act, k, E, d, f):
     """Slots of one tile, whose weights are read past the caches, of every height, beside slots of several tiles."""

@@ -352,3 +352,26 @@ def test_few_wide_tiles_are_cut_in_two(mm, dispatch_rule):
         shape = mm.make_shape(T, d, 4096, 4, 8, S, k, "bf16", "swiglu")
         assert mm.expert_plan(shape) == (False, 256)
         assert dispatch_rule("few_wide_tiles", shape, d) is want, (T, k, d, S)
+
+
+def test_row_tiles_fill_rounds_of_few_tiles(mm, dispatch_rule):
+    """Ungated products of narrow 128-row tiles: heights that fill a round (1) up to 512 tiles, counted with one more for every slot;
+    256-row tiles (2) where those may be more than a round of 256 and these are not; neither beyond, nor with a forced height of 256."""
+    for T, d, S, rows, want in ((4096, 768, 18, 0, 2), (4096, 768, 18, 128, 1), (4096, 768, 18, 256, 0), (4096, 768, 8, 0, 1),
+                                (3072, 768, 18, 0, 1), (3073, 768, 18, 0, 2), (8063, 768, 18, 0, 2), (8064, 768, 18, 0, 1),
+                                (8576, 768, 18, 0, 1), (8577, 768, 18, 0, 0), (5000, 1024, 30, 0, 0), (600, 1536, 18, 0, 2), (500, 1536, 16, 0, 1),
+                                (600, 1792, 8, 0, 1), (1000, 1792, 8, 0, 0)):
+        shape = mm.make_shape(T, d, 3072, 4, 8, S, 1, "bf16", "relu", tile_rows=rows)
+        assert dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) == want, (T, d, S, rows)
+        assert dispatch_rule("tile_share", mm.make_shape(T, d, 3072, 4, 8, S, 1, "f32", "relu"), d, False, restype=ctypes.c_int) == 0
+
+
+def test_lists_of_every_batch_fit_the_room_of_the_largest(mm, dispatch_rule):
+    for d, f, S, k, dtype, act in ((768, 3072, 18, 1, "bf16", "relu"), (256, 1024, 300, 1, "bf16", "gelu"), (1280, 2560, 16, 2, "bf16", "swiglu"),
+                                   (1536, 768, 5, 1, "bf16", "relu"), (2304, 1024, 12, 2, "bf16", "gelu"), (768, 3072, 13, 1, "f32", "relu")):
+        last = 0
+        for T in range(200, 12000, 37):
+            shape = mm.make_shape(T, d, f, 2, 8, S, k, dtype, act)
+            most = dispatch_rule("tiled_table_most", shape, restype=ctypes.c_size_t)
+            assert dispatch_rule("tiled_table_bytes", shape, restype=ctypes.c_size_t) <= most and last <= most, (T, d, f)
+            last = most
