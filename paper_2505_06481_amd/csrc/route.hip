@@ -1,7 +1,8 @@
 // Step R: per-variant gate, top-k selection and coefficients (Algorithm 2, "gate(act)";
-// section 3.2).  Three launch shapes with the same arithmetic: small batches give a token to a
+// section 3.2).  Four launch shapes with the same arithmetic: small batches give a token to a
 // workgroup whose wavefronts share out the experts (latency); large batches give a token to
-// one wavefront that keeps the token row in registers and walks the experts (throughput).
+// one wavefront that keeps the token row in registers and walks the experts, or four tokens to a workgroup, or, with
+// much to score, four tokens of a variant to a wavefront (throughput).
 //
 // The logit is an fp32 sum in the fixed order the header states: lane l owns the
 // elements i with (i div 4) mod 64 == l, which is exactly what a coalesced 4-element
@@ -190,6 +191,65 @@ __device__ __forceinline__ void select_topk(const float* __restrict__ lds_logit,
                 if (map_row) slot[(size_t)t * k + j] = min(max(map_row[seli[j]], 0), S - 1);
             }
     }
+}
+
+// The same for four tokens of a wavefront at once, E <= 16: lanes 16 i .. 16 i + 15 look after token i's experts (its
+// logits at lds_logit + i * kMaxE, its number in `t`, `map` the table's entry for this lane's expert if `look_up`; `write`: not
+// for the repeats that fill a group).
+__device__ __forceinline__ void select_topk4(const float* __restrict__ lds_logit, int lane, int E, int k, int t, bool write,
+                                             int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+                                             bool look_up, int map, int32_t* __restrict__ slot, int S, int gate)
+{
+    const int e = lane & 15;
+    const float mine = e < E ? lds_logit[(lane >> 4) * kMaxE + e] : -INFINITY;
+    bool taken = e >= E;
+    float sel[kMaxTopK];
+    int seli[kMaxTopK];
+#pragma unroll
+    for (int j = 0; j < kMaxTopK; ++j) {
+        if (j < k) {
+            float bv = taken ? -INFINITY : mine;
+            int be = taken ? kNoExpert : e;
+            for_offsets_below(E, [&](auto off) {  // within 16 lanes
+                const float ov = lane_xor<decltype(off)::value>(bv);
+                const int oe = lane_xor<decltype(off)::value>(be);
+                const bool take = oe != kNoExpert && (be == kNoExpert || ov > bv || (ov == bv && oe < be));
+                bv = take ? ov : bv;
+                be = take ? oe : be;
+            });
+            sel[j] = bv;
+            seli[j] = be;
+            taken = taken || be == e;
+        }
+    }
+    float tot = 0.0f;
+    if (gate == MMOE_GATE_ALL) {
+        if (e < E) tot += expf(mine - sel[0]);
+        for_offsets_below(E, [&](auto off) { tot += lane_xor<decltype(off)::value>(tot); });
+    }
+    int place[kMaxTopK];
+    if (look_up) {
+#pragma unroll
+        for (int j = 0; j < kMaxTopK; ++j)
+            if (j < k) place[j] = __shfl(map, (lane & 48) | (seli[j] & 15), kWave);
+    }
+    if (e != 0 || !write) return;
+    float z[kMaxTopK];
+    float picked = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kMaxTopK; ++j)
+        if (j < k) {
+            z[j] = expf(sel[j] - sel[0]);
+            picked += z[j];
+        }
+    if (gate != MMOE_GATE_ALL) tot = picked;
+#pragma unroll
+    for (int j = 0; j < kMaxTopK; ++j)
+        if (j < k) {
+            topk_idx[(size_t)t * k + j] = seli[j];
+            topk_w[(size_t)t * k + j] = z[j] / tot;
+            if (look_up) slot[(size_t)t * k + j] = min(max(place[j], 0), S - 1);  // the clamp as in select_topk
+        }
 }
 
 // One workgroup per token; wavefront w scores experts w, w+8, ...  A token's dot product
@@ -408,6 +468,150 @@ __global__ __launch_bounds__(kRouteTokWaves* kWave) void route_token_kernel(
     select_topk(mylogit, lane, E, k, t, topk_idx, topk_w, M ? lds_map[wave] : nullptr, slot, S, gate);
 }
 
+// bf16 batches with much to score: four tokens of one variant against four or eight experts to a wavefront, straight from
+// memory.  A router row is then read and unpacked once for four tokens, a token row once for as many experts, where the
+// other kernels unpack one or both for every product; bound by vector issue and, at the small end, by the latency of the
+// loads, which only other wavefronts hide: chunks requested ahead cost the registers of those (1037 tokens of 2048, 64 experts, four
+// chunks in flight 30.2 us, two 20.1, one 19.9).  Time against the other kernels: route_in_tiles.
+//
+// Groups: a chunk of 64 tokens is cut, variant by variant in the order of their first tokens, into groups of four of a
+// variant (the last one of a variant filled up with repeats, which are not written); workgroup or wavefront j of a chunk
+// finds group j from the 64 ids by ballots, and leaves if there are fewer.
+constexpr int kTileChunk = 64, kTileTokens = 4;
+inline int tile_groups(int V) { return kTileChunk / kTileTokens + (3 * V + 3) / 4 < kTileChunk ? kTileChunk / kTileTokens + (3 * V + 3) / 4 : kTileChunk; }
+
+// SOLO: every wavefront of four has a group of its own and scores all experts (E <= EB); otherwise the W wavefronts of a
+// workgroup share a group, EB experts at a time each.
+template <int EB, int W, bool SOLO>
+__global__ __launch_bounds__(W* kWave) void route_tile_kernel(
+    const uint16_t* __restrict__ X, const int32_t* __restrict__ vid, const uint16_t* __restrict__ Wr,
+    const float* __restrict__ br, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int Tn, int d,
+    int V, int E, int k, const int32_t* __restrict__ M, int32_t* __restrict__ slot, int S, int gate, int groups)
+{
+    constexpr int TB = kTileTokens;
+    static_assert(EB % 4 == 0 && TB == 4 && W >= TB, "sums of four experts share a butterfly; a wavefront selects for a token");
+    __shared__ float lds_logit[SOLO ? W : 1][TB][kMaxE];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int unit = SOLO ? blockIdx.x * W + wave : blockIdx.x;
+    const int chunk = unit / groups, base = chunk * kTileChunk;
+    if (base >= Tn) return;  // uniform over the wavefront, and over the workgroup where it shares a group
+    int j = unit - chunk * groups;
+
+    const bool there = base + lane < Tn;
+    const int mv = there ? min(max(vid[base + lane], 0), V - 1) : -1;  // out-of-range ids are the caller's error; stay in bounds
+    unsigned long long todo = __ballot(there), members = 0;
+    int v = 0, n = 0;
+    while (todo) {
+        v = __builtin_amdgcn_readlane(mv, (int)__builtin_ctzll(todo));
+        members = __ballot(mv == v);
+        n = __popcll(members);
+        const int g = (n + TB - 1) / TB;
+        if (j < g) break;
+        j -= g;
+        todo &= ~members;
+    }
+    if (!todo) return;  // the chunk has fewer groups; uniform as above
+    const int rank = __popcll(members & ((1ull << lane) - 1ull));
+    int tok[TB];
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+        tok[i] = base + (int)__builtin_ctzll(__ballot(mv == v && rank == min(TB * j + i, n - 1)));
+    const int have = min(TB, n - TB * j);
+
+    __shared__ int32_t lds_map[SOLO ? 1 : kMaxE];
+    int map = 0;
+    if (M && SOLO) map = M[(size_t)v * E + min(lane & 15, E - 1)];
+    if (M && !SOLO)
+        for (int e = threadIdx.x; e < E; e += W * kWave) lds_map[e] = M[(size_t)v * E + e];
+
+    const uint16_t* xrow[TB];
+#pragma unroll
+    for (int i = 0; i < TB; ++i) xrow[i] = X + (size_t)tok[i] * d;
+    const uint16_t* wbase = Wr + (size_t)v * E * d;
+    const int nc = d / 256;
+    float* const logit = &lds_logit[SOLO ? wave : 0][0][0];
+    for (int e0 = SOLO ? 0 : wave * EB; e0 < E; e0 += W * EB) {
+        const uint16_t* wrow[EB];
+#pragma unroll
+        for (int b = 0; b < EB; ++b) wrow[b] = wbase + (size_t)min(e0 + b, E - 1) * d;
+        float acc[TB][EB];
+#pragma unroll
+        for (int i = 0; i < TB; ++i)
+#pragma unroll
+            for (int b = 0; b < EB; ++b) acc[i][b] = 0.0f;
+        for (int c = 0; c < nc; ++c) {
+            const int o = 256 * c + 4 * lane;
+            u32x2 xv[TB], wv[EB];
+#pragma unroll
+            for (int i = 0; i < TB; ++i) xv[i] = *reinterpret_cast<const u32x2*>(xrow[i] + o);
+#pragma unroll
+            for (int b = 0; b < EB; ++b) wv[b] = *reinterpret_cast<const u32x2*>(wrow[b] + o);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {  // ascending i within the lane
+                float x[TB];
+#pragma unroll
+                for (int i = 0; i < TB; ++i) x[i] = Raw4<uint16_t>::get(xv[i], q);
+#pragma unroll
+                for (int b = 0; b < EB; ++b) {
+                    const float w = Raw4<uint16_t>::get(wv[b], q);
+#pragma unroll
+                    for (int i = 0; i < TB; ++i) acc[i][b] = __builtin_fmaf(x[i], w, acc[i][b]);
+                }
+            }
+        }
+#pragma unroll
+        for (int b0 = 0; b0 < EB; b0 += 4) {
+            const int e = e0 + b0 + lane / 16;
+            const bool mine = (lane & 15) == 0 && e < E;
+            const float bias = br && mine ? br[(size_t)v * E + e] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < TB; ++i) {
+                const float p = butterfly4(acc[i][b0], acc[i][b0 + 1], acc[i][b0 + 2], acc[i][b0 + 3]);
+                if (mine) logit[i * kMaxE + e] = br ? p + bias : p;
+            }
+        }
+    }
+    if (SOLO) {
+        // one wavefront's LDS operations execute in program order, the fence keeps the compiler from moving them
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int i = lane >> 4, t = i == 0 ? tok[0] : i == 1 ? tok[1] : i == 2 ? tok[2] : tok[3];
+        select_topk4(logit, lane, E, k, t, i < have, topk_idx, topk_w, M != nullptr, map, slot, S, gate);
+        return;
+    }
+    __syncthreads();
+    if (wave >= have) return;
+    const int t = wave == 0 ? tok[0] : wave == 1 ? tok[1] : wave == 2 ? tok[2] : tok[3];
+    select_topk(logit + wave * kMaxE, lane, E, k, t, topk_idx, topk_w, M ? lds_map : nullptr, slot, S, gate);
+}
+
+template <int EB, int W, bool SOLO>
+static void launch_tiles(const mmoe_shape& s, const void* X, const int32_t* vid, const void* Wr, const float* br,
+                         int32_t* topk_idx, float* topk_w, hipStream_t st, const int32_t* M, int32_t* slot)
+{
+    const int groups = tile_groups(s.V);
+    const int64_t units = (int64_t)((s.T + kTileChunk - 1) / kTileChunk) * groups;
+    const dim3 grid((unsigned)(SOLO ? (units + W - 1) / W : units));
+    hipLaunchKernelGGL((route_tile_kernel<EB, W, SOLO>), grid, dim3(W * kWave), 0, st, (const uint16_t*)X, vid, (const uint16_t*)Wr,
+                       br, topk_idx, topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S, s.gate, groups);
+}
+
+// Measured against the other kernels, us, caches warm / cold, two to four variants:
+//   8 experts   2500 tokens of 4096 18.2 : 16.4 / 27.8 : 24.2   8192 of 4096 41.4 : 24.5 / 59.0 : 44.5   16384 of 4096 82 : 49 / 105 : 70
+//               8000 of 768 10.6 : 9.1 / 15.4 : 14.2   16000 of 2048 38 : 22 / 53 : 38   1500 of 4096 14.9 : 16.1 / 18.8 : 23.1
+//               4096 of 768 6.8 : 7.4 / 11.0 : 11.6
+//   16          9000 of 2048 40 : 26 / 49 : 39   600 of 1024 5.7 : 6.2 / 8.4 : 10.7
+//   32          700 of 3072 19.7 : 11.4 / 23.0 : 20.4   8000 of 1024 35.8 : 27.0 / 41.4 : 33.7   600 of 1024 8.3 : 7.4 / 11.1 : 12.2
+//   64          1037 of 2048 28.6 : 19.8 / 32.3 : 24.0   4000 of 2048 54 : 39 / 59 : 47   16000 of 256 42.8 : 42.1 / 49.8 : 46.5
+//               512 of 2048 16.4 : 13.6 / 19.0 : 20.6   256 of 2048 11.3 : 13.3 / 15.6 : 20.3
+// Wavefronts of eight experts with fewer than seven to score would idle.
+constexpr int64_t kTileScores = 45 << 20;  // elements multiplied
+bool route_in_tiles(const mmoe_shape& s)
+{
+    return s.dtype == MMOE_BF16 && s.E >= 7 && s.T >= (s.E <= 8 ? kRouteTokMinT : 640) && (int64_t)s.T * s.d_model * s.E >= kTileScores;
+}
+
 // Most LDS for the token rows of a group: fp32 rows of 4096.  Over kRouteGroupLarge the rows, which have to arrive before the
 // first score, take long enough that there has to be something to score.  fp32 rows of 3584 and 4096, two variants, us,
 // caches warm / cold, the other kernel : groups, by tokens and experts:
@@ -445,6 +649,15 @@ bool route_in_groups(const mmoe_shape& s)
 int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const void* Wr, const float* br,
                  int32_t* topk_idx, float* topk_w, hipStream_t st, const int32_t* M, int32_t* slot)
 {
+    if (route_in_tiles(s)) {
+        // (with one workgroup of eight wavefronts to a group the few tokens of small batches occupy more of the chip)
+        if (s.E <= 8) launch_tiles<8, 4, true>(s, X, vid, Wr, br, topk_idx, topk_w, st, M, slot);
+        else if (s.E <= 16) launch_tiles<4, 4, false>(s, X, vid, Wr, br, topk_idx, topk_w, st, M, slot);
+        else if (s.E <= 32) launch_tiles<4, 8, false>(s, X, vid, Wr, br, topk_idx, topk_w, st, M, slot);
+        else if (s.T < kRouteTokMinT) launch_tiles<8, 8, false>(s, X, vid, Wr, br, topk_idx, topk_w, st, M, slot);
+        else launch_tiles<8, 4, false>(s, X, vid, Wr, br, topk_idx, topk_w, st, M, slot);
+        return launch_status();
+    }
     // Large batches of a common hidden size: a wavefront per token (the token row is read
     // once); with more to score, a workgroup per four tokens; otherwise a workgroup per token (lower
     // latency, any d).

@@ -354,6 +354,37 @@ def test_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, rows):
             assert dispatch_rule("xcd_runs", case.shape, 1, restype=ctypes.c_int) == 1
 
 
+@pytest.mark.parametrize("T,d,V,E,k,gate", [
+    (2051, 4096, 1, 8, 2, "selected"), (2113, 4096, 3, 7, 7, "all"), (2100, 2816, 70, 8, 1, "all"),   # a group to a wavefront; more variants than a chunk has tokens
+    (1300, 4096, 4, 9, 2, "selected"), (1025, 3072, 2, 16, 4, "all"),                                  # to a workgroup, with every number of wavefronts
+    (1000, 3072, 3, 17, 8, "selected"), (644, 2560, 5, 32, 2, "all"), (641, 3072, 3, 33, 4, "all"), (650, 1280, 2, 67, 3, "selected"),
+    (2049, 512, 3, 66, 4, "all"), (2050, 256, 2, 255, 8, "selected")])
+def test_router_tiles_agree_bit_for_bit(mm, gc, dispatch_rule, T, d, V, E, k, gate):
+    """Groups of four tokens of a variant, the last ones of a chunk of 64 not full, against the parts of the batch on the kernels
+    for fewer tokens: the same picks, the same bits of every coefficient, and in the layer the same slots."""
+    cfg = synth.Config(f"tiles_{T}_{d}_{E}", T, d, 256, V, E, k, "bf16", "relu", seed=1900 + T + E, bias_alpha=0.5, gate=gate)
+    inp = synth.make_inputs(cfg, weights=False)
+    X, Wr, br = gc.to_dev(inp["X"], "bf16"), gc.to_dev(inp["Wr"], "bf16"), torch.from_numpy(inp["br"]).cuda()
+    vid = torch.from_numpy(inp["vid"]).cuda()
+    make = lambda n: mm.make_shape(n, d, 256, V, E, E, k, "bf16", "relu", gate=gate)
+    assert dispatch_rule("route_in_tiles", make(T))
+    idx, w = mm.route(make(T), X, vid, Wr, br)
+    none, _ = mm.route(make(T), X, vid, Wr)
+    for t0 in range(0, T, 300):
+        n = min(300, T - t0)
+        assert not dispatch_rule("route_in_tiles", make(n))
+        part_idx, part_w = mm.route(make(n), X[t0:t0 + n], vid[t0:t0 + n], Wr, br)
+        assert torch.equal(part_idx, idx[t0:t0 + n]) and torch.equal(part_w, w[t0:t0 + n]), t0
+        assert torch.equal(mm.route(make(n), X[t0:t0 + n], vid[t0:t0 + n], Wr)[0], none[t0:t0 + n]), t0
+
+
+@pytest.mark.parametrize("T,E,k,d", [(1300, 8, 2, 4608), (2100, 8, 1, 3072), (650, 16, 2, 4608)])
+def test_layer_behind_router_tiles(mm, gc, oracle, dispatch_rule, T, E, k, d):
+    cfg = synth.Config(f"tiles_layer_{T}_{E}", T, d, 256, 3, E, k, "bf16", "relu", seed=2000 + T, bias_alpha=0.5)
+    case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
+    assert dispatch_rule("route_in_tiles", case.shape) == (T * d * E >= 45 << 20 and T >= (2048 if E <= 8 else 640))
+
+
 def expert_lists(mm, gc, oracle, d, f, act, counts, tile_rows=0):
     """The expert stage on slots of `counts` rows, against the oracle; its shape and the tile lists it has left in the
     workspace behind H (int32)."""
