@@ -71,14 +71,9 @@ __global__ __launch_bounds__(kPermThreads) void slot_scan_kernel(const int32_t* 
         for (int s0 = 0; s0 < S; s0 += kWave) {
             int s = s0 + threadIdx.x;
             int c = s < S ? tot[s] : 0;
-            int incl = c;
-#pragma unroll
-            for (int dlt = 1; dlt < kWave; dlt <<= 1) {
-                int o = __shfl_up(incl, dlt, kWave);
-                if ((int)threadIdx.x >= dlt) incl += o;
-            }
+            const int incl = wave_scan(c);
             if (s < S) off[s] = carry + incl - c;
-            carry += __shfl(incl, kWave - 1, kWave);
+            carry += last_lane(incl);
         }
         if (threadIdx.x == 0) off[S] = carry;
     }
@@ -171,12 +166,12 @@ __global__ __launch_bounds__(kPermThreads) void slot_scatter_kernel(const int32_
             for (int s0 = 0; s0 < S; s0 += kWave) {
                 const int sl = s0 + threadIdx.x;
                 const int c = sl < S ? tot[sl] : 0;
-                const int incl = wave_scan(c, lane);
+                const int incl = wave_scan(c);
                 if (sl < S) {
                     tot[sl] = carry + incl - c;
                     if (b == nblk) offsets[sl] = carry + incl - c;
                 }
-                carry += __shfl(incl, kWave - 1, kWave);
+                carry += last_lane(incl);
             }
             if (b == nblk && threadIdx.x == 0) offsets[S] = carry;
         }
@@ -306,7 +301,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(
             tot += c;
         }
     }
-    const int incl = wave_scan(tot, lane);
+    const int incl = wave_scan(tot);
     if (lane == kWave - 1) part[wave] = incl;
     __syncthreads();
     int before = 0;
