@@ -725,6 +725,22 @@ int xcd_runs(const mmoe_shape& s, int prod)
     return (even ? 2 : 4) * rows >= weights ? kRunsAlways : kRunsNever;
 }
 
+// The same for the down products in fp32, where token rows are twice as much of the traffic and the lines are the same: 768 x
+// 3072, 13 slots, 2000 tokens read 264 MB in turn, of which 148 token rows.  Panels : runs, layer, us, three pools in turn:
+//   768 x 3072   13 slots  2000 tokens 175 : 172   4096 311 : 282   GELU, bias 2.5 330 : 270   1000, bias 0.5 156.6 : 154.0   200 83.7 : 82.7
+//                24 slots  3000, bias 0.5 309 : 262   500 134.2 : 133.3
+//   1536 x 4096, 12 slots, 1000 tokens 252 : 231   256 x 2048 GELU, 12 slots, 2000 pairs, bias 0.5 86.4 : 79.6
+//   as many panels as XCDs or more  1024 x 2048 SwiGLU, 13 slots, 2400 pairs 225 : 222   2048 x 1024 GELU, 12 slots, 700 tokens 107.7 : 107.2
+//   4096 x 1024, 12 slots, 300 tokens 117.8 : 117.1
+// (The up product in runs too: 2000 tokens 172 : 179.)
+bool f32_down_in_runs(const mmoe_shape& s)
+{
+    int nt_up, nt, nb_up, nb_down;
+    tiled_nts(s, kFRows, nt_up, nt, nb_up, nb_down);
+    const int64_t P = (int64_t)s.T * s.top_k, rows = P * (nt < kXcds ? nt : kXcds), weights = (int64_t)s.S * s.d_model;
+    return (nt % kXcds == 0 ? 2 : 4) * rows >= weights;
+}
+
 static TiledPlan tiled_plan(const mmoe_shape& s)
 {
     TiledPlan p;
@@ -735,7 +751,8 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
     p.tall[0] = up == kTall;
     p.tall[1] = down == kTall;
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, tile_rows_of(s, p.bm, up), tile_rows_of(s, p.bm, down),
-                     s.dtype == MMOE_F32, xcd_runs(s, 0), xcd_runs(s, 1), (int)(kLoneBytes / slot_bytes(s)) + 1);
+                     s.dtype == MMOE_F32, xcd_runs(s, 0), s.dtype == MMOE_F32 && f32_down_in_runs(s) ? kRunsAlways : xcd_runs(s, 1),
+                     (int)(kLoneBytes / slot_bytes(s)) + 1);
     return p;
 }
 
@@ -768,7 +785,7 @@ size_t tiled_table_most(const mmoe_shape& s)
                 for (int share : {kPlain, kFill, kTall}) {
                     const int NT = prod == 0 ? (s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb)) : s.d_model / (wide * nb);
                     const int cap = row_tiles_cap(P, s.S, NT, tile_rows_of(s, bm, share), f32);
-                    const int64_t n = (int64_t)list_count(NT, prod == 0 || f32 ? kRunsNever : kRunsAlways) * list_len(cap, NT);
+                    const int64_t n = (int64_t)list_count(NT, prod == 0 ? kRunsNever : kRunsAlways) * list_len(cap, NT);
                     most = n > most ? n : most;
                 }
         at += most;

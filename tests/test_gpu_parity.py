@@ -509,6 +509,16 @@ def test_row_tiles_that_fill_whole_rounds(mm, gc, oracle, dispatch_rule, T, V, E
     assert (share(f, True), share(d, False)) == (up, down)
 
 
+@pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,runs", [
+    (900, 2, 6, 1, 768, 512, "relu", 1.0, True), (1300, 1, 5, 1, 256, 768, "gelu", 0.5, True),         # six panels a slot, two or four
+    (700, 2, 8, 2, 1024, 256, "swiglu", 2.0, True), (500, 1, 3, 2, 2304, 256, "swiglu", 0.5, True),    # as many panels as XCDs and more
+    (60, 1, 1, 1, 256, 256, "relu", 0.0, True), (330, 1, 24, 1, 2048, 256, "relu", 0.3, False)])
+def test_fp32_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f, act, alpha, runs):
+    cfg = synth.Config(f"runs_f32_{T}_{d}", T, d, f, V, E, k, "f32", act, seed=2100 + T, bias_alpha=alpha)
+    case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
+    assert mm.expert_plan(case.shape) == (False, 96) and dispatch_rule("f32_down_in_runs", case.shape) is runs
+
+
 @pytest.mark.parametrize("d,counts", [
     (768, [512, 540, 490, 515, 520, 500, 530, 489]),                                   # 128 rows: 43 row tiles, 258 tiles, in full height
     (768, [350, 128, 360, 140, 330, 90, 129, 340, 100, 380, 128, 160, 350, 120, 345, 355, 110, 141]), (256, [3000, 1, 0, 900])])
