@@ -33,6 +33,13 @@
 //   tokens    global -> registers two steps ahead, split once for the workgroup one step ahead, three bf16 planes -> LDS
 //             (two stages, 16-byte pieces swizzled, f32_piece) -> fragments.  The one barrier of a step stands before
 //             its last fragment, so the next step's first fragment is fetched while matrix instructions run.
+// AHEAD: products of about one tile for each compute unit.  One wavefront on a SIMD does its loads, its splitting and
+// its matrix instructions one behind the other, so the tile goes to eight wavefronts of 16 features each, and what they split is
+// requested three steps ahead, global -> LDS along the rows (20 cycles per KB), a part of LDS for each wavefront, which alone reads it.
+// The waits are written out: nothing else in the loop goes through the vector memory, and what else there were would only make a
+// wait longer, since a wait names how many requests younger than the one it wants may be in flight.  Down product of 2000
+// tokens, 768 x 3072, 13 slots: 91 -> 84 us; layers and the line: f32_ahead.  (Four wavefronts with requests ahead: 178 us for the
+// layer, 172 without.)
 // Measured against the fp32 instruction (ffn_tiled_f32.hip), layer: 768 x 3072 top-1, 13 slots, 2000 tokens 234 -> 176 us,
 // 4096 tokens 437 -> 346; 1024 x 2048 SwiGLU top-2, 13 slots, 1200 tokens 357 -> 232, 3000 tokens 780 -> 489 (of which the
 // multiplication by 2^24 is 2 to 4 %).  Error of those layers against float64: 3.6e-7 -> 2.4e-7 and 5.1e-7 -> 2.8e-7.
@@ -46,12 +53,11 @@ namespace mmoe {
 // What a product writes: as in ffn_tiled.hip, with H in fp32.
 enum { kModeReluH = 0, kModeSwigluH = 1, kModePlainF32 = 2, kModeGeluH = 3, kModeGatedY = 4 };
 
-constexpr int kFThreads = 256;
+constexpr int kAheadWaves = 8;
 constexpr int kFK = 32;            // k per step
 constexpr int kChain = 128;        // k per chain of matrix instructions
 constexpr int kChainF32 = 64;      // and on the fp32 instruction
 constexpr int kFUnroll = kChain / kFK;
-constexpr int kNB = 2;             // 16-row weight blocks per wavefront
 static_assert(256 % kChain == 0 && kFUnroll % 2 == 0, "K is a multiple of 256; two sets of registers in turn");
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -82,15 +88,24 @@ __device__ __forceinline__ void split4(f32x4 v, u32x2 (&part)[3])
 // 16 different columns of 256 bytes.
 __device__ __forceinline__ int f32_piece(int row, int g) { return row * 64 + ((g ^ (-(row >> 2) & 3)) << 4); }
 
-template <int MODE>
-__global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
+template <int MODE, int WAVES>
+__global__ __launch_bounds__(WAVES * kWave, 2) void split_f32_kernel(
     const float* __restrict__ A, const int32_t* __restrict__ perm, int kdiv, const int32_t* __restrict__ tab, int hdr,
     int list_at, int list_stride, const float* __restrict__ W0, const float* __restrict__ W1, float* __restrict__ out,
     int K, int N, const int32_t* __restrict__ sink_perm, const float* __restrict__ sink_w)
 {
+    constexpr bool AHEAD = WAVES == kAheadWaves;
+    constexpr int kFThreads = WAVES * kWave;
+    constexpr int kNB = AHEAD ? 1 : 2;        // 16-row weight blocks per wavefront
+    static_assert(!AHEAD || MODE != kModeSwigluH, "a gated wavefront has a block of each matrix");
     constexpr int kPlane = kFRows * kFK * 2;  // bytes of one part of a token tile
     constexpr int kStage = 3 * kPlane;
-    __shared__ __attribute__((aligned(256))) char lds[2 * kStage];
+    // AHEAD: what the wavefronts have requested, each in a part of its own: weights, then tokens, kRing steps
+    constexpr int kPieceRows = kFThreads / 8;  // token rows that the workgroup brings in with one instruction each
+    constexpr int kRing = 3, kWRaw = kNB * 16 * kFK * 4, kTRaw = 1024;  // bytes of a wavefront's weights of a step; of a token piece
+    constexpr int kPieces = (kFRows + kPieceRows - 1) / kPieceRows, kMine = kRing * (kWRaw + kPieces * kTRaw);
+    __shared__ __attribute__((aligned(1024))) char lds[2 * kStage + (AHEAD ? WAVES * kMine : 0)];
+    typedef __attribute__((address_space(3))) void* lptr_t;
 
     // workgroup id -> tile: entry blockIdx.x / 8 of this XCD's list
     const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
@@ -107,7 +122,7 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int li = lane & 15, g = lane >> 4;
-    const int n0 = nt * (kFeatF32 * kOut) + wave * (16 * kOut);
+    const int n0 = nt * (16 * kOut * WAVES) + wave * (16 * kOut);
 
     // Lane (li, g) of an operand holds, of a step's 32 k, the four from 4 g on and the four from 16 + 4 g on.
     auto token_row = [&](int row) {  // input row of the tile's row
@@ -121,16 +136,16 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
 
     auto run = [&](auto njc) {
         constexpr int NJ = decltype(njc)::value;  // 16-row fragments of the tile that hold rows
-        constexpr int NP = (NJ + 1) / 2;          // pieces of four k that a thread brings in per step
-        // piece i * 256 + tid: row (i * 256 + tid) / 8, four k from 4 (tid % 8) on; rows past the end re-read the last
+        constexpr int NP = (16 * NJ + kPieceRows - 1) / kPieceRows;  // pieces of four k that a thread brings in per step
+        // piece i * kFThreads + tid: row (i * kFThreads + tid) / 8, four k from 4 (tid % 8) on; rows past the end re-read the last
         // one (never stored)
         const float* asrc[NP];
 #pragma unroll
-        for (int i = 0; i < NP; ++i) asrc[i] = token_row(min(i * 32 + (tid >> 3), cnt - 1)) + 4 * (tid & 7);
-        const int adst = f32_piece(tid >> 3, tid & 3) + 8 * ((tid >> 2) & 1);  // + 2048 per 32 rows
+        for (int i = 0; i < NP; ++i) asrc[i] = token_row(min(i * kPieceRows + (tid >> 3), cnt - 1)) + 4 * (tid & 7);
+        const int adst = f32_piece(tid >> 3, tid & 3) + 8 * ((tid >> 2) & 1);  // + 64 bytes a row for later pieces
         const int fsrc = f32_piece(li, g);                                     // + 1024 per fragment
         // an odd number of fragments: the last pieces are the first two wavefronts'
-        auto brings = [&](int i) { return 2 * i + 1 < NJ || wave < 2; };
+        auto brings = [&](int i) { return (i + 1) * kPieceRows <= 16 * NJ || i * kPieceRows + 8 * wave < 16 * NJ; };
 
         f32x4 tot[NJ][kNB], acc[NJ][kNB];
 #pragma unroll
@@ -141,12 +156,49 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
                 acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
         const int steps = K / kFK, last = steps - 1;  // a multiple of 8
+        // AHEAD: requests of step t, into its place of the ring; kReq instructions
+        constexpr int kReq = 2 * kNB + NP;
+        char* const mine = lds + 2 * kStage + wave * kMine;
+        uint32_t woff[2 * kNB];
+        const char* wsrc = reinterpret_cast<const char*>(W0 + ((size_t)s * N + n0) * K);
+#pragma unroll
+        for (int i = 0; i < 2 * kNB; ++i) {
+            const int r = 8 * i + (lane >> 3);  // of the wavefront's weight rows
+            woff[i] = (uint32_t)r * (uint32_t)K * 4u + (((lane & 7) ^ (r & 7)) << 4);
+        }
+        auto request = [&](int t, int at) {
+            const size_t ko = (size_t)min(t, last) * (kFK * 4);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {  // token rows may lie more than 4 GB apart
+                const uint32_t dst = (uint32_t)(uintptr_t)(lptr_t)(mine + kRing * kWRaw + (at * kPieces + i) * kTRaw);
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(reinterpret_cast<const char*>(asrc[i]) + ko), "s"(dst) : "m0", "memory");
+            }
+#pragma unroll
+            for (int i = 0; i < 2 * kNB; ++i) {
+                const uint32_t dst = (uint32_t)(uintptr_t)(lptr_t)(mine + at * kWRaw + i * 1024);
+                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(woff[i]), "s"(wsrc + ko), "s"(dst) : "m0", "memory");
+            }
+        };
         f32x4 wr[kNB][2], ar[NP];   // weights and tokens of a step, as loaded
+        // the requests of the kRing - 1 steps after step t may be in flight
+        auto fetch = [&](int at) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kRing - 1) * kReq) : "memory");
+            const char* w = mine + at * kWRaw;
+#pragma unroll
+            for (int i = 0; i < NP; ++i) ar[i] = *reinterpret_cast<const f32x4*>(mine + kRing * kWRaw + (at * kPieces + i) * kTRaw + lane * 16);
+#pragma unroll
+            for (int i = 0; i < kNB; ++i)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    wr[i][h] = *reinterpret_cast<const f32x4*>(w + (16 * i + li) * 128 + (((g + 4 * h) ^ (li & 7)) << 4));
+        };
         u32x2 wp[2][kNB][2][3];     // weights split: [step][block][half][part]
         auto load_w = [&](int t, int i, int h) {  // past the end: a harmless reload
+            if (AHEAD) return;
             wr[i][h] = *reinterpret_cast<const f32x4*>(wrow[i] + (size_t)min(t, last) * kFK + 16 * h);
         };
         auto load_a = [&](int t, int i) {
+            if (AHEAD) return;
             if (brings(i)) ar[i] = *reinterpret_cast<const f32x4*>(asrc[i] + (size_t)min(t, last) * kFK);
         };
         auto put_a = [&](char* stage, int i) {
@@ -154,7 +206,7 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
             u32x2 x[3];
             split4(ar[i], x);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(stage + p * kPlane + i * 2048 + adst) = x[p];
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<u32x2*>(stage + p * kPlane + i * (kPieceRows * 64) + adst) = x[p];
         };
         u32x4 x[2][3];  // parts of this fragment and of the next
         auto get_x = [&](int set, int j, const char* stage) {
@@ -172,6 +224,11 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
                                                                         __builtin_bit_cast(bf16x8, x[set][xpart[q]]), acc[j][i], 0, 0, 0);
                 }
         };
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int t = 0; t < kRing; ++t) request(t, t);
+            fetch(0);
+        }
 #pragma unroll
         for (int i = 0; i < NP; ++i) load_a(0, i);
 #pragma unroll
@@ -189,10 +246,21 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
         __syncthreads();
         get_x(0, 0, lds);
         int cur = 0, nxt = kStage;  // stages of this step and of the next
+        int at = 0;                 // place of this step in the ring
         for (int t0 = 0; t0 < steps; t0 += kFUnroll) {
 #pragma unroll
             for (int u = 0; u < kFUnroll; ++u) {
                 const int t = t0 + u;
+                if constexpr (AHEAD) {
+                    // what was fetched of step t has been split (and is waited for here), so its place takes step t + kRing
+#pragma unroll
+                    for (int i = 0; i < 2 * kNB; ++i) asm volatile("" ::"v"(wr[i / 2][i % 2]));
+#pragma unroll
+                    for (int i = 0; i < NP; ++i) asm volatile("" ::"v"(ar[i]));
+                    request(t + kRing, at);
+                    at = at == kRing - 1 ? 0 : at + 1;
+                    fetch(at);
+                }
 #pragma unroll
                 for (int n = 0; n < NJ; ++n) {
                     const int set = (u * NJ + n) & 1;  // NJ * kFUnroll is even
@@ -238,6 +306,7 @@ __global__ __launch_bounds__(kFThreads, 2) void split_f32_kernel(
                 nxt = kStage - cur;
             }
         }
+        if (AHEAD) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing on its way into LDS when the workgroup ends
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -329,7 +398,14 @@ static void launch_product(const TiledPlan& p, int prod, const void* A, const in
                            const void* W0, const void* W1, void* out, int K, int N, hipStream_t st,
                            GateSink sink = GateSink())
 {
-    hipLaunchKernelGGL((split_f32_kernel<MODE>), dim3(p.L.len[prod] * kXcds), dim3(kFThreads), 0, st, (const float*)A, perm,
+    auto kernel = split_f32_kernel<MODE, 4>;
+    int waves = 4;
+    if constexpr (MODE != kModeSwigluH)
+        if (p.ahead[prod]) {
+            kernel = split_f32_kernel<MODE, kAheadWaves>;
+            waves = kAheadWaves;
+        }
+    hipLaunchKernelGGL(kernel, dim3(p.L.len[prod] * kXcds), dim3(waves * kWave), 0, st, (const float*)A, perm,
                        kdiv, tab, kXcds * prod, p.L.list[prod], p.L.lists[prod] == 1 ? 0 : p.L.len[prod], (const float*)W0,
                        (const float*)W1, (float*)out, K, N, sink.perm, sink.w);
 }

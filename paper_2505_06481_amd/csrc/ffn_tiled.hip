@@ -642,7 +642,7 @@ int tile_share(const mmoe_shape& s, int N, bool up)
 // its matrix pipes, which bound them, so it counts as working on one tile at a time.
 static TileRows tile_rows_of(const mmoe_shape& s, int bm, int share)
 {
-    if (s.dtype == MMOE_F32) return {kFRows / 32, 4, 1, 32, false};
+    if (s.dtype == MMOE_F32) return {kFRows / 32, 4, 1, 32, share == kFill};
     if (bm == kBMBig) return {8, 20, 1, 32, false};
     if (share == kTall) return {8, 4, 2, 32, true};
     if (share == kFill) return {4, 4, 1, 32, true};
@@ -741,13 +741,31 @@ bool f32_down_in_runs(const mmoe_shape& s)
     return (nt % kXcds == 0 ? 2 : 4) * rows >= weights;
 }
 
+// fp32 on bf16 parts: eight wavefronts to a tile, one tile for each compute unit and heights that fill the round (ffn_split_f32.hip)?
+// Where tiles of 64 rows, counted with one more for every slot, are little more than a round: taller ones are bound by LDS, where
+// eight wavefronts read every token fragment; and in reductions long enough for the prologue.  Four : eight wavefronts (the
+// down products in runs either way), layer, us, three pools in turn, by that count:
+//   184 (up)  2048 x 1024 GELU, 12 slots, 700 tokens 107.0 : 90.6      240  768 x 3072, 8 slots, 2000 GELU 171.7 : 167.6
+//   186 768 x 3072, 13 slots, 1000, bias 0.5 153.8 : 153.4             270  13 slots, 2000 171.3 : 164.2
+//   past the line  318  13 slots, 2500, bias 0.5 199 : 210             480  4096 tokens 290 : 306    426  24 slots, 3000 261 : 277
+//   K = 512  512 x 512, 12 slots, 3000 (236) 56.0 : 57.4               K = 1024  768 x 1024, 12 slots, 900 (162) 62.6 : 62.7
+constexpr int kAheadTiles = 288, kAheadReduction = 1024;
+bool f32_ahead(const mmoe_shape& s, int N, bool up)
+{
+    if (s.dtype != MMOE_F32 || (up && s.act == MMOE_SWIGLU) || !f32_in_parts(s, N, false)) return false;
+    const int64_t P = (int64_t)s.T * s.top_k;
+    return (up ? s.d_model : s.d_ff) >= kAheadReduction && ((P + 63) / 64 + s.S) * (N / (2 * kFeatF32)) <= kAheadTiles;
+}
+
 static TiledPlan tiled_plan(const mmoe_shape& s)
 {
     TiledPlan p;
     p.bm = planned_tile_rows(s);
     p.lone = lone_tiles(s);
     tiled_nts(s, p.bm, p.nt_up, p.nt_down, p.nb_up, p.nb_down);
-    const int up = tile_share(s, s.d_ff, true), down = tile_share(s, s.d_model, false);
+    p.ahead[0] = f32_ahead(s, s.d_ff, true);
+    p.ahead[1] = f32_ahead(s, s.d_model, false);
+    const int up = p.ahead[0] ? kFill : tile_share(s, s.d_ff, true), down = p.ahead[1] ? kFill : tile_share(s, s.d_model, false);
     p.tall[0] = up == kTall;
     p.tall[1] = down == kTall;
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, tile_rows_of(s, p.bm, up), tile_rows_of(s, p.bm, down),
