@@ -98,7 +98,8 @@ typedef struct {
     int32_t tile_rows; /* tuning, normally 0: token rows per tile of the matrix-core expert kernels.
                           0 chooses by shape: 128 rows (two workgroups per compute unit) when tiles are
                           short-lived (d_model <= 1536, or few rows per slot on average: under 100 up to
-                          d_model 2048, under 64 beyond), 256 rows otherwise.  128 or 256 forces that height for the call.  Either height sums
+                          d_model 2048, under 64 beyond; a product without a gate takes 256 rows there too where 128 would be
+                          more tiles than compute units and 256 are not), 256 rows otherwise.  128 or 256 forces that height for the call.  Either height sums
                           every output element in the same order: the results are bit-identical.  Any
                           other value: MMOE_ERR_DIM.  Ignored by fp32 and by shapes that use the streaming kernels. */
 } mmoe_shape;
