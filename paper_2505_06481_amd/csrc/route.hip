@@ -290,6 +290,7 @@ __global__ __launch_bounds__(kRouteWaves* kWave) void route_kernel(
 // 1024 tokens of 3072 elements, 64 experts, bf16: 39.1 (workgroup per token) -> 27.5 us, fp32 62.7 -> 25.5;
 // 8192 tokens of 4096, 64 experts: 237 (wavefront per token) -> 158 us; of 2304, 8 experts: 76.6 -> 35.7 us.
 constexpr int kRouteGroup = 4;
+constexpr int kGroupRound = 256 * kRouteGroup;  // tokens of a workgroup for each compute unit
 constexpr int kRouteGroupWaves = 16;
 
 template <typename T>
@@ -568,21 +569,6 @@ static void launch_tiles(const mmoe_shape& s, const void* X, const int32_t* vid,
                        br, topk_idx, topk_w, s.T, s.d_model, s.V, s.E, s.top_k, M, slot, s.S, s.gate, groups);
 }
 
-// Measured against the other kernels, us, caches warm / cold, two to four variants:
-//   8 experts   2500 tokens of 4096 18.2 : 16.4 / 27.8 : 24.2   8192 of 4096 41.4 : 24.5 / 59.0 : 44.5   16384 of 4096 82 : 49 / 105 : 70
-//               8000 of 768 10.6 : 9.1 / 15.4 : 14.2   16000 of 2048 38 : 22 / 53 : 38   1500 of 4096 14.9 : 16.1 / 18.8 : 23.1
-//               4096 of 768 6.8 : 7.4 / 11.0 : 11.6
-//   16          9000 of 2048 40 : 26 / 49 : 39   600 of 1024 5.7 : 6.2 / 8.4 : 10.7
-//   32          700 of 3072 19.7 : 11.4 / 23.0 : 20.4   8000 of 1024 35.8 : 27.0 / 41.4 : 33.7   600 of 1024 8.3 : 7.4 / 11.1 : 12.2
-//   64          1037 of 2048 28.6 : 19.8 / 32.3 : 24.0   4000 of 2048 54 : 39 / 59 : 47   16000 of 256 42.8 : 42.1 / 49.8 : 46.5
-//               512 of 2048 16.4 : 13.6 / 19.0 : 20.6   256 of 2048 11.3 : 13.3 / 15.6 : 20.3
-// Wavefronts of eight experts with fewer than seven to score would idle.
-constexpr int64_t kTileScores = 45 << 20;  // elements multiplied
-bool route_in_tiles(const mmoe_shape& s)
-{
-    return s.dtype == MMOE_BF16 && s.E >= 7 && s.T >= (s.E <= 8 ? kRouteTokMinT : 640) && (int64_t)s.T * s.d_model * s.E >= kTileScores;
-}
-
 // Most LDS for the token rows of a group: fp32 rows of 4096.  Over kRouteGroupLarge the rows, which have to arrive before the
 // first score, take long enough that there has to be something to score.  fp32 rows of 3584 and 4096, two variants, us,
 // caches warm / cold, the other kernel : groups, by tokens and experts:
@@ -617,10 +603,69 @@ bool route_in_groups(const mmoe_shape& s)
     return (s.d_model >= 2304 || s.T >= kRouteTokMinT) && s.T >= 768 && (int64_t)s.T * s.d_model >= ((int64_t)1 << 21);
 }
 
+// Four tokens of a variant to a wavefront?  Measured against the other kernels, other : tiles, us.  Caches warm / cold, two to
+// four variants:
+//   8 experts   2500 tokens of 4096 18.2 : 16.4 / 27.8 : 24.2   8192 of 4096 41.4 : 24.5 / 59.0 : 44.5   16384 of 4096 82 : 49 / 105 : 70
+//               8000 of 768 10.6 : 9.1 / 15.4 : 14.2   16000 of 2048 38 : 22 / 53 : 38   1500 of 4096 14.9 : 16.1 / 18.8 : 23.1
+//               4096 of 768 6.8 : 7.4 / 11.0 : 11.6   2049 of 3072 10.4 : 12.6 / -   3000 of 2048 10.2 : 11.2 / -
+//   16          9000 of 2048 40 : 26 / 49 : 39   600 of 1024 5.7 : 6.2 / 8.4 : 10.7
+//   32          700 of 3072 19.7 : 11.4 / 23.0 : 20.4   8000 of 1024 35.8 : 27.0 / 41.4 : 33.7   600 of 1024 8.3 : 7.4 / 11.1 : 12.2
+//   64          1037 of 2048 28.6 : 19.8 / 32.3 : 24.0   4000 of 2048 54 : 39 / 59 : 47   512 of 2048 16.4 : 13.6 / 19.0 : 20.6
+// Wavefronts of eight experts with fewer than seven to score would idle.
+//
+// kTileVariants: in any order, the tokens of many variants leave more of the groups partly filled, and there may be more groups.
+// Mixed tokens, 8 / 16 / 32 / 64 variants:
+//   32 experts  8000 of 1024  34.0 : 29.4 / 34.2 : 36.9 / 34.8 : 56.7 / 35.8 : 105.6
+//   8           8192 of 4096  40.3 : 23.8 / 40.5 : 30.1 / 40.9 : 34.1 / 42.2 : 54.2    8000 of 768 10.5 : 9.5 / 10.5 : 10.7 / 10.7 : 13.7 / 11.4 : 25.5
+//   64          4000 of 2048  67.1 : 36.9 / 67.8 : 48.7 / 69.8 : 62.7 / 83.2 : 106.5
+// Rows of up to 1024 elements, where there is less to share: 12 experts, 4096 of 1024, 8 variants 9.8 : 10.8.
+//
+// Batches of a few rounds of route_group_kernel (a round: a workgroup to every compute unit): where neighbouring tokens are of one
+// variant, its groups read a router row once for four tokens too, with eight chunks in flight.  They win with few experts, and
+// with more where they fill their rounds.  Tiles in their time, one variant / four, mixed / four, one after the other:
+//   12 experts  1024 of 4096 1.13 / 1.30 / 1.12   2040 of 4096 1.29 / 0.92 / 1.25   13, 3072 of 8192, eight, one after the other 1.28
+//   16          1024 of 3072 1.12 / 0.83 / 1.09   1200 of 5120 1.15 / 0.75 / 1.16   1500 of 2304 0.81 / 0.51 / 0.80
+//   32          1024 of 4096 1.28 / 0.87 / 1.17   1200 of 4096 0.86 / 0.59 / 0.83   1800 of 4096 0.84 / 0.77 / 1.14   2040 1.16 / 0.77 / 1.15
+//   64          900 of 4096 0.71 / 0.71 / 0.98    1024 1.13 / 0.72 / 1.00           1500 0.72 / 0.45 / 0.68   2040 1.03 / 0.73 / 1.01
+// (Left over: 48 experts, 900 of 8192, four, one after the other 1.07; 65, 6144 of 4096 1.13.)
+//
+// Short rows: few chunks to a sum and its butterfly, so wavefronts with fewer experts than they have room for cost more than
+// the tokens' shared rows save.  12000 tokens of 512, four variants: 9 experts 1.13, 16 1.02, 17 1.21, 32 0.96, 48 0.84; of 768 0.99,
+// 0.88, 1.05, 0.78, 0.68; of 256, 64 experts 3000 tokens 1.05, 5000 0.92.  And a second pass over the experts that has few of them:
+// 33 experts, 2048 tokens of 2048 1.22 / 0.89 / 1.18, 5000 0.87 / 0.89 / 1.11, 8000 1.00 / 0.76 / 1.00.
+constexpr int64_t kTileScores = 45 << 20;  // elements multiplied
+constexpr int kTileVariants = 8;
+bool route_in_tiles(const mmoe_shape& s)
+{
+    if (s.dtype != MMOE_BF16 || s.E < 7 || s.V > kTileVariants || (int64_t)s.T * s.d_model * s.E < kTileScores) return false;
+    const bool groups = route_in_groups(s), short_rows = s.d_model < 1024 && s.T >= kRouteTokMinT;
+    if (s.E <= 8) return s.T >= (groups || s.d_model >= 2304 ? 2304 : 4096);
+    if (s.T < 640) return false;
+    const int past = s.T % kGroupRound;  // tokens of the groups' last round, 0 if it is full
+    if (s.E >= 48) {
+        if (groups && s.T <= 3 * kGroupRound) return past != 0 && past <= kGroupRound * 15 / 16;
+        return !short_rows || (s.T >= 3584 && (s.d_model > 256 || s.E >= 64));
+    }
+    if ((s.d_model <= 1024 && s.V > 4) || (s.E < 12 && s.d_model > 4096)) return false;
+    if (groups && s.T <= 2 * kGroupRound) return s.E >= 24 && s.T > kGroupRound && past != 0 && past <= kGroupRound * 3 / 8;
+    if (groups && s.T < 6 * kGroupRound && s.d_model >= 3584) return false;
+    if (s.E > 32 && s.T > 2 * kGroupRound * 15 / 16) return s.T >= 8192 && s.d_model >= 1024;
+    return !short_rows || (s.d_model == 768 && s.E % 16 == 0);
+}
+
+enum RouteKernel { kRoutePerToken, kRouteTokens, kRouteGroups, kRouteTiles };
+int route_kernel_for(const mmoe_shape& s)
+{
+    if (route_in_tiles(s)) return kRouteTiles;
+    if (route_in_groups(s)) return kRouteGroups;
+    return wavefront_per_token(s) ? kRouteTokens : kRoutePerToken;
+}
+
 int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const void* Wr, const float* br,
                  int32_t* topk_idx, float* topk_w, hipStream_t st, const int32_t* M, int32_t* slot)
 {
-    if (route_in_tiles(s)) {
+    const int which = route_kernel_for(s);
+    if (which == kRouteTiles) {
         // (with one workgroup of eight wavefronts to a group the few tokens of small batches occupy more of the chip)
         if (s.E <= 8) launch_tiles<8, 4, true>(s, X, vid, Wr, br, topk_idx, topk_w, st, M, slot);
         else if (s.E <= 16) launch_tiles<4, 4, false>(s, X, vid, Wr, br, topk_idx, topk_w, st, M, slot);
@@ -633,8 +678,7 @@ int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const v
     // once); with more to score, a workgroup per four tokens; otherwise a workgroup per token (lower
     // latency, any d).
     const int nc = s.d_model / 256;
-    const bool groups = route_in_groups(s);
-    if (wavefront_per_token(s) && !groups) {
+    if (which == kRouteTokens) {
         dim3 grid((s.T + kRouteTokWaves - 1) / kRouteTokWaves), block(kRouteTokWaves * kWave);
 #define MMOE_ROUTE_TOK(NC)                                                                                          \
     case NC:                                                                                                        \
@@ -659,7 +703,7 @@ int launch_route(const mmoe_shape& s, const void* X, const int32_t* vid, const v
         return launch_status();
     }
     dim3 grid(s.T), block(kRouteWaves * kWave);
-    if (groups) {
+    if (which == kRouteGroups) {
         const size_t group_bytes = (size_t)kRouteGroup * s.d_model * elem_size(s.dtype);
         const dim3 g4((s.T + kRouteGroup - 1) / kRouteGroup);
         const dim3 b16(kRouteGroupWaves * kWave);

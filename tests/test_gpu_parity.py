@@ -355,10 +355,10 @@ def test_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, rows):
 
 
 @pytest.mark.parametrize("T,d,V,E,k,gate", [
-    (2051, 4096, 1, 8, 2, "selected"), (2113, 4096, 3, 7, 7, "all"), (2100, 2816, 70, 8, 1, "all"),   # a group to a wavefront; more variants than a chunk has tokens
-    (1300, 4096, 4, 9, 2, "selected"), (1025, 3072, 2, 16, 4, "all"),                                  # to a workgroup, with every number of wavefronts
-    (1000, 3072, 3, 17, 8, "selected"), (644, 2560, 5, 32, 2, "all"), (641, 3072, 3, 33, 4, "all"), (650, 1280, 2, 67, 3, "selected"),
-    (2049, 512, 3, 66, 4, "all"), (2050, 256, 2, 255, 8, "selected")])
+    (2307, 4096, 1, 8, 2, "selected"), (2369, 4096, 3, 7, 7, "all"), (2500, 2816, 8, 8, 1, "all"),   # a group to a wavefront
+    (2700, 2048, 8, 9, 2, "selected"), (2570, 3072, 2, 16, 4, "all"),                                # to a workgroup, with every number of wavefronts
+    (1999, 2048, 3, 17, 8, "selected"), (644, 2560, 5, 32, 2, "all"), (641, 3072, 3, 33, 4, "all"), (650, 1280, 2, 67, 3, "selected"),
+    (3649, 512, 3, 66, 4, "all"), (3586, 256, 2, 255, 8, "selected")])
 def test_router_tiles_agree_bit_for_bit(mm, gc, dispatch_rule, T, d, V, E, k, gate):
     """Groups of four tokens of a variant, the last ones of a chunk of 64 not full, against the parts of the batch on the kernels
     for fewer tokens: the same picks, the same bits of every coefficient, and in the layer the same slots."""
@@ -378,11 +378,13 @@ def test_router_tiles_agree_bit_for_bit(mm, gc, dispatch_rule, T, d, V, E, k, ga
         assert torch.equal(mm.route(make(n), X[t0:t0 + n], vid[t0:t0 + n], Wr)[0], none[t0:t0 + n]), t0
 
 
-@pytest.mark.parametrize("T,E,k,d", [(1300, 8, 2, 4608), (2100, 8, 1, 3072), (650, 16, 2, 4608)])
+@pytest.mark.parametrize("T,E,k,d", [(2400, 8, 1, 3072), (2600, 16, 2, 2304), (650, 32, 2, 2304), (650, 64, 3, 1280), (4200, 48, 1, 1024)])
 def test_layer_behind_router_tiles(mm, gc, oracle, dispatch_rule, T, E, k, d):
+    """Every launch of the tile kernel looks the slots up: a group to a wavefront, and to a workgroup with four and eight wavefronts of
+    four and of eight experts."""
     cfg = synth.Config(f"tiles_layer_{T}_{E}", T, d, 256, 3, E, k, "bf16", "relu", seed=2000 + T, bias_alpha=0.5)
     case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
-    assert dispatch_rule("route_in_tiles", case.shape) == (T * d * E >= 45 << 20 and T >= (2048 if E <= 8 else 640))
+    assert dispatch_rule("route_in_tiles", case.shape)
 
 
 def expert_lists(mm, gc, oracle, d, f, act, counts, tile_rows=0):
