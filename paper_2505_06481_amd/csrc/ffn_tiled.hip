@@ -617,23 +617,41 @@ int planned_tile_rows(const mmoe_shape& s)
 // one for every slot, a target height is chosen that just fills whole rounds of one tile for each compute unit, down to one
 // sub-tile (kFill); and where 128 rows to a tile do not do, but 256 do, tiles are 256 rows by 128 features and one round
 // (kTall: tiled_narrow_kernel, one workgroup to a compute unit).  kPlain: rounds of two tiles for each compute unit.
-// Plain : as the rule says, layer, us, three pools in turn, equally used slots unless a router bias is given:
-//   kTall  768 x 3072, 18 slots  4096 tokens 99.1 : 90.4, bias 0.5 100.9 : 90.2   8000 132.7 : 128.2
-//          24 slots, 4096 tokens, bias 1 111.9 : 103.2, GELU bias 2.5 99.0 : 87.6   1280 x 3328 GELU, 13 slots, 9000 242.9 : 243.5
-//   kFill  768 x 3072   8 slots  4096 tokens 84.7 : 75.3   18 slots  600 60.5 : 58.2   1000 63.4 : 61.8   2000 76.7 : 72.7
-//          11 slots, 1500 63.3 : 56.7   12 slots, 3000 77.3 : 71.6   1280 x 2560, 16 slots, 1200, bias 0.5 82.2 : 78.1
-//          1536 x 2048, 16 slots, 3000 92.8 : 92.6   512 x 2048, 32 slots, 3000 62.3 : 62.4
-//   past the line, with kFill and with kTall  1024 x 4096, 30 slots, 5000 (560 tiles) 183.2 : 187.5 : 193.4
-//          2048 x 1280, 90 slots, 4148 pairs 328.4 : 331.0 : -   768 x 3072, 14 slots, 12000 (648) 180.3 : 176.4 : 169.8
+// The figures are of 2100 layers, random in widths (d_model to 1536, d_ff to 4096), tokens, slots and router bias: time of the layer
+// with the product so shared out in the time with it plain, mean (largest).
+//
+// Down products, in runs of tiles.  kFill, from 48 rows per slot on, 0.95 (1.05) over up to two rounds.  Where tiles are short because
+// slots have few rows, what they move bounds them, and two to a compute unit hide each other's waits: with fewer rows 0.94 (1.07)
+// within half a round, over it 0.98 (1.22: 1280 x 4096, 28 slots, 803 tokens, bias 2.5 67 : 82 us).
+// kTall, where kFill is more than a round: reductions of 2048 and more, 64 rows per slot and more 0.94 (1.04) where kFill has 0.97
+// (1.05); shorter reductions 0.98 (1.05) where kFill has 0.98 (1.03): few steps, and nothing else on the compute unit while the
+// prologue waits; fewer rows 1.00 (1.18).
+//
+// Up products, panel by panel: XCDs whose panels are of larger slots have more tiles than compute units, which one tile to each
+// does not even out.  Where panels divide among the XCDs, kFill 0.97 (1.03) over up to two rounds; otherwise within half a round
+// and up to 128 rows per slot 0.94 (1.01), more rows 0.96 (1.09), up to two rounds 0.99 (1.10).  kTall 1.05 (1.35).
+//
+// Layers, us, three pools in turn, plain : so, equally used slots unless a router bias is given:
+//   down, kTall  768 x 3072, 18 slots  4096 tokens 99.1 : 90.4, bias 0.5 100.9 : 90.2   8000 132.7 : 128.2
+//                24 slots, 4096 tokens, bias 1 111.9 : 103.2, GELU bias 2.5 99.0 : 87.6
+//   down, kFill  768 x 3072   8 slots  4096 tokens 84.7 : 75.3   18 slots  1000 63.4 : 61.8   2000 76.7 : 72.7
+//                11 slots, 1500 63.3 : 56.7   12 slots, 3000 77.3 : 71.6   512 x 2048, 32 slots, 3000 62.3 : 62.4
+//   past the lines, with kFill and with kTall  1024 x 4096, 30 slots, 5000 (560 tiles) 183.2 : 187.5 : 193.4
+//          768 x 3072, 14 slots, 12000 (648) 180.3 : 176.4 : 169.8; 768 x 3072, 18 slots, 600 (33 rows) 60.5 : 58.2 : -
+// (More than a round of 256-row tiles is faster in one of these two layers and slower in the other; two are no line.)
 enum TileShare { kPlain, kFill, kTall };
 constexpr int kFillRounds = 2;
 int tile_share(const mmoe_shape& s, int N, bool up)
 {
     if (s.dtype == MMOE_F32 || planned_tile_rows(s) != kBMSmall || planned_nb(s, kBMSmall, N, up) != 1) return kPlain;
     const int64_t P = (int64_t)s.T * s.top_k, nt = N / 128, most = ((P + kBMSmall - 1) / kBMSmall + s.S) * nt;
+    const bool half_round = most <= kCus / 2, fills = most <= kFillRounds * kCus;
+    if (up) return (nt % kXcds == 0 ? fills : half_round && P <= (int64_t)128 * s.S) ? kFill : kPlain;
+    if (!half_round && P < (int64_t)48 * s.S) return kPlain;
     // (slots of 256-row tiles counted as five eighths of a tile more than their rows fill)
-    if (most > kCus && (8 * P / kBMBig + 5 * s.S) * nt <= 8 * kCus && !s.tile_rows) return kTall;
-    return most <= kFillRounds * kCus ? kFill : kPlain;
+    const bool tall = most > kCus && (8 * P / kBMBig + 5 * s.S) * nt <= 8 * kCus;
+    if (tall && !s.tile_rows && s.d_ff >= 2048 && P >= (int64_t)64 * s.S) return kTall;
+    return fills ? kFill : kPlain;
 }
 
 // Heights of a product's row tiles.  Shorter ones than five eighths of a full tile are bound by what they move, unless they
@@ -766,8 +784,7 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
     p.ahead[0] = f32_ahead(s, s.d_ff, true);
     p.ahead[1] = f32_ahead(s, s.d_model, false);
     const int up = p.ahead[0] ? kFill : tile_share(s, s.d_ff, true), down = p.ahead[1] ? kFill : tile_share(s, s.d_model, false);
-    p.tall[0] = up == kTall;
-    p.tall[1] = down == kTall;
+    p.tall_down = down == kTall;
     p.L = tile_lists(s.T * s.top_k, s.S, p.nt_up, p.nt_down, tile_rows_of(s, p.bm, up), tile_rows_of(s, p.bm, down),
                      s.dtype == MMOE_F32, xcd_runs(s, 0), s.dtype == MMOE_F32 && f32_down_in_runs(s) ? kRunsAlways : xcd_runs(s, 1),
                      (int)(kLoneBytes / slot_bytes(s)) + 1);
@@ -801,6 +818,7 @@ size_t tiled_table_most(const mmoe_shape& s)
         for (int bm : {kBMSmall, kBMBig})
             for (int nb : {1, 2})
                 for (int share : {kPlain, kFill, kTall}) {
+                    if (prod == 0 && share == kTall) continue;
                     const int NT = prod == 0 ? (s.act == MMOE_SWIGLU ? s.d_ff / wide : s.d_ff / (wide * nb)) : s.d_model / (wide * nb);
                     const int cap = row_tiles_cap(P, s.S, NT, tile_rows_of(s, bm, share), f32);
                     const int64_t n = (int64_t)list_count(NT, prod == 0 ? kRunsNever : kRunsAlways) * list_len(cap, NT);
@@ -833,7 +851,7 @@ static void launch_plain_product(const TiledPlan& p, int prod, const void* A, co
                                  GateSink sink = GateSink())
 {
     const int nb = prod == 0 ? p.nb_up : p.nb_down;
-    if ((p.bm == kBMBig || p.tall[prod]) && nb == 1) launch_product<MODE, kBMBig, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
+    if ((p.bm == kBMBig || (prod == 1 && p.tall_down)) && nb == 1) launch_product<MODE, kBMBig, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else if (p.bm == kBMBig) launch_product<MODE, kBMBig, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else if (nb == 2) launch_product<MODE, kBMSmall, 2>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);
     else launch_product<MODE, kBMSmall, 1>(p, prod, A, perm, kdiv, tab, W0, nullptr, out, K, N, st, sink);

@@ -320,7 +320,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
 bool lone_tiles(const mmoe_shape& s);
 struct TiledPlan {
     int bm, nt_up, nt_down, nb_up, nb_down;
-    bool tall[2];  // 256-row tiles beside a height of 128 (tile_share), per product
+    bool tall_down;  // 256-row tiles of the down product beside a height of 128 (tile_share)
     bool ahead[2];  // fp32 parts: eight wavefronts to a tile (f32_ahead), per product
     bool lone;  // the kernels that read the panels of one-tile slots past the caches (lone_tiles)
     TileLists L;

@@ -499,9 +499,11 @@ def test_few_used_slots_of_large_pools_stay_cached(mm, gc, oracle, dispatch_rule
 
 @pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,up,down", [
     # a round that 128 rows to a tile do not fill evenly, tiles of every height up to 256 rows; either product, each output
-    (3500, 2, 14, 1, 768, 256, "relu", 0.5, 1, 2), (3300, 2, 12, 1, 256, 1024, "gelu", 1.0, 2, 1), (1800, 1, 16, 2, 768, 512, "swiglu", 0.6, 0, 2),
-    (700, 2, 8, 1, 1024, 1280, "relu", 2.0, 1, 1), (70, 1, 1, 1, 256, 256, "gelu", 0.0, 1, 1),     # rows that a round has room for
-    (2600, 1, 9, 1, 1280, 2048, "relu", 2.5, 2, 2), (2900, 1, 40, 1, 1280, 256, "relu", 1.0, 1, 0)])  # both tall; more than a round
+    (3500, 2, 14, 1, 768, 2048, "relu", 0.5, 0, 2), (1800, 1, 16, 2, 768, 2048, "swiglu", 0.6, 0, 2), (2600, 1, 9, 1, 1280, 2048, "relu", 2.5, 1, 2),
+    (3500, 2, 14, 1, 768, 256, "relu", 0.5, 0, 1), (3300, 2, 12, 1, 256, 1024, "gelu", 1.0, 1, 1), (1800, 1, 16, 2, 768, 512, "swiglu", 0.6, 0, 1),
+    (700, 2, 8, 1, 1024, 1280, "relu", 2.0, 0, 1), (70, 1, 1, 1, 256, 256, "gelu", 0.0, 1, 1),     # rows that a round has room for
+    (600, 2, 6, 1, 512, 768, "relu", 0.5, 1, 1), (700, 1, 16, 1, 1280, 256, "gelu", 0.5, 1, 0),
+    (2900, 1, 40, 1, 1280, 256, "relu", 1.0, 1, 0), (700, 1, 30, 1, 1280, 512, "relu", 1.0, 0, 0)])  # more than a round, few rows per slot
 def test_row_tiles_that_fill_whole_rounds(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f, act, alpha, up, down):
     """Row tiles of a height that gives every compute unit one (1), of up to 256 rows where 128 do not do (2), and plain ones."""
     cfg = synth.Config(f"fill_{T}_{d}", T, d, f, V, E, k, "bf16", act, seed=1700 + T, bias_alpha=alpha)
@@ -532,12 +534,12 @@ def test_fp32_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f
     assert mm.expert_plan(case.shape) == (False, 96) and dispatch_rule("f32_down_in_runs", case.shape) is runs
 
 
-@pytest.mark.parametrize("d,counts", [
-    (768, [512, 540, 490, 515, 520, 500, 530, 489]),                                   # 128 rows: 43 row tiles, 258 tiles, in full height
-    (768, [350, 128, 360, 140, 330, 90, 129, 340, 100, 380, 128, 160, 350, 120, 345, 355, 110, 141]), (256, [3000, 1, 0, 900])])
-def test_one_tile_to_a_compute_unit(mm, gc, oracle, dispatch_rule, d, counts):
-    shape, tab = expert_lists(mm, gc, oracle, d, 256, "relu", counts)
-    assert mm.expert_plan(shape) == (False, 128) and dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) in (1, 2)
+@pytest.mark.parametrize("d,f,counts,share", [
+    (768, 256, [512, 540, 490, 515, 520, 500, 530, 489], 1),                           # 128 rows: 43 row tiles, 258 tiles, in full height
+    (768, 2048, [350, 128, 360, 140, 330, 90, 129, 340, 100, 380, 128, 160, 350, 120, 345, 355, 110, 141], 2), (256, 256, [3000, 1, 0, 900], 1)])
+def test_one_tile_to_a_compute_unit(mm, gc, oracle, dispatch_rule, d, f, counts, share):
+    shape, tab = expert_lists(mm, gc, oracle, d, f, "relu", counts)
+    assert mm.expert_plan(shape) == (False, 128) and dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) == share
     assert in_runs(tab[8:16]) and 24 < tab[8:16].max() <= 32
 
 

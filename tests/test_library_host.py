@@ -384,15 +384,25 @@ def test_few_wide_tiles_are_cut_in_two(mm, dispatch_rule):
 
 
 def test_row_tiles_fill_rounds_of_few_tiles(mm, dispatch_rule):
-    """Ungated products of narrow 128-row tiles: heights that fill a round (1) up to 512 tiles, counted with one more for every slot;
-    256-row tiles (2) where those may be more than a round of 256 and these are not; neither beyond, nor with a forced height of 256."""
-    for T, d, S, rows, want in ((4096, 768, 18, 0, 2), (4096, 768, 18, 128, 1), (4096, 768, 18, 256, 0), (4096, 768, 8, 0, 1),
-                                (3072, 768, 18, 0, 1), (3073, 768, 18, 0, 2), (8063, 768, 18, 0, 2), (8064, 768, 18, 0, 1),
-                                (8576, 768, 18, 0, 1), (8577, 768, 18, 0, 0), (5000, 1024, 30, 0, 0), (600, 1536, 18, 0, 2), (500, 1536, 16, 0, 1),
-                                (600, 1792, 8, 0, 1), (1000, 1792, 8, 0, 0)):
-        shape = mm.make_shape(T, d, 3072, 4, 8, S, 1, "bf16", "relu", tile_rows=rows)
-        assert dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) == want, (T, d, S, rows)
-        assert dispatch_rule("tile_share", mm.make_shape(T, d, 3072, 4, 8, S, 1, "f32", "relu"), d, False, restype=ctypes.c_int) == 0
+    """Ungated products of narrow 128-row tiles.  Down: heights that fill a round (1) up to 512 tiles, counted with one more for every
+    slot, from 48 rows per slot on or up to 128 tiles; 256-row tiles (2) where those may be more than a round of 256 and these are not,
+    in reductions from 2048 and with 64 rows per slot on; neither beyond, nor with a forced height of 256.  Up: 1, where panels divide
+    among the XCDs or tiles are half a round and slots have up to 128 rows."""
+    for T, d, f, S, rows, want in ((4096, 768, 3072, 18, 0, 2), (4096, 768, 3072, 18, 128, 1), (4096, 768, 3072, 18, 256, 0), (4096, 768, 3072, 8, 0, 1),
+                                   (3072, 768, 3072, 18, 0, 1), (3073, 768, 3072, 18, 0, 2), (8063, 768, 3072, 18, 0, 2), (8064, 768, 3072, 18, 0, 1),
+                                   (8576, 768, 3072, 18, 0, 1), (8577, 768, 3072, 18, 0, 0), (5000, 1024, 3072, 30, 0, 0), (600, 1536, 3072, 18, 0, 0),
+                                   (500, 1536, 3072, 16, 0, 0), (768, 1536, 3072, 16, 0, 1), (767, 1536, 3072, 16, 0, 0), (600, 1792, 3072, 8, 0, 1), (1000, 1792, 3072, 8, 0, 0),
+                                   (4096, 768, 1792, 18, 0, 1), (4096, 768, 2048, 18, 0, 2), (1216, 1280, 3072, 19, 0, 2), (1215, 1280, 3072, 19, 0, 1),
+                                   (900, 1280, 3072, 19, 0, 0), (330, 512, 2048, 28, 0, 1), (513, 512, 3072, 28, 0, 0)):
+        shape = mm.make_shape(T, d, f, 4, 8, S, 1, "bf16", "relu", tile_rows=rows)
+        assert dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) == want, (T, d, f, S, rows)
+        assert dispatch_rule("tile_share", mm.make_shape(T, d, f, 4, 8, S, 1, "f32", "relu"), d, False, restype=ctypes.c_int) == 0
+    for T, f, S, want in ((1024, 1024, 8, 1), (4096, 1024, 8, 1), (7168, 1024, 8, 1), (7169, 1024, 8, 0), (2304, 768, 3, 0), (384, 768, 3, 1), (385, 768, 3, 0),
+                          (2048, 768, 16, 0), (600, 768, 16, 1), (641, 768, 16, 0), (2600, 1280, 14, 0), (3500, 2048, 1, 1)):
+        for act in ("relu", "gelu"):
+            shape = mm.make_shape(T, 768, f, 4, 8, S, 1, "bf16", act)
+            assert dispatch_rule("tile_share", shape, f, True, restype=ctypes.c_int) == want, (T, f, S)
+        assert dispatch_rule("tile_share", mm.make_shape(T, 768, f, 4, 8, S, 2, "bf16", "swiglu"), f, True, restype=ctypes.c_int) == 0
 
 
 def test_lists_of_every_batch_fit_the_room_of_the_largest(mm, dispatch_rule):
