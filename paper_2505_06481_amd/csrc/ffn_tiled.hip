@@ -743,36 +743,50 @@ int xcd_runs(const mmoe_shape& s, int prod)
     return (even ? 2 : 4) * rows >= weights ? kRunsAlways : kRunsNever;
 }
 
-// The same for the down products in fp32, where token rows are twice as much of the traffic and the lines are the same: 768 x
-// 3072, 13 slots, 2000 tokens read 264 MB in turn, of which 148 token rows.  Panels : runs, layer, us, three pools in turn:
+// The same for the down products in fp32, where token rows are twice as much of the traffic: 768 x 3072, 13 slots, 2000 tokens read
+// 264 MB in turn, of which 148 token rows.  The time of 10900 layers with runs in the time with panels in turn, random in widths, rows,
+// slots, picks and router bias, mean (largest; share over 1.02), from a quarter of the traffic in token rows on:
+//   fewer panels than XCDs   0.90 (1.06; 0.01) on bf16 parts, 0.96 (1.03; 0.00) on the fp32 instruction
+//   more, not dividing among the XCDs   0.97 (1.03; 0.00) up to 400 tiles of 64 rows, counted with one more for every slot; over
+//                            it 0.99 (1.09; 0.10): an XCD's panels even out by themselves
+//   dividing among the XCDs  1.00 (1.15; 0.06): nothing to even out
+// Below that share of token rows up to 1.28.  Panels : runs, layer, us:
 //   768 x 3072   13 slots  2000 tokens 175 : 172   4096 311 : 282   GELU, bias 2.5 330 : 270   1000, bias 0.5 156.6 : 154.0   200 83.7 : 82.7
 //                24 slots  3000, bias 0.5 309 : 262   500 134.2 : 133.3
 //   1536 x 4096, 12 slots, 1000 tokens 252 : 231   256 x 2048 GELU, 12 slots, 2000 pairs, bias 0.5 86.4 : 79.6
-//   as many panels as XCDs or more  1024 x 2048 SwiGLU, 13 slots, 2400 pairs 225 : 222   2048 x 1024 GELU, 12 slots, 700 tokens 107.7 : 107.2
-//   4096 x 1024, 12 slots, 300 tokens 117.8 : 117.1
-// (The up product in runs too: 2000 tokens 172 : 179.)
+// (The up product in runs too: 768 x 3072, 13 slots, 2000 tokens 172 : 179.)
+constexpr int kF32RunTiles = 400;
 bool f32_down_in_runs(const mmoe_shape& s)
 {
     int nt_up, nt, nb_up, nb_down;
     tiled_nts(s, kFRows, nt_up, nt, nb_up, nb_down);
     const int64_t P = (int64_t)s.T * s.top_k, rows = P * (nt < kXcds ? nt : kXcds), weights = (int64_t)s.S * s.d_model;
-    return (nt % kXcds == 0 ? 2 : 4) * rows >= weights;
+    if (nt % kXcds == 0 || 4 * rows < weights) return false;
+    return nt < kXcds || ((P + 63) / 64 + s.S) * nt <= kF32RunTiles;
 }
 
 // fp32 on bf16 parts: eight wavefronts to a tile, one tile for each compute unit and heights that fill the round (ffn_split_f32.hip)?
-// Where tiles of 64 rows, counted with one more for every slot, are little more than a round: taller ones are bound by LDS, where
-// eight wavefronts read every token fragment; and in reductions long enough for the prologue.  Four : eight wavefronts (the
-// down products in runs either way), layer, us, three pools in turn, by that count:
-//   184 (up)  2048 x 1024 GELU, 12 slots, 700 tokens 107.0 : 90.6      240  768 x 3072, 8 slots, 2000 GELU 171.7 : 167.6
-//   186 768 x 3072, 13 slots, 1000, bias 0.5 153.8 : 153.4             270  13 slots, 2000 171.3 : 164.2
-//   past the line  318  13 slots, 2500, bias 0.5 199 : 210             480  4096 tokens 290 : 306    426  24 slots, 3000 261 : 277
-//   K = 512  512 x 512, 12 slots, 3000 (236) 56.0 : 57.4               K = 1024  768 x 1024, 12 slots, 900 (162) 62.6 : 62.7
-constexpr int kAheadTiles = 288, kAheadReduction = 1024;
+// Where tiles of 64 rows, counted with three quarters of one more for every slot, are a round: taller ones are bound by LDS, where
+// eight wavefronts read every token fragment; and in reductions long enough for the prologue.  The time of layers with the product so
+// in the time with four wavefronts, random as for f32_down_in_runs, mean (largest; share over 1.02):
+//   down products, in runs where the rule says so  0.97 (1.03; 0.01) of 2350   from there up to a count of 288 with a whole tile for
+//                              every slot 0.99 (1.08): 768 x 3072, 8 slots, 2500 tokens 188 : 201, 5 slots of 512 x 2816, 4020 178 : 189
+//   up products, panel by panel, so that XCDs with more tiles than compute units take another round, which two and three smaller
+//   workgroups on a compute unit even out:
+//     panels dividing among the XCDs  0.95 (1.02; 0.01) of 80     ten panels and more, up to 64 rows per slot 0.94 (1.06; 0.05) of 56
+//     others  1.01 (1.16; 0.33): 3072 x 768, 16 slots, 1084 tokens, bias 2.5 137 : 161, 1280 x 512, 12 slots, 2653 87 : 96
+// Four : eight wavefronts, layer, us, three pools in turn, with the down products in runs either way:
+//   2048 x 1024 GELU, 12 slots, 700 tokens (up) 107.0 : 90.6           768 x 3072, 8 slots, 2000 GELU 171.7 : 167.6
+//   768 x 3072, 13 slots, 1000, bias 0.5 153.8 : 153.4   2000 171.3 : 164.2
+//   past the line  13 slots, 2500, bias 0.5 199 : 210    4096 290 : 306    24 slots, 3000 261 : 277
+//   K = 512  512 x 512, 12 slots, 3000 56.0 : 57.4       K = 1024  768 x 1024, 12 slots, 900 62.6 : 62.7
+constexpr int kAheadReduction = 1024, kAheadPanels = 10, kAheadRows = 64;
 bool f32_ahead(const mmoe_shape& s, int N, bool up)
 {
     if (s.dtype != MMOE_F32 || (up && s.act == MMOE_SWIGLU) || !f32_in_parts(s, N, false)) return false;
-    const int64_t P = (int64_t)s.T * s.top_k;
-    return (up ? s.d_model : s.d_ff) >= kAheadReduction && ((P + 63) / 64 + s.S) * (N / (2 * kFeatF32)) <= kAheadTiles;
+    const int64_t P = (int64_t)s.T * s.top_k, nt = N / (2 * kFeatF32);
+    if ((up ? s.d_model : s.d_ff) < kAheadReduction || (P + 48 * (int64_t)s.S) * nt > 64 * kCus) return false;
+    return !up || nt % kXcds == 0 || (nt >= kAheadPanels && P <= (int64_t)kAheadRows * s.S);
 }
 
 static TiledPlan tiled_plan(const mmoe_shape& s)

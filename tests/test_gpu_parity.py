@@ -514,9 +514,10 @@ def test_row_tiles_that_fill_whole_rounds(mm, gc, oracle, dispatch_rule, T, V, E
 
 
 @pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,ahead", [
-    (1900, 2, 5, 1, 768, 1024, "relu", 1.0, (False, True)), (800, 1, 5, 1, 1536, 1536, "gelu", 0.5, (True, True)),    # tiles of every height
+    (1900, 2, 5, 1, 768, 1024, "relu", 1.0, (False, True)), (650, 1, 5, 1, 2048, 2048, "gelu", 0.5, (True, True)),    # tiles of every height
+    (800, 1, 5, 1, 1536, 1536, "gelu", 0.5, (False, True)), (480, 1, 8, 1, 1536, 1536, "relu", 1.0, (True, True)),
     (1700, 1, 4, 2, 768, 1024, "swiglu", 2.5, (False, False)), (1000, 2, 8, 2, 768, 1280, "swiglu", 1.0, (False, True)),
-    (2100, 1, 5, 1, 1280, 768, "relu", 0.3, (True, False)), (3400, 1, 4, 1, 512, 1024, "gelu", 2.0, (False, True))])
+    (1700, 1, 5, 1, 1280, 1024, "relu", 0.3, (True, False)), (3400, 1, 4, 1, 512, 1024, "gelu", 2.0, (False, True))])
 def test_fp32_tiles_of_eight_wavefronts(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f, act, alpha, ahead):
     cfg = synth.Config(f"ahead_{T}_{d}", T, d, f, V, E, k, "f32", act, seed=2200 + T, bias_alpha=alpha)
     case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
@@ -526,7 +527,8 @@ def test_fp32_tiles_of_eight_wavefronts(mm, gc, oracle, dispatch_rule, T, V, E, 
 
 @pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,runs", [
     (900, 2, 6, 1, 768, 512, "relu", 1.0, True), (1300, 1, 5, 1, 256, 768, "gelu", 0.5, True),         # six panels a slot, two or four
-    (700, 2, 8, 2, 1024, 256, "swiglu", 2.0, True), (500, 1, 3, 2, 2304, 256, "swiglu", 0.5, True),    # as many panels as XCDs and more
+    (700, 2, 8, 2, 1280, 256, "swiglu", 2.0, True), (500, 1, 3, 2, 2304, 256, "swiglu", 0.5, True),    # more panels than XCDs, as many
+    (700, 2, 8, 2, 1024, 256, "swiglu", 2.0, False),
     (60, 1, 1, 1, 256, 256, "relu", 0.0, True), (330, 1, 24, 1, 2048, 256, "relu", 0.3, False)])
 def test_fp32_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f, act, alpha, runs):
     cfg = synth.Config(f"runs_f32_{T}_{d}", T, d, f, V, E, k, "f32", act, seed=2100 + T, bias_alpha=alpha)

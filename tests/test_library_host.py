@@ -405,6 +405,29 @@ def test_row_tiles_fill_rounds_of_few_tiles(mm, dispatch_rule):
         assert dispatch_rule("tile_share", mm.make_shape(T, 768, f, 4, 8, S, 2, "bf16", "swiglu"), f, True, restype=ctypes.c_int) == 0
 
 
+def test_fp32_tiles_of_eight_wavefronts_where_they_are_one_round(mm, dispatch_rule):
+    """Tiles of 64 rows, counted with three quarters of one more for every slot, in up to 256, reductions from 1024 on; up products
+    only where panels divide among the XCDs, or with ten panels and more and up to 64 rows per slot.  (T, d, f, S, up, down)"""
+    for T, d, f, S, up, down in ((2000, 768, 3072, 13, False, True), (2346, 768, 3072, 8, False, True), (2347, 768, 3072, 8, False, False),
+                                 (2500, 768, 3072, 8, False, False), (4020, 512, 2816, 5, False, False), (1900, 768, 768, 8, False, False),
+                                 (700, 2048, 1024, 12, True, False), (1472, 2048, 1024, 12, True, False), (1473, 2048, 1024, 12, False, False),
+                                 (1084, 3072, 768, 16, False, False), (608, 2560, 1280, 9, False, False), (2653, 1280, 512, 12, False, False),
+                                 (640, 1792, 1280, 10, True, True), (641, 1792, 1280, 10, False, True)):
+        shape = mm.make_shape(T, d, f, 4, min(S, 8), S, 1, "f32", "relu")
+        assert (dispatch_rule("f32_ahead", shape, f, True), dispatch_rule("f32_ahead", shape, d, False)) == (up, down), (T, d, f, S)
+        assert not dispatch_rule("f32_ahead", mm.make_shape(T, d, f, 4, min(S, 8), S, 1, "f32", "swiglu"), f, True)
+        assert not dispatch_rule("f32_ahead", mm.make_shape(T, d, f, 4, min(S, 8), S, 1, "bf16", "relu"), d, False)
+
+
+def test_fp32_down_products_in_runs_only_of_few_uneven_panels(mm, dispatch_rule):
+    """Fewer panels than XCDs; more that do not divide among them up to 400 tiles; from a quarter of the traffic in token rows on."""
+    for T, d, S, want in ((2000, 768, 13, True), (4096, 768, 32, True), (700, 768, 22, True), (700, 768, 23, False), (2600, 1024, 13, False), (900, 512, 24, False),
+                          (2000, 1024, 8, False), (1024, 1280, 24, True), (1025, 1280, 24, False), (3000, 2304, 12, False), (330, 2048, 24, False),
+                          (500, 2304, 6, True)):
+        shape = mm.make_shape(T, d, 3072, 4, 6, S, 1, "f32", "relu")
+        assert not mm.expert_plan(shape)[0] and dispatch_rule("f32_down_in_runs", shape) is want, (T, d, S)
+
+
 def test_lists_of_every_batch_fit_the_room_of_the_largest(mm, dispatch_rule):
     for d, f, S, k, dtype, act in ((768, 3072, 18, 1, "bf16", "relu"), (256, 1024, 300, 1, "bf16", "gelu"), (1280, 2560, 16, 2, "bf16", "swiglu"),
                                    (1536, 768, 5, 1, "bf16", "relu"), (2304, 1024, 12, 2, "bf16", "gelu"), (768, 3072, 13, 1, "f32", "relu")):
