@@ -8,12 +8,16 @@ namespace mmoe {
 
 constexpr int kCombThreads = 256;
 
-// Bound by HBM for large batches, by the chain of loads for small ones.  Rows that the caches cannot hold anyway are read past
-// them (kNT), and a small batch's row is shared out to a workgroup for every 1024 elements.  Before : now, us, two picks: 1 token of
-// 4096 3.05 : 2.06, 64 tokens 3.31 : 2.31, 8192 65.4 : 57.9 (5.8 TB/s), 16384 132 : 113; either way round 777 tokens past the caches 7.1 :
-// 7.6, 1037 of 2048, four picks, shared out 7.7 : 8.2.
+// Bound by HBM for large batches, by the chain of loads for small ones.  A small batch's row is shared out to a workgroup for every 1024
+// elements.  Before : now, us, two picks: 1 token of 4096 3.05 : 2.06, 64 tokens 3.31 : 2.31; either way round 1037 of 2048, four picks 7.7 :
+// 8.2.  Rows that the product before cannot have left in the last-level cache (256 MB) are read past the caches (kNT): of what
+// still is there they would be read from memory.  Through : past, us in the layer, by MB of expert outputs:
+//   two picks of 4096   150 34.9 : 37.3   172 39.5 : 39.9   219 49.9 : 49.6   231 54.5 : 51.8   256 63.2 : 58.2   375 90.3 : 80.8   512 124.9 : 112.5
+//   four of 2048        141 30.2 : 31.8   172 34.3 : 36.5   203 43.7 : 43.8   225 48.0 : 45.6   269 65.7 : 55.9   500 120.7 : 106.8
+//   four of 4096        144 33.1 : 35.6   188 38.6 : 42.8   219 43.7 : 45.1   244 50.7 : 52.7   262 62.3 : 60.2   375 97.0 : 76.5
 constexpr int kCombSmall = 512;                           // tokens
-constexpr int64_t kCombLarge = (int64_t)128 << 20;        // bytes of expert outputs: half of the last-level cache
+constexpr int64_t kCombLarge = (int64_t)224 << 20;        // bytes of expert outputs
+bool combine_past_the_caches(const mmoe_shape& s) { return (int64_t)s.T * s.top_k * s.d_model * 4 > kCombLarge; }
 
 template <bool kBf16, bool kNT>
 __global__ __launch_bounds__(kCombThreads) void combine_kernel(const f32x4* __restrict__ Yg,
@@ -56,7 +60,7 @@ int launch_combine(const mmoe_shape& s, const float* Yg, const int32_t* inv_perm
 {
     const int d4 = s.d_model / 4;
     const dim3 grid(s.T, s.T < kCombSmall ? (d4 + kCombThreads - 1) / kCombThreads : 1), block(kCombThreads);
-    const bool large = (int64_t)s.T * s.top_k * s.d_model * 4 > kCombLarge;
+    const bool large = combine_past_the_caches(s);
     const auto kernel = s.dtype == MMOE_BF16 ? (large ? combine_kernel<true, true> : combine_kernel<true, false>)
                                              : (large ? combine_kernel<false, true> : combine_kernel<false, false>);
     hipLaunchKernelGGL(kernel, grid, block, 0, st, (const f32x4*)Yg, inv_perm, topk_w, Y, d4, s.top_k);

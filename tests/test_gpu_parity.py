@@ -525,6 +525,26 @@ def test_fp32_tiles_of_eight_wavefronts(mm, gc, oracle, dispatch_rule, T, V, E, 
     assert (dispatch_rule("f32_ahead", case.shape, f, True), dispatch_rule("f32_ahead", case.shape, d, False)) == ahead, case.shape.S
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_large_combinations_agree_bit_for_bit(mm, dispatch_rule, dtype):
+    """Expert outputs read past the caches, the last token's rows too, against the parts of the batch, through the caches and with a row
+    shared out to several workgroups."""
+    T, d, k = 897, 8192, 8
+    make = lambda n: mm.make_shape(n, d, 256, 1, k, k, k, dtype, "relu")
+    gen = torch.Generator("cuda").manual_seed(23)
+    Yg = torch.randn((T * k, d), generator=gen, device="cuda")
+    inv = torch.randperm(T * k, generator=gen, device="cuda").to(torch.int32)
+    w = torch.rand((T, k), generator=gen, device="cuda")
+    assert dispatch_rule("combine_past_the_caches", make(T)) and not dispatch_rule("combine_past_the_caches", make(600))
+    Y = mm.combine(make(T), Yg, inv, w)
+    for t0, t1 in ((0, 600), (600, T)):
+        part = mm.combine(make(t1 - t0), Yg, inv[t0 * k:t1 * k].contiguous(), w[t0:t1].contiguous())
+        assert torch.equal(part, Y[t0:t1]), t0
+    want = (Yg[inv.long()].view(T, k, d) * w[:, :, None]).sum(1)
+    # sums of eight products below 5 in size, in another order: 8 * 2^-24 * 40; bf16 rounds the result, 2^-9 of it
+    assert torch.allclose(Y.float(), want, rtol=2.0 ** -8 if dtype == "bf16" else 0.0, atol=2e-5)
+
+
 @pytest.mark.parametrize("T,V,E,k,d,f,act,alpha,runs", [
     (900, 2, 6, 1, 768, 512, "relu", 1.0, True), (1300, 1, 5, 1, 256, 768, "gelu", 0.5, True),         # six panels a slot, two or four
     (700, 2, 8, 2, 1280, 256, "swiglu", 2.0, True), (500, 1, 3, 2, 2304, 256, "swiglu", 0.5, True),    # more panels than XCDs, as many

@@ -428,6 +428,12 @@ def test_fp32_down_products_in_runs_only_of_few_uneven_panels(mm, dispatch_rule)
         assert not mm.expert_plan(shape)[0] and dispatch_rule("f32_down_in_runs", shape) is want, (T, d, S)
 
 
+def test_combination_reads_past_the_caches_only_what_they_cannot_hold(mm, dispatch_rule):
+    for T, d, k, want in ((4800, 4096, 2, False), (7168, 4096, 2, False), (7169, 4096, 2, True), (8192, 4096, 2, True), (673, 7424, 8, False), (3500, 4096, 4, False)):
+        for dtype in ("bf16", "f32"):
+            assert dispatch_rule("combine_past_the_caches", mm.make_shape(T, d, 256, 1, 8, 8, k, dtype, "relu")) is want, (T, d, k)
+
+
 def test_lists_of_every_batch_fit_the_room_of_the_largest(mm, dispatch_rule):
     for d, f, S, k, dtype, act in ((768, 3072, 18, 1, "bf16", "relu"), (256, 1024, 300, 1, "bf16", "gelu"), (1280, 2560, 16, 2, "bf16", "swiglu"),
                                    (1536, 768, 5, 1, "bf16", "relu"), (2304, 1024, 12, 2, "bf16", "gelu"), (768, 3072, 13, 1, "f32", "relu")):
