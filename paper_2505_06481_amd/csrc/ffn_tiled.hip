@@ -805,14 +805,16 @@ static TiledPlan tiled_plan(const mmoe_shape& s)
     return p;
 }
 
+size_t planned_table_bytes(const mmoe_shape& s) { return align256(tiled_plan(s).L.bytes); }
+
 size_t tiled_table_bytes(const mmoe_shape& s)
 {
     if (use_skinny(s)) return 0;
     size_t most = 0;
-    for (int rows : {kBMSmall, kBMBig}) {  // tile_rows is a field of the call, not of the workspace
-        mmoe_shape forced = s;
-        forced.tile_rows = rows;
-        const size_t b = align256(tiled_plan(forced).L.bytes);
+    for (int rows : {0, kBMSmall, kBMBig}) {  // tile_rows is a field of the call, not of the workspace; 0 has plans of its own
+        mmoe_shape call = s;
+        call.tile_rows = rows;
+        const size_t b = planned_table_bytes(call);
         most = b > most ? b : most;
     }
     return most;

@@ -410,9 +410,10 @@ int mmoe_layer_forward(const mmoe_shape* shape, const void* X, const int32_t* vi
 // own copy of the array at its own address; the address is looked up once per device.
 // The size limit a caller sees (static_need) counts the tile lists at a plain rate of their own; the slack is for
 // what they take beyond that.  Per product, with NT feature tiles, that is 18 S (3/4 NT + 7) + P bytes at most in bf16
-// (eight lists of 9/8 (P/128 + S) ceil(NT/8) entries of 16 bytes against the rate's two).  A shape that has lists and
+// (eight lists of 9/8 (P/128 + S) ceil(NT/8) entries of 16 bytes against the rate's two); lists of heights that fill a round
+// (row_tiles_cap) may instead have up to 256 / NT row tiles more than P/128 + S, 32 KB of entries.  A shape that has lists and
 // is within the limit has d_model * d_ff <= 2^22, so NT <= 128, or over 16 S pairs, so S NT <= 2^14: 2.1 MB with
-// S = 1024 and both products.  fp32 (tiles of 64 or 128 features, lists for tiles of two
+// S = 1024 and both products, and 64 KB.  fp32 (tiles of 64 or 128 features, lists for tiles of two
 // sub-tiles, over 12 S pairs): under 1.5 MB.
 constexpr size_t kStaticSlack = (size_t)4 << 20;
 static __device__ __align__(256) unsigned char scratch[MMOE_STATIC_WORKSPACE_BYTES + kStaticSlack];

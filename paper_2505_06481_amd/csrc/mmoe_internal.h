@@ -138,6 +138,8 @@ int launch_ffn_tiled(const mmoe_shape& s, const void* rows, const int32_t* perm,
                      const void* W1p, const void* W3p, const void* W2p, void* H, float* Yg, int32_t* tab,
                      hipStream_t st, hipEvent_t mid = nullptr, bool tab_ready = false,
                      SlotFilter filt = SlotFilter(), GateSink sink = GateSink());
+size_t planned_table_bytes(const mmoe_shape& s);  // what launch_ffn_tiled writes to `tab` for exactly this shape
+// The most of it with any tile_rows.
 size_t tiled_table_bytes(const mmoe_shape& s);
 // Most that tiled_table_bytes() returns for a batch of up to this shape's tokens.
 size_t tiled_table_most(const mmoe_shape& s);

@@ -2,6 +2,7 @@
 the header declares, sizes the workspace, and turns bad arguments into error codes."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -432,6 +433,43 @@ def test_combination_reads_past_the_caches_only_what_they_cannot_hold(mm, dispat
     for T, d, k, want in ((4800, 4096, 2, False), (7168, 4096, 2, False), (7169, 4096, 2, True), (8192, 4096, 2, True), (673, 7424, 8, False), (3500, 4096, 4, False)):
         for dtype in ("bf16", "f32"):
             assert dispatch_rule("combine_past_the_caches", mm.make_shape(T, d, 256, 1, 8, 8, k, dtype, "relu")) is want, (T, d, k)
+
+
+def test_lists_of_every_plan_fit_the_scratch_that_is_asked_for(mm, dispatch_rule):
+    """What mmoe_expert_ffn asks for behind H is never less than the lists of the plan it then launches: whatever height the call asks
+    for, 256-row tiles of the down product beside a height of 128 among them, and heights that fill a round."""
+    rng, tall, filled = random.Random(7), 0, 0
+    size = lambda name, shape: dispatch_rule(name, shape, restype=ctypes.c_size_t)
+    for _ in range(20000):
+        d, f, S, k = 256 * rng.randint(1, 8), 256 * rng.randint(1, 16), rng.randint(1, 40), rng.choice([1, 1, 2])
+        T, dtype, act = int(100 * 120 ** rng.random()), rng.choice(["bf16", "bf16", "bf16", "f32"]), rng.choice(["relu", "gelu", "swiglu"])
+        asked = set()
+        for rows in (0, 128, 256):
+            shape = mm.make_shape(T, d, f, 2, min(S, 8), S, min(k, S), dtype, act, tile_rows=rows)
+            if mm.expert_plan(shape)[0]:
+                continue
+            asked.add(size("tiled_table_bytes", shape))
+            assert size("planned_table_bytes", shape) <= min(asked), (T, d, f, S, k, dtype, act, rows)
+            share = dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int)
+            tall, filled = tall + (share == 2), filled + (share == 1)
+        assert len(asked) <= 1
+    assert tall > 100 and filled > 1000
+
+
+def test_static_entry_point_has_room_for_what_it_accepts(mm):
+    """The lists are counted at a plain rate against the limit; what they take beyond it fits the 4 MB of slack, tile heights that
+    fill a round among them."""
+    rng, accepted, beyond = random.Random(8), 0, 0
+    for _ in range(60000):
+        S, dtype = int(1024 ** rng.random()), rng.choice(["bf16", "bf16", "f32"])
+        k, act = rng.choice([1, 1, 2, 4]), rng.choice(["relu", "gelu", "swiglu"])
+        shape = mm.make_shape(int(30000 ** rng.random()), 256 * int(64 ** rng.random()), 256 * int(64 ** rng.random()), 2, max(k, min(S, 8)), S, k, dtype, act)
+        if static_refuses(mm, shape) or mm.workspace_bytes(shape) == 0:
+            continue
+        accepted += 1
+        beyond = max(beyond, mm.workspace_bytes(shape) - mm.STATIC_WORKSPACE_BYTES)
+        assert beyond <= 4 << 20, (shape.T, shape.d_model, shape.d_ff, S, k, dtype, act)
+    assert accepted > 10000 and beyond > 0
 
 
 def test_lists_of_every_batch_fit_the_room_of_the_largest(mm, dispatch_rule):
