@@ -474,7 +474,7 @@ def main():
                    "slot_rows_min_med_max": [int(res["counts"].min()), int(sorted(res["counts"])[S // 2]),
                                              int(res["counts"].max())],
                    "slot_rows": [int(c) for c in res["counts"]],
-                   "expert_kernels": "weight-streaming" if skinny else f"matrix-core, {tile_rows}-row tiles"},
+                   "expert_kernels": "weight-streaming" if skinny else f"matrix-core, tiles of up to {tile_rows} rows (up product)"},
         "layer_tflops": layer_flops / (ms * 1e-3) / 1e12,
         "stages_ms": res["stages_ms"],
         "stages_GBps": stage_rates(cfg, res["stages_ms"]),

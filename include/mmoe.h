@@ -98,8 +98,9 @@ typedef struct {
     int32_t tile_rows; /* tuning, normally 0: token rows per tile of the matrix-core expert kernels.
                           0 chooses by shape: 128 rows (two workgroups per compute unit) when tiles are
                           short-lived (d_model <= 1536, or few rows per slot on average: under 100 up to
-                          d_model 2048, under 64 beyond; a product without a gate takes 256 rows there too where 128 would be
-                          more tiles than compute units and 256 are not), 256 rows otherwise.  128 or 256 forces that height for the call.  Either height sums
+                          d_model 2048, under 64 beyond; the down product takes 256 rows there too where 128 would be
+                          more tiles than compute units and 256 are not, with d_ff of 2048 and more and 64 rows per slot
+                          and more), 256 rows otherwise.  128 or 256 forces that height for the call.  Either height sums
                           every output element in the same order: the results are bit-identical.  Any
                           other value: MMOE_ERR_DIM.  Ignored by fp32 and by shapes that use the streaming kernels. */
 } mmoe_shape;
@@ -274,7 +275,8 @@ int mmoe_layer_forward_events(const mmoe_shape *shape, const void *X, const int3
  * mmoe_expert_ffn and mmoe_layer_forward will use for this shape.  *streaming = 1: the
  * weight-streaming kernels (few rows per slot), *tile_rows = 32
  * (rows of a slot per pass over its weights); *streaming = 0: the matrix-core kernels with
- * tiles of *tile_rows (128 or 256; fp32: 96) token rows.  The choice depends on the shape only.
+ * tiles of up to *tile_rows (128 or 256; fp32: 96) token rows.  Where that is 128 and the shape's tile_rows is 0, tiles of
+ * the down product may have up to 256.  The choice depends on the shape only.
  */
 int mmoe_expert_plan(const mmoe_shape *shape, int *streaming, int *tile_rows);
 

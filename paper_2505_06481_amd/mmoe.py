@@ -273,7 +273,8 @@ def probe_ceilings(gib: int = 4):
 
 
 def expert_plan(shape: Shape):
-    """(streaming, tile_rows): the expert-stage kernels the library will use for this shape."""
+    """(streaming, tile_rows): the expert-stage kernels the library will use for this shape.  Where ``tile_rows`` is 128 and the
+    shape's own is 0, tiles of the down product may have up to 256 rows."""
     streaming, rows = ctypes.c_int(), ctypes.c_int()
     _check(lib().mmoe_expert_plan(ctypes.byref(shape), ctypes.byref(streaming), ctypes.byref(rows)),
            "mmoe_expert_plan")

@@ -204,6 +204,24 @@ def test_expert_plan_at_its_lines(mm, d, f, S, P, want):
     assert mm.expert_plan(mm.make_shape(P, d, f, 1, S, S, 1, "bf16", "relu")) == want
 
 
+def test_expert_plan_says_where_down_tiles_may_be_taller(mm, dispatch_rule):
+    """256-row tiles of the down product where the plan says 128: with the shape's tile_rows 0 only, never of the up product, and the
+    header and the binding say so."""
+    taller = 0
+    for T in range(1000, 9000, 37):
+        for d, S in ((768, 18), (768, 24), (1280, 12)):
+            for rows in (0, 128, 256):
+                shape = mm.make_shape(T, d, 3072, 4, 8, S, 1, "bf16", "relu", tile_rows=rows)
+                if dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) == 2:
+                    taller += 1
+                    assert rows == 0 and mm.expert_plan(shape) == (False, 128)
+                assert dispatch_rule("tile_share", shape, 3072, True, restype=ctypes.c_int) != 2
+    assert taller
+    header = re.sub(r"[\s*]+", " ", open(os.path.join(ROOT, "include", "mmoe.h")).read())
+    assert "Where that is 128 and the shape's tile_rows is 0, tiles of the down product may have up to 256" in header
+    assert "tiles of the down product may have up to 256" in re.sub(r"\s+", " ", mm.expert_plan.__doc__)
+
+
 @pytest.mark.parametrize("P,want", [(96, (True, 32)), (97, (False, 96))])
 def test_expert_plan_f32(mm, P, want):
     assert mm.expert_plan(mm.make_shape(P, 768, 3072, 1, 8, 8, 1, "f32", "relu")) == want
