@@ -303,15 +303,26 @@ def test_streaming_slots_of_several_passes_in_large_pools(mm, gc, oracle, dispat
     assert ref["counts"].max() > 32 and (ref["counts"] > 0).sum() > (ref["counts"] > 32).sum()
 
 
+PER_TOKEN, TOKENS, GROUPS, TILES = range(4)  # router kernels: a workgroup per token, a wavefront per token, a workgroup per four, tiles
+
+
+@pytest.fixture(scope="module")
+def router_kernel(dispatch_rule):
+    return lambda shape: dispatch_rule("route_kernel_for", shape, restype=ctypes.c_int)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_router_with_every_remainder_of_experts(mm, gc, oracle, dtype):
+def test_router_with_every_remainder_of_experts(mm, gc, oracle, router_kernel, dtype):
     """Numbers of experts around the four whose sums share a butterfly and around a wavefront's lanes, on each router
-    kernel (a workgroup per token, a wavefront per token, a workgroup per four): the oracle's picks, and its coefficients to rounding."""
-    for T, d in ((70, 512), (2050, 256), (2051, 768), (771, 4096), (2100, 2304)):
+    kernel (a workgroup per token, a wavefront per token, a workgroup per four): the oracle's picks, and its coefficients to rounding.
+    (Nine variants: too many for tiles.)"""
+    for T, d, kernel in ((70, 512, PER_TOKEN), (2050, 256, TOKENS), (2051, 768, TOKENS), (771, 4096, GROUPS), (2100, 2304, GROUPS)):
         for E in (1, 2, 3, 4, 5, 8, 9, 17, 33, 64, 67):
-            cfg = synth.Config(f"route_{dtype}_{T}_{d}_{E}", T, d, 256, 3, E, min(E, 4), dtype, "relu", seed=1500 + T + E, bias_alpha=0.5, gate="all")
+            cfg = synth.Config(f"route_{dtype}_{T}_{d}_{E}", T, d, 256, 9, E, min(E, 4), dtype, "relu", seed=1500 + T + E, bias_alpha=0.5, gate="all")
             inp = synth.make_inputs(cfg, weights=False)
-            shape = mm.make_shape(T, d, 256, 3, E, E, cfg.top_k, dtype, "relu", gate="all")
+            shape = mm.make_shape(T, d, 256, 9, E, E, cfg.top_k, dtype, "relu", gate="all")
+            few = dtype == "f32" and d == 4096 and E < 5  # long rows of fp32 and little to score
+            assert router_kernel(shape) == (PER_TOKEN if few else kernel), (T, d, E)
             idx, w = mm.route(shape, gc.to_dev(inp["X"], dtype), torch.from_numpy(inp["vid"]).cuda(), gc.to_dev(inp["Wr"], dtype),
                               torch.from_numpy(inp["br"]).cuda())
             torch.cuda.synchronize()
@@ -321,22 +332,22 @@ def test_router_with_every_remainder_of_experts(mm, gc, oracle, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_router_kernels_agree_bit_for_bit(mm, gc, dispatch_rule, dtype):
+def test_router_kernels_agree_bit_for_bit(mm, gc, router_kernel, dtype):
     """Batches on a wavefront per token (rows of the router in registers four and two at a time) and on groups of four, and their
-    parts on a workgroup per token: the same picks and the same bits of every coefficient."""
+    parts on a workgroup per token: the same picks and the same bits of every coefficient.  (Nine variants: too many for tiles.)"""
     for T, d, groups in ((2050, 256, False), (2049, 768, False), (2049, 2048, False), (2050, 3072, False), (2050, 4096, False),
                          (771, 4096, True), (2053, 2304, True), (2051, 3072, True)):
         for E in ((1, 2, 3, 5, 6, 7, 9) if not groups else (17, 66) if d == 3072 else (6, 7, 33)):
-            cfg = synth.Config(f"bits_{dtype}_{T}_{d}_{E}", T, d, 256, 3, E, min(E, 4), dtype, "relu", seed=1700 + T + E, bias_alpha=0.5, gate="all")
+            cfg = synth.Config(f"bits_{dtype}_{T}_{d}_{E}", T, d, 256, 9, E, min(E, 4), dtype, "relu", seed=1700 + T + E, bias_alpha=0.5, gate="all")
             inp = synth.make_inputs(cfg, weights=False)
             X, Wr, br = gc.to_dev(inp["X"], dtype), gc.to_dev(inp["Wr"], dtype), torch.from_numpy(inp["br"]).cuda()
             vid = torch.from_numpy(inp["vid"]).cuda()
-            make = lambda n: mm.make_shape(n, d, 256, 3, E, E, cfg.top_k, dtype, "relu", gate="all")
-            assert dispatch_rule("route_in_groups", make(T)) is groups
+            make = lambda n: mm.make_shape(n, d, 256, 9, E, E, cfg.top_k, dtype, "relu", gate="all")
+            assert router_kernel(make(T)) == (GROUPS if groups else TOKENS), (T, d, E)
             idx, w = mm.route(make(T), X, vid, Wr, br)
             for t0 in range(0, T, 700):
                 n = min(700, T - t0)
-                assert not dispatch_rule("route_in_groups", make(n))
+                assert router_kernel(make(n)) == PER_TOKEN, (n, d, E)
                 part_idx, part_w = mm.route(make(n), X[t0:t0 + n], vid[t0:t0 + n], Wr, br)
                 assert torch.equal(part_idx, idx[t0:t0 + n]) and torch.equal(part_w, w[t0:t0 + n]), (T, d, E, t0)
 
@@ -359,7 +370,7 @@ def test_down_tiles_in_runs(mm, gc, oracle, dispatch_rule, rows):
     (2700, 2048, 8, 9, 2, "selected"), (2570, 3072, 2, 16, 4, "all"),                                # to a workgroup, with every number of wavefronts
     (1999, 2048, 3, 17, 8, "selected"), (644, 2560, 5, 32, 2, "all"), (641, 3072, 3, 33, 4, "all"), (650, 1280, 2, 67, 3, "selected"),
     (3649, 512, 3, 66, 4, "all"), (3586, 256, 2, 255, 8, "selected")])
-def test_router_tiles_agree_bit_for_bit(mm, gc, dispatch_rule, T, d, V, E, k, gate):
+def test_router_tiles_agree_bit_for_bit(mm, gc, router_kernel, T, d, V, E, k, gate):
     """Groups of four tokens of a variant, the last ones of a chunk of 64 not full, against the parts of the batch on the kernels
     for fewer tokens: the same picks, the same bits of every coefficient, and in the layer the same slots."""
     cfg = synth.Config(f"tiles_{T}_{d}_{E}", T, d, 256, V, E, k, "bf16", "relu", seed=1900 + T + E, bias_alpha=0.5, gate=gate)
@@ -367,24 +378,24 @@ def test_router_tiles_agree_bit_for_bit(mm, gc, dispatch_rule, T, d, V, E, k, ga
     X, Wr, br = gc.to_dev(inp["X"], "bf16"), gc.to_dev(inp["Wr"], "bf16"), torch.from_numpy(inp["br"]).cuda()
     vid = torch.from_numpy(inp["vid"]).cuda()
     make = lambda n: mm.make_shape(n, d, 256, V, E, E, k, "bf16", "relu", gate=gate)
-    assert dispatch_rule("route_in_tiles", make(T))
+    assert router_kernel(make(T)) == TILES
     idx, w = mm.route(make(T), X, vid, Wr, br)
     none, _ = mm.route(make(T), X, vid, Wr)
     for t0 in range(0, T, 300):
         n = min(300, T - t0)
-        assert not dispatch_rule("route_in_tiles", make(n))
+        assert router_kernel(make(n)) == PER_TOKEN
         part_idx, part_w = mm.route(make(n), X[t0:t0 + n], vid[t0:t0 + n], Wr, br)
         assert torch.equal(part_idx, idx[t0:t0 + n]) and torch.equal(part_w, w[t0:t0 + n]), t0
         assert torch.equal(mm.route(make(n), X[t0:t0 + n], vid[t0:t0 + n], Wr)[0], none[t0:t0 + n]), t0
 
 
 @pytest.mark.parametrize("T,E,k,d", [(2400, 8, 1, 3072), (2600, 16, 2, 2304), (650, 32, 2, 2304), (650, 64, 3, 1280), (4200, 48, 1, 1024)])
-def test_layer_behind_router_tiles(mm, gc, oracle, dispatch_rule, T, E, k, d):
+def test_layer_behind_router_tiles(mm, gc, oracle, router_kernel, T, E, k, d):
     """Every launch of the tile kernel looks the slots up: a group to a wavefront, and to a workgroup with four and eight wavefronts of
     four and of eight experts."""
     cfg = synth.Config(f"tiles_layer_{T}_{E}", T, d, 256, 3, E, k, "bf16", "relu", seed=2000 + T, bias_alpha=0.5)
     case, _ = staged_vs_oracle(mm, gc, oracle, cfg)
-    assert dispatch_rule("route_in_tiles", case.shape)
+    assert router_kernel(case.shape) == TILES
 
 
 def expert_lists(mm, gc, oracle, d, f, act, counts, tile_rows=0):
@@ -627,28 +638,30 @@ def test_router_row_lengths(mm, gc, oracle, dtype, d):
 @pytest.mark.parametrize("T,d,E,k,dtype", [(911, 2304, 3, 1, "bf16"), (2053, 1280, 17, 4, "f32"), (770, 2816, 130, 8, "bf16"),
                                            (1031, 2304, 16, 2, "f32"), (2049, 3072, 16, 2, "bf16"), (2050, 1536, 64, 4, "f32"),
                                            (2051, 3328, 8, 2, "bf16"), (2052, 6144, 1, 1, "bf16")])
-def test_router_token_groups(mm, gc, oracle, T, d, E, k, dtype):
-    """Four tokens to a workgroup: variants mixed inside the groups, a last group of one to four tokens, experts
+def test_router_token_groups(mm, gc, oracle, router_kernel, T, d, E, k, dtype):
+    """Four tokens to a workgroup: variants (too many for tiles) mixed inside the groups, a last group of one to four tokens, experts
     that do and do not divide among the wavefronts.  Picks equal, coefficients to fp32."""
     rng = np.random.default_rng(T)
     def stored(a):
         t = torch.from_numpy(a.astype(np.float32))
         return t if dtype == "f32" else t.bfloat16()
-    V = 3
+    V = 9
     X, Wr = stored(rng.standard_normal((T, d))), stored(0.02 * rng.standard_normal((V, E, d)))
     vid = torch.from_numpy(rng.integers(0, V, T).astype(np.int32))
     br = torch.from_numpy(rng.standard_normal((V, E)).astype(np.float32))
     for gate in ("selected", "all"):
         shape = mm.make_shape(T, d, 256, V, E, E, k, dtype, "relu", gate=gate)
+        assert router_kernel(shape) == GROUPS
         idx, w = mm.route(shape, X.cuda(), vid.cuda(), Wr.cuda(), br.cuda())
         ref_idx, ref_w, _ = oracle.route(gc.bits(X), vid.numpy(), gc.bits(Wr), br.numpy(), k, dtype, gate=gate)
         assert np.array_equal(idx.cpu().numpy(), ref_idx), gate
         np.testing.assert_allclose(w.cpu().numpy(), ref_w, rtol=2e-6, atol=1e-7)
 
 
-def test_router_token_groups_look_up_slots(mm, gc, oracle):
+def test_router_token_groups_look_up_slots(mm, gc, oracle, router_kernel):
     """The layer on a batch whose router takes four tokens to a workgroup: every stage and the fused call."""
-    staged_vs_oracle(mm, gc, oracle, synth.Config("route_groups", 915, 2304, 256, 3, 8, 2, "bf16", "swiglu", seed=901))
+    case, _ = staged_vs_oracle(mm, gc, oracle, synth.Config("route_groups", 915, 2304, 256, 3, 8, 2, "bf16", "swiglu", seed=901))
+    assert router_kernel(case.shape) == GROUPS
 
 
 @pytest.mark.parametrize("S", [1, 2, 63, 64, 65, 1024])
