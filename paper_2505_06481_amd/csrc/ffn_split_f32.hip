@@ -144,7 +144,7 @@ __global__ __launch_bounds__(WAVES * kWave, 2) void split_f32_kernel(
         for (int i = 0; i < NP; ++i) asrc[i] = token_row(min(i * kPieceRows + (tid >> 3), cnt - 1)) + 4 * (tid & 7);
         const int adst = f32_piece(tid >> 3, tid & 3) + 8 * ((tid >> 2) & 1);  // + 64 bytes a row for later pieces
         const int fsrc = f32_piece(li, g);                                     // + 1024 per fragment
-        // an odd number of fragments: the last pieces are the first two wavefronts'
+        // where the fragments do not fill the last pieces, those are the first wavefronts': two of four, or two, four or six of eight
         auto brings = [&](int i) { return (i + 1) * kPieceRows <= 16 * NJ || i * kPieceRows + 8 * wave < 16 * NJ; };
 
         f32x4 tot[NJ][kNB], acc[NJ][kNB];

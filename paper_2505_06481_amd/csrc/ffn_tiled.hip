@@ -660,11 +660,11 @@ int tile_share(const mmoe_shape& s, int N, bool up)
 // its matrix pipes, which bound them, so it counts as working on one tile at a time.
 static TileRows tile_rows_of(const mmoe_shape& s, int bm, int share)
 {
-    if (s.dtype == MMOE_F32) return {kFRows / 32, 4, 1, 32, share == kFill};
-    if (bm == kBMBig) return {8, 20, 1, 32, false};
-    if (share == kTall) return {8, 4, 2, 32, true};
-    if (share == kFill) return {4, 4, 1, 32, true};
-    return {4, 10, 1, 64, false};
+    if (s.dtype == MMOE_F32) return {kFRows / 32, 4, 1, 5, share == kFill};
+    if (bm == kBMBig) return {8, 20, 1, 5, false};
+    if (share == kTall) return {8, 4, 2, 5, true};
+    if (share == kFill) return {4, 4, 1, 5, true};
+    return {4, 10, 1, 6, false};
 }
 
 // Are panels read past the caches where a tile is the only one of its slot?  Where slots of one tile are likely, and

@@ -63,7 +63,7 @@ struct TileRows {
     int upt;      // most 32-row sub-tiles of a row tile
     int hq_lo;    // least target height, in quarters of a sub-tile
     int hq_step;  // quarters between two target heights
-    int conc;     // tiles that an XCD works on in the time of one, for the choice of the height
+    int conc_log2;  // log2 of the tiles that an XCD works on in the time of one (`conc`), for the choice of the height
     bool fill;    // the lists have room for as many row tiles as fill whole rounds of the chip
 };
 
@@ -88,7 +88,7 @@ inline int row_tiles_cap(int P, int S, int NT, const TileRows& r, bool f32)
     const int u = f32 ? 2 : r.upt;
     const int full = (P + 32 * u - 1) / (32 * u) + S, cap = full + (full + 7) / 8;
     if (!r.fill) return cap;
-    const int round = kXcds * r.conc;  // tiles
+    const int round = kXcds << r.conc_log2;  // tiles
     const int64_t filled = ((int64_t)full * NT + round - 1) / round * round / NT;
     return filled > cap ? (int)filled : cap;
 }
@@ -166,7 +166,7 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
     __shared__ int total[kXcds];       // entries of every XCD's list
     __shared__ int units_all, chosen_hq;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int conc = L.rows[p].conc, upt = L.rows[p].upt, hq_step = L.rows[p].hq_step;
+    const int conc_log2 = L.rows[p].conc_log2, conc = 1 << conc_log2, upt = L.rows[p].upt, hq_step = L.rows[p].hq_step;
     int4* lists = reinterpret_cast<int4*>(tab);
     auto units_of = [&](int s) { return s >= S || filt.skips(s) ? 0 : (off[s + 1] - off[s] + 31) >> 5; };
     auto tiles_at = [&](int u, int hq) { return max(div24(u + upt - 1, upt), div24(4 * u + hq - 1, hq)); };
@@ -203,8 +203,8 @@ __device__ __forceinline__ void build_tile_lists(const int* off, int32_t* __rest
         float cost = INFINITY;
         // no rows at all, or more tiles than the lists hold (the tallest candidate always fits)
         if (lane < ncand && M > 0 && M <= L.rows_cap[p]) {
-            const int rounds = (int)(((int64_t)M * NT + kXcds * conc - 1) >> (conc == 32 ? 8 : 9));
-            static_assert(kXcds == 8, "rounds of 32 and of 64 tiles an XCD");
+            static_assert(kXcds == 8, "rounds are shifts");
+            const int rounds = (int)(((int64_t)M * NT + kXcds * conc - 1) >> (3 + conc_log2));
             cost = (float)rounds * (0.5f + (float)U / (float)M);
         }
         int best = lane;
