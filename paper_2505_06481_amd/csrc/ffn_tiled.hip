@@ -617,19 +617,20 @@ int planned_tile_rows(const mmoe_shape& s)
 // one for every slot, a target height is chosen that just fills whole rounds of one tile for each compute unit, down to one
 // sub-tile (kFill); and where 128 rows to a tile do not do, but 256 do, tiles are 256 rows by 128 features and one round
 // (kTall: tiled_narrow_kernel, one workgroup to a compute unit).  kPlain: rounds of two tiles for each compute unit.
-// The figures are of 2100 layers, random in widths (d_model to 1536, d_ff to 4096), tokens, slots and router bias: time of the layer
-// with the product so shared out in the time with it plain, mean (largest).
+// The figures are of 35000 layers, random in widths, tokens, picks, slots and router bias: time of the layer with the product so shared
+// out in the time with it plain, mean (largest; share over 1.02).
 //
-// Down products, in runs of tiles.  kFill, from 48 rows per slot on, 0.95 (1.05) over up to two rounds.  Where tiles are short because
-// slots have few rows, what they move bounds them, and two to a compute unit hide each other's waits: with fewer rows 0.94 (1.07)
-// within half a round, over it 0.98 (1.22: 1280 x 4096, 28 slots, 803 tokens, bias 2.5 67 : 82 us).
-// kTall, where kFill is more than a round: reductions of 2048 and more, 64 rows per slot and more 0.94 (1.04) where kFill has 0.97
-// (1.05); shorter reductions 0.98 (1.05) where kFill has 0.98 (1.03): few steps, and nothing else on the compute unit while the
-// prologue waits; fewer rows 1.00 (1.18).
+// Down products, in runs of tiles.  kFill over up to two rounds, from 32 rows per slot on 0.96 (1.20; 0.01); with fewer, slots of a little
+// more than 32 rows become two short tiles, which what they move bounds, and two to a compute unit hide each other's waits: up to
+// kFewTiles full tiles of rows, within a round 0.95 (1.25; 0.00), more 0.99 (1.29; 0.12: 512 x 6656, 80 slots, 622 tokens, two picks).
+// kTall, where kFill is more than a round: reductions of 2048 and more, 64 rows per slot and more 0.93 (1.07; 0.02) where kFill has 0.96
+// (1.14; 0.04); shorter reductions 0.98 (1.10; 0.12) where kFill has 0.98 (1.06; 0.01): few steps, and nothing else on the compute unit
+// while the prologue waits; fewer rows 0.99 (1.24; 0.10).
 //
 // Up products, panel by panel: XCDs whose panels are of larger slots have more tiles than compute units, which one tile to each
-// does not even out.  Where panels divide among the XCDs, kFill 0.97 (1.03) over up to two rounds; otherwise within half a round
-// and up to 128 rows per slot 0.94 (1.01), more rows 0.96 (1.09), up to two rounds 0.99 (1.10).  kTall 1.05 (1.35).
+// does not even out.  Where panels divide among the XCDs, kFill 0.98 (1.10; 0.03) over up to two rounds; otherwise with up to kFewTiles
+// full tiles of rows, within a round 0.93 (1.06; 0.00), and within half a round up to 128 rows per slot 0.93 (1.14; 0.01); more 0.99
+// (1.19; 0.17).  kTall, of 2100 such layers, 1.05 (1.35).
 //
 // Layers, us, three pools in turn, plain : so, equally used slots unless a router bias is given:
 //   down, kTall  768 x 3072, 18 slots  4096 tokens 99.1 : 90.4, bias 0.5 100.9 : 90.2   8000 132.7 : 128.2
@@ -637,17 +638,17 @@ int planned_tile_rows(const mmoe_shape& s)
 //   down, kFill  768 x 3072   8 slots  4096 tokens 84.7 : 75.3   18 slots  1000 63.4 : 61.8   2000 76.7 : 72.7
 //                11 slots, 1500 63.3 : 56.7   12 slots, 3000 77.3 : 71.6   512 x 2048, 32 slots, 3000 62.3 : 62.4
 //   past the lines, with kFill and with kTall  1024 x 4096, 30 slots, 5000 (560 tiles) 183.2 : 187.5 : 193.4
-//          768 x 3072, 14 slots, 12000 (648) 180.3 : 176.4 : 169.8; 768 x 3072, 18 slots, 600 (33 rows) 60.5 : 58.2 : -
+//          768 x 3072, 14 slots, 12000 (648) 180.3 : 176.4 : 169.8
 // (More than a round of 256-row tiles is faster in one of these two layers and slower in the other; two are no line.)
 enum TileShare { kPlain, kFill, kTall };
-constexpr int kFillRounds = 2;
+constexpr int kFillRounds = 2, kFewTiles = 32;
 int tile_share(const mmoe_shape& s, int N, bool up)
 {
     if (s.dtype == MMOE_F32 || planned_tile_rows(s) != kBMSmall || planned_nb(s, kBMSmall, N, up) != 1) return kPlain;
     const int64_t P = (int64_t)s.T * s.top_k, nt = N / 128, most = ((P + kBMSmall - 1) / kBMSmall + s.S) * nt;
-    const bool half_round = most <= kCus / 2, fills = most <= kFillRounds * kCus;
-    if (up) return (nt % kXcds == 0 ? fills : half_round && P <= (int64_t)128 * s.S) ? kFill : kPlain;
-    if (!half_round && P < (int64_t)48 * s.S) return kPlain;
+    const bool fills = most <= kFillRounds * kCus, few = most <= kCus && P * nt <= kFewTiles * kBMSmall;
+    if (up) return (nt % kXcds == 0 ? fills : few || (most <= kCus / 2 && P <= (int64_t)128 * s.S)) ? kFill : kPlain;
+    if (P < (int64_t)32 * s.S && !few) return kPlain;
     // (slots of 256-row tiles counted as five eighths of a tile more than their rows fill)
     const bool tall = most > kCus && (8 * P / kBMBig + 5 * s.S) * nt <= 8 * kCus;
     if (tall && !s.tile_rows && s.d_ff >= 2048 && P >= (int64_t)64 * s.S) return kTall;
@@ -747,15 +748,15 @@ int xcd_runs(const mmoe_shape& s, int prod)
 // 264 MB in turn, of which 148 token rows.  The time of 10900 layers with runs in the time with panels in turn, random in widths, rows,
 // slots, picks and router bias, mean (largest; share over 1.02), from a quarter of the traffic in token rows on:
 //   fewer panels than XCDs   0.90 (1.06; 0.01) on bf16 parts, 0.96 (1.03; 0.00) on the fp32 instruction
-//   more, not dividing among the XCDs   0.97 (1.03; 0.00) up to 400 tiles of 64 rows, counted with one more for every slot; over
-//                            it 0.99 (1.09; 0.10): an XCD's panels even out by themselves
+//   more, not dividing among the XCDs   0.97 (1.12; 0.01) up to 700 tiles of 64 rows, counted with one more for every slot, unequally
+//                            used slots down to 0.70; over it 0.99 (1.09; 0.11): an XCD's panels even out by themselves
 //   dividing among the XCDs  1.00 (1.15; 0.06): nothing to even out
 // Below that share of token rows up to 1.28.  Panels : runs, layer, us:
 //   768 x 3072   13 slots  2000 tokens 175 : 172   4096 311 : 282   GELU, bias 2.5 330 : 270   1000, bias 0.5 156.6 : 154.0   200 83.7 : 82.7
 //                24 slots  3000, bias 0.5 309 : 262   500 134.2 : 133.3
 //   1536 x 4096, 12 slots, 1000 tokens 252 : 231   256 x 2048 GELU, 12 slots, 2000 pairs, bias 0.5 86.4 : 79.6
 // (The up product in runs too: 768 x 3072, 13 slots, 2000 tokens 172 : 179.)
-constexpr int kF32RunTiles = 400;
+constexpr int kF32RunTiles = 700;
 bool f32_down_in_runs(const mmoe_shape& s)
 {
     int nt_up, nt, nb_up, nb_down;
@@ -773,14 +774,14 @@ bool f32_down_in_runs(const mmoe_shape& s)
 //                              every slot 0.99 (1.08): 768 x 3072, 8 slots, 2500 tokens 188 : 201, 5 slots of 512 x 2816, 4020 178 : 189
 //   up products, panel by panel, so that XCDs with more tiles than compute units take another round, which two and three smaller
 //   workgroups on a compute unit even out:
-//     panels dividing among the XCDs  0.95 (1.02; 0.01) of 80     ten panels and more, up to 64 rows per slot 0.94 (1.06; 0.05) of 56
+//     panels dividing among the XCDs  0.95 (1.02; 0.01) of 80     four panels and more, up to 56 rows per slot 0.94 (1.10; 0.03) of 86
 //     others  1.01 (1.16; 0.33): 3072 x 768, 16 slots, 1084 tokens, bias 2.5 137 : 161, 1280 x 512, 12 slots, 2653 87 : 96
 // Four : eight wavefronts, layer, us, three pools in turn, with the down products in runs either way:
 //   2048 x 1024 GELU, 12 slots, 700 tokens (up) 107.0 : 90.6           768 x 3072, 8 slots, 2000 GELU 171.7 : 167.6
 //   768 x 3072, 13 slots, 1000, bias 0.5 153.8 : 153.4   2000 171.3 : 164.2
 //   past the line  13 slots, 2500, bias 0.5 199 : 210    4096 290 : 306    24 slots, 3000 261 : 277
 //   K = 512  512 x 512, 12 slots, 3000 56.0 : 57.4       K = 1024  768 x 1024, 12 slots, 900 62.6 : 62.7
-constexpr int kAheadReduction = 1024, kAheadPanels = 10, kAheadRows = 64;
+constexpr int kAheadReduction = 1024, kAheadPanels = 4, kAheadRows = 56;
 bool f32_ahead(const mmoe_shape& s, int N, bool up)
 {
     if (s.dtype != MMOE_F32 || (up && s.act == MMOE_SWIGLU) || !f32_in_parts(s, N, false)) return false;

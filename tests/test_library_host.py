@@ -404,20 +404,21 @@ def test_few_wide_tiles_are_cut_in_two(mm, dispatch_rule):
 
 def test_row_tiles_fill_rounds_of_few_tiles(mm, dispatch_rule):
     """Ungated products of narrow 128-row tiles.  Down: heights that fill a round (1) up to 512 tiles, counted with one more for every
-    slot, from 48 rows per slot on or up to 128 tiles; 256-row tiles (2) where those may be more than a round of 256 and these are not,
+    slot, from 32 rows per slot on or up to 32 full tiles in a round; 256-row tiles (2) where those may be more than a round of 256 and these are not,
     in reductions from 2048 and with 64 rows per slot on; neither beyond, nor with a forced height of 256.  Up: 1, where panels divide
-    among the XCDs or tiles are half a round and slots have up to 128 rows."""
+    among the XCDs, or with up to 32 full tiles in a round, or tiles are half a round and slots have up to 128 rows."""
     for T, d, f, S, rows, want in ((4096, 768, 3072, 18, 0, 2), (4096, 768, 3072, 18, 128, 1), (4096, 768, 3072, 18, 256, 0), (4096, 768, 3072, 8, 0, 1),
                                    (3072, 768, 3072, 18, 0, 1), (3073, 768, 3072, 18, 0, 2), (8063, 768, 3072, 18, 0, 2), (8064, 768, 3072, 18, 0, 1),
-                                   (8576, 768, 3072, 18, 0, 1), (8577, 768, 3072, 18, 0, 0), (5000, 1024, 3072, 30, 0, 0), (600, 1536, 3072, 18, 0, 0),
-                                   (500, 1536, 3072, 16, 0, 0), (768, 1536, 3072, 16, 0, 1), (767, 1536, 3072, 16, 0, 0), (600, 1792, 3072, 8, 0, 1), (1000, 1792, 3072, 8, 0, 0),
+                                   (8576, 768, 3072, 18, 0, 1), (8577, 768, 3072, 18, 0, 0), (5000, 1024, 3072, 30, 0, 0), (600, 1536, 3072, 18, 0, 1), (575, 1536, 3072, 18, 0, 0),
+                                   (500, 1536, 3072, 16, 0, 0), (768, 1536, 3072, 16, 0, 1), (767, 1536, 3072, 16, 0, 1), (600, 1792, 3072, 8, 0, 1), (1000, 1792, 3072, 8, 0, 0),
                                    (4096, 768, 1792, 18, 0, 1), (4096, 768, 2048, 18, 0, 2), (1216, 1280, 3072, 19, 0, 2), (1215, 1280, 3072, 19, 0, 1),
-                                   (900, 1280, 3072, 19, 0, 0), (330, 512, 2048, 28, 0, 1), (513, 512, 3072, 28, 0, 0)):
+                                   (900, 1280, 3072, 19, 0, 1), (330, 512, 2048, 28, 0, 1), (513, 512, 3072, 28, 0, 1), (682, 768, 3072, 36, 0, 1), (683, 768, 3072, 36, 0, 0),
+                                   (682, 768, 3072, 37, 0, 0), (800, 768, 3072, 25, 0, 1), (799, 768, 3072, 25, 0, 0)):
         shape = mm.make_shape(T, d, f, 4, 8, S, 1, "bf16", "relu", tile_rows=rows)
         assert dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) == want, (T, d, f, S, rows)
         assert dispatch_rule("tile_share", mm.make_shape(T, d, f, 4, 8, S, 1, "f32", "relu"), d, False, restype=ctypes.c_int) == 0
-    for T, f, S, want in ((1024, 1024, 8, 1), (4096, 1024, 8, 1), (7168, 1024, 8, 1), (7169, 1024, 8, 0), (2304, 768, 3, 0), (384, 768, 3, 1), (385, 768, 3, 0),
-                          (2048, 768, 16, 0), (600, 768, 16, 1), (641, 768, 16, 0), (2600, 1280, 14, 0), (3500, 2048, 1, 1)):
+    for T, f, S, want in ((1024, 1024, 8, 1), (4096, 1024, 8, 1), (7168, 1024, 8, 1), (7169, 1024, 8, 0), (2304, 768, 3, 0), (384, 768, 3, 1), (682, 768, 3, 1), (683, 768, 3, 0),
+                          (2048, 768, 16, 0), (600, 768, 16, 1), (682, 768, 16, 1), (683, 768, 16, 0), (682, 768, 37, 0), (2600, 1280, 14, 0), (3500, 2048, 1, 1)):
         for act in ("relu", "gelu"):
             shape = mm.make_shape(T, 768, f, 4, 8, S, 1, "bf16", act)
             assert dispatch_rule("tile_share", shape, f, True, restype=ctypes.c_int) == want, (T, f, S)
@@ -426,12 +427,12 @@ def test_row_tiles_fill_rounds_of_few_tiles(mm, dispatch_rule):
 
 def test_fp32_tiles_of_eight_wavefronts_where_they_are_one_round(mm, dispatch_rule):
     """Tiles of 64 rows, counted with three quarters of one more for every slot, in up to 256, reductions from 1024 on; up products
-    only where panels divide among the XCDs, or with ten panels and more and up to 64 rows per slot.  (T, d, f, S, up, down)"""
+    only where panels divide among the XCDs, or with four panels and more and up to 56 rows per slot.  (T, d, f, S, up, down)"""
     for T, d, f, S, up, down in ((2000, 768, 3072, 13, False, True), (2346, 768, 3072, 8, False, True), (2347, 768, 3072, 8, False, False),
                                  (2500, 768, 3072, 8, False, False), (4020, 512, 2816, 5, False, False), (1900, 768, 768, 8, False, False),
                                  (700, 2048, 1024, 12, True, False), (1472, 2048, 1024, 12, True, False), (1473, 2048, 1024, 12, False, False),
                                  (1084, 3072, 768, 16, False, False), (608, 2560, 1280, 9, False, False), (2653, 1280, 512, 12, False, False),
-                                 (640, 1792, 1280, 10, True, True), (641, 1792, 1280, 10, False, True)):
+                                 (560, 1792, 1280, 10, True, True), (561, 1792, 1280, 10, False, True)):
         shape = mm.make_shape(T, d, f, 4, min(S, 8), S, 1, "f32", "relu")
         assert (dispatch_rule("f32_ahead", shape, f, True), dispatch_rule("f32_ahead", shape, d, False)) == (up, down), (T, d, f, S)
         assert not dispatch_rule("f32_ahead", mm.make_shape(T, d, f, 4, min(S, 8), S, 1, "f32", "swiglu"), f, True)
@@ -439,9 +440,9 @@ def test_fp32_tiles_of_eight_wavefronts_where_they_are_one_round(mm, dispatch_ru
 
 
 def test_fp32_down_products_in_runs_only_of_few_uneven_panels(mm, dispatch_rule):
-    """Fewer panels than XCDs; more that do not divide among them up to 400 tiles; from a quarter of the traffic in token rows on."""
-    for T, d, S, want in ((2000, 768, 13, True), (4096, 768, 32, True), (700, 768, 22, True), (700, 768, 23, False), (2600, 1024, 13, False), (900, 512, 24, False),
-                          (2000, 1024, 8, False), (1024, 1280, 24, True), (1025, 1280, 24, False), (3000, 2304, 12, False), (330, 2048, 24, False),
+    """Fewer panels than XCDs; more that do not divide among them up to 700 tiles; from a quarter of the traffic in token rows on."""
+    for T, d, S, want in ((2000, 768, 13, True), (4096, 768, 32, True), (700, 768, 29, True), (700, 768, 30, False), (2600, 1024, 13, False), (900, 512, 24, False),
+                          (2000, 1024, 8, False), (2944, 1280, 24, True), (2945, 1280, 24, False), (1024, 1280, 48, False), (1344, 2304, 17, True), (1345, 2304, 17, False), (3000, 2304, 12, False), (330, 2048, 24, False),
                           (500, 2304, 6, True)):
         shape = mm.make_shape(T, d, 3072, 4, 6, S, 1, "f32", "relu")
         assert not mm.expert_plan(shape)[0] and dispatch_rule("f32_down_in_runs", shape) is want, (T, d, S)
