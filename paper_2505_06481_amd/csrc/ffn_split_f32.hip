@@ -37,8 +37,8 @@
 // its matrix instructions one behind the other, so the tile goes to eight wavefronts of 16 features each, and what they split is
 // requested three steps ahead, global -> LDS along the rows (20 cycles per KB), a part of LDS for each wavefront, which alone reads it.
 // The waits are written out: nothing else in the loop goes through the vector memory, and what else there were would only make a
-// wait longer, since a wait names how many requests younger than the one it wants may be in flight.  Down product of 2000
-// tokens, 768 x 3072, 13 slots: 91 -> 84 us; layers and the line: f32_ahead.  (Four wavefronts with requests ahead: 178 us for the
+// wait longer, since a wait names how many requests younger than the one it wants may be in flight.  The layer of 2000
+// tokens, 768 x 3072, 13 slots: 171 -> 164 us; other layers and the line: f32_ahead.  (Four wavefronts with requests ahead: 178 us for the
 // layer, 172 without.)
 // Measured against the fp32 instruction (ffn_tiled_f32.hip), layer: 768 x 3072 top-1, 13 slots, 2000 tokens 234 -> 176 us,
 // 4096 tokens 437 -> 346; 1024 x 2048 SwiGLU top-2, 13 slots, 1200 tokens 357 -> 232, 3000 tokens 780 -> 489 (of which the
