@@ -622,31 +622,36 @@ bool route_in_groups(const mmoe_shape& s)
 //
 // Batches of a few rounds of route_group_kernel (a round: a workgroup to every compute unit): where neighbouring tokens are of one
 // variant, its groups read a router row once for four tokens too, with eight chunks in flight.  They win with few experts, and
-// with more where they fill their rounds.  Tiles in their time, one variant / four, mixed / four, one after the other:
+// with more where they fill their rounds: the line for one variant.  Variants that take turns are the ordinary batch, where tiles win
+// from 16 experts on.  Tiles in their time, one variant / four, mixed / four, one after the other:
 //   12 experts  1024 of 4096 1.13 / 1.30 / 1.12   2040 of 4096 1.29 / 0.92 / 1.25   13, 3072 of 8192, eight, one after the other 1.28
 //   16          1024 of 3072 1.12 / 0.83 / 1.09   1200 of 5120 1.15 / 0.75 / 1.16   1500 of 2304 0.81 / 0.51 / 0.80
 //   32          1024 of 4096 1.28 / 0.87 / 1.17   1200 of 4096 0.86 / 0.59 / 0.83   1800 of 4096 0.84 / 0.77 / 1.14   2040 1.16 / 0.77 / 1.15
 //   64          900 of 4096 0.71 / 0.71 / 0.98    1024 1.13 / 0.72 / 1.00           1500 0.72 / 0.45 / 0.68   2040 1.03 / 0.73 / 1.01
-// (Left over: 48 experts, 900 of 8192, four, one after the other 1.07; 65, 6144 of 4096 1.13.)
+// Layers with variants in turn or at random, other : tiles: 32 experts, 1733 tokens of 2816 141 : 123, 3184 of 3584 309 : 288, 808 of 3328 453 : 448;
+// 16, 4275 of 3840 134 : 124, 1425 of 2304 405 : 399, 1825 of 3840 502 : 504; 64, 982 of 2560 170 : 159.
+// (Left over, variants one after the other: the last figures of the table; 48 experts, 900 of 8192 1.07; 65, 6144 of 4096 1.13.)
 //
 // Short rows: few chunks to a sum and its butterfly, so wavefronts with fewer experts than they have room for cost more than
 // the tokens' shared rows save.  12000 tokens of 512, four variants: 9 experts 1.13, 16 1.02, 17 1.21, 32 0.96, 48 0.84; of 768 0.99,
 // 0.88, 1.05, 0.78, 0.68; of 256, 64 experts 3000 tokens 1.05, 5000 0.92.  And a second pass over the experts that has few of them:
 // 33 experts, 2048 tokens of 2048 1.22 / 0.89 / 1.18, 5000 0.87 / 0.89 / 1.11, 8000 1.00 / 0.76 / 1.00.
+// With several variants, layers: 64 experts, 3319 tokens of 768 78 : 67, 2085 184 : 176, 2116 of 512 304 : 300.
 constexpr int64_t kTileScores = 45 << 20;  // elements multiplied
 constexpr int kTileVariants = 8;
 bool route_in_tiles(const mmoe_shape& s)
 {
     if (s.dtype != MMOE_BF16 || s.E < 7 || s.V > kTileVariants || (int64_t)s.T * s.d_model * s.E < kTileScores) return false;
-    const bool groups = route_in_groups(s), short_rows = s.d_model < 1024 && s.T >= kRouteTokMinT;
+    const bool groups = route_in_groups(s), short_rows = s.d_model < 1024 && s.T >= kRouteTokMinT, mixed = s.V > 1;
     if (s.E <= 8) return s.T >= (groups || s.d_model >= 2304 ? 2304 : 4096);
     if (s.T < 640) return false;
     const int past = s.T % kGroupRound;  // tokens of the groups' last round, 0 if it is full
     if (s.E >= 48) {
-        if (groups && s.T <= 3 * kGroupRound) return past != 0 && past <= kGroupRound * 15 / 16;
-        return !short_rows || (s.T >= 3584 && (s.d_model > 256 || s.E >= 64));
+        if (groups && !mixed && s.T <= 3 * kGroupRound) return past != 0 && past <= kGroupRound * 15 / 16;
+        return !short_rows || (mixed && s.d_model > 256) || (s.T >= 3584 && (s.d_model > 256 || s.E >= 64));
     }
     if ((s.d_model <= 1024 && s.V > 4) || (s.E < 12 && s.d_model > 4096)) return false;
+    if (groups && mixed && s.E >= 16 && s.E <= 32) return s.E >= 24 || s.d_model < 3584 || s.T > 2 * kGroupRound;
     if (groups && s.T <= 2 * kGroupRound) return s.E >= 24 && s.T > kGroupRound && past != 0 && past <= kGroupRound * 3 / 8;
     if (groups && s.T < 6 * kGroupRound && s.d_model >= 3584) return false;
     if (s.E > 32 && s.T > 2 * kGroupRound * 15 / 16) return s.T >= 8192 && s.d_model >= 1024;

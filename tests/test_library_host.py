@@ -364,17 +364,18 @@ def test_routers_of_few_scores_take_no_groups_of_long_rows(mm, dispatch_rule):
 
 def test_routers_in_tiles_only_where_groups_of_a_variant_fill(mm, dispatch_rule):
     """bf16 batches with much to score go to tiles (four tokens of a variant to a wavefront) with up to eight variants, up to four
-    if rows are short; not in the first rounds of the groups of any four tokens if experts are few or the rounds full; and not
+    if rows are short; of one variant, or with few experts, not in the first rounds of the groups of any four tokens if the rounds are full; and not
     where wavefronts would have few experts each.  (T, d, V, E, tiles)"""
     for T, d, V, E, want in ((8192, 4096, 8, 8, True), (8192, 4096, 9, 8, False), (8000, 1024, 64, 32, False), (8388600, 256, 64, 32, False),
                              (4096, 1024, 4, 12, True), (4096, 1024, 5, 12, False), (4096, 1024, 8, 48, True),
                              (2303, 3072, 2, 8, False), (2304, 3072, 2, 8, True), (3000, 2048, 2, 8, False), (4096, 2048, 2, 8, True),
                              (1024, 4096, 4, 12, False), (2048, 4096, 4, 12, False), (2049, 4096, 4, 12, False), (6144, 4096, 4, 12, True), (2049, 3072, 4, 12, True),
-                             (1024, 4096, 2, 32, False), (1025, 4096, 2, 32, True), (1408, 4096, 2, 32, True), (1409, 4096, 2, 32, False),
-                             (900, 4096, 2, 64, True), (960, 4096, 2, 64, True), (961, 4096, 2, 64, False), (961, 2048, 2, 64, True), (1024, 4096, 2, 64, False), (1025, 4096, 2, 64, True),
-                             (1984, 4096, 2, 64, True), (1985, 4096, 2, 64, False), (3072, 4096, 2, 64, False), (3073, 4096, 2, 64, True), (4096, 4096, 2, 64, True),
+                             (1024, 4096, 1, 32, False), (1025, 4096, 1, 32, True), (1408, 4096, 1, 32, True), (1409, 4096, 1, 32, False), (1024, 4096, 2, 32, True), (1733, 2816, 3, 32, True),
+                             (3184, 3584, 4, 32, True), (4275, 3840, 2, 16, True), (4275, 3840, 1, 16, False), (2048, 3584, 2, 16, False), (2049, 3584, 2, 16, True), (2048, 3328, 2, 16, True), (2049, 4096, 2, 15, False),
+                             (900, 4096, 1, 64, True), (960, 4096, 1, 64, True), (961, 4096, 1, 64, False), (961, 2048, 1, 64, True), (1024, 4096, 1, 64, False), (1024, 4096, 2, 64, True), (1025, 4096, 1, 64, True),
+                             (1984, 4096, 1, 64, True), (1985, 4096, 1, 64, False), (1985, 4096, 2, 64, True), (3072, 4096, 1, 64, False), (3073, 4096, 1, 64, True), (4096, 4096, 2, 64, True),
                              (1037, 2048, 2, 64, True), (640, 3072, 2, 32, True), (639, 3072, 2, 32, False),
-                             (12000, 512, 4, 16, False), (12000, 768, 4, 16, True), (12000, 768, 4, 17, False), (3583, 512, 2, 64, False), (3584, 512, 2, 64, True),
+                             (12000, 512, 4, 16, False), (12000, 768, 4, 16, True), (12000, 768, 4, 17, False), (3583, 512, 1, 64, False), (2100, 512, 2, 64, True), (3088, 256, 2, 64, False), (3584, 512, 2, 64, True),
                              (12000, 256, 2, 48, False), (12000, 256, 2, 64, True), (8191, 2048, 2, 33, False), (8192, 2048, 2, 33, True), (5000, 2048, 2, 48, True)):
         shape = mm.make_shape(T, d, 256, V, E, E, 1, "bf16", "relu")
         assert dispatch_rule("route_in_tiles", shape) is want, (T, d, V, E)
