@@ -622,7 +622,9 @@ int planned_tile_rows(const mmoe_shape& s)
 //
 // Down products, in runs of tiles.  kFill over up to two rounds, from 32 rows per slot on 0.96 (1.20; 0.01); with fewer, slots of a little
 // more than 32 rows become two short tiles, which what they move bounds, and two to a compute unit hide each other's waits: up to
-// kFewTiles full tiles of rows, within a round 0.95 (1.25; 0.00), more 0.99 (1.29; 0.12: 512 x 6656, 80 slots, 622 tokens, two picks).
+// kFewTiles full tiles of rows, within a round 0.95 (1.25; 0.00), more 0.99 (1.29; 0.12: 512 x 6656, 80 slots, 622 tokens, two
+// picks), but 0.98 (1.03; 0.00) of reductions from 2048 on whose panels divide among the XCDs (4096 x 14336, 9 slots, 124 tokens, two picks, bias
+// 2.5 550 : 477, 447 layers of those widths 0.99).
 // kTall, where kFill is more than a round: reductions of 2048 and more, 64 rows per slot and more 0.93 (1.07; 0.02) where kFill has 0.96
 // (1.14; 0.04); shorter reductions 0.98 (1.10; 0.12) where kFill has 0.98 (1.06; 0.01): few steps, and nothing else on the compute unit
 // while the prologue waits; fewer rows 0.99 (1.24; 0.10).
@@ -648,7 +650,7 @@ int tile_share(const mmoe_shape& s, int N, bool up)
     const int64_t P = (int64_t)s.T * s.top_k, nt = N / 128, most = ((P + kBMSmall - 1) / kBMSmall + s.S) * nt;
     const bool fills = most <= kFillRounds * kCus, few = most <= kCus && P * nt <= kFewTiles * kBMSmall;
     if (up) return (nt % kXcds == 0 ? fills : few || (most <= kCus / 2 && P <= (int64_t)128 * s.S)) ? kFill : kPlain;
-    if (P < (int64_t)32 * s.S && !few) return kPlain;
+    if (P < (int64_t)32 * s.S && !few && (nt % kXcds != 0 || s.d_ff < 2048)) return kPlain;
     // (slots of 256-row tiles counted as five eighths of a tile more than their rows fill)
     const bool tall = most > kCus && (8 * P / kBMBig + 5 * s.S) * nt <= 8 * kCus;
     if (tall && !s.tile_rows && s.d_ff >= 2048 && P >= (int64_t)64 * s.S) return kTall;

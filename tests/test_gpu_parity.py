@@ -540,7 +540,8 @@ def test_few_used_slots_of_large_pools_stay_cached(mm, gc, oracle, dispatch_rule
     (3500, 2, 14, 1, 768, 256, "relu", 0.5, 0, 1), (3300, 2, 12, 1, 256, 1024, "gelu", 1.0, 1, 1), (1800, 1, 16, 2, 768, 512, "swiglu", 0.6, 0, 1),
     (700, 2, 8, 1, 1024, 1280, "relu", 2.0, 0, 1), (70, 1, 1, 1, 256, 256, "gelu", 0.0, 1, 1),     # rows that a round has room for
     (600, 2, 6, 1, 512, 768, "relu", 0.5, 1, 1), (700, 1, 16, 1, 1280, 256, "gelu", 0.5, 1, 1), (450, 1, 15, 1, 1280, 768, "relu", 1.0, 1, 0),
-    (2900, 1, 40, 1, 1280, 256, "relu", 1.0, 1, 0), (900, 1, 30, 1, 1280, 768, "relu", 1.0, 0, 0)])  # more than a round, few rows per slot
+    (2900, 1, 40, 1, 1280, 256, "relu", 1.0, 1, 0), (900, 1, 30, 1, 1280, 768, "relu", 1.0, 0, 0),
+    (700, 1, 40, 1, 1024, 2048, "relu", 2.0, 0, 1)])  # more than a round, few rows per slot
 def test_row_tiles_that_fill_whole_rounds(mm, gc, oracle, dispatch_rule, T, V, E, k, d, f, act, alpha, up, down):
     """Row tiles of a height that gives every compute unit one (1), of up to 256 rows where 128 do not do (2), and plain ones."""
     cfg = synth.Config(f"fill_{T}_{d}", T, d, f, V, E, k, "bf16", act, seed=1700 + T, bias_alpha=alpha)

@@ -405,7 +405,7 @@ def test_few_wide_tiles_are_cut_in_two(mm, dispatch_rule):
 
 def test_row_tiles_fill_rounds_of_few_tiles(mm, dispatch_rule):
     """Ungated products of narrow 128-row tiles.  Down: heights that fill a round (1) up to 512 tiles, counted with one more for every
-    slot, from 32 rows per slot on or up to 32 full tiles in a round; 256-row tiles (2) where those may be more than a round of 256 and these are not,
+    slot, from 32 rows per slot on, or up to 32 full tiles in a round, or where panels of a reduction from 2048 on divide among the XCDs; 256-row tiles (2) where those may be more than a round of 256 and these are not,
     in reductions from 2048 and with 64 rows per slot on; neither beyond, nor with a forced height of 256.  Up: 1, where panels divide
     among the XCDs, or with up to 32 full tiles in a round, or tiles are half a round and slots have up to 128 rows."""
     for T, d, f, S, rows, want in ((4096, 768, 3072, 18, 0, 2), (4096, 768, 3072, 18, 128, 1), (4096, 768, 3072, 18, 256, 0), (4096, 768, 3072, 8, 0, 1),
@@ -414,7 +414,8 @@ def test_row_tiles_fill_rounds_of_few_tiles(mm, dispatch_rule):
                                    (500, 1536, 3072, 16, 0, 0), (768, 1536, 3072, 16, 0, 1), (767, 1536, 3072, 16, 0, 1), (600, 1792, 3072, 8, 0, 1), (1000, 1792, 3072, 8, 0, 0),
                                    (4096, 768, 1792, 18, 0, 1), (4096, 768, 2048, 18, 0, 2), (1216, 1280, 3072, 19, 0, 2), (1215, 1280, 3072, 19, 0, 1),
                                    (900, 1280, 3072, 19, 0, 1), (330, 512, 2048, 28, 0, 1), (513, 512, 3072, 28, 0, 1), (682, 768, 3072, 36, 0, 1), (683, 768, 3072, 36, 0, 0),
-                                   (682, 768, 3072, 37, 0, 0), (800, 768, 3072, 25, 0, 1), (799, 768, 3072, 25, 0, 0)):
+                                   (682, 768, 3072, 37, 0, 0), (800, 768, 3072, 25, 0, 1), (799, 768, 3072, 25, 0, 0),
+                                   (248, 4096, 14336, 9, 0, 1), (700, 1024, 2048, 40, 0, 1), (700, 1024, 1792, 40, 0, 0)):
         shape = mm.make_shape(T, d, f, 4, 8, S, 1, "bf16", "relu", tile_rows=rows)
         assert dispatch_rule("tile_share", shape, d, False, restype=ctypes.c_int) == want, (T, d, f, S, rows)
         assert dispatch_rule("tile_share", mm.make_shape(T, d, f, 4, 8, S, 1, "f32", "relu"), d, False, restype=ctypes.c_int) == 0
