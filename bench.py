@@ -33,9 +33,9 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # to one version of the kernel's sources (the kernel file and the tile-list builder that decides
 # which tiles it runs); with any other version `traffic` is null.
 TRAFFIC = {
-    "ffn_tiled.hip": {"sources": ("ffn_tiled.hip", "tile_table.h"), "sha256": "8d67ebc16917639d64f7d0d34ea9b5e570154a138871600db16ce23ddadc0c94",
+    "ffn_tiled.hip": {"sources": ("ffn_tiled.hip", "tile_table.h"), "sha256": "af912b7051101efc3ef1a3b2488f65fa88e95e75fca8c9b4e711c546199e2e40",
                       "workload": "mixtral_prefill_bf16_v2_t8192",
-                      "fetch_bytes": 11589812763, "write_bytes": 469763291},
+                      "fetch_bytes": 11661108068, "write_bytes": 469763337},
     "ffn_skinny.hip": {"sources": ("ffn_skinny.hip",), "sha256": "53c8d2f4cf0ad569d8a1db40c2f666cd4782cebba9d6fcf637fa5d1ec974524a",
                        "workload": "mixtral_decode_bf16_v2_t64",
                        "fetch_bytes": 3057741466, "write_bytes": 3670590},
